@@ -71,90 +71,146 @@ __global__ void k_sample(DevProblem pr, int S, const float* __restrict__ X, int 
 // coordinates (source grid x y z, target grid x y z); coordinates pinned to
 // the box (border points) are not variables.
 
-constexpr int kPtTile = 128;  // selected solutions staged in LDS at a time
+// Multi-point elements (such as the paper's per-cube tetrahedra): the
+// variables of element f are the coordinates of its points
+// fos_pts[fos_off[f] .. fos_off[f+1]) in order, 6 per point (source x y z,
+// target x y z), at most kEstPoints points.  The distribution is estimated
+// over all of them jointly (full covariance).
+constexpr int kEstPoints = 4, kEstVars = 6 * kEstPoints, kEstTri = kEstVars * (kEstVars + 1) / 2;
+constexpr int kEstTile = 192;  // selected solutions staged in LDS at a time
 
-// Per element f: mean [F][6] of the point's coordinates over the solutions
-// sel[0..n_sel) (indices outside [0, S) are skipped), and chol [F][21], the
-// lower Cholesky factor (rows 0..5, row r holding columns 0..r) of their
-// maximum-likelihood covariance (divisor: the number of solutions used)
-// restricted to the free coordinates; pinned rows and columns are 0, and a
-// pivot that is not positive (a rank-deficient selection) gives a zero
-// column.  Sums run over sel in order, in FP64.
-__global__ __launch_bounds__(64) void k_estimate(DevProblem pr, int S, const float* __restrict__ X, int n_sel,
-                                                 const int* __restrict__ sel, int F, const int* __restrict__ pts,
-                                                 double* __restrict__ mean, double* __restrict__ chol) {
-  // one wave per point: the selected solutions' 6 coordinates are staged in LDS
-  // tiles; lane c < 6 sums mean component c and lane e < 21 covariance entry e,
-  // each over the selection in order
-  __shared__ float s_x[kPtTile][6];
-  __shared__ int s_ok[kPtTile];
-  __shared__ double s_m[6];
-  __shared__ double s_C[21];
+__device__ __forceinline__ double readlane64(double v, int l) {
+  const long long u = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, l), hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), l);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Mean and Cholesky factor of the elements' distributions, for elements of up
+// to NP points (NP = 1: the single points pts[f], off null; else CSR).  Per
+// element f: mean [F][NV] of the variables over the solutions sel[0..n_sel)
+// (indices outside [0, S) are skipped), and chol [F][NE], the lower Cholesky
+// factor (row r holding columns 0..r) of their maximum-likelihood covariance
+// (divisor: the number of solutions used) restricted to the free variables;
+// rows and columns of pinned coordinates, and of variables beyond 6 x (number
+// of points), are 0, and a pivot that is not positive (a rank-deficient
+// selection) gives a zero column.  Elements with no point, more than NP
+// points, an invalid point or no valid solution get zeros.
+//
+// One workgroup per element, one thread per covariance entry.  There are few
+// elements in a call (5 to 75), so the kernel is bound by the length of its
+// chain, not by the chip: the centred variables are staged once in FP64, each
+// entry is one pass over them in selection order, and the factorisation keeps
+// row r in the registers of lane r and subtracts column k's products as soon
+// as the column is known (the order of the products of an entry is that of
+// the row-by-row form).  On 64 elements of 4 points over 200 solutions: 208 us
+// a call with the factorisation on one thread and two staging passes.
+template <int NP>
+__global__ __launch_bounds__(NP == 1 ? 64 : 320) void k_estimate(DevProblem pr, int S, const float* __restrict__ X,
+                                                                 int n_sel, const int* __restrict__ sel, int F,
+                                                                 const int* __restrict__ off,
+                                                                 const int* __restrict__ pts,
+                                                                 double* __restrict__ mean, double* __restrict__ chol) {
+  constexpr int NV = 6 * NP, NE = NV * (NV + 1) / 2, WG = NP == 1 ? 64 : 320;
+  static_assert(NE <= WG, "one thread per covariance entry");
+  __shared__ float s_x[kEstTile][NV];
+  __shared__ double s_d[kEstTile][NV];  // centred, 0 for skipped solutions and pinned variables
+  __shared__ double s_mu[NV];
+  __shared__ double s_C[NE];
+  __shared__ bool s_ok[kEstTile], s_free[NV];
   const int f = blockIdx.x, t = threadIdx.x;
-  double* mu = mean + (size_t)f * 6;
-  double* L = chol + (size_t)f * 21;
-  if (t < 6) mu[t] = 0.0;
-  if (t < 21) L[t] = 0.0;
-  const int p = pts[f];
-  if (p < 0 || p >= pr.P || n_sel < 1) return;
-  const int idx[3] = {p % pr.n[0], (p / pr.n[0]) % pr.n[1], p / (pr.n[0] * pr.n[1])};
-  bool fr[6];
-  for (int c = 0; c < 6; ++c) fr[c] = idx[c % 3] > 0 && idx[c % 3] < pr.n[c % 3] - 1;
-  int n = 0;
-  for (int i = 0; i < n_sel; ++i) n += sel[i] >= 0 && sel[i] < S;
-  if (n == 0) return;
-  auto stage = [&](int i0) {
-    const int rows = min(kPtTile, n_sel - i0);
-    for (int q = t; q < rows * 6; q += 64) {
-      const int i = q / 6, c = q % 6, si = sel[i0 + i];
-      s_x[i][c] = si >= 0 && si < S ? X[(((size_t)si * 2 + c / 3) * pr.P + p) * 3 + c % 3] : 0.f;
+  double* mu = mean + (size_t)f * NV;
+  double* L = chol + (size_t)f * NE;
+  const int b = off ? off[f] : f, np = off ? off[f + 1] - b : 1;
+  bool ok = b >= 0 && np >= 1 && np <= NP && (!off || b + np <= off[F]);
+  for (int k = 0; ok && k < np; ++k) ok = pts[b + k] >= 0 && pts[b + k] < pr.P;
+  int n = 0;  // solutions used
+  if (ok)
+    for (int i0 = 0; i0 < n_sel; i0 += WG) {
+      const int s = i0 + t < n_sel ? sel[i0 + t] : -1;
+      n += __syncthreads_count(s >= 0 && s < S);
     }
-    for (int i = t; i < rows; i += 64) s_ok[i] = sel[i0 + i] >= 0 && sel[i0 + i] < S;
+  if (n == 0) {
+    for (int i = t; i < NV; i += WG) mu[i] = 0.0;
+    for (int i = t; i < NE; i += WG) L[i] = 0.0;
+    return;
+  }
+  const int nv = 6 * np;
+  if (t < NV) {  // variable t: point t / 6, coordinate t % 6; free unless pinned to the box
+    bool fr = false;
+    if (t < nv) {
+      const int p = pts[b + t / 6], a = t % 3;
+      const int idx = a == 0 ? p % pr.n[0] : (a == 1 ? (p / pr.n[0]) % pr.n[1] : p / (pr.n[0] * pr.n[1]));
+      fr = idx > 0 && idx < pr.n[a] - 1;
+    }
+    s_free[t] = fr;
+  }
+  auto stage = [&](int i0) {
+    const int rows = min(kEstTile, n_sel - i0);
+    for (int q = t; q < rows * NV; q += WG) {
+      const int i = q / NV, v = q % NV, s = sel[i0 + i];
+      const bool use = s >= 0 && s < S;
+      float x = 0.f;
+      if (use && v < nv) {
+        const int p = pts[b + v / 6], c = v % 6;
+        x = X[(((size_t)s * 2 + c / 3) * pr.P + p) * 3 + c % 3];
+      }
+      s_x[i][v] = x;
+      if (v == 0) s_ok[i] = use;
+    }
     __syncthreads();
     return rows;
   };
   double m = 0.0;
-  for (int i0 = 0; i0 < n_sel; i0 += kPtTile) {
-    const int rows = stage(i0);
-    if (t < 6)
-      for (int i = 0; i < rows; ++i)
-        if (s_ok[i]) m += (double)s_x[i][t];
-    __syncthreads();
-  }
-  if (t < 6) s_m[t] = m / n;
-  __syncthreads();
-  int r = 0;
-  while (t < 21 && (r + 1) * (r + 2) / 2 <= t) ++r;
-  const int c = t - r * (r + 1) / 2;
-  double acc = 0.0;
-  for (int i0 = 0; i0 < n_sel; i0 += kPtTile) {
-    const int rows = stage(i0);
-    if (t < 21)
-      for (int i = 0; i < rows; ++i)
-        if (s_ok[i]) {
-          const double dr = fr[r] ? (double)s_x[i][r] - s_m[r] : 0.0;
-          const double dc = fr[c] ? (double)s_x[i][c] - s_m[c] : 0.0;
-          acc += dr * dc;
-        }
-    __syncthreads();
-  }
-  if (t < 21) s_C[t] = acc / n;
-  __syncthreads();
-  if (t != 0) return;
-  double l[21] = {0};
-  for (int r2 = 0; r2 < 6; ++r2)
-    for (int c2 = 0; c2 <= r2; ++c2) {
-      double v = s_C[r2 * (r2 + 1) / 2 + c2];
-      for (int k = 0; k < c2; ++k) v -= l[r2 * (r2 + 1) / 2 + k] * l[c2 * (c2 + 1) / 2 + k];
-      if (c2 == r2)
-        l[r2 * (r2 + 1) / 2 + r2] = v > 0.0 ? sqrt(v) : 0.0;
-      else {
-        const double d = l[c2 * (c2 + 1) / 2 + c2];
-        l[r2 * (r2 + 1) / 2 + c2] = d > 0.0 ? v / d : 0.0;
-      }
+  int rows = 0;
+  for (int i0 = 0; i0 < n_sel; i0 += kEstTile) {
+    rows = stage(i0);
+    if (t < NV) {
+#pragma unroll 8
+      for (int i = 0; i < rows; ++i) m += (double)s_x[i][t];  // skipped solutions add 0
     }
-  for (int k = 0; k < 6; ++k) mu[k] = s_m[k];
-  for (int k = 0; k < 21; ++k) L[k] = l[k];
+    if (i0 + kEstTile < n_sel) __syncthreads();
+  }
+  if (t < NV) s_mu[t] = m / n;
+  __syncthreads();
+  int r = 0;  // entry t: row r, column c
+  while (t < NE && (r + 1) * (r + 2) / 2 <= t) ++r;
+  const int c = t < NE ? t - r * (r + 1) / 2 : 0;
+  double acc = 0.0;
+  for (int i0 = 0; i0 < n_sel; i0 += kEstTile) {
+    if (n_sel > kEstTile) rows = stage(i0);  // a single tile is still there
+    for (int q = t; q < rows * NV; q += WG) {
+      const int i = q / NV, v = q % NV;
+      s_d[i][v] = s_ok[i] && s_free[v] ? (double)s_x[i][v] - s_mu[v] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int i = 0; i < rows; ++i) acc += s_d[i][r] * s_d[i][c];
+    if (i0 + kEstTile < n_sel) __syncthreads();
+  }
+  if (t < NE) s_C[t] = s_free[r] && s_free[c] ? acc / n : 0.0;
+  __syncthreads();
+  if (t < 64) {
+    const int row = min(t, NV - 1), base = row * (row + 1) / 2;  // lanes past the last row repeat it
+    double v[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = k <= row ? s_C[base + k] : 0.0;
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+      if (k < nv) {
+        const double pivot = readlane64(v[k], k);
+        const double d = pivot > 0.0 ? sqrt(pivot) : 0.0;
+        const double l = row == k ? d : (d > 0.0 ? v[k] / d : 0.0);
+        v[k] = l;
+#pragma unroll
+        for (int j = k + 1; j < NV; ++j) v[j] -= l * readlane64(l, j);
+      }
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+      if (t < NV && k <= row) s_C[base + k] = v[k];
+  }
+  __syncthreads();
+  if (t < NV) mu[t] = s_mu[t];
+  if (t < NE) L[t] = s_C[t];
 }
 
 // cand [S][F][K][2][3]: mean + sqrt(mult[f]) L z on the free coordinates of
@@ -199,130 +255,6 @@ __global__ void k_sample_est(DevProblem pr, int S, const float* __restrict__ X, 
     }
     out[c] = (float)(rint((v + 0.5) * kLat) / kLat - 0.5);
   }
-}
-
-// Multi-point elements (such as the paper's per-cube tetrahedra): the
-// variables of element f are the coordinates of its points
-// fos_pts[fos_off[f] .. fos_off[f+1]) in order, 6 per point (source x y z,
-// target x y z), at most kEstPoints points.  The distribution is estimated
-// over all of them jointly (full covariance).
-constexpr int kEstPoints = 4, kEstVars = 6 * kEstPoints, kEstTri = kEstVars * (kEstVars + 1) / 2;
-constexpr int kEstTile = 128;  // selected solutions staged in LDS at a time
-
-// One 64-thread workgroup per element: mean [F][kEstVars] and the lower
-// Cholesky factor chol [F][kEstTri] (row r holding columns 0..r) of the
-// maximum-likelihood covariance of the free variables over the solutions
-// sel[0..n_sel) (indices outside [0, S) skipped); rows and columns of pinned
-// coordinates, and of variables beyond 6 x (number of points), are 0; a
-// non-positive pivot gives a zero column.  Elements with no point, more than
-// kEstPoints points or an invalid point get zeros.
-__global__ __launch_bounds__(64) void k_estimate_el(DevProblem pr, int S, const float* __restrict__ X, int n_sel,
-                                                    const int* __restrict__ sel, int F, const int* __restrict__ off,
-                                                    const int* __restrict__ pts, double* __restrict__ mean,
-                                                    double* __restrict__ chol) {
-  __shared__ double s_mu[kEstVars];
-  __shared__ double s_C[kEstTri];
-  __shared__ int s_valid;
-  __shared__ float s_x[kEstTile][kEstVars];
-  __shared__ int s_ok[kEstTile];
-  const int f = blockIdx.x, t = threadIdx.x;
-  double* mu = mean + (size_t)f * kEstVars;
-  double* L = chol + (size_t)f * kEstTri;
-  for (int i = t; i < kEstVars; i += 64) mu[i] = 0.0;
-  for (int i = t; i < kEstTri; i += 64) L[i] = 0.0;
-  const int b = off[f], np = off[f + 1] - b;
-  if (t == 0) {
-    int ok = b >= 0 && np >= 1 && np <= kEstPoints && b + np <= off[F];
-    for (int k = 0; ok && k < np; ++k) ok = pts[b + k] >= 0 && pts[b + k] < pr.P;
-    s_valid = ok;
-  }
-  __syncthreads();
-  if (!s_valid) return;
-  const int nv = 6 * np;
-  int n = 0;  // solutions used
-  for (int i = 0; i < n_sel; ++i) n += sel[i] >= 0 && sel[i] < S;
-  if (n == 0) return;
-  // variable v: point v / 6, coordinate v % 6; free unless pinned to the box
-  auto is_free = [&](int v) {
-    const int p = pts[b + v / 6], a = v % 3;
-    const int idx = a == 0 ? p % pr.n[0] : (a == 1 ? (p / pr.n[0]) % pr.n[1] : p / (pr.n[0] * pr.n[1]));
-    return idx > 0 && idx < pr.n[a] - 1;
-  };
-  // the selected solutions' coordinates, staged in LDS tiles of kEstTile rows;
-  // every sum still runs over the selection in order
-  auto stage = [&](int i0) {
-    const int rows = min(kEstTile, n_sel - i0);
-    for (int q = t; q < rows * nv; q += 64) {
-      const int i = q / nv, v = q % nv;
-      const int si = sel[i0 + i];
-      float x = 0.f;
-      if (si >= 0 && si < S) {
-        const int p = pts[b + v / 6], c = v % 6;
-        x = X[(((size_t)si * 2 + c / 3) * pr.P + p) * 3 + c % 3];
-      }
-      s_x[i][v] = x;
-    }
-    for (int i = t; i < rows; i += 64) s_ok[i] = sel[i0 + i] >= 0 && sel[i0 + i] < S;
-    __syncthreads();
-    return rows;
-  };
-  double m = 0.0;
-  for (int i0 = 0; i0 < n_sel; i0 += kEstTile) {
-    const int rows = stage(i0);
-    if (t < nv)
-      for (int i = 0; i < rows; ++i)
-        if (s_ok[i]) m += (double)s_x[i][t];
-    __syncthreads();
-  }
-  if (t < nv) s_mu[t] = m / n;
-  __syncthreads();
-  constexpr int kPer = (kEstTri + 63) / 64;  // covariance entries per thread
-  const int ne = nv * (nv + 1) / 2;
-  double acc[kPer];
-  int er[kPer], ec[kPer];
-  bool ef[kPer];
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int e = t + 64 * k;
-    int r = 0;
-    if (e < ne)
-      while ((r + 1) * (r + 2) / 2 <= e) ++r;
-    er[k] = r;
-    ec[k] = e - r * (r + 1) / 2;
-    ef[k] = e < ne && is_free(r) && is_free(ec[k]);
-    acc[k] = 0.0;
-  }
-  for (int i0 = 0; i0 < n_sel; i0 += kEstTile) {
-    const int rows = stage(i0);
-#pragma unroll
-    for (int k = 0; k < kPer; ++k)
-      if (ef[k]) {
-        const double mr = s_mu[er[k]], mc = s_mu[ec[k]];
-        for (int i = 0; i < rows; ++i)
-          if (s_ok[i]) acc[k] += ((double)s_x[i][er[k]] - mr) * ((double)s_x[i][ec[k]] - mc);
-      }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int k = 0; k < kPer; ++k)
-    if (t + 64 * k < ne) s_C[t + 64 * k] = acc[k] / n;
-  __syncthreads();
-  if (t == 0) {  // in place: s_C becomes the factor
-    for (int r = 0; r < nv; ++r)
-      for (int c = 0; c <= r; ++c) {
-        double v = s_C[r * (r + 1) / 2 + c];
-        for (int k = 0; k < c; ++k) v -= s_C[r * (r + 1) / 2 + k] * s_C[c * (c + 1) / 2 + k];
-        if (c == r)
-          s_C[r * (r + 1) / 2 + r] = v > 0.0 ? sqrt(v) : 0.0;
-        else {
-          const double d = s_C[c * (c + 1) / 2 + c];
-          s_C[r * (r + 1) / 2 + c] = d > 0.0 ? v / d : 0.0;
-        }
-      }
-  }
-  __syncthreads();
-  if (t < nv) mu[t] = s_mu[t];
-  for (int e = t; e < nv * (nv + 1) / 2; e += 64) L[e] = s_C[e];
 }
 
 // cand [S][fos_off[F]][2][3] for multi-point elements: mean + sqrt(mult[f]) L z
@@ -757,8 +689,7 @@ dsm_status dsm_estimate_distributions(dsm_problem* p, int32_t S, const float* X,
   if (!p || S < 0 || F < 0 || n_sel < 0) return DSM_ERR_ARG;
   if (F == 0) return DSM_OK;  // empty buffers may be null
   if (!fos_pts || !mean || !chol || (n_sel > 0 && (!X || !sel))) return DSM_ERR_ARG;
-  k_estimate<<<(unsigned)F, 64, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, fos_pts, mean,
-                                                                        chol);
+  k_estimate<1><<<(unsigned)F, 64, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, nullptr, fos_pts, mean, chol);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
 
@@ -783,7 +714,8 @@ dsm_status dsm_estimate_elements(dsm_problem* p, int32_t S, const float* X, int3
   if (!p || S < 0 || F < 0 || n_sel < 0) return DSM_ERR_ARG;
   if (F == 0) return DSM_OK;  // empty buffers may be null
   if (!fos_off || !fos_pts || !mean || !chol || (n_sel > 0 && (!X || !sel))) return DSM_ERR_ARG;
-  k_estimate_el<<<(unsigned)F, 64, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, fos_off, fos_pts, mean, chol);
+  k_estimate<kEstPoints><<<(unsigned)F, 320, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, fos_off, fos_pts, mean,
+                                                                      chol);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
 
