@@ -213,94 +213,72 @@ __global__ __launch_bounds__(NP == 1 ? 64 : 320) void k_estimate(DevProblem pr, 
   if (t < NE) L[t] = s_C[t];
 }
 
-// cand [S][F][K][2][3]: mean + sqrt(mult[f]) L z on the free coordinates of
-// single point pts[f], z ~ N(0, I) from the counter-based generator (6 draws
+// Candidates drawn from the estimated distributions: mean + sqrt(mult) L z on
+// the free variables, z ~ N(0, I) from the counter-based generator (NV draws
 // per candidate, counters as in k_sample); pinned coordinates keep the
 // solution's value; clamped to the image box and rounded to the 1/128-voxel
-// lattice (half to even).
-__global__ void k_sample_est(DevProblem pr, int S, const float* __restrict__ X, int F, const int* __restrict__ pts, int K,
-                             const double* __restrict__ mean, const double* __restrict__ chol,
-                             const float* __restrict__ mult, int n_clusters, const int* __restrict__ cluster,
-                             const double* __restrict__ shift, const unsigned char* __restrict__ ams, double delta,
-                             unsigned long long seed, unsigned long long counter,
-                             const unsigned long long* __restrict__ counter_dev, float* __restrict__ cand) {
-  const int64_t row = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+// lattice (half to even).  NP = 1: K candidates cand [S][F][K][2][3] of the
+// single points pts[f] (off null); else one candidate cand [S][fos_off[F]][2][3]
+// of the elements of up to NP points.  An invalid point, element or cluster
+// gives NaN (flagged as non-finite by the evaluator); elements with malformed
+// offsets are not written.
+//
+// A group of LG lanes per candidate, lane v drawing and combining variable v
+// (z passed between the lanes), so that the FP64 logarithm and cosine of the
+// draws, which bound the kernel, run once per lane instead of NV times in a
+// row, and nothing is kept in scratch memory.  Candidates are numbered with
+// the element slowest, so the groups of a wave read the same factor.
+template <int NP, int LG>
+__global__ __launch_bounds__(256) void k_sample_dist(DevProblem pr, int S, const float* __restrict__ X, int F,
+                                                     const int* __restrict__ off, const int* __restrict__ pts, int K,
+                                                     const double* __restrict__ mean, const double* __restrict__ chol,
+                                                     const float* __restrict__ mult, int n_clusters,
+                                                     const int* __restrict__ cluster, const double* __restrict__ shift,
+                                                     const unsigned char* __restrict__ ams, double delta,
+                                                     unsigned long long seed, unsigned long long counter,
+                                                     const unsigned long long* __restrict__ counter_dev,
+                                                     float* __restrict__ cand) {
+  constexpr int NV = 6 * NP, NE = NV * (NV + 1) / 2;
+  static_assert(NV <= LG && 64 % LG == 0, "one lane per variable");
+  const int64_t g = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / LG;
+  const int v = threadIdx.x % LG;
   if (counter_dev) counter += *counter_dev;
-  if (row >= (int64_t)S * F * K) return;
-  const int f = (int)((row / K) % F);
-  const int s = (int)(row / ((int64_t)F * K));
-  const int p = pts[f];
-  float* out = cand + row * 6;
+  if (g >= (int64_t)S * F * K) return;
+  const int f = (int)(g / ((int64_t)S * K));
+  const int64_t sk = g - (int64_t)f * S * K;
+  const int s = (int)(sk / K);
+  const int64_t row = ((int64_t)s * F + f) * K + (sk - (int64_t)s * K);
+  const int b = off ? off[f] : f, np = off ? off[f + 1] - b : 1;
+  if (off && (b < 0 || np < 0 || b + np > off[F])) return;  // malformed offsets: nothing of this element to write
+  float* out = off ? cand + ((size_t)s * off[F] + b) * 6 : cand + row * 6;
   const int cl = cluster ? cluster[s] : 0;
-  if (p < 0 || p >= pr.P || cl < 0 || cl >= n_clusters) {
-    for (int c = 0; c < 6; ++c) out[c] = NAN;  // flagged as non-finite by the evaluator
-    return;
-  }
-  const size_t d = (size_t)cl * F + f;  // distribution of the solution's cluster
-  const double* mu = mean + d * 6;
-  const double* L = chol + d * 21;
-  const double sc = sqrt((double)mult[d]);
-  double z[6];
-  for (int c = 0; c < 6; ++c) z[c] = normal(seed, counter * 0x100000000ull + (unsigned long long)(row * 6 + c));
-  const int idx[3] = {p % pr.n[0], (p / pr.n[0]) % pr.n[1], p / (pr.n[0] * pr.n[1])};
-  for (int c = 0; c < 6; ++c) {
-    const int g = c / 3, a = c % 3;
-    double v = X[(((size_t)s * 2 + g) * pr.P + p) * 3 + a];
-    if (idx[a] > 0 && idx[a] < pr.n[a] - 1) {
-      double w = 0.0;
-      for (int t = 0; t <= c; ++t) w += L[c * (c + 1) / 2 + t] * z[t];
-      double m = mu[c];
-      if (shift && ams[s]) m += delta * (double)mult[d] * shift[(size_t)p * 6 + c];  // anticipated mean shift
-      v = fmin(fmax(m + sc * w, -0.5), pr.D[a] - 0.5);
-    }
-    out[c] = (float)(rint((v + 0.5) * kLat) / kLat - 0.5);
-  }
-}
-
-// cand [S][fos_off[F]][2][3] for multi-point elements: mean + sqrt(mult[f]) L z
-// on the element's free variables, z ~ N(0, I) (kEstVars draws per solution
-// and element, counters as in k_sample); pinned coordinates keep the
-// solution's value; clamped to the box and rounded to the lattice.  Elements
-// that k_estimate_el rejects get NaN candidates.
-__global__ void k_sample_el(DevProblem pr, int S, const float* __restrict__ X, int F, const int* __restrict__ off,
-                            const int* __restrict__ pts, const double* __restrict__ mean,
-                            const double* __restrict__ chol, const float* __restrict__ mult, int n_clusters,
-                            const int* __restrict__ cluster, const double* __restrict__ shift,
-                            const unsigned char* __restrict__ ams, double delta, unsigned long long seed, unsigned long long counter,
-                            const unsigned long long* __restrict__ counter_dev, float* __restrict__ cand) {
-  const int64_t row = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (counter_dev) counter += *counter_dev;
-  if (row >= (int64_t)S * F) return;
-  const int s = (int)(row / F), f = (int)(row % F);
-  const int b = off[f], np = off[f + 1] - b, total = off[F];
-  if (b < 0 || np < 0 || b + np > total) return;  // malformed offsets: nothing of this element to write
-  const int cl = cluster ? cluster[s] : 0;
-  bool ok = np >= 1 && np <= kEstPoints && cl >= 0 && cl < n_clusters;
+  bool ok = np >= 1 && np <= NP && cl >= 0 && cl < n_clusters;
   for (int k = 0; ok && k < np; ++k) ok = pts[b + k] >= 0 && pts[b + k] < pr.P;
   if (!ok) {
-    for (int k = 0; k < np; ++k)
-      for (int c = 0; c < 6; ++c) cand[((size_t)s * total + b + k) * 6 + c] = NAN;
+    for (int e = v; e < 6 * np; e += LG) out[e] = NAN;
     return;
   }
+  const int nv = 6 * np;
   const size_t d = (size_t)cl * F + f;  // distribution of the solution's cluster
-  const double* mu = mean + d * kEstVars;
-  const double* L = chol + d * kEstTri;
-  const double sc = sqrt((double)mult[d]);
-  double z[kEstVars];
-  for (int v = 0; v < 6 * np; ++v) z[v] = normal(seed, counter * 0x100000000ull + (unsigned long long)(row * kEstVars + v));
-  for (int v = 0; v < 6 * np; ++v) {
-    const int p = pts[b + v / 6], c = v % 6, g = c / 3, a = c % 3;
-    const int idx = a == 0 ? p % pr.n[0] : (a == 1 ? (p / pr.n[0]) % pr.n[1] : p / (pr.n[0] * pr.n[1]));
-    double x = X[(((size_t)s * 2 + g) * pr.P + p) * 3 + a];
-    if (idx > 0 && idx < pr.n[a] - 1) {
-      double w = 0.0;
-      for (int k = 0; k <= v; ++k) w += L[v * (v + 1) / 2 + k] * z[k];
-      double m = mu[v];
-      if (shift && ams[s]) m += delta * (double)mult[d] * shift[(size_t)p * 6 + c];  // anticipated mean shift
-      x = fmin(fmax(m + sc * w, -0.5), pr.D[a] - 0.5);
-    }
-    cand[((size_t)s * total + b + v / 6) * 6 + c] = (float)(rint((x + 0.5) * kLat) / kLat - 0.5);
+  const double* L = chol + d * NE + v * (v + 1) / 2;
+  double z = 0.0, w = 0.0;
+  if (v < nv) z = normal(seed, counter * 0x100000000ull + (unsigned long long)(row * NV + v));
+#pragma unroll 6
+  for (int k = 0; k < nv; ++k) {
+    const double zk = __shfl(z, k, LG);
+    if (k <= v && v < nv) w += L[k] * zk;
   }
+  if (v >= nv) return;
+  const int p = pts[b + v / 6], c = v % 6, gr = c / 3, a = c % 3;
+  const int idx = a == 0 ? p % pr.n[0] : (a == 1 ? (p / pr.n[0]) % pr.n[1] : p / (pr.n[0] * pr.n[1]));
+  double x = X[(((size_t)s * 2 + gr) * pr.P + p) * 3 + a];
+  if (idx > 0 && idx < pr.n[a] - 1) {
+    const double sc = sqrt((double)mult[d]);
+    double m = mean[d * NV + v];
+    if (shift && ams[s]) m += delta * (double)mult[d] * shift[(size_t)p * 6 + c];  // anticipated mean shift
+    x = fmin(fmax(m + sc * w, -0.5), pr.D[a] - 0.5);
+  }
+  out[v] = (float)(rint((x + 0.5) * kLat) / kLat - 0.5);
 }
 
 // Accept / apply one colour class of single-point elements.
@@ -702,8 +680,8 @@ dsm_status dsm_sample_estimated(dsm_problem* p, int32_t S, const float* X, int32
   const int64_t n = (int64_t)S * F * K;
   if (n == 0) return DSM_OK;  // empty buffers may be null
   if (!X || !fos_pts || !mean || !chol || !mult || !cand || n_clusters < 1 || (shift && !ams)) return DSM_ERR_ARG;
-  k_sample_est<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(
-      p->dev, S, X, F, fos_pts, K, mean, chol, mult, n_clusters, cluster, shift, ams, delta, seed, counter,
+  k_sample_dist<1, 8><<<(unsigned)((n + 31) / 32), 256, 0, (hipStream_t)stream>>>(
+      p->dev, S, X, F, nullptr, fos_pts, K, mean, chol, mult, n_clusters, cluster, shift, ams, delta, seed, counter,
       (const unsigned long long*)counter_dev, cand);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
@@ -729,8 +707,8 @@ dsm_status dsm_sample_elements(dsm_problem* p, int32_t S, const float* X, int32_
   if (n == 0) return DSM_OK;  // empty buffers may be null
   if (!X || !fos_off || !fos_pts || !mean || !chol || !mult || !cand || n_clusters < 1 || (shift && !ams))
     return DSM_ERR_ARG;
-  k_sample_el<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(
-      p->dev, S, X, F, fos_off, fos_pts, mean, chol, mult, n_clusters, cluster, shift, ams, delta, seed, counter,
+  k_sample_dist<kEstPoints, 32><<<(unsigned)((n + 7) / 8), 256, 0, (hipStream_t)stream>>>(
+      p->dev, S, X, F, fos_off, fos_pts, 1, mean, chol, mult, n_clusters, cluster, shift, ams, delta, seed, counter,
       (const unsigned long long*)counter_dev, cand);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }

@@ -55,3 +55,61 @@ def test_estimate_tiles(tiny_problem, n_sel):
     rmean, _, rchol = G.estimate(X, sel, p1, w.mesh)
     np.testing.assert_allclose(mean.cpu().numpy(), rmean, rtol=1e-12, atol=1e-12)
     np.testing.assert_allclose(chol.cpu().numpy(), np.array([G.packed_lower(L) for L in rchol]), rtol=1e-9, atol=1e-12)
+
+
+# rows that end inside a wave's lane groups; elements of every number of points, an invalid one, K candidates a point
+@pytest.mark.parametrize("S,K", [(1, 1), (7, 3), (33, 2)])
+def test_sampled_variables_follow_their_factor(tiny_problem, S, K):
+    """With one factor column set at a time to 1, the candidates of variable v
+    and of the column's own variable take the same draw; so L z is checked
+    against the draws themselves (a diagonal factor), variable by variable."""
+    w, gp = tiny_problem
+    X = _random_population(w, S, S + K)
+    tets = gp.topology()["tets"]
+    inner = 13  # the only point of the 3^3 mesh with 6 free coordinates
+    off = np.array([0, 1, 5, 10, 12], dtype=np.int32)  # 1 point, 4 points, 5 points (rejected), 2 points
+    pts = np.concatenate([[inner], tets[3], [0, 1, 2, 3, 4], [inner, inner]]).astype(np.int32)
+    F = len(off) - 1
+    rng = np.random.default_rng(3 * S + K)
+    mean = rng.uniform(8, 20, (1, F, 24))
+    low = np.tril(rng.uniform(0.2, 1.0, (F, 24, 24)))
+    mult = rng.uniform(0.5, 2.0, (1, F)).astype(np.float32)
+
+    def sample(Ls, mu):
+        packed = np.array([[G.packed_lower(L) for L in Ls]])
+        return gp.sample_elements(_t(X), _t(off), _t(pts), _t(mu), _t(packed), _t(mult), 5, 9).cpu().numpy()
+
+    # each draw at 1/1024 of a voxel a unit would round away; spread it over 256 lattice steps instead
+    eye = np.repeat(2.0 * np.eye(24)[None], F, axis=0)
+    zero = np.full((1, F, 24), 15.5)
+    draws = (sample(eye, zero).astype(np.float64) - 15.5) / 2.0
+    cand = sample(low, mean).astype(np.float64)
+    free = W.free_mask(w.mesh)
+    for f in (0, 1, 3):
+        n = 6 * (off[f + 1] - off[f])
+        fr = np.concatenate([np.tile(free[p], 2) for p in pts[off[f]:off[f + 1]]])
+        cur = np.concatenate([X[:, :, p].reshape(S, 6) for p in pts[off[f]:off[f + 1]]], axis=1).astype(np.float64)
+        z = draws[:, off[f]:off[f + 1]].reshape(S, n) / np.sqrt(mult[0, f])
+        z[:, ~fr] = 0.0  # pinned variables' draws do not show: leave them out of the factor
+        L = low[f][:n, :n] * fr[None, :]
+        got = cand[:, off[f]:off[f + 1]].reshape(S, n)
+        if fr.all():
+            want = mean[0, f, :n] + np.sqrt(mult[0, f]) * z @ L.T
+            # a draw is known to half a lattice step (1/256) over 2 sqrt(mult); L's rows sum to at most n
+            tol = 1 / 256 + n / 2 / 256
+            inside = (want > 0) & (want < 31)
+            assert np.all(np.abs(got - want)[inside] <= tol)
+        assert np.all(got[:, ~fr] == cur[:, ~fr])
+        assert np.all(np.rint((got + 0.5) * 128) == (got + 0.5) * 128)
+    assert np.all(np.isnan(cand[:, off[2]:off[3]]))
+    # single points: candidate k of point f of solution s takes draws 6 ((s F + f) K + k) ...; one call of K
+    # candidates equals the K-fold repetition of the points in a call of one
+    p1 = np.array([inner, 4, -1, 22], dtype=np.int32)
+    m1, l1 = rng.uniform(8, 20, (1, 4, 6)), np.tril(rng.uniform(0.2, 1.0, (4, 6, 6)))
+    pk1 = np.array([[G.packed_lower(L) for L in l1]])
+    mu1 = rng.uniform(0.5, 2, (1, 4)).astype(np.float32)
+    a = gp.sample_estimated(_t(X), _t(p1), K, _t(m1), _t(pk1), _t(mu1), 5, 9).cpu().numpy().reshape(S, 4, K, 6)
+    r = np.repeat(np.arange(4), K)
+    b = gp.sample_estimated(_t(X), _t(p1[r]), 1, _t(m1[:, r]), _t(pk1[:, r]), _t(mu1[:, r]), 5, 9)
+    np.testing.assert_array_equal(a, b.cpu().numpy().reshape(S, 4, K, 6))
+    assert np.all(np.isnan(a[:, 2])) and not np.any(np.isnan(a[:, [0, 1, 3]]))
