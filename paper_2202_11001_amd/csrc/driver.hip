@@ -281,16 +281,25 @@ __global__ __launch_bounds__(256) void k_sample_dist(DevProblem pr, int S, const
   out[v] = (float)(rint((x + 0.5) * kLat) / kLat - 0.5);
 }
 
-// Accept / apply one colour class of single-point elements.
-__global__ void k_accept(DevProblem pr, int S, float* __restrict__ X, int F, const int* __restrict__ off,
-                         const int* __restrict__ pts, const float* __restrict__ cand, const double* __restrict__ part_old,
-                         const double* __restrict__ part_new, const uint32_t* __restrict__ flags,
-                         const double* __restrict__ terms_cand, double* __restrict__ cache,
-                         const double* __restrict__ obj, int n_arch, const double* __restrict__ arch,
-                         const int* __restrict__ single_objective, unsigned char* __restrict__ accepted) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= S * F) return;
-  const int s = e / F, f = e % F;
+// Accept / apply one colour class of elements, one wave per (solution,
+// element) pair: the lanes share the scan of the archive (64 rows a round, up
+// to the first row of padding) and the copy of the element's coordinates and
+// of its points' candidate terms.  With a thread per pair, a pair's dependent
+// loads (up to the whole archive, then up to 4 x 48 tetrahedra x 3 terms) ran
+// one after another: 75 us a class of the phantom's 6^3 grid (2,000 pairs).
+__global__ __launch_bounds__(256) void k_accept(DevProblem pr, int S, float* __restrict__ X, int F,
+                                                const int* __restrict__ off, const int* __restrict__ pts,
+                                                const float* __restrict__ cand, const double* __restrict__ part_old,
+                                                const double* __restrict__ part_new, const uint32_t* __restrict__ flags,
+                                                const double* __restrict__ terms_cand, double* __restrict__ cache,
+                                                const double* __restrict__ obj, int n_arch,
+                                                const double* __restrict__ arch,
+                                                const int* __restrict__ single_objective,
+                                                unsigned char* __restrict__ accepted) {
+  const int64_t e = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;  // the same on every lane of a wave
+  const int lane = threadIdx.x & 63;
+  if (e >= (int64_t)S * F) return;
+  const int s = (int)(e / F), f = (int)(e - (int64_t)s * F);
   bool acc = flags[e] == 0u;
   if (acc) {
     double d[3], nv[3];
@@ -306,21 +315,31 @@ __global__ void k_accept(DevProblem pr, int S, float* __restrict__ X, int F, con
     if (so >= 0 && so < 3) {
       acc = d[so] < 0.0;  // a single-objective cluster's member: improve that objective
     } else if (!acc && n_arch > 0) {
-      bool dominated = false, improves = false;
+      bool improves = false;
       for (int o = 0; o < 3; ++o) improves = improves || d[o] < 0.0;
-      for (int q = 0; q < n_arch && !dominated; ++q) {
-        if (arch[(size_t)q * 3] == INFINITY) break;  // padding ends the archive
-        bool ale = true, alt = false;
-        for (int o = 0; o < 3; ++o) {
-          ale = ale && arch[(size_t)q * 3 + o] <= nv[o];
-          alt = alt || arch[(size_t)q * 3 + o] < nv[o];
+      bool dominated = false;
+      for (int q0 = 0; improves && q0 < n_arch && !dominated; q0 += 64) {
+        const int q = q0 + lane;
+        bool end = q >= n_arch, dom = false;
+        if (!end) {
+          const double* a = arch + (size_t)q * 3;
+          end = a[0] == INFINITY;  // padding ends the archive
+          bool ale = true, alt = false;
+          for (int o = 0; o < 3; ++o) {
+            ale = ale && a[o] <= nv[o];
+            alt = alt || a[o] < nv[o];
+          }
+          dom = ale && alt;
         }
-        dominated = ale && alt;
+        const unsigned long long ends = __ballot(end), doms = __ballot(dom);
+        const unsigned long long before = ends ? (ends & -ends) - 1 : ~0ull;  // rows ahead of the end
+        dominated = (doms & before) != 0;
+        if (ends) break;
       }
       acc = improves && !dominated;
     }
   }
-  if (accepted) accepted[e] = acc ? 1 : 0;
+  if (accepted && lane == 0) accepted[e] = acc ? 1 : 0;
   if (!acc) return;
   // the element's points: pts[off[f] .. off[f+1]) with candidates at
   // [s][off[F]][2][3], or the single point pts[f] without off
@@ -328,11 +347,12 @@ __global__ void k_accept(DevProblem pr, int S, float* __restrict__ X, int F, con
   for (int j = j0; j < j1; ++j) {
     const int p = pts[j];
     if (p < 0 || p >= pr.P) continue;  // such elements are flagged by the evaluator
-    for (int c = 0; c < 6; ++c)
-      X[(((size_t)s * 2 + c / 3) * pr.P + p) * 3 + c % 3] = cand[((size_t)s * n + j) * 6 + c];
-    for (int k = pr.star_off[p]; k < pr.star_off[p + 1]; ++k) {
-      const size_t t = (size_t)s * pr.T + pr.star[k];
-      for (int o = 0; o < 3; ++o) cache[t * 3 + o] = terms_cand[t * 3 + o];
+    if (lane < 6)
+      X[(((size_t)s * 2 + lane / 3) * pr.P + p) * 3 + lane % 3] = cand[((size_t)s * n + j) * 6 + lane];
+    const int k0 = pr.star_off[p], m = 3 * (pr.star_off[p + 1] - k0);
+    for (int i = lane; i < m; i += 64) {
+      const size_t t = ((size_t)s * pr.T + pr.star[k0 + i / 3]) * 3 + i % 3;
+      cache[t] = terms_cand[t];
     }
   }
 }
@@ -382,56 +402,70 @@ __global__ void k_donor(int S, int P, const float* __restrict__ X, int n, const 
 // accepted candidates of the cluster's solutions, compared with the
 // distribution's mean variable by variable in units of the variable's standard
 // deviation (sqrt of the row norm of L); the largest ratio, or -1 without an
-// accepted candidate.  One wave per (cluster, element): the candidates are
-// staged in LDS tiles and lane v sums variable v over the solutions in order.
-constexpr int kSdrTile = 128;
+// accepted candidate.  One workgroup per (cluster, element): its threads test
+// a solution each and list the accepted ones in order, then only those are
+// staged and summed (lane v variable v, in solution order): few of a cluster's
+// solutions accept, and a pass over all of them took 61 us for 500 solutions,
+// most of it waiting for one row after another.
+constexpr int kSdrTile = 256;
 
-__global__ __launch_bounds__(64) void k_sdr(int S, int F, const int* __restrict__ off, const float* __restrict__ cand,
-                                            const unsigned char* __restrict__ accepted, int n_clusters,
-                                            const int* __restrict__ cluster, const double* __restrict__ mean,
-                                            const double* __restrict__ chol, int nvar, double* __restrict__ sdr) {
+__global__ __launch_bounds__(kSdrTile) void k_sdr(int S, int F, const int* __restrict__ off,
+                                                  const float* __restrict__ cand,
+                                                  const unsigned char* __restrict__ accepted, int n_clusters,
+                                                  const int* __restrict__ cluster, const double* __restrict__ mean,
+                                                  const double* __restrict__ chol, int nvar, double* __restrict__ sdr) {
   __shared__ float s_x[kSdrTile][kEstVars];
-  __shared__ int s_use[kSdrTile];
-  const int e = blockIdx.x, lane = threadIdx.x;
+  __shared__ int s_row[kSdrTile];
+  __shared__ int s_cnt[kSdrTile / 64];
+  __shared__ double s_L[kEstTri];
+  const int e = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int j = e / F, f = e % F;
   const int b = off[f], np = off[f + 1] - b, total = off[F];
   const int nv = 6 * np;
   if (b < 0 || np < 1 || nv > nvar || b + np > total) {
-    if (lane == 0) sdr[e] = -1.0;
+    if (t == 0) sdr[e] = -1.0;
     return;
   }
+  const int tri = nvar * (nvar + 1) / 2;
+  for (int i = t; i < tri; i += kSdrTile) s_L[i] = chol[(size_t)e * tri + i];
   double sum = 0.0;
   int n = 0;
   for (int s0 = 0; s0 < S; s0 += kSdrTile) {
-    const int rows = min(kSdrTile, S - s0);
-    for (int i = lane; i < rows; i += 64) {
-      const int s = s0 + i;
-      s_use[i] = (cluster ? cluster[s] : 0) == j && accepted[(size_t)s * F + f];
+    const int s = s0 + t;
+    const bool use = s < S && (cluster ? cluster[s] : 0) == j && accepted[(size_t)s * F + f];
+    const unsigned long long m = __ballot(use);
+    if (lane == 0) s_cnt[wave] = __popcll(m);
+    __syncthreads();
+    int at = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)), rows = 0;
+    for (int w = 0; w < kSdrTile / 64; ++w) {
+      at += w < wave ? s_cnt[w] : 0;
+      rows += s_cnt[w];
+    }
+    if (use) s_row[at] = s;
+    __syncthreads();
+    for (int q = t; q < rows * nv; q += kSdrTile) {
+      const int i = q / nv, v = q - i * nv;
+      s_x[i][v] = cand[((size_t)s_row[i] * total + b) * 6 + v];
     }
     __syncthreads();
-    for (int q = lane; q < rows * nv; q += 64) {
-      const int i = q / nv, v = q % nv;
-      s_x[i][v] = s_use[i] ? cand[((size_t)(s0 + i) * total + b) * 6 + v] : 0.f;
+    if (t < nv) {
+#pragma unroll 4
+      for (int i = 0; i < rows; ++i) sum += (double)s_x[i][t];
     }
-    __syncthreads();
-    for (int i = 0; i < rows; ++i)
-      if (s_use[i]) {
-        if (lane < nv) sum += (double)s_x[i][lane];
-        ++n;
-      }
+    n += rows;
     __syncthreads();
   }
   if (n == 0) {
-    if (lane == 0) sdr[e] = -1.0;
+    if (t == 0) sdr[e] = -1.0;
     return;
   }
+  if (wave != 0) return;
   double r = 0.0;
   if (lane < nv) {
-    const double* mu = mean + (size_t)e * nvar;
-    const double* L = chol + (size_t)e * (nvar * (nvar + 1) / 2);
+    const double* L = s_L + lane * (lane + 1) / 2;
     double s2 = 0.0;
-    for (int k = 0; k <= lane; ++k) s2 += L[lane * (lane + 1) / 2 + k] * L[lane * (lane + 1) / 2 + k];
-    if (s2 > 0.0) r = fabs(sum / n - mu[lane]) / sqrt(s2);
+    for (int k = 0; k <= lane; ++k) s2 += L[k] * L[k];
+    if (s2 > 0.0) r = fabs(sum / n - mean[(size_t)e * nvar + lane]) / sqrt(s2);
   }
   for (int m = 32; m >= 1; m >>= 1) r = fmax(r, __shfl_xor(r, m, 64));  // the maximum does not depend on order
   if (lane == 0) sdr[e] = r;
@@ -744,7 +778,7 @@ dsm_status dsm_accept(dsm_problem* p, int32_t S, float* X, int32_t F, const int3
     return DSM_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
   if (F > 0)
-    k_accept<<<(S * F + 255) / 256, 256, 0, st>>>(p->dev, S, X, F, nullptr, fos_pts, cand, part_old, part_new, flags,
+    k_accept<<<(unsigned)(((int64_t)S * F + 3) / 4), 256, 0, st>>>(p->dev, S, X, F, nullptr, fos_pts, cand, part_old, part_new, flags,
                                                    terms_cand, terms_cache, obj, n_archive, archive, single_objective,
                                                    accepted);
   if (hipGetLastError() != hipSuccess) return DSM_ERR_DEVICE;
@@ -758,7 +792,7 @@ dsm_status dsm_improvement_ratio(int32_t S, int32_t F, const int32_t* fos_off, c
   const int64_t n = (int64_t)n_clusters * F;
   if (n == 0) return DSM_OK;
   if (!fos_off || !mean || !chol || !sdr || (S > 0 && (!cand || !accepted))) return DSM_ERR_ARG;
-  k_sdr<<<(unsigned)n, 64, 0, (hipStream_t)stream>>>(S, F, fos_off, cand, accepted, n_clusters, cluster, mean, chol,
+  k_sdr<<<(unsigned)n, kSdrTile, 0, (hipStream_t)stream>>>(S, F, fos_off, cand, accepted, n_clusters, cluster, mean, chol,
                                                     n_vars, sdr);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
@@ -785,7 +819,7 @@ dsm_status dsm_accept_elements(dsm_problem* p, int32_t S, float* X, int32_t F, c
     return DSM_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
   if (F > 0)
-    k_accept<<<(S * F + 255) / 256, 256, 0, st>>>(p->dev, S, X, F, fos_off, fos_pts, cand, part_old, part_new, flags,
+    k_accept<<<(unsigned)(((int64_t)S * F + 3) / 4), 256, 0, st>>>(p->dev, S, X, F, fos_off, fos_pts, cand, part_old, part_new, flags,
                                                    terms_cand, terms_cache, obj, n_archive, archive, single_objective,
                                                    accepted);
   if (hipGetLastError() != hipSuccess) return DSM_ERR_DEVICE;

@@ -113,3 +113,68 @@ def test_sampled_variables_follow_their_factor(tiny_problem, S, K):
     b = gp.sample_estimated(_t(X), _t(p1[r]), 1, _t(m1[:, r]), _t(pk1[:, r]), _t(mu1[:, r]), 5, 9)
     np.testing.assert_array_equal(a, b.cpu().numpy().reshape(S, 4, K, 6))
     assert np.all(np.isnan(a[:, 2])) and not np.any(np.isnan(a[:, [0, 1, 3]]))
+
+
+# archives that end inside, at and after a wave's 64 rows, with and without padding
+@pytest.mark.parametrize("n_arch,pad", [(0, 0), (1, 70), (63, 1), (64, 0), (64, 64), (65, 200), (130, 0)])
+def test_acceptance_against_archives(tiny_problem, n_arch, pad):
+    w, gp = tiny_problem
+    S, pts = 24, np.array([0, 2, 13, 26], dtype=np.int32)
+    F = len(pts)
+    rng = np.random.default_rng(n_arch + pad)
+    X = _random_population(w, S, 5)
+    cand = W.candidates(X, np.arange(F + 1), pts, w.mesh, w.dims, 1.0, 6).astype(np.float32)
+    obj = rng.uniform(1, 2, (S, 3))
+    old = rng.uniform(0, 1, (S, F, 3))
+    new = old + rng.choice([-0.2, 0.0, 0.2], (S, F, 3))
+    flags = rng.choice([0, 0, 0, 1], (S, F)).astype(np.int32)
+    arch = rng.uniform(0.9, 2.2, (n_arch, 3))
+    behind = np.concatenate([np.full((min(pad, 1), 3), np.inf), np.zeros((max(pad - 1, 0), 3))])  # not looked at
+    arch_all = np.concatenate([arch, behind])
+    tc, cache = rng.uniform(0, 1, (2, S, gp.T, 3))
+    d = new - old
+    dX, dcache, dobj = _t(X.copy()), _t(cache.copy()), _t(obj.copy())
+    acc = torch.empty((S, F), dtype=torch.uint8, device=DEV)
+    gp.accept(dX, _t(pts), _t(cand), _t(old), _t(new), _t(flags), _t(tc), dcache, dobj,
+              archive=_t(arch_all) if len(arch_all) else None, accepted=acc)
+    nv = obj[:, None] + d
+    want = (d <= 0).all(2) & (d < 0).any(2)
+    if len(arch_all):
+        dom = ((arch[None, None] <= nv[:, :, None]).all(3) & (arch[None, None] < nv[:, :, None]).any(3)).any(2)
+        want |= (d < 0).any(2) & ~dom
+    want &= flags == 0
+    np.testing.assert_array_equal(acc.cpu().numpy() != 0, want)
+    eX, ecache = X.copy(), cache.copy()
+    topo = gp.topology()
+    for s in range(S):
+        for f in np.nonzero(want[s])[0]:
+            p = pts[f]
+            eX[s, :, p] = cand[s, f]
+            star = topo["star"][topo["star_off"][p]:topo["star_off"][p + 1]]
+            ecache[s, star] = tc[s, star]
+    # stars of the four points overlap on this small mesh, but every element copies the same terms_cand rows
+    np.testing.assert_array_equal(dX.cpu().numpy(), eX)
+    np.testing.assert_array_equal(dcache.cpu().numpy(), ecache)
+
+
+# solutions that fill a tile of 256, spill over it by one, and take two; all, some and none accepted
+@pytest.mark.parametrize("S,share", [(1, 1.0), (64, 0.5), (256, 1.0), (257, 0.3), (520, 1.0), (520, 0.0)])
+def test_improvement_ratio_tiles(S, share):
+    rng = np.random.default_rng(S)
+    F, C = 3, 2
+    off = np.array([0, 4, 5, 10], dtype=np.int32)  # 4 points, 1 point, 5 points (rejected)
+    cand = rng.normal(30, 3, (S, 10, 2, 3)).astype(np.float32)
+    acc = (rng.uniform(0, 1, (S, F)) < share).astype(np.uint8)
+    cl = rng.integers(0, C, S).astype(np.int32)
+    mean = rng.normal(30, 1, (C, F, 24))
+    Ls = np.tril(rng.uniform(0.5, 1.5, (C, F, 24, 24)))
+    packed = np.array([[G.packed_lower(Ls[j, f]) for f in range(F)] for j in range(C)])
+    got = dsm.improvement_ratio(_t(off), _t(cand), _t(acc), _t(mean), _t(packed), cluster=_t(cl)).cpu().numpy()
+    for j in range(C):
+        for f in range(2):
+            n = 6 * (off[f + 1] - off[f])
+            rows = [cand[s, off[f]:off[f + 1]].reshape(-1) for s in range(S) if cl[s] == j and acc[s, f]]
+            L = Ls[j, f][:n, :n]
+            want = G.standard_deviation_ratio(np.array(rows).reshape(-1, n), mean[j, f, :n], L @ L.T)
+            np.testing.assert_allclose(got[j, f], want, rtol=1e-9, atol=1e-12)
+    assert np.all(got[:, 2] == -1.0)
