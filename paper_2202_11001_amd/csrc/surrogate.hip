@@ -58,49 +58,6 @@ struct MlpW {
   const float *b1, *b2, *b3;             // FP32 biases
 };
 
-// LDS tile of one wave: 16 rows x 128 columns of BF16 with a padded stride
-constexpr int kLdsStride = 136;
-
-// Y[16][16] (+bias) = A[16][K] x W^T, W [ncols][K] row-major BF16; A is either
-// a global BF16 matrix (rows a_row0.., stride a_stride, rows >= nrows zero) or an
-// LDS tile.  Applies ReLU and stores BF16 into `out` (LDS tile) when relu_out.
-template <int K>
-__device__ __forceinline__ f32x4 tile_product(const unsigned short* A, int a_stride, bool a_valid, const unsigned short* W,
-                                              int col0, int lane) {
-  const int i = lane & 15, kb = lane >> 4;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int kk = 0; kk < K / 32; ++kk) {
-    const u16x8 a = a_valid ? load8(A + (size_t)i * a_stride + 32 * kk + 8 * kb) : zero8();
-    const u16x8 b = load8(W + (size_t)(col0 + i) * K + 32 * kk + 8 * kb);
-    acc = mfma(a, b, acc);
-  }
-  return acc;
-}
-
-// Forward pass of 16 rows held by one wave.  x: global BF16 rows (stride 192)
-// of which `valid` exist.  Leaves H1 and H2 (BF16, post-ReLU) in LDS tiles and
-// returns the outputs of row 4*kb + r, column i in y[r] (columns >= 3 are 0).
-__device__ void forward16(const MlpW& w, const unsigned short* x, bool row_valid, unsigned short* h1,
-                          unsigned short* h2, int lane, f32x4& y) {
-  const int i = lane & 15, kb = lane >> 4;
-  for (int ct = 0; ct < kHid / 16; ++ct) {
-    const f32x4 acc = tile_product<kIn>(x, kIn, row_valid, w.w1, 16 * ct, lane);
-    const float b = w.b1[16 * ct + i];
-    for (int r = 0; r < 4; ++r) h1[(4 * kb + r) * kLdsStride + 16 * ct + i] = f2bf(fmaxf(acc[r] + b, 0.f));
-  }
-  __syncthreads();
-  for (int ct = 0; ct < kHid / 16; ++ct) {
-    const f32x4 acc = tile_product<kHid>(h1, kLdsStride, true, w.w2, 16 * ct, lane);
-    const float b = w.b2[16 * ct + i];
-    for (int r = 0; r < 4; ++r) h2[(4 * kb + r) * kLdsStride + 16 * ct + i] = f2bf(fmaxf(acc[r] + b, 0.f));
-  }
-  __syncthreads();
-  const f32x4 acc = tile_product<kHid>(h2, kLdsStride, true, w.w3, 0, lane);
-  const float b = w.b3[i];
-  for (int r = 0; r < 4; ++r) y[r] = i < kOut ? acc[r] + b : 0.f;
-}
-
 // Screening forward pass: 64 rows per workgroup of 4 waves.  The rows are
 // staged in LDS once; each wave computes a 32-column slice of a layer for all
 // 64 rows, so every weight fragment read from memory serves 4 row blocks.
@@ -183,196 +140,271 @@ __global__ __launch_bounds__(256) void k_mlp_forward64(MlpW w, const unsigned sh
   }
 }
 
-// Training rows: forward and backward of 16 minibatch rows per wave.  Writes
-// the transposed BF16 operands of the weight-gradient products (inputs X, H1,
-// H2 and output gradients dY, dZ2, dZ1, all [features][batch]) and the per-row
-// squared error.  Loss = (1/B) sum_rows sum_{3 outputs} (y - t)^2.
+// One training step is three kernels: forward and backward of the minibatch
+// rows (k_mlp_rows), the weight and bias gradients (k_mlp_wgrad) and the update
+// (k_mlp_update).  At 4096 rows each is a few microseconds of a chain of
+// dependent loads on a mostly idle chip, so the step is bound by the number of
+// kernels and by how short each chain is: a step took 150 us as nine kernels
+// (three weight-gradient products of 31 us each, one wave per 16x16 tile
+// waiting for each step's operands; rows 28; bias sums 16; Adam, operand
+// refresh and row draws 5 each).  The sums over the batch keep their order
+// (one accumulator per gradient entry over the whole batch): Adam's first
+// steps turn a changed rounding of a small gradient into a change of the
+// weights, so slices of the batch summed apart (the faster form by itself)
+// moved trained weights by 1e-4 within 8 steps.
+
+// k_mlp_rows writes the transposed BF16 operands of the weight-gradient
+// products (inputs X, H1, H2 and output gradients dY, dZ2, dZ1, all
+// [features][batch]) and the per-row squared error.  Loss = (1/B) sum_rows
+// sum_{3 outputs} (y - t)^2.
 struct TrainWs {
   unsigned short *xt, *h1t, *h2t, *dyt, *dz2t, *dz1t;  // [192|128|128|16|128|128][ld]
   float* row_loss;                                      // [B]
   int ld;                                               // B rounded up to a multiple of 32; rows past B are zero
 };
 
-__global__ __launch_bounds__(64) void k_mlp_rows(MlpW w, const unsigned short* __restrict__ xb,
-                                                 const float* __restrict__ targets, const int* __restrict__ idx, int B,
-                                                 TrainWs ws) {
-  __shared__ __align__(16) unsigned short h1[16 * kLdsStride], h2[16 * kLdsStride], dz[16 * kLdsStride];
-  __shared__ __align__(16) unsigned short xr[16 * kIn];
-  __shared__ __align__(16) unsigned short dy[16 * 32];
-  __shared__ float sq[16][4];
-  const int lane = threadIdx.x, i = lane & 15, kb = lane >> 4;
-  const int b0 = blockIdx.x * 16;
-  // gather the 16 input rows into LDS (rows past B are zero)
-  for (int e = lane; e < 16 * kIn / 8; e += 64) {
-    const int r = e / (kIn / 8), c = e % (kIn / 8);
-    const u16x8 v = (b0 + r < B) ? load8(xb + (size_t)idx[b0 + r] * kIn + 8 * c) : zero8();
-    *(u16x8*)(xr + r * kIn + 8 * c) = v;
-  }
-  __syncthreads();
-  f32x4 y;
-  forward16(w, xr, true, h1, h2, lane, y);
-  // dY = 2 (y - t) / (3 B), rows past B contribute nothing
-  for (int r = 0; r < 4; ++r) {
-    const int row = 4 * kb + r, brow = b0 + row;
-    float g = 0.f, e2 = 0.f;
-    if (i < kOut && brow < B) {
-      const float d = y[r] - targets[(size_t)idx[brow] * kOut + i];
-      e2 = d * d;
-      g = 2.f * d / (3.f * (float)B);
-    }
-    dy[row * 32 + i] = f2bf(g);
-    dy[row * 32 + 16 + i] = 0;
-    if (i < 4) sq[row][i] = i < kOut ? e2 : 0.f;
-  }
-  __syncthreads();
-  if (lane < 16 && b0 + lane < B) ws.row_loss[b0 + lane] = sq[lane][0] + sq[lane][1] + sq[lane][2];
-  // transposed copies of X, H1, H2, dY
-  for (int e = lane; e < 16 * kIn; e += 64) {
-    const int r = e % 16, c = e / 16;
-    if (b0 + r < ws.ld) ws.xt[(size_t)c * ws.ld + b0 + r] = xr[r * kIn + c];
-  }
-  for (int e = lane; e < 16 * kHid; e += 64) {
-    const int r = e % 16, c = e / 16;
-    if (b0 + r < ws.ld) {
-      ws.h1t[(size_t)c * ws.ld + b0 + r] = h1[r * kLdsStride + c];
-      ws.h2t[(size_t)c * ws.ld + b0 + r] = h2[r * kLdsStride + c];
-    }
-  }
-  for (int e = lane; e < 16 * kOutPad; e += 64) {
-    const int r = e % 16, c = e / 16;
-    if (b0 + r < ws.ld) ws.dyt[(size_t)c * ws.ld + b0 + r] = dy[r * 32 + c];
-  }
-  // dZ2 = (dY W3) * [H2 > 0]: A = dY [16][32] (columns >= 16 zero), B[o][j] = W3t[j][o]
-  for (int ct = 0; ct < kHid / 16; ++ct) {
-    const u16x8 a = load8(dy + i * 32 + 8 * kb);
-    const u16x8 bm = kb < 2 ? load8(w.w3t + (size_t)(16 * ct + i) * kOutPad + 8 * kb) : zero8();
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mfma(a, bm, acc);
-    for (int r = 0; r < 4; ++r) {
-      const int row = 4 * kb + r, col = 16 * ct + i;
-      const float g = bf2f(h2[row * kLdsStride + col]) > 0.f ? acc[r] : 0.f;
-      dz[row * kLdsStride + col] = f2bf(g);
-    }
-  }
-  __syncthreads();
-  for (int e = lane; e < 16 * kHid; e += 64) {
-    const int r = e % 16, c = e / 16;
-    if (b0 + r < ws.ld) ws.dz2t[(size_t)c * ws.ld + b0 + r] = dz[r * kLdsStride + c];
-  }
-  // dZ1 = (dZ2 W2) * [H1 > 0]: B[m][j] = W2t[j][m]
-  f32x4 accs[kHid / 16];
-  for (int ct = 0; ct < kHid / 16; ++ct) accs[ct] = tile_product<kHid>(dz, kLdsStride, true, w.w2t, 16 * ct, lane);
-  __syncthreads();
-  for (int ct = 0; ct < kHid / 16; ++ct)
-    for (int r = 0; r < 4; ++r) {
-      const int row = 4 * kb + r, col = 16 * ct + i;
-      const float g = bf2f(h1[row * kLdsStride + col]) > 0.f ? accs[ct][r] : 0.f;
-      dz[row * kLdsStride + col] = f2bf(g);
-    }
-  __syncthreads();
-  for (int e = lane; e < 16 * kHid; e += 64) {
-    const int r = e % 16, c = e / 16;
-    if (b0 + r < ws.ld) ws.dz1t[(size_t)c * ws.ld + b0 + r] = dz[r * kLdsStride + c];
-  }
-}
-
-// Weight gradients dW[o][c] = sum_b dZt[o][b] At[c][b] for one 16x16 tile per
-// wave; B is a multiple of 32 (callers pad with zero rows).
-__global__ __launch_bounds__(64) void k_mlp_wgrad(const unsigned short* __restrict__ dzt, const unsigned short* __restrict__ at,
-                                                  int B, int ncols, float* __restrict__ dw) {
-  const int lane = threadIdx.x, i = lane & 15, kb = lane >> 4;
-  const int ot = blockIdx.y, ctile = blockIdx.x;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < B; k0 += 32) {
-    const u16x8 a = load8(dzt + (size_t)(16 * ot + i) * B + k0 + 8 * kb);
-    const u16x8 b = load8(at + (size_t)(16 * ctile + i) * B + k0 + 8 * kb);
-    acc = mfma(a, b, acc);
-  }
-  for (int r = 0; r < 4; ++r) dw[(size_t)(16 * ot + 4 * kb + r) * ncols + 16 * ctile + i] = acc[r];
-}
-
-// Bias gradients and the minibatch loss: one wave per sum, lanes over the
-// batch in a fixed order, then a fixed shuffle tree (deterministic).
-__global__ __launch_bounds__(64) void k_mlp_bias_loss(const unsigned short* __restrict__ dz1t,
-                                                      const unsigned short* __restrict__ dz2t,
-                                                      const unsigned short* __restrict__ dyt,
-                                                      const float* __restrict__ row_loss, int B, int ld,
-                                                      float* __restrict__ grad, float* __restrict__ loss_out) {
-  const int t = blockIdx.x, lane = threadIdx.x;
-  const unsigned short* src = nullptr;
-  float* dst = nullptr;
-  if (t < kHid) {
-    src = dz1t + (size_t)t * ld;
-    dst = grad + kB1 + t;
-  } else if (t < 2 * kHid) {
-    src = dz2t + (size_t)(t - kHid) * ld;
-    dst = grad + kB2 + (t - kHid);
-  } else if (t < 2 * kHid + kOutPad) {
-    src = dyt + (size_t)(t - 2 * kHid) * ld;
-    dst = grad + kB3 + (t - 2 * kHid);
-  }
-  float acc = 0.f;
-  if (src) {
-    for (int b = lane; b < B; b += 64) acc += bf2f(src[b]);
-  } else {
-    for (int b = lane; b < B; b += 64) acc += row_loss[b];
-  }
-  for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-  if (lane == 0) {
-    if (src)
-      *dst = acc;
-    else if (loss_out)
-      *loss_out = acc / (3.f * (float)B);
-  }
-}
-
-// Adam step on the FP32 master parameters, then refresh of the BF16 operand copies.
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m, float* __restrict__ v,
-                       float lr, float b1, float b2, float eps, float c1, float c2) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= kNParams) return;
-  const float gi = g[t];
-  const float mi = b1 * m[t] + (1.f - b1) * gi;
-  const float vi = b2 * v[t] + (1.f - b2) * gi * gi;
-  m[t] = mi;
-  v[t] = vi;
-  p[t] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-}
-
-__global__ void k_refresh_bf16(const float* __restrict__ p, unsigned short* w1, unsigned short* w2, unsigned short* w3,
-                               unsigned short* w2t, unsigned short* w3t) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < kHid * kIn) w1[t] = f2bf(p[kW1 + t]);
-  if (t < kHid * kHid) {
-    const int o = t / kHid, c = t % kHid;
-    w2[t] = f2bf(p[kW2 + t]);
-    w2t[c * kHid + o] = f2bf(p[kW2 + t]);
-  }
-  if (t < kOutPad * kHid) {
-    const int o = t / kHid, c = t % kHid;
-    w3[t] = f2bf(p[kW3 + t]);
-    w3t[c * kOutPad + o] = f2bf(p[kW3 + t]);
-  }
-}
-
-// Counter-based minibatch indices (splitmix64 of (seed, step, slot)).
-__global__ void k_batch_indices(unsigned long long seed, int step, int N, int B, int Bpad, int* idx) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= Bpad) return;
-  if (b >= B) {
-    idx[b] = 0;
-    return;
-  }
+// Row of the data that minibatch slot b of a step holds: counter-based
+// (splitmix64 of (seed, step, slot)), or slot b itself for step < 0.
+__device__ __forceinline__ int batch_row(unsigned long long seed, int step, int N, int b) {
+  if (step < 0) return b;
   unsigned long long z = seed + 0x9e3779b97f4a7c15ull * ((unsigned long long)step * 0x100000001ull + (unsigned long long)b + 1);
   z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
   z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
   z ^= z >> 31;
-  idx[b] = (int)(z % (unsigned long long)N);
+  return (int)(z % (unsigned long long)N);
 }
 
-__global__ void k_iota(int n, int* idx) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < n) idx[b] = b;
+// Stores an LDS tile of 16 rows (stride `stride`) x ncols transposed at
+// dst [ncols][ld], columns b0 .. b0 + 15: 16 bytes (8 rows of a column) a store.
+__device__ __forceinline__ void store_transposed(const unsigned short* tile, int stride, int ncols, unsigned short* dst,
+                                                 int ld, int b0, int tid) {
+  for (int e = tid; e < 2 * ncols; e += 256) {
+    const int c = e >> 1, r0 = 8 * (e & 1);
+    u16x8 v;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = tile[(r0 + r) * stride + c];
+    *(u16x8*)(dst + (size_t)c * ld + b0 + r0) = v;  // ld and b0 are multiples of 16
+  }
+}
+
+// 16 rows per workgroup, each of the 4 waves computing 32 of the 128 columns
+// of a layer; its weight fragments are loaded before the rows arrive.
+__global__ __launch_bounds__(256) void k_mlp_rows(MlpW w, const unsigned short* __restrict__ xb,
+                                                  const float* __restrict__ targets, unsigned long long seed, int step,
+                                                  int N, int B, TrainWs ws) {
+  __shared__ __align__(16) unsigned short xr[16 * kXs], h1[16 * kHs], h2[16 * kHs], dz2[16 * kHs], dz1[16 * kHs];
+  __shared__ __align__(16) unsigned short dy[16 * 32];
+  __shared__ float sq[16][4];
+  __shared__ int s_idx[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, kb = lane >> 4;
+  const int b0 = blockIdx.x * 16;
+  u16x8 w1[2][kIn / 32], w2[2][kHid / 32], w2t[2][kHid / 32];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int col = 32 * wave + 16 * t + i;
+#pragma unroll
+    for (int kk = 0; kk < kIn / 32; ++kk) w1[t][kk] = load8(w.w1 + (size_t)col * kIn + 32 * kk + 8 * kb);
+#pragma unroll
+    for (int kk = 0; kk < kHid / 32; ++kk) {
+      w2[t][kk] = load8(w.w2 + (size_t)col * kHid + 32 * kk + 8 * kb);
+      w2t[t][kk] = load8(w.w2t + (size_t)col * kHid + 32 * kk + 8 * kb);
+    }
+  }
+  if (tid < 16) s_idx[tid] = b0 + tid < B ? batch_row(seed, step, N, b0 + tid) : 0;
+  __syncthreads();
+  // gather the 16 input rows into LDS (rows past B are zero)
+  for (int e = tid; e < 16 * kIn / 8; e += 256) {
+    const int r = e / (kIn / 8), c = e % (kIn / 8);
+    const u16x8 v = (b0 + r < B) ? load8(xb + (size_t)s_idx[r] * kIn + 8 * c) : zero8();
+    *(u16x8*)(xr + r * kXs + 8 * c) = v;
+  }
+  __syncthreads();
+  // H1 = relu(X W1^T + b1), H2 = relu(H1 W2^T + b2): this lane's columns stay
+  // in registers as the ReLU masks of the backward pass
+  unsigned short m1[2][4], m2[2][4];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int col = 32 * wave + 16 * t + i;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < kIn / 32; ++kk) acc = mfma(*(const u16x8*)(xr + i * kXs + 32 * kk + 8 * kb), w1[t][kk], acc);
+    const float b = w.b1[col];
+    for (int r = 0; r < 4; ++r) h1[(4 * kb + r) * kHs + col] = m1[t][r] = f2bf(fmaxf(acc[r] + b, 0.f));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int col = 32 * wave + 16 * t + i;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < kHid / 32; ++kk) acc = mfma(*(const u16x8*)(h1 + i * kHs + 32 * kk + 8 * kb), w2[t][kk], acc);
+    const float b = w.b2[col];
+    for (int r = 0; r < 4; ++r) h2[(4 * kb + r) * kHs + col] = m2[t][r] = f2bf(fmaxf(acc[r] + b, 0.f));
+  }
+  __syncthreads();
+  if (wave == 0) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < kHid / 32; ++kk)
+      acc = mfma(*(const u16x8*)(h2 + i * kHs + 32 * kk + 8 * kb), load8(w.w3 + (size_t)i * kHid + 32 * kk + 8 * kb), acc);
+    const float bias = w.b3[i];
+    // dY = 2 (y - t) / (3 B), rows past B contribute nothing
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * kb + r;
+      float g = 0.f, e2 = 0.f;
+      if (i < kOut && b0 + row < B) {
+        const float d = acc[r] + bias - targets[(size_t)s_idx[row] * kOut + i];
+        e2 = d * d;
+        g = 2.f * d / (3.f * (float)B);
+      }
+      dy[row * 32 + i] = f2bf(g);
+      dy[row * 32 + 16 + i] = 0;
+      if (i < 4) sq[row][i] = i < kOut ? e2 : 0.f;
+    }
+  }
+  __syncthreads();
+  if (tid < 16 && b0 + tid < B) ws.row_loss[b0 + tid] = sq[tid][0] + sq[tid][1] + sq[tid][2];
+  // dZ2 = (dY W3) * [H2 > 0]: A = dY [16][32] (columns >= 16 zero), B[o][j] = W3t[j][o]
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int col = 32 * wave + 16 * t + i;
+    const u16x8 bm = kb < 2 ? load8(w.w3t + (size_t)col * kOutPad + 8 * kb) : zero8();
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    acc = mfma(*(const u16x8*)(dy + i * 32 + 8 * kb), bm, acc);
+    for (int r = 0; r < 4; ++r) dz2[(4 * kb + r) * kHs + col] = (short)m2[t][r] > 0 ? f2bf(acc[r]) : (unsigned short)0;
+  }
+  __syncthreads();
+  // dZ1 = (dZ2 W2) * [H1 > 0]: B[m][j] = W2t[j][m]
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int col = 32 * wave + 16 * t + i;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < kHid / 32; ++kk) acc = mfma(*(const u16x8*)(dz2 + i * kHs + 32 * kk + 8 * kb), w2t[t][kk], acc);
+    for (int r = 0; r < 4; ++r) dz1[(4 * kb + r) * kHs + col] = (short)m1[t][r] > 0 ? f2bf(acc[r]) : (unsigned short)0;
+  }
+  __syncthreads();
+  store_transposed(xr, kXs, kIn, ws.xt, ws.ld, b0, tid);
+  store_transposed(h1, kHs, kHid, ws.h1t, ws.ld, b0, tid);
+  store_transposed(h2, kHs, kHid, ws.h2t, ws.ld, b0, tid);
+  store_transposed(dy, 32, kOutPad, ws.dyt, ws.ld, b0, tid);
+  store_transposed(dz2, kHs, kHid, ws.dz2t, ws.ld, b0, tid);
+  store_transposed(dz1, kHs, kHid, ws.dz1t, ws.ld, b0, tid);
+}
+
+// Weight gradients dW[o][c] = sum_b dZt[o][b] At[c][b], one wave per 16x16
+// tile of a layer's matrix, and, in further waves, the bias gradients and the
+// minibatch loss (lanes over the batch in a fixed order, then a fixed shuffle
+// tree).  A tile is one chain of matrix instructions over the batch; the wave
+// keeps the operands of kAhead steps of 32 rows in flight in registers, since
+// a step's operands take about 40 times as long to arrive from L2 as its
+// instruction takes to issue.
+constexpr int kTiles1 = (kHid / 16) * (kIn / 16), kTiles2 = (kHid / 16) * (kHid / 16), kTiles3 = kHid / 16;
+constexpr int kTiles = kTiles1 + kTiles2 + kTiles3, kBiases = 2 * kHid + kOutPad;
+constexpr int kAhead = 16;
+
+__global__ __launch_bounds__(64) void k_mlp_wgrad(TrainWs ws, int B, float* __restrict__ grad,
+                                                  float* __restrict__ loss_out) {
+  const int lane = threadIdx.x, i = lane & 15, kb = lane >> 4, ld = ws.ld;
+  int tile = blockIdx.x;
+  if (tile >= kTiles) {
+    const int t = tile - kTiles;
+    float acc = 0.f;
+    if (t < kBiases) {
+      const unsigned short* src = t < kHid ? ws.dz1t + (size_t)t * ld
+                                           : (t < 2 * kHid ? ws.dz2t + (size_t)(t - kHid) * ld
+                                                           : ws.dyt + (size_t)(t - 2 * kHid) * ld);
+#pragma unroll 16
+      for (int b = lane; b < B; b += 64) acc += bf2f(src[b]);
+    } else {
+      if (!loss_out) return;
+#pragma unroll 16
+      for (int b = lane; b < B; b += 64) acc += ws.row_loss[b];
+    }
+    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (lane != 0) return;
+    if (t < kBiases)
+      grad[t < kHid ? kB1 + t : (t < 2 * kHid ? kB2 + (t - kHid) : kB3 + (t - 2 * kHid))] = acc;
+    else
+      *loss_out = acc / (3.f * (float)B);
+    return;
+  }
+  const unsigned short *dzt, *at;
+  int ncols, ow;  // columns of the layer, offset of its weights
+  if (tile < kTiles1) {
+    dzt = ws.dz1t, at = ws.xt, ncols = kIn, ow = kW1;
+  } else if (tile < kTiles1 + kTiles2) {
+    tile -= kTiles1;
+    dzt = ws.dz2t, at = ws.h1t, ncols = kHid, ow = kW2;
+  } else {
+    tile -= kTiles1 + kTiles2;
+    dzt = ws.dyt, at = ws.h2t, ncols = kHid, ow = kW3;
+  }
+  const int ot = tile / (ncols / 16), ct = tile % (ncols / 16);
+  const unsigned short* pa = dzt + (size_t)(16 * ot + i) * ld + 8 * kb;
+  const unsigned short* pb = at + (size_t)(16 * ct + i) * ld + 8 * kb;
+  const int nk = ld / 32, last = 32 * (nk - 1);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  u16x8 a[kAhead], b[kAhead];
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) {  // steps past the last one load it again and are not used
+    a[j] = load8(pa + min(32 * j, last));
+    b[j] = load8(pb + min(32 * j, last));
+  }
+  int k = 0;
+  for (; k + kAhead <= nk; k += kAhead) {
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      acc = mfma(a[j], b[j], acc);
+      const int next = min(32 * (k + kAhead + j), last);
+      a[j] = load8(pa + next);
+      b[j] = load8(pb + next);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j)
+    if (k + j < nk) acc = mfma(a[j], b[j], acc);
+  for (int r = 0; r < 4; ++r) grad[ow + (size_t)(16 * ot + 4 * kb + r) * ncols + 16 * ct + i] = acc[r];
+}
+
+// Adam step on the FP32 master parameters, with the BF16 operand copies.
+struct Operands {
+  unsigned short *w1, *w2, *w3, *w2t, *w3t;
+};
+
+__device__ __forceinline__ void refresh_operand(int t, float x, const Operands& o) {
+  const unsigned short b = f2bf(x);
+  if (t < kB1) {
+    o.w1[t] = b;
+  } else if (t >= kW2 && t < kB2) {
+    const int e = t - kW2;
+    o.w2[e] = b;
+    o.w2t[(e % kHid) * kHid + e / kHid] = b;
+  } else if (t >= kW3 && t < kB3) {
+    const int e = t - kW3;
+    o.w3[e] = b;
+    o.w3t[(e % kHid) * kOutPad + e / kHid] = b;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_mlp_update(const float* __restrict__ grad, float* __restrict__ p,
+                                                    float* __restrict__ m, float* __restrict__ v, float lr, float b1,
+                                                    float b2, float eps, float c1, float c2, Operands ops) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= kNParams) return;
+  const float gi = grad[t];
+  const float mi = b1 * m[t] + (1.f - b1) * gi;
+  const float vi = b2 * v[t] + (1.f - b2) * gi * gi;
+  m[t] = mi;
+  v[t] = vi;
+  const float x = p[t] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  p[t] = x;
+  refresh_operand(t, x, ops);
+}
+
+__global__ void k_refresh_bf16(const float* __restrict__ p, Operands ops) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < kNParams) refresh_operand(t, p[t], ops);
 }
 
 // ---------------------------------------------------------------- features
@@ -616,7 +648,6 @@ struct dsm_surrogate {
   unsigned short *d_xt = nullptr, *d_h1t = nullptr, *d_h2t = nullptr, *d_dyt = nullptr, *d_dz2t = nullptr,
                  *d_dz1t = nullptr;
   float* d_row_loss = nullptr;
-  int* d_idx = nullptr;
   // screening workspace for max_rows rows
   unsigned short* d_featb = nullptr;  // [max_rows][192]
   float* d_pred = nullptr;            // [max_rows][3]
@@ -649,31 +680,29 @@ void free_sur(dsm_surrogate* m) {
   void* bufs[] = {m->d_params, m->d_m,      m->d_v,        m->d_grad,     m->d_w1,      m->d_w2,   m->d_w3,
                   m->d_w2t,    m->d_w3t,    m->d_in_mean,  m->d_in_rstd,  m->d_out_mean, m->d_out_rstd,
                   m->d_out_scale, m->d_xt,  m->d_h1t,      m->d_h2t,      m->d_dyt,     m->d_dz2t, m->d_dz1t,
-                  m->d_row_loss, m->d_idx,  m->d_featb,    m->d_pred};
+                  m->d_row_loss, m->d_featb,    m->d_pred};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   delete m;
 }
 
+Operands operands(const dsm_surrogate* m) { return Operands{m->d_w1, m->d_w2, m->d_w3, m->d_w2t, m->d_w3t}; }
+
 hipError_t refresh(dsm_surrogate* m, hipStream_t st) {
-  k_refresh_bf16<<<(kHid * kIn + 255) / 256, 256, 0, st>>>(m->d_params, m->d_w1, m->d_w2, m->d_w3, m->d_w2t, m->d_w3t);
+  k_refresh_bf16<<<(kNParams + 255) / 256, 256, 0, st>>>(m->d_params, operands(m));
   return hipGetLastError();
 }
 
-// forward + backward of B rows given by d_idx; writes the gradient into d_grad
-hipError_t gradient_pass(dsm_surrogate* m, const unsigned short* feats, const float* targets, int B, float* loss,
-                         hipStream_t st) {
+// Forward and backward of B rows (those of minibatch `step` of the N rows, or
+// rows 0..B-1 for step < 0); writes the gradient to grad and the loss to loss (or null).
+hipError_t gradient_pass(dsm_surrogate* m, const unsigned short* feats, const float* targets, int step, int N, int B,
+                         float* loss, float* grad, hipStream_t st) {
   const int ld = (B + 31) / 32 * 32;
   TrainWs ws{m->d_xt, m->d_h1t, m->d_h2t, m->d_dyt, m->d_dz2t, m->d_dz1t, m->d_row_loss, ld};
-  k_mlp_rows<<<ld / 16, 64, 0, st>>>(weights(m), feats, targets, m->d_idx, B, ws);
+  k_mlp_rows<<<ld / 16, 256, 0, st>>>(weights(m), feats, targets, m->desc.seed, step, N, B, ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_mlp_wgrad<<<dim3(kIn / 16, kHid / 16), 64, 0, st>>>(m->d_dz1t, m->d_xt, ld, kIn, m->d_grad + kW1);
-  k_mlp_wgrad<<<dim3(kHid / 16, kHid / 16), 64, 0, st>>>(m->d_dz2t, m->d_h1t, ld, kHid, m->d_grad + kW2);
-  k_mlp_wgrad<<<dim3(kHid / 16, kOutPad / 16), 64, 0, st>>>(m->d_dyt, m->d_h2t, ld, kHid, m->d_grad + kW3);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_mlp_bias_loss<<<2 * kHid + kOutPad + 1, 64, 0, st>>>(m->d_dz1t, m->d_dz2t, m->d_dyt, m->d_row_loss, B, ld,
-                                                                    m->d_grad, loss);
+  k_mlp_wgrad<<<kTiles + kBiases + 1, 64, 0, st>>>(ws, B, grad, loss);
   return hipGetLastError();
 }
 
@@ -723,7 +752,6 @@ dsm_status dsm_surrogate_create(const dsm_surrogate_desc* d, dsm_surrogate** out
   S_TRY(hipMalloc(&m->d_dz2t, 2 * kHid * B));
   S_TRY(hipMalloc(&m->d_dz1t, 2 * kHid * B));
   S_TRY(hipMalloc(&m->d_row_loss, sizeof(float) * B));
-  S_TRY(hipMalloc(&m->d_idx, sizeof(int) * B));
   S_TRY(hipMalloc(&m->d_featb, 2 * kIn * (size_t)d->max_rows));
   S_TRY(hipMalloc(&m->d_pred, sizeof(float) * kOut * (size_t)d->max_rows));
   // He-uniform initial weights, zero biases (host, from the seed); identity scaling
@@ -748,7 +776,6 @@ dsm_status dsm_surrogate_create(const dsm_surrogate_desc* d, dsm_surrogate** out
   S_TRY(hipMemcpy(m->d_params, p.data(), sizeof(float) * kNParams, hipMemcpyHostToDevice));
   S_TRY(hipMemset(m->d_m, 0, sizeof(float) * kNParams));
   S_TRY(hipMemset(m->d_v, 0, sizeof(float) * kNParams));
-  S_TRY(hipMemset(m->d_grad, 0, sizeof(float) * kNParams));
   std::vector<float> zeros(kIn, 0.f), ones(kIn, 1.f);
   S_TRY(hipMemcpy(m->d_in_mean, zeros.data(), sizeof(float) * kIn, hipMemcpyHostToDevice));
   S_TRY(hipMemcpy(m->d_in_rstd, ones.data(), sizeof(float) * kIn, hipMemcpyHostToDevice));
@@ -883,9 +910,7 @@ dsm_status dsm_surrogate_gradient(dsm_surrogate* m, int32_t N, const uint16_t* f
   if (!m || !feats_bf16 || !targets || !grad) return sfail(DSM_ERR_ARG, "null argument");
   if (N < 1 || N > m->bpad) return sfail(DSM_ERR_CAPACITY, "N outside [1, max_batch]");
   hipStream_t st = (hipStream_t)stream;
-  k_iota<<<(m->bpad + 255) / 256, 256, 0, st>>>(N, m->d_idx);
-  hipError_t e = gradient_pass(m, (const unsigned short*)feats_bf16, targets, N, loss, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(grad, m->d_grad, sizeof(float) * kNParams, hipMemcpyDeviceToDevice, st);
+  const hipError_t e = gradient_pass(m, (const unsigned short*)feats_bf16, targets, -1, N, N, loss, grad, st);
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }
 
@@ -898,15 +923,14 @@ dsm_status dsm_surrogate_train(dsm_surrogate* m, int32_t N, const uint16_t* feat
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   for (int k = 0; k < steps && e == hipSuccess; ++k) {
-    k_batch_indices<<<(batch + 255) / 256, 256, 0, st>>>(m->desc.seed, (int)m->step, N, batch, batch, m->d_idx);
-    e = gradient_pass(m, (const unsigned short*)feats_bf16, targets, batch, loss ? loss + k : nullptr, st);
+    e = gradient_pass(m, (const unsigned short*)feats_bf16, targets, (int)m->step, N, batch, loss ? loss + k : nullptr,
+                      m->d_grad, st);
     if (e != hipSuccess) break;
     m->step++;
     const float c1 = 1.f - powf(m->desc.beta1, (float)m->step), c2 = 1.f - powf(m->desc.beta2, (float)m->step);
-    k_adam<<<(kNParams + 255) / 256, 256, 0, st>>>(m->d_params, m->d_grad, m->d_m, m->d_v, m->desc.lr, m->desc.beta1,
-                                                  m->desc.beta2, m->desc.eps, c1, c2);
+    k_mlp_update<<<(kNParams + 255) / 256, 256, 0, st>>>(m->d_grad, m->d_params, m->d_m, m->d_v, m->desc.lr,
+                                                         m->desc.beta1, m->desc.beta2, m->desc.eps, c1, c2, operands(m));
     e = hipGetLastError();
-    if (e == hipSuccess) e = refresh(m, st);
   }
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 from oracle import gomea_ref as G
+from oracle import surrogate_ref as R
 from paper_2202_11001_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -178,3 +179,25 @@ def test_improvement_ratio_tiles(S, share):
             want = G.standard_deviation_ratio(np.array(rows).reshape(-1, n), mean[j, f, :n], L @ L.T)
             np.testing.assert_allclose(got[j, f], want, rtol=1e-9, atol=1e-12)
     assert np.all(got[:, 2] == -1.0)
+
+
+# batch sizes around the 16-row blocks and the 16 steps of 32 rows that are kept in flight
+@pytest.mark.parametrize("N", [1, 17, 480, 512, 513, 1024, 4096, 6000])
+def test_gradient_batches(N):
+    rng = np.random.default_rng(N)
+    p = rng.normal(0, 0.15, R.NPARAMS).astype(np.float32)
+    p[R.W3 + R.OUT * R.HID:R.B3] = 0.0
+    p[R.B3 + R.OUT:] = 0.0
+    x = torch.from_numpy(rng.normal(size=(N, R.IN)).astype(np.float32)).to(torch.bfloat16)
+    t = rng.normal(size=(N, R.OUT)).astype(np.float32)
+    sur = dsm.Surrogate(seed=1, max_rows=64, max_batch=6016)
+    sur.params(p)
+    g, loss = sur.gradient(x.view(torch.int16).to(DEV), _t(t))
+    want_loss, want = R.loss_and_grad(p.astype(np.float64), x.double().numpy(), t.astype(np.float64), bf16_round=True)
+    # FP32 sums of the same BF16 operands: a hidden value can round to the neighbouring BF16 number, which moves a
+    # row's share of a gradient by 2^-8; per parameter block the largest entry bounds it
+    assert float(loss.item()) == pytest.approx(want_loss, rel=1e-3)
+    g = g.cpu().numpy().astype(np.float64)
+    for a, b in ((R.W1, R.B1), (R.B1, R.W2), (R.W2, R.B2), (R.B2, R.W3), (R.W3, R.B3), (R.B3, R.NPARAMS)):
+        tol = 1e-3 * np.abs(want[a:b]) + 5e-4 * np.abs(want[a:b]).max()
+        assert np.all(np.abs(g[a:b] - want[a:b]) <= tol)
