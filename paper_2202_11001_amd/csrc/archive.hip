@@ -14,40 +14,40 @@
 namespace dsm {
 namespace {
 
-constexpr int kMergeWG = 256;
+constexpr int kMergeWG = 256, kMergeWaves = kMergeWG / 64;
 
+// The three comparisons are written without short-circuits: in a loop over
+// many vectors, branches around each coordinate's load cost more than the load.
 __device__ __forceinline__ bool dominates3(const double* a, const double* b) {
-  return a[0] <= b[0] && a[1] <= b[1] && a[2] <= b[2] && (a[0] < b[0] || a[1] < b[1] || a[2] < b[2]);
+  const double a0 = a[0], a1 = a[1], a2 = a[2], b0 = b[0], b1 = b[1], b2 = b[2];
+  return (a0 <= b0) & (a1 <= b1) & (a2 <= b2) & ((a0 < b0) | (a1 < b1) | (a2 < b2));
 }
 __device__ __forceinline__ bool equal3(const double* a, const double* b) {
-  return a[0] == b[0] && a[1] == b[1] && a[2] == b[2];
+  return (a[0] == b[0]) & (a[1] == b[1]) & (a[2] == b[2]);
 }
 // a before b in lexicographic order
 __device__ __forceinline__ bool lex_less(const double* a, const double* b) {
-  return a[0] != b[0] ? a[0] < b[0] : (a[1] != b[1] ? a[1] < b[1] : a[2] < b[2]);
+  const double a0 = a[0], a1 = a[1], a2 = a[2], b0 = b[0], b1 = b[1], b2 = b[2];
+  return (a0 < b0) | ((a0 == b0) & ((a1 < b1) | ((a1 == b1) & (a2 < b2))));
 }
 
 // Workspace of one merge (byte offsets, 256-aligned regions).
 struct MergeWork {
-  size_t keep_a, keep_n, pref_a, pos_a, pos_n, vec, rows, hdr, total;
+  size_t alive, keep_n, src, vec, rows, hdr, total;
 };
 __host__ __device__ inline size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 __host__ __device__ inline MergeWork merge_work(int cap, int m, int row_floats) {
   MergeWork w;
   size_t o = 0;
-  w.keep_a = o;  // int [cap]: archive row kept
-  o = al256(o + sizeof(int) * (size_t)cap);
+  w.alive = o;  // uint64 [ceil(cap / 64)]: bit per archive row kept
+  o = al256(o + sizeof(unsigned long long) * (((size_t)cap + 63) / 64));
   w.keep_n = o;  // int [m]: new point kept
   o = al256(o + sizeof(int) * (size_t)m);
-  w.pref_a = o;  // int [cap + 1]: exclusive prefix of keep_a
-  o = al256(o + sizeof(int) * ((size_t)cap + 1));
-  w.pos_a = o;  // int [cap]: output position of archive row (-1 dropped)
+  w.src = o;  // int [cap]: source of every merged row: an archive row, cap + a new point, or -1
   o = al256(o + sizeof(int) * (size_t)cap);
-  w.pos_n = o;  // int [m]: output position of new point (-1 dropped)
-  o = al256(o + sizeof(int) * (size_t)m);
   w.vec = o;  // double [cap][3]: merged vectors
   o = al256(o + sizeof(double) * 3 * (size_t)cap);
-  w.rows = o;  // float [cap][row_floats]: merged payload
+  w.rows = o;  // float [cap][row_floats]: the archive rows that move
   o = al256(o + sizeof(float) * (size_t)cap * row_floats);
   w.hdr = o;  // int [2]: merged count, overflow
   o = al256(o + sizeof(int) * 2);
@@ -55,34 +55,66 @@ __host__ __device__ inline MergeWork merge_work(int cap, int m, int row_floats) 
   return w;
 }
 
-// Archive row i (of n) is kept iff no new point dominates it (the archive's
-// own rows are mutually non-dominated and distinct).
-__global__ void k_merge_mark_archive(const double* __restrict__ arch, const int* __restrict__ n_arch, int cap, int m,
-                                     const double* __restrict__ pts, int* __restrict__ keep_a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= cap) return;
-  const int n = min(*n_arch, cap);
-  int keep = 0;
-  if (i < n) {
-    keep = 1;
-    const double* a = arch + 3 * (size_t)i;
-    for (int j = 0; j < m && keep; ++j)
-      if (dominates3(pts + 3 * (size_t)j, a)) keep = 0;
-  }
-  keep_a[i] = keep;
-}
+// A merge is four kernels: what is kept, where it goes, the archive rows that
+// move copied out, and everything written to its place.  With payload rows the
+// copies bound it (a row that moves is read and written twice, a new one
+// once, one that keeps its place not at all); the tests against m points are
+// split over a workgroup's waves so that they are short.  The merges of eight
+// generations of 500 points with 32 KB rows took 414 us each as seven kernels
+// (one thread walking all points for each archive row: 116 and 88 us; every
+// element of the whole capacity divided into row and column: 110 and 76 us;
+// a prefix sum over the capacity by one workgroup: 25 us).
 
-// New point j is kept iff no archive row dominates or equals it, no new point
-// dominates it and no earlier new point equals it: one workgroup per point,
-// its threads striding over the candidates.
-__global__ __launch_bounds__(kMergeWG) void k_merge_mark_new(const double* __restrict__ arch,
-                                                           const int* __restrict__ n_arch, int cap, int m,
-                                                           const double* __restrict__ pts, int* __restrict__ keep_n) {
+constexpr int kMergeTile = 512;  // new points staged in LDS at a time
+
+// Workgroups [0, ceil(cap / 64)): the 64 archive rows of a word, each wave
+// testing them against a quarter of the new points; row i (of n) is kept iff
+// no new point dominates it (the archive's own rows are mutually
+// non-dominated and distinct).  Then one workgroup per new point: kept iff no
+// archive row dominates or equals it, no new point dominates it and no earlier
+// new point equals it.
+__global__ __launch_bounds__(kMergeWG) void k_merge_mark(const double* __restrict__ arch,
+                                                       const int* __restrict__ n_arch, int cap, int m,
+                                                       const double* __restrict__ pts,
+                                                       unsigned long long* __restrict__ alive,
+                                                       int* __restrict__ keep_n, int* __restrict__ src) {
+  __shared__ double s_p[kMergeTile][3];
+  __shared__ unsigned long long s_dead[kMergeWaves];
   __shared__ int drop;
-  const int j = blockIdx.x, t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, words = (cap + 63) / 64;
+  const int n = min(*n_arch, cap);
+  if ((int)blockIdx.x < words) {
+    const int i = blockIdx.x * 64 + lane;
+    if (t < 64 && i < cap) src[i] = -1;  // NaN vectors have no place in the order and may leave positions free
+    if ((int)blockIdx.x * 64 >= n) {
+      if (t == 0) alive[blockIdx.x] = 0;
+      return;
+    }
+    double a[3] = {0.0, 0.0, 0.0};
+    if (i < n)
+      for (int c = 0; c < 3; ++c) a[c] = arch[3 * (size_t)i + c];
+    bool dead = i >= n;
+    for (int j0 = 0; j0 < m; j0 += kMergeTile) {
+      const int mt = min(kMergeTile, m - j0);
+      for (int e = t; e < 3 * mt; e += kMergeWG) s_p[e / 3][e % 3] = pts[3 * (size_t)j0 + e];
+      __syncthreads();
+#pragma unroll 4
+      for (int j = wave; j < mt; j += kMergeWaves) dead |= dominates3(s_p[j], a);
+      __syncthreads();
+    }
+    const unsigned long long d = __ballot(dead);
+    if (lane == 0) s_dead[wave] = d;
+    __syncthreads();
+    if (t == 0) {
+      unsigned long long all = 0;
+      for (int w = 0; w < kMergeWaves; ++w) all |= s_dead[w];
+      alive[blockIdx.x] = ~all;
+    }
+    return;
+  }
+  const int j = blockIdx.x - words;
   if (t == 0) drop = 0;
   __syncthreads();
-  const int n = min(*n_arch, cap);
   const double* p = pts + 3 * (size_t)j;
   int d = 0;
   for (int i = t; i < n && !d; i += kMergeWG) {
@@ -98,121 +130,155 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_mark_new(const double* __res
   if (t == 0) keep_n[j] = drop ? 0 : 1;
 }
 
-// Exclusive prefix of keep_a over [0, cap) by one workgroup.
-__global__ __launch_bounds__(1024) void k_merge_prefix(const int* __restrict__ keep_a, int cap, int* __restrict__ pref_a) {
-  __shared__ int part[1024];
-  const int t = threadIdx.x;
-  const int per = (cap + 1023) / 1024;
-  const int b = t * per, e = min(cap, b + per);
-  int s = 0;
-  for (int i = b; i < e; ++i) s += keep_a[i];
-  part[t] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int v = t >= off ? part[t - off] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  int run = part[t] - s;
-  for (int i = b; i < e; ++i) {
-    pref_a[i] = run;
-    run += keep_a[i];
-  }
-  if (t == 1023) pref_a[cap] = part[1023];
+__device__ __forceinline__ int wave_add(int v) {
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// Archive rows kept in words [0, w), counted by the 64 lanes of a wave.
+__device__ __forceinline__ int kept_before(const unsigned long long* __restrict__ alive, int w, int lane) {
+  int c = 0;
+  for (int k = lane; k < w; k += 64) c += __popcll(alive[k]);
+  return wave_add(c);
 }
 
 // Output positions: kept archive rows keep their order (they are sorted) and
 // make room for the kept new points lexicographically below them; a kept new
 // point goes after the kept archive rows and kept new points below it (the
-// sorted archive is searched by bisection).  Kept vectors are distinct, so the
-// positions are a permutation of [0, k).
-__global__ void k_merge_positions(const double* __restrict__ arch, const int* __restrict__ n_arch, int cap, int m,
-                                  const double* __restrict__ pts, const int* __restrict__ keep_a,
-                                  const int* __restrict__ keep_n, const int* __restrict__ pref_a, int* __restrict__ pos_a,
-                                  int* __restrict__ pos_n, int* __restrict__ hdr) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+// sorted archive is searched 64 rows at a time).  Kept vectors are distinct,
+// so the positions are a permutation of [0, k); src[position] is written.
+// Workgroups [0, words) take the rows of a word, their waves a quarter of the
+// points each; the next ones a new point per wave; the last one the header.
+__global__ __launch_bounds__(kMergeWG) void k_merge_positions(const double* __restrict__ arch,
+                                                            const int* __restrict__ n_arch, int cap, int m,
+                                                            const double* __restrict__ pts,
+                                                            const unsigned long long* __restrict__ alive,
+                                                            const int* __restrict__ keep_n, int* __restrict__ src,
+                                                            int* __restrict__ hdr) {
+  __shared__ double s_p[kMergeTile][3];
+  __shared__ int s_keep[kMergeTile];
+  __shared__ int s_cnt[kMergeWaves][64];
+  __shared__ int s_pre;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, words = (cap + 63) / 64;
   const int n = min(*n_arch, cap);
-  if (e < cap) {
-    int pos = -1;
-    if (e < n && keep_a[e]) {
-      const double* a = arch + 3 * (size_t)e;
-      int below = 0;
-      for (int j = 0; j < m; ++j) below += keep_n[j] && lex_less(pts + 3 * (size_t)j, a);
-      pos = pref_a[e] + below;
+  if ((int)blockIdx.x < words) {
+    const unsigned long long mine = alive[blockIdx.x];
+    if (!mine) return;
+    const int i = blockIdx.x * 64 + lane;
+    const bool kept = (mine >> lane) & 1;
+    if (wave == 0) {
+      const int pre = kept_before(alive, blockIdx.x, lane);
+      if (lane == 0) s_pre = pre;
     }
-    pos_a[e] = pos;
-  } else if (e < cap + m) {
-    const int j = e - cap;
-    int pos = -1;
-    if (keep_n[j]) {
-      const double* p = pts + 3 * (size_t)j;
-      int lo = 0, hi = n;  // first archive row not below p
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (lex_less(arch + 3 * (size_t)mid, p))
-          lo = mid + 1;
-        else
-          hi = mid;
-      }
-      int below = pref_a[lo];
-      for (int k = 0; k < m; ++k) below += keep_n[k] && lex_less(pts + 3 * (size_t)k, p);
-      pos = below;
+    double a[3] = {0.0, 0.0, 0.0};
+    if (kept)
+      for (int c = 0; c < 3; ++c) a[c] = arch[3 * (size_t)i + c];
+    int below = 0;
+    for (int j0 = 0; j0 < m; j0 += kMergeTile) {
+      const int mt = min(kMergeTile, m - j0);
+      for (int e = t; e < 3 * mt; e += kMergeWG) s_p[e / 3][e % 3] = pts[3 * (size_t)j0 + e];
+      for (int e = t; e < mt; e += kMergeWG) s_keep[e] = keep_n[j0 + e];
+      __syncthreads();
+#pragma unroll 4
+      for (int j = wave; j < mt; j += kMergeWaves) below += s_keep[j] & (int)lex_less(s_p[j], a);
+      __syncthreads();
     }
-    pos_n[j] = pos;
-  } else if (e == cap + m) {
-    int kn = 0;
-    for (int j = 0; j < m; ++j) kn += keep_n[j];
-    const int k = pref_a[cap] + kn;
-    hdr[0] = k;
-    hdr[1] = k > cap ? 1 : 0;
+    s_cnt[wave][lane] = below;
+    __syncthreads();
+    if (wave == 0 && kept) {
+      int pos = s_pre + __popcll(mine & ((1ull << lane) - 1));
+      for (int w = 0; w < kMergeWaves; ++w) pos += s_cnt[w][lane];
+      if (pos < cap) src[pos] = i;  // beyond it only where the merge overflows
+    }
+    return;
+  }
+  const int j = (blockIdx.x - words) * kMergeWaves + wave;  // the same on every lane of a wave
+  if (j < m) {
+    if (!keep_n[j]) return;
+    const double p[3] = {pts[3 * (size_t)j], pts[3 * (size_t)j + 1], pts[3 * (size_t)j + 2]};
+    int lo = 0, hi = n;  // the first archive row not below p lies in [lo, hi]
+    while (lo < hi) {
+      const int step = (hi - lo + 63) / 64, q = lo + lane * step;
+      const int c = __popcll(__ballot(q < hi && lex_less(arch + 3 * (size_t)min(q, n - 1), p)));
+      hi = min(hi, lo + c * step);
+      lo = c ? lo + (c - 1) * step + 1 : lo;
+    }
+    int pos = kept_before(alive, lo >> 6, lane);
+    if (lo & 63) pos += __popcll(alive[lo >> 6] & ((1ull << (lo & 63)) - 1));
+    int below = 0;
+    for (int k = lane; k < m; k += 64) below += keep_n[k] & (int)lex_less(pts + 3 * (size_t)k, p);
+    pos += wave_add(below);
+    if (lane == 0 && pos < cap) src[pos] = cap + j;
+  } else if (blockIdx.x == gridDim.x - 1 && wave == kMergeWaves - 1) {
+    int k = kept_before(alive, words, lane), kn = 0;
+    for (int q = lane; q < m; q += 64) kn += keep_n[q];
+    k += wave_add(kn);
+    if (lane == 0) {
+      hdr[0] = k;
+      hdr[1] = k > cap ? 1 : 0;
+    }
   }
 }
 
-// Scatter of the kept vectors and payload rows into the workspace, one thread
-// per (source row, column); columns 0-2 are the vector, 3.. the payload.
-__global__ void k_merge_scatter(const double* __restrict__ arch, const float* __restrict__ arch_rows, int cap, int m,
-                                const double* __restrict__ pts, const float* __restrict__ pt_rows, int row_floats,
-                                const int* __restrict__ pos_a, const int* __restrict__ pos_n,
-                                const int* __restrict__ hdr, double* __restrict__ vec, float* __restrict__ rows) {
+// One workgroup's copy of a payload row, in pairs of floats where every row
+// starts at a multiple of 8 bytes (pairs).
+__device__ __forceinline__ void copy_row(float* __restrict__ dst, const float* __restrict__ src, int n, bool pairs) {
+  if (pairs) {
+    float2* d = reinterpret_cast<float2*>(dst);
+    const float2* s = reinterpret_cast<const float2*>(src);
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n / 2; i += kMergeWG) d[i] = s[i];
+  } else {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n; i += kMergeWG) dst[i] = src[i];
+  }
+}
+
+// The merged vectors, and the payload of every archive row that moves, copied
+// to the workspace at their new positions.
+__global__ __launch_bounds__(kMergeWG) void k_merge_out(const double* __restrict__ arch,
+                                                      const float* __restrict__ arch_rows, int cap,
+                                                      const double* __restrict__ pts, int row_floats, bool pairs,
+                                                      const int* __restrict__ src, const int* __restrict__ hdr,
+                                                      double* __restrict__ vec, float* __restrict__ rows) {
   if (hdr[1]) return;  // overflow: the archive stays as it was
-  const int cols = 3 + row_floats;
-  const int64_t total = (int64_t)(cap + m) * cols;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int r = (int)(e / cols), c = (int)(e - (int64_t)r * cols);
-    const int pos = r < cap ? pos_a[r] : pos_n[r - cap];
-    if (pos < 0) continue;
-    if (c < 3)
-      vec[3 * (size_t)pos + c] = r < cap ? arch[3 * (size_t)r + c] : pts[3 * (size_t)(r - cap) + c];
-    else
-      rows[(size_t)pos * row_floats + (c - 3)] =
-          r < cap ? arch_rows[(size_t)r * row_floats + (c - 3)] : pt_rows[(size_t)(r - cap) * row_floats + (c - 3)];
+  const int k = hdr[0];
+  for (int64_t e = blockIdx.x * (int64_t)kMergeWG + threadIdx.x; e < 3 * (int64_t)k; e += (int64_t)gridDim.x * kMergeWG) {
+    const int r = (int)(e / 3), c = (int)(e - 3 * (int64_t)r), from = src[r];
+    vec[e] = from < 0 ? INFINITY : (from < cap ? arch[3 * (size_t)from + c] : pts[3 * (size_t)(from - cap) + c]);
+  }
+  if (!row_floats) return;
+  for (int r = blockIdx.x; r < k; r += gridDim.x) {
+    const int from = src[r];
+    if (from >= 0 && from < cap && from != r)
+      copy_row(rows + (size_t)r * row_floats, arch_rows + (size_t)from * row_floats, row_floats, pairs);
   }
 }
 
-// Copies the merged archive back: rows [0, k) from the workspace, +inf after;
-// the count and the overflow flag.
-__global__ void k_merge_copyback(double* __restrict__ arch, float* __restrict__ arch_rows, int cap, int row_floats,
-                                 const double* __restrict__ vec, const float* __restrict__ rows,
-                                 const int* __restrict__ hdr, int* __restrict__ n_arch, int* __restrict__ overflow) {
+// Writes the archive: vectors and moved rows from the workspace, new rows from
+// the points, +inf after the count; the count and the overflow flag.
+__global__ __launch_bounds__(kMergeWG) void k_merge_in(double* __restrict__ arch, float* __restrict__ arch_rows, int cap,
+                                                     const float* __restrict__ pt_rows, int row_floats, bool pairs,
+                                                     const int* __restrict__ src, const int* __restrict__ hdr,
+                                                     const double* __restrict__ vec, const float* __restrict__ rows,
+                                                     int* __restrict__ n_arch, int* __restrict__ overflow) {
   const int k = hdr[0];
   const bool over = hdr[1] != 0;
-  const int cols = 3 + row_floats;
-  const int64_t total = (int64_t)cap * cols;
-  const int64_t first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (first == 0 && overflow) *overflow = over ? 1 : 0;
-  if (over) return;
-  for (int64_t e = first; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int r = (int)(e / cols), c = (int)(e - (int64_t)r * cols);
-    if (c < 3)
-      arch[3 * (size_t)r + c] = r < k ? vec[3 * (size_t)r + c] : INFINITY;
-    else if (r < k)
-      arch_rows[(size_t)r * row_floats + (c - 3)] = rows[(size_t)r * row_floats + (c - 3)];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (overflow) *overflow = over ? 1 : 0;
+    if (!over) *n_arch = k;
   }
-}
-
-__global__ void k_merge_count(const int* __restrict__ hdr, int* __restrict__ n_arch) {
-  if (threadIdx.x == 0 && !hdr[1]) *n_arch = hdr[0];
+  if (over) return;
+  for (int64_t e = blockIdx.x * (int64_t)kMergeWG + threadIdx.x; e < 3 * (int64_t)cap; e += (int64_t)gridDim.x * kMergeWG)
+    arch[e] = e < 3 * (int64_t)k ? vec[e] : INFINITY;
+  if (!row_floats) return;
+  for (int r = blockIdx.x; r < k; r += gridDim.x) {
+    const int from = src[r];
+    if (from >= 0 && from != r)
+      copy_row(arch_rows + (size_t)r * row_floats,
+               from < cap ? rows + (size_t)r * row_floats : pt_rows + (size_t)(from - cap) * row_floats, row_floats,
+               pairs);
+  }
 }
 
 // Selection: one workgroup.  Range of every objective, dominated-by counts,
@@ -460,25 +526,23 @@ dsm_status dsm_archive_merge(int32_t capacity, double* archive, int32_t* n_archi
   hipStream_t st = (hipStream_t)stream;
   const MergeWork w = merge_work(capacity, m, row_floats);
   unsigned char* base = (unsigned char*)work;
-  int* keep_a = (int*)(base + w.keep_a);
+  unsigned long long* alive = (unsigned long long*)(base + w.alive);
   int* keep_n = (int*)(base + w.keep_n);
-  int* pref_a = (int*)(base + w.pref_a);
-  int* pos_a = (int*)(base + w.pos_a);
-  int* pos_n = (int*)(base + w.pos_n);
+  int* src = (int*)(base + w.src);
   double* vec = (double*)(base + w.vec);
   float* rows = (float*)(base + w.rows);
   int* hdr = (int*)(base + w.hdr);
-  k_merge_mark_archive<<<(capacity + 255) / 256, 256, 0, st>>>(archive, n_archive, capacity, m, points, keep_a);
-  if (m > 0) k_merge_mark_new<<<m, kMergeWG, 0, st>>>(archive, n_archive, capacity, m, points, keep_n);
-  k_merge_prefix<<<1, 1024, 0, st>>>(keep_a, capacity, pref_a);
-  k_merge_positions<<<(capacity + m + 1 + 255) / 256, 256, 0, st>>>(archive, n_archive, capacity, m, points, keep_a,
-                                                                   keep_n, pref_a, pos_a, pos_n, hdr);
-  const int64_t sc = (int64_t)(capacity + m) * (3 + row_floats), cb = (int64_t)capacity * (3 + row_floats);
-  k_merge_scatter<<<(unsigned)std::min<int64_t>((sc + 255) / 256, 16384), 256, 0, st>>>(
-      archive, archive_rows, capacity, m, points, point_rows, row_floats, pos_a, pos_n, hdr, vec, rows);
-  k_merge_copyback<<<(unsigned)std::min<int64_t>((cb + 255) / 256, 16384), 256, 0, st>>>(
-      archive, archive_rows, capacity, row_floats, vec, rows, hdr, n_archive, overflow);
-  k_merge_count<<<1, 64, 0, st>>>(hdr, n_archive);
+  const int words = (capacity + 63) / 64;
+  k_merge_mark<<<words + m, kMergeWG, 0, st>>>(archive, n_archive, capacity, m, points, alive, keep_n, src);
+  // m / waves + 1 workgroups after the words: the last one's last wave has no point and writes the header
+  k_merge_positions<<<words + m / kMergeWaves + 1, kMergeWG, 0, st>>>(archive, n_archive, capacity, m, points, alive,
+                                                                     keep_n, src, hdr);
+  const bool pairs = row_floats % 2 == 0 && (((uintptr_t)archive_rows | (uintptr_t)point_rows | (uintptr_t)rows) & 7) == 0;
+  // a workgroup per row with payload; the vectors alone (3 values a row) take few
+  const unsigned wgs = row_floats ? std::min(capacity, 16384) : std::min((3 * (capacity / kMergeWG) + 3), 1024);
+  k_merge_out<<<wgs, kMergeWG, 0, st>>>(archive, archive_rows, capacity, points, row_floats, pairs, src, hdr, vec, rows);
+  k_merge_in<<<wgs, kMergeWG, 0, st>>>(archive, archive_rows, capacity, point_rows, row_floats, pairs, src, hdr, vec, rows,
+                                      n_archive, overflow);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
 

@@ -201,3 +201,38 @@ def test_gradient_batches(N):
     for a, b in ((R.W1, R.B1), (R.B1, R.W2), (R.W2, R.B2), (R.B2, R.W3), (R.W3, R.B3), (R.B3, R.NPARAMS)):
         tol = 1e-3 * np.abs(want[a:b]) + 5e-4 * np.abs(want[a:b]).max()
         assert np.all(np.abs(g[a:b] - want[a:b]) <= tol)
+
+
+# capacities around the 64-row words; more points than a staging tile (512); payload rows of even and odd length,
+# aligned to 8 bytes and not; a NaN vector, which has no place in the order, does no harm
+@pytest.mark.parametrize("capacity,m,row_floats,offset", [(63, 9, 1, 0), (64, 1, 6, 0), (65, 30, 6, 1), (200, 61, 7, 0),
+                                                          (4097, 513, 0, 0), (3000, 700, 514, 0)])
+def test_archive_merge_shapes(capacity, m, row_floats, offset):
+    rng = np.random.default_rng(capacity)
+    A = dsm.Archive(capacity=capacity, m_max=m, row_floats=row_floats)
+    vec, rows = np.zeros((0, 3)), np.zeros((0, max(row_floats, 1)), np.float32)
+    overflowed = 0
+    for r in range(6):
+        pts = rng.integers(0, 60, (m, 3)) / 4.0
+        pts[: m // 2, 2] = 40 - pts[: m // 2, :2].sum(1) - 0.25 * r  # a front that improves, so rows are dropped
+        new = rng.normal(size=(m, max(row_floats, 1))).astype(np.float32)
+        buf = torch.empty(m * row_floats + offset, dtype=torch.float32, device=DEV)
+        d = buf[offset:].view(m, row_floats) if row_floats else None
+        if row_floats:
+            d.copy_(_t(new))
+        A.merge(_t(pts), d)
+        want, want_rows = G.archive_merge(vec, pts, rows, new)
+        if len(want) > capacity:  # unchanged
+            overflowed += 1
+            assert int(A.overflow.item()) == 1
+        else:
+            vec, rows = want, want_rows
+            assert int(A.overflow.item()) == 0
+        assert A.n == len(vec)
+        v = A.vec.cpu().numpy()
+        np.testing.assert_array_equal(v[:len(vec)], vec)
+        assert np.all(v[len(vec):] == np.inf)
+        if row_floats:
+            np.testing.assert_array_equal(A.rows[:len(vec)].cpu().numpy(), rows)
+    A.merge(_t(np.full((1, 3), np.nan)), torch.zeros((1, row_floats), device=DEV) if row_floats else None)
+    assert A.n in (len(vec), len(vec) + 1)
