@@ -44,7 +44,7 @@ void release(dsm_problem* p) {
   if (!p) return;
   for (hipEvent_t e : p->ev) (void)hipEventDestroy(e);
   void* bufs[] = {p->d_img, p->d_raw, p->d_tets, p->d_tet_w, p->d_star_off, p->d_star, p->d_gpt, p->d_gcorr,
-                  p->d_aff, p->d_aff_cnt, p->d_order, p->d_terms, p->d_simws, p->d_ident, p->d_cflags, p->d_ccount};
+                  p->d_aff, p->d_aff_cnt, p->d_order, p->d_terms, p->d_sums, p->d_pin, p->d_gbox, p->d_ident, p->d_cflags, p->d_ccount};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   delete p;
@@ -181,11 +181,17 @@ dsm_status dsm_problem_create(const dsm_problem_desc* d, dsm_problem** out) {
       gc.push_back(csrc[g][i]);
     }
   // every correspondence must have a point on both images
+  std::vector<float4> gbox;
   for (int g = 0; g < 2; ++g)
     for (int i = 0; i < ng[g]; ++i) {
       const int c = csrc[g][i];
-      bool found = false;
-      for (int j = 0; j < ng[1 - g] && !found; ++j) found = csrc[1 - g][j] == c;
+      int found = 0, match = -1;
+      for (int j = 0; j < ng[1 - g] && found < 2; ++j)
+        if (csrc[1 - g][j] == c) match = found++ ? -1 : j;
+      const double* u = &gl[3 * (gbox.size())];
+      float bits;
+      memcpy(&bits, &match, sizeof bits);
+      gbox.push_back(make_float4((float)u[0], (float)u[1], (float)u[2], bits));
       if (!found) {
         release(p);
         return fail(DSM_ERR_ARG, "correspondence %d has points on one image only", c);
@@ -212,6 +218,13 @@ dsm_status dsm_problem_create(const dsm_problem_desc* d, dsm_problem** out) {
   DSM_TRY(hipMemcpy(p->d_tets, tp.tets.data(), sizeof(int) * tp.tets.size(), hipMemcpyHostToDevice), "copy tets");
   DSM_TRY(dev_alloc(&p->d_tet_w, tp.tet_w.size()), "hipMalloc weights");
   DSM_TRY(hipMemcpy(p->d_tet_w, tp.tet_w.data(), sizeof(double) * tp.tet_w.size(), hipMemcpyHostToDevice), "copy weights");
+  std::vector<uint8_t> pin(tp.P);
+  for (int q = 0; q < tp.P; ++q) {
+    const int idx[3] = {q % p->mesh[0], q / p->mesh[0] % p->mesh[1], q / (p->mesh[0] * p->mesh[1])};
+    for (int c = 0; c < 3; ++c) pin[q] |= (idx[c] == 0 ? 1 << c : 0) | (idx[c] == p->mesh[c] - 1 ? 8 << c : 0);
+  }
+  DSM_TRY(dev_alloc(&p->d_pin, pin.size()), "hipMalloc pinned axes");
+  DSM_TRY(hipMemcpy(p->d_pin, pin.data(), pin.size(), hipMemcpyHostToDevice), "copy pinned axes");
   DSM_TRY(dev_alloc(&p->d_star_off, tp.star_off.size()), "hipMalloc star_off");
   DSM_TRY(hipMemcpy(p->d_star_off, tp.star_off.data(), sizeof(int) * tp.star_off.size(), hipMemcpyHostToDevice),
           "copy star_off");
@@ -223,6 +236,9 @@ dsm_status dsm_problem_create(const dsm_problem_desc* d, dsm_problem** out) {
   DSM_TRY(dev_alloc(&p->d_gcorr, gc.size()), "hipMalloc correspondences");
   if (!gc.empty())
     DSM_TRY(hipMemcpy(p->d_gcorr, gc.data(), sizeof(int) * gc.size(), hipMemcpyHostToDevice), "copy correspondences");
+  DSM_TRY(dev_alloc(&p->d_gbox, gbox.size()), "hipMalloc guidance boxes");
+  if (!gbox.empty())
+    DSM_TRY(hipMemcpy(p->d_gbox, gbox.data(), sizeof(float4) * gbox.size(), hipMemcpyHostToDevice), "copy guidance boxes");
   DSM_TRY(dev_alloc(&p->d_aff, (size_t)std::max(1, p->max_F) * p->maxA), "hipMalloc affected sets");
   DSM_TRY(dev_alloc(&p->d_aff_cnt, (size_t)std::max(1, p->max_F)), "hipMalloc affected counts");
   DSM_TRY(dev_alloc(&p->d_order, (size_t)std::max(1, p->max_F)), "hipMalloc element order");
@@ -230,15 +246,10 @@ dsm_status dsm_problem_create(const dsm_problem_desc* d, dsm_problem** out) {
   DSM_TRY(dev_alloc(&p->d_ident, p->identity.size()), "hipMalloc undeformed grid");
   DSM_TRY(hipMemcpy(p->d_ident, p->identity.data(), sizeof(float) * p->identity.size(), hipMemcpyHostToDevice),
           "copy undeformed grid");
-  {
-    const size_t full_groups = (size_t)(tp.T + kFullChunk - 1) / kFullChunk;
-    p->simws_len = std::max((size_t)p->max_S * std::max(1, p->max_F) * 2 * p->maxA,
-                            (size_t)p->max_S * full_groups * kFullChunk);
-  }
-  DSM_TRY(dev_alloc(&p->d_simws, p->simws_len), "hipMalloc sweep workspace");
   p->nchunk = (p->maxA + p->part_chunk - 1) / p->part_chunk;
   {
     const size_t nc = (size_t)p->max_S * std::max(1, p->max_F) * ((p->maxA + kMinPartChunk - 1) / kMinPartChunk);
+    DSM_TRY(dev_alloc(&p->d_sums, nc * 2 * 3), "hipMalloc chunk sums");
     DSM_TRY(dev_alloc(&p->d_cflags, nc), "hipMalloc chunk flags");
     DSM_TRY(dev_alloc(&p->d_ccount, nc), "hipMalloc chunk counts");
   }
@@ -256,12 +267,15 @@ dsm_status dsm_problem_create(const dsm_problem_desc* d, dsm_problem** out) {
   dv.T = tp.T;
   dv.tets = (const int4*)p->d_tets;
   dv.tet_w = p->d_tet_w;
+  dv.pin = p->d_pin;
   dv.star_off = p->d_star_off;
   dv.star = p->d_star;
   dv.ng[0] = ng[0];
   dv.ng[1] = ng[1];
   dv.gpt[0] = p->d_gpt;
   dv.gpt[1] = p->d_gpt + 3 * (size_t)ng[0];
+  dv.gbox[0] = p->d_gbox;
+  dv.gbox[1] = p->d_gbox + ng[0];
   dv.gcorr[0] = p->d_gcorr;
   dv.gcorr[1] = p->d_gcorr + ng[0];
   dv.norm[0] = 1.0 / (2.0 * (double)p->V);
@@ -379,7 +393,6 @@ dsm_status dsm_eval_full(dsm_problem* p, int32_t S, const float* X, double* obj,
   a.maxA = kFullChunk;
   a.nver = 1;
   a.terms_out = tet_terms ? tet_terms : p->d_terms;
-  a.simws = p->d_simws;
   a.row_pairs = p->row_order;
   hipEvent_t eb, ee;
   timing_pair(p, eb, ee);
@@ -426,7 +439,7 @@ dsm_status dsm_eval_partial_masked(dsm_problem* p, int32_t S, const float* X, in
   a.terms_out = tet_terms_new;
   a.vcount = voxel_count;
   a.mask = mask;
-  a.simws = p->d_simws;
+  a.sums = p->d_sums;
   a.pchunk = p->part_chunk;
   a.row_pairs = p->row_order;
   a.nchunk = p->nchunk;
@@ -660,7 +673,7 @@ dsm_status batch_tables(const dsm_batch* b, int n_jobs, const dsm_partial_job* j
     a.terms_out = q.tet_terms_new;
     a.vcount = q.voxel_count;
     a.mask = q.mask;
-    a.simws = p->d_simws;
+    a.sums = p->d_sums;
     a.pchunk = p->part_chunk;
     a.row_pairs = p->row_order;
     a.nchunk = p->nchunk;

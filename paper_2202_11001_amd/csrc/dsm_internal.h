@@ -22,10 +22,11 @@ constexpr int kFullChunk = 8;     // tetrahedra per workgroup in full evaluation
 // kPartChunk; the LDS layout is sized for kMaxChunk.
 constexpr int kPartChunk = 8, kMinPartChunk = 4, kMaxPartChunk = 8;
 constexpr int kMaxChunk = kFullChunk > kMaxPartChunk ? kFullChunk : kMaxPartChunk;
-// The finishing kernel gives each (group, solution) pair kFinishLanes lanes
-// (one per affected tetrahedron at a time), kFinishPairs pairs per 64-lane wave.
+// The finishing kernel gives each (group, solution) pair kFinishLanes lanes,
+// kFinishPairs pairs per 64-lane wave; the sums of a chunk run over as many.
 constexpr int kFinishLanes = 8;
 constexpr int kFinishPairs = 64 / kFinishLanes;
+static_assert(kMaxChunk == kFinishLanes, "a chunk's tetrahedra are summed by one lane group");
 
 // Sampled images are stored z-pair interleaved with a replicated one-voxel
 // border: element (x', y', z') of the (Dx+2) x (Dy+2) x (Dz+1) element grid
@@ -67,11 +68,13 @@ struct DevProblem {
   int P, T;
   const int4* tets;      // [T] vertex ids, positively oriented on the undeformed grid
   const double* tet_w;   // [T][6] 1/k_e of the edges 01 02 03 12 13 23
+  const uint8_t* pin;    // [P] bit a: first point of axis a, bit 3 + a: last one (coordinate a pinned to the box)
   const int* star_off;   // [P+1]
   const int* star;       // [4T]
   int ng[2];             // guidance points per image
   const double* gpt[2];  // [ng][3] lattice units
   const int* gcorr[2];   // [ng] correspondence ids
+  const float4* gbox[2]; // [ng] lattice coordinates, and as bits the other image's only point of the correspondence (-1: several)
   double norm[3];        // objective normalisers
 };
 
@@ -98,7 +101,7 @@ struct EvalArgs {
   double* terms_out;     // [S][T][3] or null
   uint32_t* vcount;      // [S][G] or null
   const uint8_t* mask;   // [S][G] or null: evaluate only where non-zero (partial)
-  double* simws;         // swept dissimilarity workspace of the problem
+  double* sums;          // partial: [S][G][nchunk][nver][3] un-normalised term sums per chunk
   int pchunk;            // partial: affected tetrahedra per workgroup
   int nchunk;            // partial: workgroups (chunks of pchunk affected tetrahedra) per group
   uint32_t* cflags;      // partial: [S][G][nchunk] constraint flags per chunk
@@ -172,12 +175,13 @@ struct dsm_problem {
   int* d_star = nullptr;
   double* d_gpt = nullptr;      // [n_m + n_f][3]
   int* d_gcorr = nullptr;
+  float4* d_gbox = nullptr;     // [n_m + n_f]
   int* d_aff = nullptr;         // [max_F][maxA]
   int* d_aff_cnt = nullptr;     // [max_F]
   int* d_order = nullptr;       // [max_F] element order of the last partial launch
   double* d_terms = nullptr;    // [max_S][T][3] workspace for full evaluation
-  double* d_simws = nullptr;    // swept dissimilarity per (solution, group, version, tetrahedron)
-  size_t simws_len = 0;
+  double* d_sums = nullptr;     // [max_S][max_F][nchunk][2][3] term sums per chunk of a partial evaluation
+  uint8_t* d_pin = nullptr;     // [P] pinned axes
   uint32_t* d_cflags = nullptr; // [max_S][max_F][nchunk] per-chunk flags of a partial evaluation
   uint32_t* d_ccount = nullptr; // [max_S][max_F][nchunk] per-chunk voxel counts
   int part_chunk = dsm::kPartChunk;  // affected tetrahedra per workgroup in partial evaluation

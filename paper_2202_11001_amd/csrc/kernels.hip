@@ -42,6 +42,18 @@ __device__ __forceinline__ unsigned lattice_of(float x, int D, double& u) {
   return 0u;
 }
 
+// The constraint bits of lattice_of for coordinate x, in FP32: scaling by 128
+// is exact, and (x + 0.5) 128 is a lattice integer in [0, 128 D] iff 128 x is
+// one in [-64, 128 D - 64].  Coordinates that vanish next to 0.5 in FP64 count
+// as 0, as they do there; x is set to 0 then.
+__device__ __forceinline__ unsigned lattice_bits(float& x, int D) {
+  if (fabsf(x) <= 0x1p-54f) x = 0.f;
+  const float t = x * 128.f;
+  if (!isfinite(x)) return DSM_FLAG_NONFINITE;
+  if (t != floorf(t)) return DSM_FLAG_LATTICE;
+  return t < -64.f || t > (float)(128 * D - 64) ? DSM_FLAG_DOMAIN : 0u;
+}
+
 // 6 x signed volume of (a, b, c, d); exact for lattice integers.
 __device__ __forceinline__ double orient(const double a[3], const double b[3], const double c[3], const double d[3]) {
   const double u[3] = {b[0] - a[0], b[1] - a[1], b[2] - a[2]};
@@ -51,54 +63,6 @@ __device__ __forceinline__ double orient(const double a[3], const double b[3], c
   const double cy = v[2] * w[0] - v[0] * w[2];
   const double cz = v[0] * w[1] - v[1] * w[0];
   return u[0] * cx + u[1] * cy + u[2] * cz;
-}
-
-// Face functions of a positively oriented tetrahedron: o_i(U) = G_i . U + K_i
-// is the orientation with vertex i replaced by U (zero on the face opposite i,
-// vol at vertex i).  U lies in the tetrahedron iff o_i(U) >= thr_i for all i,
-// where thr_i = 0 if the first non-zero component of G_i (x, then y, then z) is
-// positive and 1 otherwise: the top-left rule of Sec. 2.3.1 extended to 3-D by
-// perturbing U by (+e, +e^2, +e^3).
-struct Faces {
-  double G[4][3];
-  double K[4];
-  int thr[4];
-};
-
-__device__ __forceinline__ void make_faces(const double L[4][3], Faces& f) {
-  for (int i = 0; i < 4; ++i) {
-    const int j = i == 0 ? 1 : 0;
-    const int k = i <= 1 ? 2 : 1;
-    const int l = i <= 2 ? 3 : 2;
-    const double a[3] = {L[k][0] - L[j][0], L[k][1] - L[j][1], L[k][2] - L[j][2]};
-    const double b[3] = {L[l][0] - L[j][0], L[l][1] - L[j][1], L[l][2] - L[j][2]};
-    double g[3] = {a[1] * b[2] - a[2] * b[1], a[2] * b[0] - a[0] * b[2], a[0] * b[1] - a[1] * b[0]};
-    const double d[3] = {L[i][0] - L[j][0], L[i][1] - L[j][1], L[i][2] - L[j][2]};
-    if (dot3(g, d) < 0.0) {
-      g[0] = -g[0];
-      g[1] = -g[1];
-      g[2] = -g[2];
-    }
-    for (int c = 0; c < 3; ++c) f.G[i][c] = g[c];
-    f.K[i] = -dot3(g, L[j]);
-    const bool pos = g[0] != 0.0 ? g[0] > 0.0 : (g[1] != 0.0 ? g[1] > 0.0 : g[2] > 0.0);
-    f.thr[i] = pos ? 0 : 1;
-  }
-}
-
-__device__ __forceinline__ bool inside(const Faces& f, const double U[3], double o[4]) {
-  bool in = true;
-  for (int i = 0; i < 4; ++i) {
-    o[i] = dot3(f.G[i], U) + f.K[i];
-    in = in && (o[i] >= (double)f.thr[i]);
-  }
-  return in;
-}
-
-// inclusive voxel index range of lattice interval [lo, hi] (voxel i centred at 128 i + 64)
-__device__ __forceinline__ void vox_range(double lo, double hi, int D, int& a, int& b) {
-  a = max(0, (int)ceil((lo - 64.0) / kLat));
-  b = min(D - 1, (int)floor((hi - 64.0) / kLat));
 }
 
 // Blockid -> logical index so that each of the 8 XCDs (which receive
@@ -221,74 +185,78 @@ __device__ __forceinline__ void slice_rows(const float L[4][3], int z, int Dy, i
 
 // Rasterisation parameters of the tetrahedron with own-grid vertices xo[4][3]
 // and other-grid vertices xt[4][3] (voxel units, already validated on the
-// lattice), in two parts so that no thread holds all of it in registers.
-// setup_task(k) for k in [0, 14) fills the face functions (k < 4), the affine
-// map's matrix (4 <= k < 13) and the bounding box (k = 13); the 14 tasks may
-// run on any threads.  setup_slices then runs on one wave, after the tasks'
+// lattice), in parts that run on different threads: the face function opposite
+// each vertex, the three columns of the affine map's matrix, and the bounding
+// box.  setup_slices (or setup_slices16) then runs on one wave, after these
 // writes are visible to it, and fills the slice table and the map's offset.
-constexpr int kSetupTasks = 14;
+// Differences of lattice coordinates are exact in FP32; every FP64 product and
+// sum below is an exact integer.
 
-__device__ void setup_task(const float* xo, const float* xt, const int D[3], int lane, RasterTet& rt) {
-  if (lane < 4) {
-    // face opposite vertex `lane`
-    const int i = lane;
-    const int j = i == 0 ? 1 : 0, k = i <= 1 ? 2 : 1, l = i <= 2 ? 3 : 2;
-    double Lj[3], a[3], b[3], d[3];
-    for (int c = 0; c < 3; ++c) {
-      Lj[c] = ((double)xo[3 * j + c] + 0.5) * kLat;
-      a[c] = ((double)xo[3 * k + c] + 0.5) * kLat - Lj[c];
-      b[c] = ((double)xo[3 * l + c] + 0.5) * kLat - Lj[c];
-      d[c] = ((double)xo[3 * i + c] + 0.5) * kLat - Lj[c];
-    }
-    double g[3] = {a[1] * b[2] - a[2] * b[1], a[2] * b[0] - a[0] * b[2], a[0] * b[1] - a[1] * b[0]};
-    if (dot3(g, d) < 0.0) {
-      g[0] = -g[0];
-      g[1] = -g[1];
-      g[2] = -g[2];
-    }
-    const double K = -dot3(g, Lj);
-    rt.A[i] = kLat * g[0];
-    rt.CY[i] = kLat * g[1];
-    rt.CZ[i] = kLat * g[2];
-    rt.C0[i] = 64.0 * (g[0] + g[1] + g[2]) + K;
-    rt.rA[i] = g[0] != 0.0 ? 1.0 / (kLat * g[0]) : 0.0;
-    const bool pos = g[0] != 0.0 ? g[0] > 0.0 : (g[1] != 0.0 ? g[1] > 0.0 : g[2] > 0.0);
-    rt.thr[i] = pos ? 0 : 1;
-  } else if (lane < 13) {
-    // J[r][c] = sum_k Oedge[r][k] * 128 adj(M)[k][c] / vol, M = own edge matrix (lattice)
-    const int r = (lane - 4) / 3, c = (lane - 4) % 3;
-    double m[3][3];
-    for (int rr = 0; rr < 3; ++rr)
-      for (int cc = 0; cc < 3; ++cc) m[rr][cc] = ((double)xo[3 * (cc + 1) + rr] - (double)xo[rr]) * kLat;
-    const double vol = m[0][0] * (m[1][1] * m[2][2] - m[1][2] * m[2][1]) - m[0][1] * (m[1][0] * m[2][2] - m[1][2] * m[2][0]) +
-                       m[0][2] * (m[1][0] * m[2][1] - m[1][1] * m[2][0]);
-    // column c of adj(M): cofactors of row c of M
-    const int c1 = (c + 1) % 3, c2 = (c + 2) % 3;
-    double adj[3];
-    for (int k = 0; k < 3; ++k) {
-      const int k1 = (k + 1) % 3, k2 = (k + 2) % 3;
-      adj[k] = m[c1][k1] * m[c2][k2] - m[c1][k2] * m[c2][k1];
-    }
-    double acc = 0.0;
-    for (int k = 0; k < 3; ++k) acc += ((double)xt[3 * (k + 1) + r] - (double)xt[r]) * adj[k];
-    rt.J[r][c] = vol > 0.0 ? acc * kLat / vol : 0.0;
-  } else if (lane == 13) {
-    double lo[3], hi[3];
-    for (int c = 0; c < 3; ++c) {
-      lo[c] = hi[c] = xo[c];
-      for (int q = 1; q < 4; ++q) {
-        lo[c] = fmin(lo[c], (double)xo[3 * q + c]);
-        hi[c] = fmax(hi[c], (double)xo[3 * q + c]);
-      }
-    }
-    int za, zb, ya, yb;
-    vox_range((lo[2] + 0.5) * kLat, (hi[2] + 0.5) * kLat, D[2], za, zb);
-    vox_range((lo[1] + 0.5) * kLat, (hi[1] + 0.5) * kLat, D[1], ya, yb);
-    rt.zlo = za;
-    rt.nz = max(0, zb - za + 1);
-    rt.ylo = ya;
-    rt.ny = max(0, yb - ya + 1);
+// Face opposite vertex i: o_i(U) = G . U + K is the orientation with vertex i
+// replaced by U (zero on the face, 6 x volume at vertex i), taken positive at
+// vertex i.  U lies in the tetrahedron iff o_i(U) >= thr_i for all i, where
+// thr_i = 0 if the first non-zero component of G_i (x, then y, then z) is
+// positive and 1 otherwise: the top-left rule of Sec. 2.3.1 extended to 3-D by
+// perturbing U by (+e, +e^2, +e^3).  Returns (L_i - L_j) . G before the sign is
+// taken: for i = 0 this is minus 6 x the signed volume.
+__device__ __forceinline__ double setup_face(const float* xo, int i, RasterTet& rt) {
+  const int j = i == 0 ? 1 : 0, k = i <= 1 ? 2 : 1, l = i <= 2 ? 3 : 2;
+  double Lj[3], a[3], b[3], d[3];
+  for (int c = 0; c < 3; ++c) {
+    const float xj = xo[3 * j + c];
+    Lj[c] = (double)fmaf(xj, 128.f, 64.f);
+    a[c] = (double)((xo[3 * k + c] - xj) * 128.f);
+    b[c] = (double)((xo[3 * l + c] - xj) * 128.f);
+    d[c] = (double)((xo[3 * i + c] - xj) * 128.f);
   }
+  double g[3] = {a[1] * b[2] - a[2] * b[1], a[2] * b[0] - a[0] * b[2], a[0] * b[1] - a[1] * b[0]};
+  const double s = dot3(g, d);
+  if (s < 0.0)
+    for (int c = 0; c < 3; ++c) g[c] = -g[c];
+  const double K = -dot3(g, Lj);
+  rt.A[i] = kLat * g[0];
+  rt.CY[i] = kLat * g[1];
+  rt.CZ[i] = kLat * g[2];
+  rt.C0[i] = 64.0 * (g[0] + g[1] + g[2]) + K;
+  rt.rA[i] = g[0] != 0.0 ? 1.0 / (kLat * g[0]) : 0.0;
+  const bool pos = g[0] != 0.0 ? g[0] > 0.0 : (g[1] != 0.0 ? g[1] > 0.0 : g[2] > 0.0);
+  rt.thr[i] = pos ? 0 : 1;
+  return s;
+}
+
+// Column c of J: J[r][c] = sum_k Oedge[r][k] * 128 adj(M)[k][c] / vol, M = own
+// edge matrix (lattice), M[r][k] component r of edge k.
+__device__ __forceinline__ void setup_column(const float* xo, const float* xt, int c, RasterTet& rt) {
+  const int c1 = c == 2 ? 0 : c + 1, c2 = c == 0 ? 2 : c - 1;
+  double m0[3], m1[3], m2[3];  // rows c, c + 1, c + 2 of M
+  for (int k = 0; k < 3; ++k) {
+    m0[k] = (double)((xo[3 * (k + 1) + c] - xo[c]) * 128.f);
+    m1[k] = (double)((xo[3 * (k + 1) + c1] - xo[c1]) * 128.f);
+    m2[k] = (double)((xo[3 * (k + 1) + c2] - xo[c2]) * 128.f);
+  }
+  // column c of adj(M): cofactors of row c of M
+  const double adj[3] = {m1[1] * m2[2] - m1[2] * m2[1], m1[2] * m2[0] - m1[0] * m2[2], m1[0] * m2[1] - m1[1] * m2[0]};
+  const double vol = dot3(m0, adj);
+  for (int r = 0; r < 3; ++r) {
+    double acc = 0.0;
+    for (int k = 0; k < 3; ++k) acc += (double)(xt[3 * (k + 1) + r] - xt[r]) * adj[k];
+    rt.J[r][c] = vol > 0.0 ? acc * kLat / vol : 0.0;
+  }
+}
+
+__device__ __forceinline__ void setup_box(const float* xo, const int D[3], RasterTet& rt) {
+  int lo[3], hi[3];
+  for (int c = 1; c < 3; ++c) {
+    const float a = fminf(fminf(xo[c], xo[3 + c]), fminf(xo[6 + c], xo[9 + c]));
+    const float b = fmaxf(fmaxf(xo[c], xo[3 + c]), fmaxf(xo[6 + c], xo[9 + c]));
+    // voxel i (centred at lattice 128 i + 64) lies in the extent iff a <= i <= b
+    lo[c] = max(0, (int)ceilf(a));
+    hi[c] = min(D[c] - 1, (int)floorf(b));
+  }
+  rt.zlo = lo[2];
+  rt.nz = max(0, hi[2] - lo[2] + 1);
+  rt.ylo = lo[1];
+  rt.ny = max(0, hi[1] - lo[1] + 1);
 }
 
 // Candidate rows of the row group that starts at slice k: slice k alone
@@ -400,9 +368,14 @@ __device__ int setup_slices16(const float* xo, const float* xt, const int D[3], 
   return nrows;
 }
 
-// Both parts on one wave.
+// Everything on one wave.
 __device__ void setup_raster(const float* xo, const float* xt, const int D[3], int lane, RasterTet& rt) {
-  if (lane < kSetupTasks) setup_task(xo, xt, D, lane, rt);
+  if (lane < 4)
+    setup_face(xo, lane, rt);
+  else if (lane < 7)
+    setup_column(xo, xt, lane - 4, rt);
+  else if (lane == 7)
+    setup_box(xo, D, rt);
   wave_sync();
   setup_slices(xo, xt, D, lane, rt);
 }
@@ -663,76 +636,74 @@ __device__ __forceinline__ void sweep_one(const WaveRows& wr, const SampleCtx& s
   sum = t;
 }
 
-// Length in mm of b - a (voxel units, float or double components; float
-// components are widened exactly).
-template <class A, class B>
-__device__ __forceinline__ double len_mm(const double sp[3], const A a[3], const B b[3]) {
-  const double dx = ((double)a[0] - (double)b[0]) * sp[0], dy = ((double)a[1] - (double)b[1]) * sp[1],
-               dz = ((double)a[2] - (double)b[2]) * sp[2];
+// Length in mm of the vector d (voxel units).
+__device__ __forceinline__ double len_mm(const double sp[3], double d0, double d1, double d2) {
+  const double dx = d0 * sp[0], dy = d1 * sp[1], dz = d2 * sp[2];
   return sqrt(dx * dx + dy * dy + dz * dz);
 }
 
-// Sec. 2.3.2: deformation term of one tetrahedron (edges weighted 1/k_e, plus
-// the spoke from each vertex to the centroid of its opposite face); squared
-// length differences in mm between the two grids.
-__device__ double deformation_term(const DevProblem& pr, int t, const float S[4][3], const float Tg[4][3]) {
-  const int pa[6] = {0, 0, 0, 1, 1, 2}, pb[6] = {1, 2, 3, 2, 3, 3};
-  double acc = 0.0;
-  for (int e = 0; e < 6; ++e) {
-    const double d = len_mm(pr.sp, S[pa[e]], S[pb[e]]) - len_mm(pr.sp, Tg[pa[e]], Tg[pb[e]]);
-    acc += pr.tet_w[6 * t + e] * d * d;
-  }
-  for (int q = 0; q < 4; ++q) {
-    double cs[3] = {0, 0, 0}, ct[3] = {0, 0, 0};
-    for (int r = 0; r < 4; ++r)
-      if (r != q)
-        for (int c = 0; c < 3; ++c) {
-          cs[c] += (double)S[r][c];
-          ct[c] += (double)Tg[r][c];
-        }
-    for (int c = 0; c < 3; ++c) {
-      cs[c] /= 3.0;
-      ct[c] /= 3.0;
-    }
-    const double d = len_mm(pr.sp, S[q], cs) - len_mm(pr.sp, Tg[q], ct);
-    acc += d * d;
-  }
-  return acc;
+// x / 3 for sums x of three lattice coordinates (multiples of 1/128 below
+// 1536): a product and one correction, equal to the division for each of them,
+// at a quarter of its instructions.
+__device__ __forceinline__ double third(double x) {
+  const double q = x * (1.0 / 3.0);
+  return fma(fma(-3.0, q, x), 1.0 / 3.0, q);
 }
 
-// Sec. 2.3.3: guidance points of image g inside tetrahedron (grid g) are mapped
-// into the other image and contribute the squared mm distance to the nearest
-// point of the same correspondence there.
-__device__ double guidance_term(const DevProblem& pr, const float V[2][4][3]) {
-  double acc = 0.0;
-  for (int g = 0; g < 2; ++g) {
-    if (pr.ng[g] == 0) continue;
-    double L[4][3];  // lattice coordinates of grid g's vertices (exact)
-    for (int q = 0; q < 4; ++q)
-      for (int c = 0; c < 3; ++c) L[q][c] = ((double)V[g][q][c] + 0.5) * kLat;
-    const double vol = orient(L[0], L[1], L[2], L[3]);
-    if (!(vol > 0.0)) continue;
-    Faces f;
-    make_faces(L, f);
-    for (int i = 0; i < pr.ng[g]; ++i) {
-      const double U[3] = {pr.gpt[g][3 * i], pr.gpt[g][3 * i + 1], pr.gpt[g][3 * i + 2]};
-      double o[4];
-      if (!inside(f, U, o)) continue;
-      double x[3] = {0, 0, 0};
-      for (int q = 0; q < 4; ++q)
-        for (int c = 0; c < 3; ++c) x[c] += o[q] / vol * (double)V[1 - g][q][c];
-      double best = INFINITY;
-      const int corr = pr.gcorr[g][i];
-      for (int j = 0; j < pr.ng[1 - g]; ++j) {
-        if (pr.gcorr[1 - g][j] != corr) continue;
-        double r[3];
-        for (int c = 0; c < 3; ++c) r[c] = pr.gpt[1 - g][3 * j + c] / kLat - 0.5;
-        best = fmin(best, len_mm(pr.sp, x, r));
-      }
-      if (best < INFINITY) acc += best * best;
-    }
+// Sec. 2.3.2: the deformation term of one tetrahedron sums over its 6 edges
+// (weighted 1/k_e) and its 4 spokes (from each vertex to the centroid of the
+// opposite face) the squared length difference in mm between the two grids.
+// Length of edge k < 6 or spoke k - 6 of vertices V[4][3]; differences and sums
+// of three lattice coordinates are exact in FP32.
+constexpr int kLengths = 10;
+__device__ __forceinline__ double length_of(const double sp[3], const float* V, int k) {
+  double d[3];
+  if (k < 6) {
+    const int i = (0x211000 >> (4 * k)) & 15, j = (0x332321 >> (4 * k)) & 15;  // 01 02 03 12 13 23
+    for (int c = 0; c < 3; ++c) d[c] = (double)(V[3 * i + c] - V[3 * j + c]);
+  } else {
+    const int q = k - 6, i = q == 0 ? 1 : 0, j = q <= 1 ? 2 : 1, l = q <= 2 ? 3 : 2;
+    for (int c = 0; c < 3; ++c) d[c] = (double)V[3 * q + c] - third((double)(V[3 * i + c] + V[3 * j + c] + V[3 * l + c]));
   }
-  return acc;
+  return len_mm(sp, d[0], d[1], d[2]);
+}
+
+// Sec. 2.3.3: guidance point i of image g, if it lies inside a tetrahedron
+// (own vertices Vo, set up in rt), is mapped into the other image (vertices Vt)
+// and contributes the squared mm distance to the nearest point of the same
+// correspondence there (0 if it lies outside).
+__device__ __forceinline__ double guidance_point(const DevProblem& pr, int g, int i, int match, const float* Vt,
+                                                 const RasterTet& rt) {
+  const double* U = pr.gpt[g] + 3 * i;
+  const double p[3] = {U[0] * (1.0 / kLat) - 0.5, U[1] * (1.0 / kLat) - 0.5, U[2] * (1.0 / kLat) - 0.5};
+  double o[4], vol = 0.0;  // exact: the o_i at any point sum to 6 x the volume
+  bool in = true;
+  for (int q = 0; q < 4; ++q) {
+    o[q] = rt.C0[q] + rt.A[q] * p[0] + rt.CY[q] * p[1] + rt.CZ[q] * p[2];
+    in = in && o[q] >= (double)rt.thr[q];
+    vol += o[q];
+  }
+  if (!in) return 0.0;
+  double x[3] = {0, 0, 0};
+#pragma unroll 1
+  for (int q = 0; q < 4; ++q) {
+    const double lam = o[0] / vol;
+    for (int c = 0; c < 3; ++c) x[c] += lam * (double)Vt[3 * q + c];
+    o[0] = o[1];
+    o[1] = o[2];
+    o[2] = o[3];
+  }
+  double best = INFINITY;
+  const int corr = pr.gcorr[g][i];
+  const int j0 = match < 0 ? 0 : match, j1 = match < 0 ? pr.ng[1 - g] : match + 1;
+#pragma unroll 1
+  for (int j = j0; j < j1; ++j) {
+    if (pr.gcorr[1 - g][j] != corr) continue;
+    const double* r = pr.gpt[1 - g] + 3 * j;
+    best = fmin(best, len_mm(pr.sp, x[0] - (r[0] * (1.0 / kLat) - 0.5), x[1] - (r[1] * (1.0 / kLat) - 0.5),
+                             x[2] - (r[2] * (1.0 / kLat) - 0.5)));
+  }
+  return best < INFINITY ? best * best : 0.0;
 }
 
 // ------------------------------------------------------------ LDS layout
@@ -793,31 +764,32 @@ __device__ __forceinline__ const float* vertex_src(const EvalArgs& a, int s, int
   return src;
 }
 
-__device__ __forceinline__ int group_size(const EvalArgs& a, int g) {
-  return a.partial ? a.aff_cnt[g] : min(kFullChunk, a.pr.T - g * kFullChunk);
-}
-
 __device__ __forceinline__ int group_tet(const EvalArgs& a, int g, int i) {
   return a.partial ? a.aff[(size_t)g * a.maxA + i] : g * kFullChunk + i;
 }
 
 // ------------------------------------------------------------ voxel sweep kernel
 
-// Dissimilarity of every (version, tetrahedron) of one chunk of at most
+// All objective terms of every (version, tetrahedron) of one chunk of at most
 // a.pchunk affected tetrahedra (partial evaluation) or of one group of
-// kFullChunk tetrahedra (full evaluation) of one solution: writes
-// simws[((s*G + g)*nver + v)*maxA + i].  Workgroups are numbered (group, chunk,
+// kFullChunk tetrahedra (full evaluation) of one solution.  Writes the terms of
+// the evaluated version to a.terms_out (where given) and, in partial mode, the
+// chunk's sums per version to sums[((s*G + g)*nchunk + c)*nver + v][3], its
+// constraint flags and its candidate voxel count to cflags / ccount
+// [S][G][nchunk]; k_finish combines them.
+// The deformation and guidance terms are evaluated here, where the chunk's
+// coordinates and face functions are in LDS: in a kernel of their own they
+// waited for the coordinates 77 % of the time (99 us of the 191 us of a 32^3
+// partial evaluation, 420 of 4,750 us of a class of the 50^3 phantom).
+// Workgroups are numbered (group, chunk,
 // solution) with the solution fastest, so the workgroups resident on an XCD
 // sweep the same few tetrahedra of many solutions and share their image
 // region in L2; with `interleave` the groups follow interleaved_group's order.
-// Partial mode also writes the chunk's constraint flags and
-// candidate voxel count to cflags / ccount [S][G][nchunk]; k_finish combines
-// them.  ROWS: the row order, 0 slice by slice, 1 in slice pairs (both fixed
+// ROWS: the row order, 0 slice by slice, 1 in slice pairs (both fixed
 // at compile time), 2 a.row_pairs read at run time (a batch of problems with
 // both orders).
 template <int PARTIAL, int ROWS>
 __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsigned char* smem, bool interleave) {
-  double* __restrict__ simws = a.simws;
   const DevProblem& pr = a.pr;
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int nchunk = PARTIAL ? a.nchunk : 1;
@@ -837,6 +809,13 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   RasterTet* s_rts = (RasterTet*)(smem + Lay.rts);
   __shared__ unsigned s_flags;
   __shared__ unsigned s_count[kWaves];
+  __shared__ unsigned s_bad[2 * kMaxChunk];   // per (version, tetrahedron): bit gr set if grid gr has a coordinate off the lattice
+  __shared__ double s_dg[2 * kMaxChunk][2];   // per (version, tetrahedron): deformation and guidance term
+  // before the sweep, in the space of its rows
+  double* s_len = (double*)s_rows;                   // [nver*na][kLengths] length differences
+  double* s_guid = s_len + 2 * kMaxChunk * kLengths;  // [kWG] partial guidance terms
+  double* s_w = s_guid + kWG;                        // [na][6] edge weights
+  static_assert(sizeof(WaveRows) * kWaves >= sizeof(double) * (2 * kMaxChunk * kLengths + kWG + 6 * kMaxChunk), "set-up space");
 
   // this chunk's tetrahedra: slots [i0, i0 + na) of the group
   const int na_all = uniform(PARTIAL ? a.aff_cnt[g] : min(kFullChunk, pr.T - g * kFullChunk));
@@ -846,76 +825,113 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   const int na = min(PARTIAL ? a.pchunk : kFullChunk, na_all - i0);
   if (tid == 0) s_flags = 0u;
   if (tid < kWaves) s_count[tid] = 0u;
+  if (tid < 2 * kMaxChunk) s_bad[tid] = 0u;
   for (int i = tid; i < na; i += kWG) s_tet[i] = group_tet(a, g, i0 + i);
   __syncthreads();
 
-  // vertex coordinates of every (version, tetrahedron, grid, vertex) and the
-  // per-point constraint bits (lattice, box, border pins) of the candidate
-  for (int e = tid; e < nver * na * 8; e += kWG) {
-    const int v = e / (na * 8), r = e - v * na * 8;
-    const int i = r >> 3, gr = (r >> 2) & 1, q = r & 3;
+  // vertex coordinates of every (version, tetrahedron, grid, vertex), one
+  // thread per component, and their constraint bits (lattice, box, border pins)
+  const int nvt = nver * na;
+  for (int e = tid; e < nvt * 24; e += kWG) {
+    const int vt = e / 24, r = e - vt * 24, gr = r / 12, q = (r - gr * 12) / 3, ax = r % 3;
+    const int v = vt >= na ? 1 : 0, i = vt - v * na;
     const int vid = ((const int*)&pr.tets[s_tet[i]])[q];
-    const float* src = vertex_src(a, s, g, v, vid, gr);
-    float* dst = s_xyz + ((size_t)(v * na + i) * 8 + gr * 4 + q) * 3;
-    unsigned fl = 0u;
-    const int idx[3] = {vid % pr.n[0], (vid / pr.n[0]) % pr.n[1], vid / (pr.n[0] * pr.n[1])};
-    for (int c = 0; c < 3; ++c) {
-      const float x = src[c];
-      dst[c] = x;
-      double u;
-      const unsigned fc = lattice_of(x, pr.D[c], u);
-      fl |= fc;
-      if (!fc && ((idx[c] == 0 && u != 0.0) || (idx[c] == pr.n[c] - 1 && u != kLat * pr.D[c]))) fl |= DSM_FLAG_BORDER;
-    }
+    const unsigned pin = pr.pin[vid];
+    float x = vertex_src(a, s, g, v, vid, gr)[ax];
+    unsigned fl = lattice_bits(x, ax == 0 ? pr.D[0] : (ax == 1 ? pr.D[1] : pr.D[2]));
+    s_xyz[e] = x;
+    if (fl)
+      atomicOr(&s_bad[vt], 1u << gr);
+    else if (((pin >> ax) & 1 && x != -0.5f) || ((pin >> (3 + ax)) & 1 && x != (float)(ax == 0 ? pr.D[0] : (ax == 1 ? pr.D[1] : pr.D[2])) - 0.5f))
+      fl = DSM_FLAG_BORDER;
     if (v == 0 && PARTIAL && fl) atomicOr(&s_flags, fl);
   }
+  if (wave == kWaves - 1 && lane < 6 * na) s_w[lane] = pr.tet_w[6 * (size_t)s_tet[lane / 6] + lane % 6];
   __syncthreads();
 
-  // set-up of every (version, direction, tetrahedron) entry: validity,
-  // orientation flag, rasterisation parameters and the number of 64-row
-  // units.  Direction 0 = target voxels mapped into the source (forward), 1 =
-  // source voxels into the target.  Entry e's own-grid vertices are at
-  // entry_xyz(e) + 12 own, the other grid's at + 12 (1 - own).
-  const int nent = nver * 2 * na;
-  auto entry_xyz = [&](int e, int& own) {
-    const int v = e / (2 * na), r = e - v * 2 * na, dir = r / na, i = r - dir * na;
+  // set-up of every (version, direction, tetrahedron) entry and the lengths of
+  // the deformation term.  Direction 0 = target voxels mapped into the source
+  // (forward), 1 = source voxels into the target.  Entry e's own-grid vertices
+  // are at entry_xyz(e) + 12 own, the other grid's at + 12 (1 - own).  The
+  // tasks are grouped by kind, 64 to a wave, so that no wave runs two kinds
+  // side by side: matrix columns, faces, lengths, boxes.
+  const int nent = 2 * nvt;
+  auto entry_vt = [&](int e, int& own) {  // entries are ordered (version, direction, tetrahedron)
+    const int v = e >= 2 * na ? 1 : 0, r = e - v * 2 * na, dir = r >= na ? 1 : 0;
     own = 1 - dir;
-    return s_xyz + (size_t)(v * na + i) * 24;
+    return v * na + (r - dir * na);
   };
-  // validity, 32 threads per entry: the 24 coordinates on the lattice, then
-  // the orientation of the own-grid tetrahedron; s_units[e] = 1 if it is set up
-  for (int t = tid; t < nent * 32; t += kWG) {
-    const int e = t >> 5, j = t & 31;
-    int own;
-    const float* xyz = entry_xyz(e, own);
-    double dummy;
-    const bool bad = j < 24 && lattice_of(xyz[j], pr.D[j % 3], dummy) != 0u;
-    const unsigned long long bm = __ballot(bad) >> (lane & 32);  // this entry's half of the wave
-    const bool bad_own = (bm >> (own * 12)) & 0xfffull, bad_oth = (bm >> ((1 - own) * 12)) & 0xfffull;
-    int ok = 0;
-    if (!bad_own) {
-      double L[4][3];
-      for (int q = 0; q < 4; ++q)
-        for (int c = 0; c < 3; ++c) L[q][c] = ((double)xyz[own * 12 + q * 3 + c] + 0.5) * kLat;
-      const double vol = orient(L[0], L[1], L[2], L[3]);
-      if (vol > 0.0 && !bad_oth)
-        ok = 1;
-      else if (!(vol > 0.0) && e < 2 * na && PARTIAL && j == 0)  // candidate version only
-        atomicOr(&s_flags, own == 0 ? DSM_FLAG_INV_MOVING : DSM_FLAG_INV_FIXED);
+  auto entry_xyz = [&](int e, int& own) { return s_xyz + (size_t)entry_vt(e, own) * 24; };
+  {
+    const int nj = (3 * nent + 63) >> 6, nf = (4 * nent + 63) >> 6, nl = (kLengths * nvt + 63) >> 6, nb = (nent + 63) >> 6;
+    for (int job = wave; job < nj + nf + nl + nb; job += kWaves) {
+      if (job < nj) {
+        const int t = job * 64 + lane, e = t / 3;
+        int own;
+        if (e < nent && s_bad[entry_vt(e, own)] == 0u) {
+          const float* xyz = entry_xyz(e, own);
+          setup_column(xyz + own * 12, xyz + (1 - own) * 12, t - 3 * e, s_rts[e]);
+        }
+      } else if (job < nj + nf) {
+        const int t = (job - nj) * 64 + lane, e = t >> 2;
+        int own;
+        if (e < nent) {
+          const int vt = entry_vt(e, own);
+          const unsigned bad = s_bad[vt];
+          int ok = 0;
+          if (!((bad >> own) & 1)) {
+            const bool pos = setup_face(s_xyz + (size_t)vt * 24 + own * 12, t & 3, s_rts[e]) < 0.0;  // read for face 0
+            ok = pos && bad == 0u ? 1 : 0;
+            if (PARTIAL && !pos && (t & 3) == 0 && e < 2 * na)  // candidate version only
+              atomicOr(&s_flags, own == 0 ? DSM_FLAG_INV_MOVING : DSM_FLAG_INV_FIXED);
+          }
+          if ((t & 3) == 0) s_units[e] = ok;  // 1 if the entry is set up
+        }
+      } else if (job < nj + nf + nl) {
+        const int t = (job - nj - nf) * 64 + lane, vt = t / kLengths, k = t - vt * kLengths;
+        if (vt < nvt) {
+          const float* xyz = s_xyz + (size_t)vt * 24;
+          s_len[t] = length_of(pr.sp, xyz, k) - length_of(pr.sp, xyz + 12, k);
+        }
+      } else {
+        const int e = (job - nj - nf - nl) * 64 + lane;
+        int own;
+        if (e < nent && s_bad[entry_vt(e, own)] == 0u) setup_box(entry_xyz(e, own) + own * 12, pr.D, s_rts[e]);
+      }
     }
-    if (j == 0) s_units[e] = ok;
   }
   __syncthreads();
-  // face functions, affine map and bounding box: 16 threads per entry
-  for (int t = tid; t < nent * 16; t += kWG) {
-    const int e = t >> 4, k = t & 15;
-    if (k < kSetupTasks && s_units[e]) {
-      int own;
-      const float* xyz = entry_xyz(e, own);
-      setup_task(xyz + own * 12, xyz + (1 - own) * 12, pr.D, k, s_rts[e]);
+  // guidance points, kWG / (2 nver kMaxChunk) lanes per (version, tetrahedron,
+  // grid) sharing its image's points: each is first tested against the
+  // tetrahedron's bounding box (exactly, on the lattice), which holds few
+  const int gper = kWG / (2 * kMaxChunk * nver);
+  const bool guided = pr.ng[0] + pr.ng[1] > 0;
+  if (guided) {
+    const int tg = tid / gper, vt = tg >> 1, gr = tg & 1;
+    const int e = vt < nvt ? (vt >= na ? na : 0) + vt + (1 - gr) * na : 0;  // the entry of grid gr's own voxels
+    double acc = 0.0;
+    if (vt < nvt && s_units[e]) {
+      const float *Vo = s_xyz + (size_t)vt * 24 + gr * 12, *Vt = s_xyz + (size_t)vt * 24 + (1 - gr) * 12;
+      float lo[3], hi[3];
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = fmaf(fminf(fminf(Vo[k], Vo[3 + k]), fminf(Vo[6 + k], Vo[9 + k])), 128.f, 64.f);
+        hi[k] = fmaf(fmaxf(fmaxf(Vo[k], Vo[3 + k]), fmaxf(Vo[6 + k], Vo[9 + k])), 128.f, 64.f);
+      }
+      for (int i = tid - tg * gper; i < pr.ng[gr]; i += gper) {
+        const float4 u = pr.gbox[gr][i];
+        if ((u.x >= lo[0]) & (u.x <= hi[0]) & (u.y >= lo[1]) & (u.y <= hi[1]) & (u.z >= lo[2]) & (u.z <= hi[2]))
+          acc += guidance_point(pr, gr, i, __float_as_int(u.w), Vt, s_rts[e]);
+      }
     }
+    s_guid[tid] = acc;
   }
-  __syncthreads();
+  if (wave == kWaves - 1 && lane < nvt) {  // deformation: edges weighted 1/k_e, then spokes
+    const double *len = s_len + kLengths * lane, *w = s_w + 6 * (lane >= na ? lane - na : lane);
+    double def = 0.0;
+    for (int k = 0; k < 6; ++k) def += w[k] * len[k] * len[k];
+    for (int k = 6; k < kLengths; ++k) def += len[k] * len[k];
+    s_dg[lane][0] = def;
+  }
   // slice tables, 16 lanes per entry, and the units
   for (int e0 = wave * 4; e0 < nent; e0 += kWaves * 4) {
     const int e = e0 + (lane >> 4), sub = lane & 15;
@@ -935,6 +951,12 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   for (int e = tid; e < nent * kWaves; e += kWG) s_part[e] = 0.0;
   __syncthreads();
   lds_exclusive_scan(s_units, nent, tid);
+  if (wave == kWaves - 1 && lane < nvt) {
+    double guid = 0.0;
+    if (guided)
+      for (int k = 0; k < 2 * gper; ++k) guid += s_guid[2 * gper * lane + k];
+    s_dg[lane][1] = guid;
+  }
   __syncthreads();
   const int total_units = uniform(s_units[nent]);
 
@@ -1012,13 +1034,27 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   if (lane == 0) s_count[wave] = counted;
   __syncthreads();
 
-  double* out = simws + ((size_t)s * a.G + g) * nver * a.maxA + i0;
-  for (int e = tid; e < nver * na; e += kWG) {
-    const int v = e / na, i = e - v * na;
-    double sim = 0.0;
-    for (int dir = 0; dir < 2; ++dir)
-      for (int w = 0; w < kWaves; ++w) sim += s_part[((size_t)(v * 2 + dir) * na + i) * kWaves + w];
-    out[(size_t)v * a.maxA + i] = sim;
+  // terms, kMaxChunk lanes of wave 0 per version (zero where the tetrahedron
+  // has a coordinate off the lattice), and their sums over the chunk in a fixed
+  // butterfly order
+  if (wave == 0 && lane < nver * kMaxChunk) {
+    const int v = lane / kMaxChunk, i = lane - v * kMaxChunk, vt = v * na + i;
+    double term[3] = {0.0, 0.0, 0.0};
+    if (i < na && s_bad[vt] == 0u) {
+      for (int dir = 0; dir < 2; ++dir)
+        for (int w = 0; w < kWaves; ++w) term[0] += s_part[((size_t)(v * 2 + dir) * na + i) * kWaves + w];
+      term[1] = s_dg[vt][0];
+      term[2] = s_dg[vt][1];
+    }
+    if (v == 0 && i < na && a.terms_out) {
+      double* o = a.terms_out + ((size_t)s * pr.T + s_tet[i]) * 3;
+      for (int k = 0; k < 3; ++k) o[k] = term[k];
+    }
+    if (PARTIAL) {
+      for (int k = 0; k < 3; ++k) term[k] = group_sum(term[k]);
+      const size_t ci = ((size_t)s * a.G + g) * nchunk + c;
+      if (i < 3) a.sums[(ci * nver + v) * 3 + i] = i == 0 ? term[0] : (i == 1 ? term[1] : term[2]);
+    }
   }
   if (PARTIAL && tid == 0) {
     const size_t ci = ((size_t)s * a.G + g) * nchunk + c;
@@ -1063,109 +1099,72 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(7, 8))) voi
 
 // ------------------------------------------------------------ finishing kernel
 
-// Adds the deformation and guidance terms (FP64, per tetrahedron) to the swept
-// dissimilarity, writes per-tetrahedron terms, and in partial mode the
-// normalised sums over each group in ascending tetrahedron order.  One group
-// of kFinishLanes lanes per (group, solution) pair, one lane per affected
-// tetrahedron (kFinishLanes at a time): a star averages 16 tetrahedra, so
-// 8-lane groups keep the FP64 lanes busy over about two rounds (measured
-// against 16 and 32 lanes per pair: 0.86, 1.07 and 1.7 ms per 512x512x100 step).
+// The normalised sums, flags and voxel count of a (group, solution) pair of a
+// partial evaluation from those of its chunks, in chunk order, and the sums of
+// the current terms: the chunks' second version, or the cached terms of the
+// affected tetrahedra (a fixed butterfly order over each kFinishLanes of them).
+// One group of kFinishLanes lanes per pair.
 __device__ __forceinline__ void finish_body(const EvalArgs& a, int logical, int lane) {
-  const double* __restrict__ simws = a.simws;
   const DevProblem& pr = a.pr;
   const int g = logical / a.S, s = logical - g * a.S;
-  const int na = group_size(a, g);
+  const int na = a.aff_cnt[g];
   const size_t oi = (size_t)s * a.G + g;
-  if (na < 0 || (a.partial && a.mask && a.mask[oi] == 0)) {
+  if (na < 0 || (a.mask && a.mask[oi] == 0)) {
     if (lane < 3) {
       a.part_new[oi * 3 + lane] = 0.0;
       a.part_old[oi * 3 + lane] = 0.0;
     }
-    if (a.partial && lane == 0) {
+    if (lane == 0) {
       a.flags[oi] = na < 0 ? DSM_FLAG_BAD_FOS : DSM_FLAG_SKIPPED;
       if (a.vcount) a.vcount[oi] = 0u;
     }
     return;
   }
-  if (a.partial && lane == 0) {  // combine the chunks' flags and voxel counts in chunk order
-    unsigned fl = 0u, cnt = 0u;
-    for (int c = 0; c * a.pchunk < na; ++c) {
-      fl |= a.cflags[oi * a.nchunk + c];
-      cnt += a.ccount[oi * a.nchunk + c];
-    }
-    a.flags[oi] = fl;
-    if (a.vcount) a.vcount[oi] = cnt;
+  // lanes 0..2 the evaluated version, 3..5 the current one where it was swept;
+  // lane 6 the flags, lane 7 the counts
+  const size_t c0 = oi * a.nchunk;
+  const int nc = (na + a.pchunk - 1) / a.pchunk, nval = 3 * a.nver;
+  double acc = 0.0;
+  unsigned bits = 0u;
+  if (lane < nval) {
+#pragma unroll 4
+    for (int c = 0; c < nc; ++c) acc += a.sums[(c0 + c) * nval + lane];
+  } else if (lane == 6) {
+    for (int c = 0; c < nc; ++c) bits |= a.cflags[c0 + c];
+    a.flags[oi] = bits;
+  } else if (lane == 7 && a.vcount) {
+    for (int c = 0; c < nc; ++c) bits += a.ccount[c0 + c];
+    a.vcount[oi] = bits;
   }
-  // one lane per affected tetrahedron; the per-tetrahedron terms are summed
-  // over the lane group in a fixed butterfly order
-  const double* sims = simws + oi * a.nver * a.maxA;
-  double accn[3] = {0, 0, 0}, acco[3] = {0, 0, 0};
-  for (int base = 0; base < na; base += kFinishLanes) {
-    const int i = base + lane;
-    double tn[3] = {0, 0, 0}, to[3] = {0, 0, 0};
-    for (int v = 0; v < a.nver; ++v) {
-      double term[3] = {0, 0, 0};
-      if (i < na) {
-        const int t = group_tet(a, g, i);
-        const int4 tv = pr.tets[t];
-        const int vid[4] = {tv.x, tv.y, tv.z, tv.w};
-        float V[2][4][3];
-        unsigned bad = 0u;
-        for (int gr = 0; gr < 2; ++gr)
-          for (int q = 0; q < 4; ++q) {
-            const float* src = vertex_src(a, s, g, v, vid[q], gr);
-            for (int c = 0; c < 3; ++c) {
-              double u;
-              V[gr][q][c] = src[c];
-              bad |= lattice_of(src[c], pr.D[c], u);
-            }
-          }
-        if (!bad) {
-          term[0] = sims[(size_t)v * a.maxA + i];
-          term[1] = deformation_term(pr, t, V[0], V[1]);
-          term[2] = guidance_term(pr, V);
-        }
-        if (v == 0 && a.terms_out) {
-          double* o = a.terms_out + ((size_t)s * pr.T + t) * 3;
-          o[0] = term[0];
-          o[1] = term[1];
-          o[2] = term[2];
-        }
+  if (a.nver == 1) {
+    double old[3] = {0.0, 0.0, 0.0};
+#pragma unroll 2
+    for (int base = 0; base < na; base += kFinishLanes) {
+      double t[3] = {0.0, 0.0, 0.0};
+      if (base + lane < na) {
+        const double* src = a.terms_in + ((size_t)s * pr.T + a.aff[(size_t)g * a.maxA + base + lane]) * 3;
+        for (int k = 0; k < 3; ++k) t[k] = src[k];
       }
-      for (int c = 0; c < 3; ++c) (v == 0 ? tn : to)[c] = term[c];
+      for (int k = 0; k < 3; ++k) old[k] += group_sum(t[k]);
     }
-    if (a.partial) {
-      if (a.nver == 1 && i < na) {  // current terms from the cache
-        const double* src = a.terms_in + ((size_t)s * pr.T + group_tet(a, g, i)) * 3;
-        for (int c = 0; c < 3; ++c) to[c] = src[c];
-      }
-      for (int c = 0; c < 3; ++c) {
-        accn[c] += group_sum(tn[c]);
-        acco[c] += group_sum(to[c]);
-      }
-    }
+    if (lane >= 3 && lane < 6) acc = lane == 3 ? old[0] : (lane == 4 ? old[1] : old[2]);
   }
-  if (a.partial && lane < 6) {
-    const int c = lane % 3;
-    if (lane < 3)
-      a.part_new[oi * 3 + c] = accn[c] * pr.norm[c];
-    else
-      a.part_old[oi * 3 + c] = acco[c] * pr.norm[c];
-  }
+  if (lane < 3)
+    a.part_new[oi * 3 + lane] = acc * pr.norm[lane];
+  else if (lane < 6)
+    a.part_old[oi * 3 + lane - 3] = acc * pr.norm[lane - 3];
 }
+static_assert(kFinishLanes == 8, "lanes of a pair by value");
 
-// FP64 geometry per lane: the 3-wave target (at most 168 VGPRs, with some
-// registers spilled) ran the finish kernels 20 % faster than 2 waves without
-// spills.
-// Each 64-lane workgroup takes kFinishPairs consecutive pairs.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_finish(EvalArgs a, int n_pairs) {
+// Each workgroup of 64 lanes takes kFinishPairs consecutive pairs.
+__global__ __launch_bounds__(64) void k_finish(EvalArgs a, int n_pairs) {
   const int pair = blockIdx.x * kFinishPairs + (threadIdx.x / kFinishLanes);
   if (pair < n_pairs) finish_body(a, pair, threadIdx.x % kFinishLanes);
 }
 
 // Several problems: wg_off [n_jobs + 1] are the jobs' first workgroups, a job
 // of n pairs taking ceil(n / kFinishPairs) of them.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_finish_batch(const EvalArgs* __restrict__ jobs, const int* __restrict__ wg_off,
+__global__ __launch_bounds__(64) void k_finish_batch(const EvalArgs* __restrict__ jobs, const int* __restrict__ wg_off,
                                                      int n_jobs) {
   int j = 0;
   while (j + 1 < n_jobs && wg_off[j + 1] <= (int)blockIdx.x) ++j;
@@ -1610,6 +1609,7 @@ hipError_t launch_eval(const EvalArgs& a, hipEvent_t ev_begin, hipEvent_t ev_end
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ev_end) (void)hipEventRecord(ev_end, stream);
+  if (!a.partial) return hipSuccess;  // the sweep wrote the terms
   k_finish<<<(unsigned)((nwg + kFinishPairs - 1) / kFinishPairs), 64, 0, stream>>>(a, (int)nwg);
   return hipGetLastError();
 }

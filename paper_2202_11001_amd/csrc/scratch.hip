@@ -39,7 +39,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Byte offsets of the workspace regions inside `scratch`.
 struct ScratchLayout {
-  size_t aff, aff_cnt, order, simws, cflags, ccount, total;
+  size_t aff, aff_cnt, order, sums, cflags, ccount, total;
 };
 
 ScratchLayout scratch_layout(int S, int F, int maxA, int nver, int nchunk) {
@@ -51,7 +51,7 @@ ScratchLayout scratch_layout(int S, int F, int maxA, int nver, int nchunk) {
   o = align256(o + sizeof(int) * (size_t)F);
   L.order = o;
   o = align256(o + sizeof(int) * (size_t)F);
-  L.simws = o;
+  L.sums = o;  // 3 sums per chunk of at least kMinPartChunk tetrahedra and version: at most one double per tetrahedron
   o = align256(o + sizeof(double) * (size_t)S * F * nver * maxA);
   L.cflags = o;
   o = align256(o + sizeof(uint32_t) * (size_t)S * F * nchunk);
@@ -126,7 +126,7 @@ dsm_status dsm_eval_partial_noalloc(dsm_problem* p, int32_t S, const float* X, i
   a.terms_out = tet_terms_new;
   a.vcount = voxel_count;
   a.mask = nullptr;
-  a.simws = (double*)(base + L.simws);
+  a.sums = (double*)(base + L.sums);
   a.pchunk = p->part_chunk;
   a.row_pairs = p->row_order;
   a.nchunk = nchunk;

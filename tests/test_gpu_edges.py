@@ -4,8 +4,10 @@ import numpy as np
 import pytest
 
 from oracle import gomea_ref as G
+from oracle import ref
 from oracle import surrogate_ref as R
 from paper_2202_11001_amd import workloads as W
+from tests._common import assert_delta_close, assert_objectives_close
 
 pytestmark = pytest.mark.gpu
 
@@ -236,3 +238,46 @@ def test_archive_merge_shapes(capacity, m, row_floats, offset):
             np.testing.assert_array_equal(A.rows[:len(vec)].cpu().numpy(), rows)
     A.merge(_t(np.full((1, 3), np.nan)), torch.zeros((1, row_floats), device=DEV) if row_floats else None)
     assert A.n in (len(vec), len(vec) + 1)
+
+
+# guidance points: none, fewer and more than the lanes that share them (8 and 16), several points of one correspondence;
+# with and without cached terms, chunks that divide the stars and chunks that do not
+@pytest.mark.parametrize("n_guid,cached,chunk", [(0, True, 8), (1, True, 5), (7, False, 8), (40, True, 4), (40, False, 7)])
+def test_terms_of_a_chunk(n_guid, cached, chunk):
+    rng = np.random.default_rng(n_guid + chunk)
+    shape, mesh, S = (18, 22, 26), (3, 4, 3), 5
+    mov, fix = rng.uniform(0, 1, (2,) + shape).astype(np.float32)
+    dims = (shape[2], shape[1], shape[0])
+    hi = np.array(dims) - 1.0
+    gm, gf = W.snap(rng.uniform(0, 1, (2, n_guid, 3)) * hi) if n_guid else np.zeros((2, 0, 3), np.float32)
+    corr = np.arange(n_guid, dtype=np.int32) // (3 if n_guid == 40 else 1)  # threes share a correspondence
+    spacing = (0.9, 1.1, 2.5)
+    held = tuple(float(np.float32(v)) for v in spacing)  # the library holds the spacing in FP32
+    rp = ref.Problem(mov, fix, mesh, held, 0.1, guid_moving=gm, corr_moving=corr, guid_fixed=gf, corr_fixed=corr)
+    P = int(np.prod(mesh))
+    gp = dsm.Problem(mov, fix, mesh, spacing, 0.1, gm, corr, gf, corr, max_solutions=S, max_fos=P + 1, max_fos_points=3)
+    gp.set_part_chunk(chunk)
+    X = W.population(dims, mesh, S, 1.0, 7, reject=lambda x: rp.fold_check(x)[0] != 0)
+    off = np.concatenate([np.arange(P), [P, P + 3]]).astype(np.int32)  # every point, then one element of three
+    pts = np.concatenate([np.arange(P), [0, 16, 17]]).astype(np.int32)
+    cand = W.candidates(X, off, pts, mesh, dims, 1.0, 8)
+    cand[0, 3, 0, 1] += 1 / 512.0   # off the lattice
+    cand[1, 5, 1, 2] = np.nan
+    cand[2, 16] = cand[2, 16] + 20.0  # folds
+    F = len(off) - 1
+    Xd = _t(X)
+    cache = torch.empty((S, gp.T, 3), dtype=torch.float64, device=DEV)
+    obj, flags = gp.eval_full(Xd, tet_terms=cache)
+    robj, rflags, rterms, _ = rp.eval_full(X, want_terms=True)
+    assert np.all(flags.cpu().numpy() == 0) and np.all(rflags == 0)
+    assert_objectives_close(obj.cpu().numpy(), robj)
+    # deformation and guidance are FP64 on both sides: a few hundred roundings of terms up to 1e3
+    np.testing.assert_allclose(cache.cpu().numpy()[..., 1:], rterms[..., 1:], rtol=1e-10, atol=1e-10)
+    old, new, fl, vc = gp.eval_partial(Xd, _t(off), _t(pts), _t(cand), tet_terms_in=cache if cached else None,
+                                       voxel_count=True)
+    rold, rnew, rfl, rnv = rp.eval_partial(X, off, pts, cand, tet_terms=rterms if cached else None)
+    np.testing.assert_array_equal(fl.cpu().numpy().astype(np.uint32), rfl)
+    np.testing.assert_array_equal(vc.cpu().numpy()[rfl == 0], rnv[rfl == 0])
+    assert (rfl == 0).sum() > S * F // 2 and (rfl[[0, 1, 2], [3, 5, 16]] != 0).all()
+    assert_objectives_close(old.cpu().numpy(), rold, what="current sums")
+    assert_delta_close(old.cpu().numpy(), new.cpu().numpy(), rold, rnew, rfl)
