@@ -98,9 +98,25 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+template <int kCtrl>
+__device__ __forceinline__ double dpp64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// Sum over the 64 lanes of a wave, all lanes active, in a fixed order: within
+// each row of 16 lanes by DPP permutations, then over the four rows.
 __device__ __forceinline__ double wave_sum(double v) {
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  v += dpp64<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp64<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp64<0x141>(v);  // row_half_mirror: the other quad of 8 lanes
+  v += dpp64<0x140>(v);  // row_mirror: the other 8 lanes of the row
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
 // Sum over the kFinishLanes lanes of a lane group, in a fixed butterfly order
@@ -123,6 +139,17 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
   return v;
 }
 
+// Inclusive prefix maximum over the 64 lanes of a wave of values >= 0, all lanes active.
+__device__ __forceinline__ int wave_incl_max(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false));
+  return v;
+}
+
 // Inclusive prefix sum within each row of 16 lanes (the lanes of a row active).
 __device__ __forceinline__ int row16_incl_scan(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);  // row_shr:1
@@ -137,9 +164,9 @@ __device__ __forceinline__ int row16_incl_scan(int v) {
 constexpr int kMaxSlices = 64;  // slice-table capacity; taller tetrahedra enumerate bounding-box rows
 
 struct RasterTet {
-  double A[4], C0[4], CY[4], CZ[4], rA[4];  // o_i(x,y,z) = A x + C0 + CY y + CZ z at voxel (x,y,z)
-  double J[3][3];  // own voxel coords -> other grid voxel coords: p' = P0 + J v
-  double P0[3];
+  // o_i(x,y,z) - thr_i = A x + C0 + CY y + CZ z at voxel (x,y,z): F[i] = (C0, CY, CZ, -1 / A or 0)
+  double F[4][4], A[4];
+  double M[3][4];  // own voxel coords -> other grid voxel coords: p' = M[.][3] + M[.][0..2] v
   int thr[4];
   int zlo, nz, ylo, ny;  // bounding box (slices, rows)
   int nrows;             // candidate rows
@@ -215,32 +242,32 @@ __device__ __forceinline__ double setup_face(const float* xo, int i, RasterTet& 
     for (int c = 0; c < 3; ++c) g[c] = -g[c];
   const double K = -dot3(g, Lj);
   rt.A[i] = kLat * g[0];
-  rt.CY[i] = kLat * g[1];
-  rt.CZ[i] = kLat * g[2];
-  rt.C0[i] = 64.0 * (g[0] + g[1] + g[2]) + K;
-  rt.rA[i] = g[0] != 0.0 ? 1.0 / (kLat * g[0]) : 0.0;
+  rt.F[i][1] = kLat * g[1];
+  rt.F[i][2] = kLat * g[2];
   const bool pos = g[0] != 0.0 ? g[0] > 0.0 : (g[1] != 0.0 ? g[1] > 0.0 : g[2] > 0.0);
+  rt.F[i][0] = 64.0 * (g[0] + g[1] + g[2]) + K - (pos ? 0.0 : 1.0);
+  rt.F[i][3] = g[0] != 0.0 ? -1.0 / (kLat * g[0]) : 0.0;
   rt.thr[i] = pos ? 0 : 1;
   return s;
 }
 
-// Column c of J: J[r][c] = sum_k Oedge[r][k] * 128 adj(M)[k][c] / vol, M = own
-// edge matrix (lattice), M[r][k] component r of edge k.
+// Column c of M: M[r][c] = sum_k Oedge[r][k] * 128 adj(E)[k][c] / vol, E = own
+// edge matrix (lattice), E[r][k] component r of edge k.
 __device__ __forceinline__ void setup_column(const float* xo, const float* xt, int c, RasterTet& rt) {
   const int c1 = c == 2 ? 0 : c + 1, c2 = c == 0 ? 2 : c - 1;
-  double m0[3], m1[3], m2[3];  // rows c, c + 1, c + 2 of M
+  double m0[3], m1[3], m2[3];  // rows c, c + 1, c + 2 of E
   for (int k = 0; k < 3; ++k) {
     m0[k] = (double)((xo[3 * (k + 1) + c] - xo[c]) * 128.f);
     m1[k] = (double)((xo[3 * (k + 1) + c1] - xo[c1]) * 128.f);
     m2[k] = (double)((xo[3 * (k + 1) + c2] - xo[c2]) * 128.f);
   }
-  // column c of adj(M): cofactors of row c of M
+  // column c of adj(E): cofactors of row c of E
   const double adj[3] = {m1[1] * m2[2] - m1[2] * m2[1], m1[2] * m2[0] - m1[0] * m2[2], m1[0] * m2[1] - m1[1] * m2[0]};
   const double vol = dot3(m0, adj);
   for (int r = 0; r < 3; ++r) {
     double acc = 0.0;
     for (int k = 0; k < 3; ++k) acc += (double)(xt[3 * (k + 1) + r] - xt[r]) * adj[k];
-    rt.J[r][c] = vol > 0.0 ? acc * kLat / vol : 0.0;
+    rt.M[r][c] = vol > 0.0 ? acc * kLat / vol : 0.0;
   }
 }
 
@@ -313,7 +340,7 @@ __device__ void setup_slices(const float* xo, const float* xt, const int D[3], i
   }
   if (lane < 3) {
     const int r = lane;
-    rt.P0[r] = (double)xt[r] - (rt.J[r][0] * (double)xo[0] + rt.J[r][1] * (double)xo[1] + rt.J[r][2] * (double)xo[2]);
+    rt.M[r][3] = (double)xt[r] - (rt.M[r][0] * (double)xo[0] + rt.M[r][1] * (double)xo[1] + rt.M[r][2] * (double)xo[2]);
   }
   wave_sync();
 }
@@ -363,7 +390,7 @@ __device__ int setup_slices16(const float* xo, const float* xt, const int D[3], 
   }
   if (sub < 3) {
     const int r = sub;
-    rt.P0[r] = (double)xt[r] - (rt.J[r][0] * (double)xo[0] + rt.J[r][1] * (double)xo[1] + rt.J[r][2] * (double)xo[2]);
+    rt.M[r][3] = (double)xt[r] - (rt.M[r][0] * (double)xo[0] + rt.M[r][1] * (double)xo[1] + rt.M[r][2] * (double)xo[2]);
   }
   return nrows;
 }
@@ -380,36 +407,74 @@ __device__ void setup_raster(const float* xo, const float* xt, const int D[3], i
   setup_slices(xo, xt, D, lane, rt);
 }
 
-// Exact x-span [x0, x1] (inclusive; empty if x0 > x1) of voxel row (y, z).
-__device__ __forceinline__ void row_span(const RasterTet& rt, int y, int z, int Dx, int& x0, int& x1) {
+// Exact x-span [x0, x1] (inclusive; empty if x0 > x1) of voxel row (y, z):
+// every face's bound rounded by the reciprocal and corrected by evaluating the
+// (integer) face function next to it.
+__device__ __forceinline__ void row_span_exact(const RasterTet& rt, double y, double z, int Dx, int& x0, int& x1) {
   int lo = 0, hi = Dx - 1;
+#pragma unroll 1
   for (int i = 0; i < 4; ++i) {
     const double A = rt.A[i];
-    // need A x + B >= thr  <=>  A x >= c
-    const double c = (double)rt.thr[i] - (rt.C0[i] + rt.CY[i] * y + rt.CZ[i] * z);
+    const double h = rt.F[i][0] + rt.F[i][1] * y + rt.F[i][2] * z;  // need A x + h >= 0
+    const double q = fmin(fmax(h * rt.F[i][3], -2.0), (double)Dx + 1.0);
     if (A > 0.0) {
-      const double q = fmin(fmax(c * rt.rA[i], -2.0), (double)Dx + 1.0);
       int x = (int)ceil(q);
-      if (A * (x - 1) >= c)
+      if (A * (x - 1) + h >= 0.0)
         x -= 1;
-      else if (A * x < c)
+      else if (A * x + h < 0.0)
         x += 1;
       lo = max(lo, x);
     } else if (A < 0.0) {
-      const double q = fmin(fmax(c * rt.rA[i], -2.0), (double)Dx + 1.0);
       int x = (int)floor(q);
-      if (A * (x + 1) >= c)
+      if (A * (x + 1) + h >= 0.0)
         x += 1;
-      else if (A * x < c)
+      else if (A * x + h < 0.0)
         x -= 1;
       hi = min(hi, x);
-    } else if (c > 0.0) {
+    } else if (h < 0.0) {
       lo = Dx;
       hi = -1;
     }
   }
   x0 = lo;
   x1 = hi;
+}
+
+// The same span for the 64 rows of a wave (used lanes: `used`).  The largest
+// lower and the smallest upper bound over the faces, each a real number within
+// 1e-12 of its exact value, decide the span by one rounding unless one of them
+// lies within 1e-9 of an integer; only then (faces through voxel centres) the
+// wave takes the exact form.  4 instead of about 28 instructions per face and
+// row: the row spans are half of the sweep's instructions on tetrahedra of
+// tens to hundreds of voxels.
+__device__ __forceinline__ void row_span(const RasterTet& rt, bool used, int y, int z, int Dx, int& x0, int& x1) {
+  const double yd = (double)y, zd = (double)z;
+  double f[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f[i][k] = rt.F[i][k];
+  double lo = -0.5, hi = (double)Dx - 0.5;  // no integer: the image's own ends are certain
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double h = f[i][0] + f[i][1] * yd + f[i][2] * zd;
+    const int side = __builtin_amdgcn_readfirstlane(__double2hiint(f[i][3]));  // a branch of the whole wave
+    if (side < 0)  // A > 0
+      lo = fmax(lo, h * f[i][3]);
+    else if (side > 0)
+      hi = fmin(hi, h * f[i][3]);
+    else if (h < 0.0)
+      lo = (double)Dx + 0.5;
+  }
+  lo = fmin(lo, (double)Dx + 0.5);
+  hi = fmax(hi, -1.5);
+  const double fl = __builtin_amdgcn_fract(lo), fh = __builtin_amdgcn_fract(hi);
+  if (__ballot(used && (fabs(fl - 0.5) > 0.5 - 1e-9 || fabs(fh - 0.5) > 0.5 - 1e-9))) {
+    row_span_exact(rt, yd, zd, Dx, x0, x1);
+  } else {
+    x0 = (int)ceil(lo);
+    x1 = (int)floor(hi);
+  }
 }
 
 // One compacted (non-empty) row: both fields are read from one LDS address.
@@ -424,6 +489,11 @@ struct WaveRows {
   int marker[128];  // per voxel slot of the current 128-voxel chunk pair: 1 where a row starts
 };
 
+// A unit's rows find their row groups by a walk over the groups that start
+// inside the unit (no LDS round trip) for up to this many, else by marks in LDS
+// and a prefix maximum, whose cost does not grow with them.
+constexpr int kWalkGroups = 3;
+
 // Computes the spans of rows [64 b, 64 b + 64) of rt, stores the non-empty
 // ones compacted (in row order) in wr, and returns the number of voxels.  With
 // a slice table, row r is y-major within its row group: y = y0 + (r - rs) of
@@ -435,7 +505,7 @@ struct WaveRows {
 // times the start (the second row of a pair reads the second value of the
 // element that holds the first row's voxel, so the two rows share the own
 // image's cache lines).  The mapped position of the first voxel is
-// P0 + J (x0, y, z) + shift.  *my_start receives the first voxel index of this
+// M (x0, y, z, 1) + shift.  *my_start receives the first voxel index of this
 // lane's row, or a large negative value if it is empty.  kPairs must equal
 // rt.pairs (a compile-time copy, so that the slice-by-slice order pays
 // nothing for the other).
@@ -453,7 +523,7 @@ __device__ __forceinline__ int build_rows(const RasterTet& rt, int b, int lane, 
     const int nz = rt.nz, ng = (nz + kPairs) >> kPairs;
     const int rsk = lane < ng ? (int)rt.rs[lane] : 0x7fffffff;
     const int y0k = lane < ng ? (int)rt.y0[lane] : 0;
-    // row r of group k (uniform), which starts at row s with y = ys
+    // row r of group k, which starts at row s with y = ys
     auto place = [&](int k, int s, int ys) {
       const int rr = r - s;
       if (kPairs) {
@@ -467,29 +537,41 @@ __device__ __forceinline__ int build_rows(const RasterTet& rt, int b, int lane, 
       }
     };
     const int jb = __popcll(__ballot(rsk <= r0)) - 1;  // rs[0] = 0
-    place(jb, __builtin_amdgcn_readlane(rsk, jb), __builtin_amdgcn_readlane(y0k, jb));
     unsigned long long inside = __ballot(rsk > r0 && rsk < r0 + 64);
-    while (inside) {
-      const int k = __builtin_ctzll(inside);
-      inside &= inside - 1;
-      const int s = __builtin_amdgcn_readlane(rsk, k);
-      if (r >= s) place(k, s, __builtin_amdgcn_readlane(y0k, k));
+    if (__popcll(inside) <= kWalkGroups) {
+      place(jb, __builtin_amdgcn_readlane(rsk, jb), __builtin_amdgcn_readlane(y0k, jb));
+      while (inside) {
+        const int k = __builtin_ctzll(inside);
+        inside &= inside - 1;
+        const int s = __builtin_amdgcn_readlane(rsk, k);
+        if (r >= s) place(k, s, __builtin_amdgcn_readlane(y0k, k));
+      }
+    } else {
+      // every group with rows marks its first one; a row's group is the
+      // largest mark at or before it
+      wr.marker[lane] = 0;
+      wave_sync();
+      const int at = rsk - r0;
+      if (lane < ng && at > 0 && at < 64 && rt.rs[lane + 1] > rsk) wr.marker[at] = lane;
+      wave_sync();
+      const int k = wave_incl_max(lane == 0 ? jb : wr.marker[lane]);
+      place(k, (int)rt.rs[k], (int)rt.y0[k]);
     }
   } else {
     y = rt.ylo + r % rt.ny;
     z = rt.zlo + r / rt.ny;
   }
+  int x0, x1;
+  row_span(rt, r < rt.nrows, y, z, D[0], x0, x1);
   if (r < rt.nrows) {
-    int x0, x1;
-    row_span(rt, y, z, D[0], x0, x1);
     if (x1 >= x0) {
       len = x1 - x0 + 1;
       lin = base + z * sz + y * sy + x0;
       if (kOwnBytes) lin = (lin - h * sz) * 8 + 4 * h;
       const double v[3] = {(double)x0, (double)y, (double)z};
-      bx = (float)(rt.P0[0] + rt.J[0][0] * v[0] + rt.J[0][1] * v[1] + rt.J[0][2] * v[2] + shift);
-      by = (float)(rt.P0[1] + rt.J[1][0] * v[0] + rt.J[1][1] * v[1] + rt.J[1][2] * v[2] + shift);
-      bz = (float)(rt.P0[2] + rt.J[2][0] * v[0] + rt.J[2][1] * v[1] + rt.J[2][2] * v[2] + shift);
+      bx = (float)(rt.M[0][3] + rt.M[0][0] * v[0] + rt.M[0][1] * v[1] + rt.M[0][2] * v[2] + shift);
+      by = (float)(rt.M[1][3] + rt.M[1][0] * v[0] + rt.M[1][1] * v[1] + rt.M[1][2] * v[2] + shift);
+      bz = (float)(rt.M[2][3] + rt.M[2][0] * v[0] + rt.M[2][1] * v[1] + rt.M[2][2] * v[2] + shift);
     }
   }
   const int incl = wave_incl_scan(len);
@@ -679,8 +761,9 @@ __device__ __forceinline__ double guidance_point(const DevProblem& pr, int g, in
   double o[4], vol = 0.0;  // exact: the o_i at any point sum to 6 x the volume
   bool in = true;
   for (int q = 0; q < 4; ++q) {
-    o[q] = rt.C0[q] + rt.A[q] * p[0] + rt.CY[q] * p[1] + rt.CZ[q] * p[2];
-    in = in && o[q] >= (double)rt.thr[q];
+    const double over = rt.F[q][0] + rt.A[q] * p[0] + rt.F[q][1] * p[1] + rt.F[q][2] * p[2];
+    in = in && over >= 0.0;
+    o[q] = over + (double)rt.thr[q];
     vol += o[q];
   }
   if (!in) return 0.0;
@@ -982,16 +1065,16 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
     if (e != cur) {
       if (cur >= 0) {
         const double tot = wave_sum((double)sum - (double)comp);
-        if (lane == 0) s_part[(size_t)cur * kWaves + wave] += tot;
+        if (lane == 0) s_part[(size_t)cur * kWaves + wave] = tot;  // a wave's units of an entry are consecutive
         sum = comp = 0.f;
       }
       cur = e;
       const int r = e - (e / (2 * na)) * 2 * na, dir = r / na;
       const int own = 1 - dir;
       rtp = s_rts + e;
-      jx = uniformf((float)rtp->J[0][0]);
-      jy = uniformf((float)rtp->J[1][0]);
-      jz = uniformf((float)rtp->J[2][0]);
+      jx = uniformf((float)rtp->M[0][0]);
+      jy = uniformf((float)rtp->M[1][0]);
+      jz = uniformf((float)rtp->M[2][0]);
       sc.own = own ? rs[1] : rs[0];
       sc.oth = own ? rs[0] : rs[1];
     }
@@ -1029,7 +1112,7 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   }
   if (cur >= 0) {
     const double tot = wave_sum((double)sum - (double)comp);
-    if (lane == 0) s_part[(size_t)cur * kWaves + wave] += tot;
+    if (lane == 0) s_part[(size_t)cur * kWaves + wave] = tot;
   }
   if (lane == 0) s_count[wave] = counted;
   __syncthreads();

@@ -281,3 +281,31 @@ def test_terms_of_a_chunk(n_guid, cached, chunk):
     assert (rfl == 0).sum() > S * F // 2 and (rfl[[0, 1, 2], [3, 5, 16]] != 0).all()
     assert_objectives_close(old.cpu().numpy(), rold, what="current sums")
     assert_delta_close(old.cpu().numpy(), new.cpu().numpy(), rold, rnew, rfl)
+
+
+# faces through voxel centres (whole-voxel and half-voxel vertices, undeformed cubes of equal sides), where a span's end
+# is an integer and has to be decided exactly; many short slices (marks) and few long ones (walk) per unit
+@pytest.mark.parametrize("dims,mesh,step", [((17, 17, 17), (3, 3, 3), 0.0), ((17, 17, 17), (3, 3, 3), 1.0),
+                                            ((24, 24, 24), (7, 7, 7), 0.5), ((40, 9, 33), (3, 3, 9), 1.0),
+                                            ((64, 120, 10), (3, 3, 3), 1.0), ((30, 30, 30), (6, 6, 6), 1 / 128)])
+def test_owner_map_with_faces_through_centres(dims, mesh, step):
+    rng = np.random.default_rng(int(sum(dims) + 1000 * step))
+    shape = (dims[2], dims[1], dims[0])
+    img = np.zeros(shape, np.float32)
+    rp = ref.Problem(img, img, mesh, (1.0, 1.0, 1.0), 0.1)
+    gp = dsm.Problem(img, img, mesh, max_solutions=1)
+    base = W.regular_grid(dims, mesh).astype(np.float64)
+    free = W.free_mask(mesh)
+    for _ in range(6):
+        x = base.copy()
+        if step:
+            h = np.array(dims) / (np.array(mesh) - 1)
+            moved = np.rint((base + rng.uniform(-0.2, 0.2, base.shape) * h) / step) * step
+            x = np.where(free, np.clip(moved, -0.5, np.array(dims) - 0.5), base)
+        x = W.snap(x)
+        if rp.fold_check(np.stack([x, x])[None])[0][0]:
+            continue
+        owner, overlap = gp.rasterize_owner(_t(x))
+        want, count = rp.owner_bruteforce(x)
+        assert int(overlap.item()) == 0 and np.all(count == 1)
+        np.testing.assert_array_equal(owner.cpu().numpy(), want)
