@@ -169,8 +169,8 @@ dsm_status dsm_eval_partial(dsm_problem* p, int32_t S, const float* X, int32_t F
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * partial evaluation as dsm_eval_partial, with identical results, whose
- * workspace (affected sets, element order, per-tetrahedron swept sums,
- * per-chunk flags and voxel counts) lives in a fixed array of
+ * workspace (affected sets, a table of the chunks where it fits, the chunks'
+ * sums, flags and voxel counts) lives in a fixed array of
  * DSM_SCRATCH_BYTES per device, held from the first call on a device until
  * the process ends, instead of the problem's create-time workspace; S and F
  * are therefore not bounded by max_solutions / max_fos.  The call allocates

@@ -44,7 +44,7 @@ void release(dsm_problem* p) {
   if (!p) return;
   for (hipEvent_t e : p->ev) (void)hipEventDestroy(e);
   void* bufs[] = {p->d_img, p->d_raw, p->d_tets, p->d_tet_w, p->d_star_off, p->d_star, p->d_gpt, p->d_gcorr,
-                  p->d_aff, p->d_aff_cnt, p->d_order, p->d_terms, p->d_sums, p->d_pin, p->d_gbox, p->d_ident, p->d_cflags, p->d_ccount};
+                  p->d_aff, p->d_aff_cnt, p->d_slots, p->d_terms, p->d_sums, p->d_pin, p->d_gbox, p->d_ident, p->d_cflags, p->d_ccount};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   delete p;
@@ -241,7 +241,9 @@ dsm_status dsm_problem_create(const dsm_problem_desc* d, dsm_problem** out) {
     DSM_TRY(hipMemcpy(p->d_gbox, gbox.data(), sizeof(float4) * gbox.size(), hipMemcpyHostToDevice), "copy guidance boxes");
   DSM_TRY(dev_alloc(&p->d_aff, (size_t)std::max(1, p->max_F) * p->maxA), "hipMalloc affected sets");
   DSM_TRY(dev_alloc(&p->d_aff_cnt, (size_t)std::max(1, p->max_F)), "hipMalloc affected counts");
-  DSM_TRY(dev_alloc(&p->d_order, (size_t)std::max(1, p->max_F)), "hipMalloc element order");
+  DSM_TRY(dev_alloc(&p->d_slots, 1 + (size_t)std::min(std::max(1, p->max_F), kOrderMax) *
+                                         ((p->maxA + kMinPartChunk - 1) / kMinPartChunk)),
+          "hipMalloc slot table");
   DSM_TRY(dev_alloc(&p->d_terms, (size_t)p->max_S * tp.T * 3), "hipMalloc term workspace");
   DSM_TRY(dev_alloc(&p->d_ident, p->identity.size()), "hipMalloc undeformed grid");
   DSM_TRY(hipMemcpy(p->d_ident, p->identity.data(), sizeof(float) * p->identity.size(), hipMemcpyHostToDevice),
@@ -416,7 +418,7 @@ dsm_status dsm_eval_partial_masked(dsm_problem* p, int32_t S, const float* X, in
     return fail(DSM_ERR_ARG, "null argument");
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = launch_affected(p->dev, F, fos_off, fos_pts, p->max_pts, p->maxA, p->d_aff, p->d_aff_cnt, st);
-  if (e == hipSuccess && F <= kOrderMax) e = launch_order(F, p->d_aff_cnt, p->d_order, st);
+  if (e == hipSuccess && F <= kOrderMax) e = launch_slots(F, p->d_aff_cnt, p->part_chunk, p->d_slots, st);
   if (e != hipSuccess) return hip_fail(e, "affected-set launch");
   EvalArgs a{};
   a.pr = p->dev;
@@ -429,7 +431,7 @@ dsm_status dsm_eval_partial_masked(dsm_problem* p, int32_t S, const float* X, in
   a.cand = cand;
   a.aff = p->d_aff;
   a.aff_cnt = p->d_aff_cnt;
-  a.order = F <= kOrderMax ? p->d_order : nullptr;
+  a.slots = F <= kOrderMax ? p->d_slots : nullptr;
   a.maxA = p->maxA;
   a.nver = tet_terms_in ? 1 : 2;
   a.terms_in = tet_terms_in;
@@ -602,7 +604,8 @@ struct BatchSetJob {
   const int* fos_pts;
   int* aff;
   int* aff_cnt;
-  int* order;  // null: no ordering launch
+  int pchunk;
+  int2* slots;  // null: no slot table
 };
 
 struct dsm_batch {
@@ -663,7 +666,7 @@ dsm_status batch_tables(const dsm_batch* b, int n_jobs, const dsm_partial_job* j
     a.cand = q.cand;
     a.aff = p->d_aff;
     a.aff_cnt = p->d_aff_cnt;
-    a.order = q.F <= kOrderMax ? p->d_order : nullptr;
+    a.slots = q.F <= kOrderMax ? p->d_slots : nullptr;
     a.maxA = p->maxA;
     a.nver = q.tet_terms_in ? 1 : 2;
     a.terms_in = q.tet_terms_in;
@@ -738,7 +741,8 @@ dsm_status dsm_eval_partial_batch(dsm_batch* b, int32_t n_jobs, const dsm_partia
     if (jobs[j].S > 0 && jobs[j].F > 0) {
       e = launch_affected(args[j].pr, jobs[j].F, jobs[j].fos_off, jobs[j].fos_pts, jobs[j].problem->max_pts,
                           args[j].maxA, args[j].aff ? jobs[j].problem->d_aff : nullptr, jobs[j].problem->d_aff_cnt, st);
-      if (e == hipSuccess && args[j].order) e = launch_order(jobs[j].F, jobs[j].problem->d_aff_cnt, jobs[j].problem->d_order, st);
+      if (e == hipSuccess && args[j].slots)
+        e = launch_slots(jobs[j].F, jobs[j].problem->d_aff_cnt, args[j].pchunk, jobs[j].problem->d_slots, st);
     }
   if (e != hipSuccess) return hip_fail(e, "affected-set launch");
   if (b->pending && (e = hipEventSynchronize(b->copied)) != hipSuccess) return hip_fail(e, "job table wait");
@@ -785,7 +789,7 @@ dsm_status dsm_batch_set_jobs(dsm_batch* b, int32_t n_jobs, const dsm_partial_jo
     if (a.S <= 0 || a.G <= 0) continue;
     dsm_problem* p = jobs[j].problem;
     b->set.push_back(BatchSetJob{a.pr, a.G, p->max_pts, a.maxA, a.fos_off, a.fos_pts, p->d_aff, p->d_aff_cnt,
-                                 a.order ? p->d_order : nullptr});
+                                 a.pchunk, a.slots ? p->d_slots : nullptr});
   }
   b->set_per_xcd = n_jobs > 0 ? off[n_jobs] : 0;
   b->set_total_finish = n_jobs > 0 ? foff[n_jobs] : 0;
@@ -803,7 +807,7 @@ dsm_status dsm_batch_run(dsm_batch* b, void* stream) {
   hipError_t e = hipSuccess;
   for (const BatchSetJob& q : b->set) {
     e = launch_affected(q.pr, q.F, q.fos_off, q.fos_pts, q.max_pts, q.maxA, q.aff, q.aff_cnt, st);
-    if (e == hipSuccess && q.order) e = launch_order(q.F, q.aff_cnt, q.order, st);
+    if (e == hipSuccess && q.slots) e = launch_slots(q.F, q.aff_cnt, q.pchunk, q.slots, st);
     if (e != hipSuccess) return hip_fail(e, "affected-set launch");
   }
   e = launch_eval_batch(b->d_set_jobs, b->d_set_off, b->set_n, b->set_per_xcd, b->set_total_finish, b->set_lds,

@@ -91,7 +91,7 @@ struct EvalArgs {
   const float* cand;     // [S][fos_off[G]][2][3]
   const int* aff;        // [G][maxA] affected tetrahedra, ascending
   const int* aff_cnt;    // [G], -1 = malformed element
-  const int* order;      // [G] order of the elements over the XCDs (partial), or null
+  const int2* slots;     // partial: slot table of the launch (launch_slots), or null
   int maxA;
   int nver;              // 1: candidate only; 2: candidate and current recomputed
   const double* terms_in;  // [S][T][3] cache of current terms or null
@@ -127,11 +127,10 @@ hipError_t launch_fold(const DevProblem& pr, int S, const float* X, uint32_t* fl
 hipError_t launch_affected(const DevProblem& pr, int F, const int* fos_off, const int* fos_pts, int max_pts,
                            int maxA, int* aff, int* aff_cnt, hipStream_t stream);
 hipError_t launch_eval(const EvalArgs& a, hipEvent_t ev_begin, hipEvent_t ev_end, hipStream_t stream);
-// Orders the G elements of a partial launch so that the XCDs' contiguous
-// ranges carry similar work (costs from the affected counts).  Only for
-// G <= kOrderMax; larger launches use a fixed interleaved order.
+// Slot table of a partial launch of G <= kOrderMax elements, in chunks of
+// pchunk: slots [1 + G * ceil(maxA / pchunk)].  Larger launches have none.
 constexpr int kOrderMax = 4096;
-hipError_t launch_order(int G, const int* aff_cnt, int* order, hipStream_t stream);
+hipError_t launch_slots(int G, const int* aff_cnt, int pchunk, int2* slots, hipStream_t stream);
 // wg_off_dev [2][n_jobs + 1]: the jobs' per-XCD slot offsets in the sweep (a
 // job of n workgroups takes ceil(n / 8) slots on each XCD; per_xcd slots in
 // all), then their workgroup offsets in the finishing kernel (a job of n
@@ -178,7 +177,7 @@ struct dsm_problem {
   float4* d_gbox = nullptr;     // [n_m + n_f]
   int* d_aff = nullptr;         // [max_F][maxA]
   int* d_aff_cnt = nullptr;     // [max_F]
-  int* d_order = nullptr;       // [max_F] element order of the last partial launch
+  int2* d_slots = nullptr;      // slot table of the last partial launch of at most kOrderMax elements
   double* d_terms = nullptr;    // [max_S][T][3] workspace for full evaluation
   double* d_sums = nullptr;     // [max_S][max_F][nchunk][2][3] term sums per chunk of a partial evaluation
   uint8_t* d_pin = nullptr;     // [P] pinned axes

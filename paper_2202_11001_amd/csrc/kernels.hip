@@ -68,13 +68,14 @@ __device__ __forceinline__ double orient(const double a[3], const double b[3], c
 // Blockid -> logical index so that each of the 8 XCDs (which receive
 // workgroups round robin) processes one contiguous range of logical indices;
 // consecutive logical indices share a FOS element and hence an image region.
-__device__ __forceinline__ int xcd_logical(int bid, int n) {
-  const int x = bid & 7, k = bid >> 3;
+// Index k on XCD x of n; -1 beyond the XCD's range.
+__device__ __forceinline__ int xcd_logical(int x, int k, int n) {
   const int q = n >> 3, r = n & 7;
-  return x * q + min(x, r) + k;
+  return k < q + (x < r ? 1 : 0) ? x * q + min(x, r) + k : -1;
 }
 
-// Element order of a single-problem partial launch: every eighth element,
+// Element order of a partial launch without a slot table (more than kOrderMax
+// elements, or no room for one): every eighth element,
 // starting from 0, then from 1, and so on.  The logical workgroup space is
 // element-major and each XCD takes a contiguous range of it, so in mesh order
 // the XCDs holding the border layers (whose points have smaller stars) would
@@ -864,24 +865,34 @@ __device__ __forceinline__ int group_tet(const EvalArgs& a, int g, int i) {
 // coordinates and face functions are in LDS: in a kernel of their own they
 // waited for the coordinates 77 % of the time (99 us of the 191 us of a 32^3
 // partial evaluation, 420 of 4,750 us of a class of the 50^3 phantom).
-// Workgroups are numbered (group, chunk,
-// solution) with the solution fastest, so the workgroups resident on an XCD
-// sweep the same few tetrahedra of many solutions and share their image
-// region in L2; with `interleave` the groups follow interleaved_group's order.
+// Workgroups are numbered (group, chunk, solution) with the solution fastest,
+// so the workgroups resident on an XCD sweep the same few tetrahedra of many
+// solutions and share their image region in L2; partial launches number the
+// chunks that exist by the slot table (k_slots).
 // ROWS: the row order, 0 slice by slice, 1 in slice pairs (both fixed
 // at compile time), 2 a.row_pairs read at run time (a batch of problems with
 // both orders).
 template <int PARTIAL, int ROWS>
-__device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsigned char* smem, bool interleave) {
+__device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsigned char* smem) {
   const DevProblem& pr = a.pr;
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int nchunk = PARTIAL ? a.nchunk : 1;
-  const int gl = logical / (a.S * nchunk), rem = logical - gl * (a.S * nchunk);
   // g and the counts below are the same on every lane; saying so keeps the
   // values derived from them (the direction of an entry, hence the image
   // buffer a load reads) in scalar registers
-  const int g = uniform(PARTIAL && a.order ? a.order[gl] : (interleave ? interleaved_group(gl, a.G) : gl));
-  const int c = rem / a.S, s = rem - c * a.S;
+  int g, c, s;
+  if (PARTIAL && a.slots) {
+    const int slot = logical / a.S;
+    const int2 gc = a.slots[1 + slot];
+    g = uniform(gc.x);
+    c = uniform(gc.y);
+    s = logical - slot * a.S;
+  } else {
+    const int gl = logical / (a.S * nchunk), rem = logical - gl * (a.S * nchunk);
+    g = uniform(PARTIAL ? interleaved_group(gl, a.G) : gl);
+    c = rem / a.S;
+    s = rem - c * a.S;
+  }
   const int nver = a.nver;
   const EvalLayout Lay = eval_layout(kMaxChunk, nver);
   int* s_tet = (int*)(smem + Lay.tet);
@@ -1151,17 +1162,19 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
 template <int PARTIAL, int ROWS>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_sweep(EvalArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  sweep_body<PARTIAL, ROWS>(a, xcd_logical(blockIdx.x, a.S * a.G * (PARTIAL ? a.nchunk : 1)), smem, PARTIAL != 0);
+  const int n = PARTIAL && a.slots ? a.S * a.slots[0].x : a.S * a.G * (PARTIAL ? a.nchunk : 1);
+  const int logical = xcd_logical(blockIdx.x & 7, blockIdx.x >> 3, n);
+  if (logical >= 0) sweep_body<PARTIAL, ROWS>(a, logical, smem);
 }
 
 // Several problems in one launch.  Each job's workgroup range is split into 8
 // equal contiguous parts, part x running on XCD x (hardware workgroup ids go
 // round-robin over the XCDs): xcd_off[j] is the first per-XCD slot of job j,
-// and a job with n workgroups takes ceil(n / 8) slots on every XCD, the
+// and a job of at most n workgroups takes ceil(n / 8) slots on every XCD, the
 // surplus slots exiting at once.  So every XCD gets an eighth of every job
 // (jobs of very different tetrahedron sizes would otherwise load the XCDs
 // unevenly), and within a part the workgroups of one element's solutions stay
-// together.  Elements follow interleaved_group's order within a job.
+// together.
 // Arguments read through the job table take more registers than kernel
 // arguments; the 7-wave target (at most 72 VGPRs) ran small problems 5 %
 // faster than 6 waves.  ROWS as for sweep_body.
@@ -1174,10 +1187,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(7, 8))) voi
   while (j + 1 < n_jobs && xcd_off[j + 1] <= k) ++j;
   j = uniform(j);
   const EvalArgs& a = jobs[j];
-  const int n8 = uniform(xcd_off[j + 1] - xcd_off[j]);
-  const int logical = x * n8 + (k - uniform(xcd_off[j]));
-  if (logical >= a.S * a.G * a.nchunk) return;
-  sweep_body<1, ROWS>(a, logical, smem, true);
+  const int n = uniform(a.slots ? a.S * a.slots[0].x : a.S * a.G * a.nchunk);
+  const int logical = xcd_logical(x, k - uniform(xcd_off[j]), n);
+  if (logical >= 0) sweep_body<1, ROWS>(a, logical, smem);
 }
 
 // ------------------------------------------------------------ finishing kernel
@@ -1625,16 +1637,26 @@ hipError_t launch_fold(const DevProblem& pr, int S, const float* X, uint32_t* fl
   return e;
 }
 
-// Element order of a partial launch (G <= kOrderMax): the elements sorted by
+// Slot table of a partial launch (G <= kOrderMax): the elements sorted by
 // their number of affected tetrahedra, descending (ties by index), are dealt
 // to the 8 XCDs in rounds of 8 in alternating direction (0..7, 7..0, ...); the
-// order lists XCD 0's elements, then XCD 1's, and so on.  Each XCD's
-// contiguous range of the element-major workgroup space then holds elements of
-// similar total cost.  Bitonic sort of (cost, index) keys in LDS, one
-// workgroup.
-__global__ __launch_bounds__(1024) void k_order(int G, const int* __restrict__ aff_cnt, int* __restrict__ order) {
+// order lists XCD 0's elements, then XCD 1's, and so on, so that each XCD's
+// contiguous range of the workgroup space holds elements of similar total
+// cost.  The table then numbers the chunks of every element in that order:
+// slots[0].x = their number, slots[1 + i] = (element, chunk).  A launch has
+// room for the largest possible element everywhere (its chunk count is only
+// known on the device); by the table the workgroups that exist come first on
+// every XCD and the others exit on one scalar load.  Without it every second
+// or third workgroup looked up its element to find it had no such chunk: 520
+// of 3,600 us on a class of the phantom's tetrahedra, 770 of 6,000 us on the
+// uneven half-resolution batch.  Bitonic sort of (cost, index) keys in LDS,
+// one workgroup.
+__global__ __launch_bounds__(1024) void k_slots(int G, const int* __restrict__ aff_cnt, int pchunk,
+                                                int2* __restrict__ slots) {
   __shared__ unsigned long long key[kOrderMax];
-  const int t = threadIdx.x;
+  __shared__ int s_order[kOrderMax];
+  __shared__ int s_wave[16];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   int n = 1;
   while (n < G) n <<= 1;
   for (int i = t; i < n; i += 1024)
@@ -1659,13 +1681,31 @@ __global__ __launch_bounds__(1024) void k_order(int G, const int* __restrict__ a
     const int r = i & 15, x = r < 8 ? r : 15 - r;
     int start = 0;  // elements dealt to the XCDs before x
     for (int y = 0; y < x; ++y) start += 2 * nb + (y < rem ? 1 : 0) + (15 - y < rem ? 1 : 0);
-    order[start + (i >> 4) * 2 + (r >= 8 ? 1 : 0)] = (int)(unsigned)(key[i] & 0xffffffffull);
+    s_order[start + (i >> 4) * 2 + (r >= 8 ? 1 : 0)] = (int)(unsigned)(key[i] & 0xffffffffull);
   }
+  __syncthreads();
+  int base = 1;
+  for (int i0 = 0; i0 < G; i0 += 1024) {  // 1024 elements at a time: prefix of their chunks
+    const int i = i0 + t, g = i < G ? s_order[i] : 0;
+    const int nc = i < G ? (max(aff_cnt[g], 0) + pchunk - 1) / pchunk : 0;
+    const int incl = wave_incl_scan(nc);
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int at = base + incl - nc, all = 0;
+    for (int w = 0; w < 16; ++w) {
+      at += w < wave ? s_wave[w] : 0;
+      all += s_wave[w];
+    }
+    for (int c = 0; c < nc; ++c) slots[at + c] = make_int2(g, c);
+    base += all;
+    __syncthreads();
+  }
+  if (t == 0) slots[0] = make_int2(base - 1, 0);
 }
 
-hipError_t launch_order(int G, const int* aff_cnt, int* order, hipStream_t stream) {
+hipError_t launch_slots(int G, const int* aff_cnt, int pchunk, int2* slots, hipStream_t stream) {
   if (G <= 0 || G > kOrderMax) return hipSuccess;
-  k_order<<<1, 1024, 0, stream>>>(G, aff_cnt, order);
+  k_slots<<<1, 1024, 0, stream>>>(G, aff_cnt, pchunk, slots);
   return hipGetLastError();
 }
 
@@ -1679,16 +1719,18 @@ hipError_t launch_affected(const DevProblem& pr, int F, const int* fos_off, cons
 hipError_t launch_eval(const EvalArgs& a, hipEvent_t ev_begin, hipEvent_t ev_end, hipStream_t stream) {
   const int64_t nwg = (int64_t)a.S * a.G;
   if (nwg <= 0) return hipSuccess;
+  // a multiple of 8: every XCD gets an eighth of the workgroups that exist, rounded up
+  const unsigned grid = (unsigned)((nwg * (a.partial ? a.nchunk : 1) + 7) / 8 * 8);
   const size_t lds = eval_lds_bytes(kMaxChunk, a.nver);
   if (ev_begin) (void)hipEventRecord(ev_begin, stream);
   if (a.partial && a.row_pairs)
-    k_sweep<1, 1><<<(unsigned)(nwg * a.nchunk), kWG, lds, stream>>>(a);
+    k_sweep<1, 1><<<grid, kWG, lds, stream>>>(a);
   else if (a.partial)
-    k_sweep<1, 0><<<(unsigned)(nwg * a.nchunk), kWG, lds, stream>>>(a);
+    k_sweep<1, 0><<<grid, kWG, lds, stream>>>(a);
   else if (a.row_pairs)
-    k_sweep<0, 1><<<(unsigned)nwg, kWG, lds, stream>>>(a);
+    k_sweep<0, 1><<<grid, kWG, lds, stream>>>(a);
   else
-    k_sweep<0, 0><<<(unsigned)nwg, kWG, lds, stream>>>(a);
+    k_sweep<0, 0><<<grid, kWG, lds, stream>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ev_end) (void)hipEventRecord(ev_end, stream);

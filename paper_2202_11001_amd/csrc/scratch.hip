@@ -1,7 +1,6 @@
 // Partial evaluation that allocates nothing: its workspace (affected sets,
-// element order, swept dissimilarity per tetrahedron, per-chunk flags and
-// voxel counts) lives in a fixed device array instead of the problem's
-// create-time workspace.  The kernels are those of dsm_eval_partial.
+// slot table, term sums, flags and voxel counts per chunk) lives in a fixed
+// device array instead of the problem's create-time workspace.  The kernels are those of dsm_eval_partial.
 #include <stdio.h>
 
 #include <mutex>
@@ -39,7 +38,8 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Byte offsets of the workspace regions inside `scratch`.
 struct ScratchLayout {
-  size_t aff, aff_cnt, order, sums, cflags, ccount, total;
+  size_t aff, aff_cnt, sums, cflags, ccount, total;
+  size_t slots;  // behind the rest, used where it fits
 };
 
 ScratchLayout scratch_layout(int S, int F, int maxA, int nver, int nchunk) {
@@ -49,8 +49,6 @@ ScratchLayout scratch_layout(int S, int F, int maxA, int nver, int nchunk) {
   o = align256(o + sizeof(int) * (size_t)F * maxA);
   L.aff_cnt = o;
   o = align256(o + sizeof(int) * (size_t)F);
-  L.order = o;
-  o = align256(o + sizeof(int) * (size_t)F);
   L.sums = o;  // 3 sums per chunk of at least kMinPartChunk tetrahedra and version: at most one double per tetrahedron
   o = align256(o + sizeof(double) * (size_t)S * F * nver * maxA);
   L.cflags = o;
@@ -58,6 +56,7 @@ ScratchLayout scratch_layout(int S, int F, int maxA, int nver, int nchunk) {
   L.ccount = o;
   o = align256(o + sizeof(uint32_t) * (size_t)S * F * nchunk);
   L.total = o;
+  L.slots = o;
   return L;
 }
 
@@ -100,10 +99,12 @@ dsm_status dsm_eval_partial_noalloc(dsm_problem* p, int32_t S, const float* X, i
   if ((e = scratch_address(device, &base)) != hipSuccess) return set_error(DSM_ERR_DEVICE, hipGetErrorString(e));
   int* aff = (int*)(base + L.aff);
   int* aff_cnt = (int*)(base + L.aff_cnt);
-  int* order = (int*)(base + L.order);
+  // slot table of the chunks: a matter of speed only, so a call whose workspace leaves no room for it goes without
+  const size_t slot_bytes = sizeof(int2) * (1 + (size_t)F * nchunk);
+  int2* slots = F <= kOrderMax && L.slots + slot_bytes <= kScratchBytes ? (int2*)(base + L.slots) : nullptr;
   hipStream_t st = (hipStream_t)stream;
   e = launch_affected(p->dev, F, fos_off, fos_pts, p->max_pts, p->maxA, aff, aff_cnt, st);
-  if (e == hipSuccess && F <= kOrderMax) e = launch_order(F, aff_cnt, order, st);
+  if (e == hipSuccess && slots) e = launch_slots(F, aff_cnt, p->part_chunk, slots, st);
   if (e != hipSuccess) return set_error(DSM_ERR_DEVICE, hipGetErrorString(e));
   EvalArgs a{};
   a.pr = p->dev;
@@ -116,7 +117,7 @@ dsm_status dsm_eval_partial_noalloc(dsm_problem* p, int32_t S, const float* X, i
   a.cand = cand;
   a.aff = aff;
   a.aff_cnt = aff_cnt;
-  a.order = F <= kOrderMax ? order : nullptr;
+  a.slots = slots;
   a.maxA = p->maxA;
   a.nver = nver;
   a.terms_in = tet_terms_in;

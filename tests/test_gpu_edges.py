@@ -309,3 +309,35 @@ def test_owner_map_with_faces_through_centres(dims, mesh, step):
         want, count = rp.owner_bruteforce(x)
         assert int(overlap.item()) == 0 and np.all(count == 1)
         np.testing.assert_array_equal(owner.cpu().numpy(), want)
+
+
+# as many elements as the slot table takes (4096), and more, which go without; malformed and empty elements among them
+# (and nothing else); chunks that divide the stars and chunks that do not
+@pytest.mark.parametrize("F,chunk", [(1, 8), (9, 4), (1025, 7), (4096, 8), (4097, 5)])
+def test_slot_table_covers_every_chunk(F, chunk):
+    w = W.tiny()
+    gp = dsm.Problem.from_workload(w, max_solutions=2, max_fos=5000, max_fos_points=2)
+    gp.set_part_chunk(chunk)
+    rng = np.random.default_rng(F)
+    X = w.population(S=2)
+    size = rng.integers(0, 4, F)  # 0 to 3 points: 3 is malformed
+    if F == 9:
+        size = np.array([0, 3] * 4 + [3])
+    off = np.concatenate([[0], np.cumsum(size)]).astype(np.int32)
+    pts = rng.integers(0, w.P, off[-1]).astype(np.int32)
+    cand = W.candidates(X, off, pts, w.mesh, w.dims, 1.0, 3) if off[-1] else np.zeros((2, 0, 2, 3), np.float32)
+    Xd = _t(X)
+    cache = torch.empty((2, gp.T, 3), dtype=torch.float64, device=DEV)
+    gp.eval_full(Xd, tet_terms=cache)
+
+    def run(f0, f1, method):
+        o = off[f0:f1 + 1]
+        return method(Xd, _t(o - o[0]), _t(np.append(pts[o[0]:o[-1]], 0).astype(np.int32)),
+                      _t(np.concatenate([cand[:, o[0]:o[-1]]], axis=1)), tet_terms_in=cache, voxel_count=True)
+
+    whole = [t.cpu().numpy() for t in run(0, F, gp.eval_partial)]
+    parts = [run(a, min(a + 300, F), gp.eval_partial_noalloc) for a in range(0, F, 300)]
+    for k in range(4):
+        np.testing.assert_array_equal(whole[k], np.concatenate([p[k].cpu().numpy() for p in parts], axis=1))
+    assert np.all((whole[2] == 64) == (size == 3)[None])
+    assert np.all(whole[3][:, size == 0] == 0) and np.all(whole[1][:, size == 0] == 0)
