@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "dsm_internal.h"
@@ -33,10 +34,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
 // FP32 -> BF16, round to nearest even
-__device__ __forceinline__ unsigned short f2bf(float x) {
-  const unsigned u = __float_as_uint(x);
-  return (unsigned short)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-}
+__device__ __forceinline__ unsigned short f2bf(float x) { return __builtin_bit_cast(unsigned short, (__bf16)x); }
 __device__ __forceinline__ float bf2f(unsigned short b) { return __uint_as_float((unsigned)b << 16); }
 
 __device__ __forceinline__ f32x4 mfma(const u16x8& a, const u16x8& b, const f32x4& c) {
@@ -58,87 +56,118 @@ struct MlpW {
   const float *b1, *b2, *b3;             // FP32 biases
 };
 
-// Screening forward pass: 64 rows per workgroup of 4 waves.  The rows are
-// staged in LDS once; each wave computes a 32-column slice of a layer for all
-// 64 rows, so every weight fragment read from memory serves 4 row blocks.
+// Forward pass of 64 rows by a workgroup of 4 waves, each computing a
+// 32-column slice of a layer for all rows, with its slice of every layer's
+// weights in registers: the workgroups are persistent and take tile after tile,
+// so the weights are read once per workgroup instead of once per 64 rows (at
+// 1.2 M rows that was 1.6 GB from L2 and the longest part of the pass).
 constexpr int kXs = kIn + 8;  // padded LDS strides (BF16 elements)
 constexpr int kHs = kHid + 8;
+constexpr int kTileRows = 64;
 
-__global__ __launch_bounds__(256) void k_mlp_forward64(MlpW w, const unsigned short* __restrict__ xb, int N,
-                                                       float* __restrict__ out) {
-  __shared__ __align__(16) unsigned short xs[64 * kXs];  // inputs, then H2
-  __shared__ __align__(16) unsigned short h1[64 * kHs];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, kb = lane >> 4;
-  const int row0 = blockIdx.x * 64;
-  for (int e = tid; e < 64 * kIn / 8; e += 256) {
-    const int r = e / (kIn / 8), c = e % (kIn / 8);
-    const u16x8 v = row0 + r < N ? load8(xb + (size_t)(row0 + r) * kIn + 8 * c) : zero8();
-    *(u16x8*)(xs + r * kXs + 8 * c) = v;
+struct WaveWeights {
+  u16x8 w1[2][kIn / 32], w2[2][kHid / 32], w3[kHid / 32];
+  float b1[2], b2[2], b3;
+};
+
+__device__ __forceinline__ void load_weights(const MlpW& w, int wave, int lane, WaveWeights& r) {
+  const int i = lane & 15, kb = lane >> 4;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int col = 32 * wave + 16 * t + i;
+#pragma unroll
+    for (int kk = 0; kk < kIn / 32; ++kk) r.w1[t][kk] = load8(w.w1 + (size_t)col * kIn + 32 * kk + 8 * kb);
+#pragma unroll
+    for (int kk = 0; kk < kHid / 32; ++kk) r.w2[t][kk] = load8(w.w2 + (size_t)col * kHid + 32 * kk + 8 * kb);
+    r.b1[t] = w.b1[col];
+    r.b2[t] = w.b2[col];
   }
-  __syncthreads();
-  // layer 1: H1 = relu(X W1^T + b1), wave -> columns [32 wave, 32 wave + 32)
-  {
-    f32x4 acc[2][4];
-    for (int t = 0; t < 2; ++t)
-      for (int rb = 0; rb < 4; ++rb) acc[t][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int kk = 0; kk < kIn / 32; ++kk) {
-      u16x8 b[2];
-      for (int t = 0; t < 2; ++t) b[t] = load8(w.w1 + (size_t)(32 * wave + 16 * t + i) * kIn + 32 * kk + 8 * kb);
+  for (int kk = 0; kk < kHid / 32; ++kk) r.w3[kk] = load8(w.w3 + (size_t)i * kHid + 32 * kk + 8 * kb);
+  r.b3 = w.b3[i];
+}
+
+// out = relu(in W^T + b) for this wave's 32 columns of 64 rows (LDS tiles).
+template <int K>
+__device__ __forceinline__ void layer64(const unsigned short* in, int in_stride, const u16x8 (&w)[2][K / 32],
+                                        const float (&b)[2], unsigned short* out, int wave, int lane) {
+  const int i = lane & 15, kb = lane >> 4;
+  f32x4 acc[2][4];
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
-        const u16x8 a = *(const u16x8*)(xs + (16 * rb + i) * kXs + 32 * kk + 8 * kb);
-        for (int t = 0; t < 2; ++t) acc[t][rb] = mfma(a, b[t], acc[t][rb]);
-      }
-    }
-    for (int t = 0; t < 2; ++t) {
-      const int col = 32 * wave + 16 * t + i;
-      const float bias = w.b1[col];
-      for (int rb = 0; rb < 4; ++rb)
-        for (int r = 0; r < 4; ++r) h1[(16 * rb + 4 * kb + r) * kHs + col] = f2bf(fmaxf(acc[t][rb][r] + bias, 0.f));
-    }
-  }
-  __syncthreads();
-  // layer 2: H2 = relu(H1 W2^T + b2) into the input buffer (no longer needed)
-  unsigned short* h2 = xs;
-  {
-    f32x4 acc[2][4];
-    for (int t = 0; t < 2; ++t)
-      for (int rb = 0; rb < 4; ++rb) acc[t][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int kk = 0; kk < kHid / 32; ++kk) {
-      u16x8 b[2];
-      for (int t = 0; t < 2; ++t) b[t] = load8(w.w2 + (size_t)(32 * wave + 16 * t + i) * kHid + 32 * kk + 8 * kb);
+    for (int rb = 0; rb < 4; ++rb) acc[t][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
-        const u16x8 a = *(const u16x8*)(h1 + (16 * rb + i) * kHs + 32 * kk + 8 * kb);
-        for (int t = 0; t < 2; ++t) acc[t][rb] = mfma(a, b[t], acc[t][rb]);
-      }
+  for (int kk = 0; kk < K / 32; ++kk)
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb) {
+      const u16x8 a = *(const u16x8*)(in + (16 * rb + i) * in_stride + 32 * kk + 8 * kb);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) acc[t][rb] = mfma(a, w[t][kk], acc[t][rb]);
     }
-    for (int t = 0; t < 2; ++t) {  // the barrier after layer 1 ordered every read of the inputs before this
-      const int col = 32 * wave + 16 * t + i;
-      const float bias = w.b2[col];
-      for (int rb = 0; rb < 4; ++rb)
-        for (int r = 0; r < 4; ++r) h2[(16 * rb + 4 * kb + r) * kHs + col] = f2bf(fmaxf(acc[t][rb][r] + bias, 0.f));
-    }
-  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out[(16 * rb + 4 * kb + r) * kHs + 32 * wave + 16 * t + i] = f2bf(fmaxf(acc[t][rb][r] + b[t], 0.f));
+}
+
+// Outputs of a tile's rows from the inputs in xs, all threads of the workgroup,
+// after a barrier; xs is overwritten with the second hidden layer.  where(i) is
+// the output row of the tile's row i, negative if there is none.
+template <class Where>
+__device__ __forceinline__ void mlp_tile(const WaveWeights& w, unsigned short* xs, unsigned short* h1, Where where,
+                                         float* __restrict__ out, int wave, int lane) {
+  const int i = lane & 15, kb = lane >> 4;
+  layer64<kIn>(xs, kXs, w.w1, w.b1, h1, wave, lane);
+  __syncthreads();  // H1 complete, and every read of the inputs done
+  layer64<kHid>(h1, kHs, w.w2, w.b2, xs, wave, lane);
   __syncthreads();
   // layer 3: Y = H2 W3^T + b3, wave -> row block `wave`
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int kk = 0; kk < kHid / 32; ++kk) {
-    const u16x8 a = *(const u16x8*)(h2 + (16 * wave + i) * kHs + 32 * kk + 8 * kb);
-    const u16x8 b = load8(w.w3 + (size_t)i * kHid + 32 * kk + 8 * kb);
-    acc = mfma(a, b, acc);
-  }
-  if (i < kOut) {
-    const float bias = w.b3[i];
+  for (int kk = 0; kk < kHid / 32; ++kk) acc = mfma(*(const u16x8*)(xs + (16 * wave + i) * kHs + 32 * kk + 8 * kb), w.w3[kk], acc);
+  if (i < kOut)
     for (int r = 0; r < 4; ++r) {
-      const int row = row0 + 16 * wave + 4 * kb + r;
-      if (row < N) out[(size_t)row * kOut + i] = acc[r] + bias;
+      const int64_t row = where(16 * wave + 4 * kb + r);
+      if (row >= 0) out[(size_t)row * kOut + i] = acc[r] + w.b3;
     }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp_forward(
+    MlpW w, const unsigned short* __restrict__ xb, int N, float* __restrict__ out) {
+  __shared__ __align__(16) unsigned short xs[kTileRows * kXs];  // inputs, then H2
+  __shared__ __align__(16) unsigned short h1[kTileRows * kHs];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  WaveWeights ww;
+  load_weights(w, wave, lane, ww);
+  constexpr int kPer = kTileRows * kIn / 8 / 256;  // 16-byte pieces of a tile per thread
+  u16x8 next[kPer];
+  auto fetch = [&](int64_t row0) {  // the tile after the current one, in flight while that is computed
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int e = tid + 256 * q, r = e / (kIn / 8), c = e % (kIn / 8);
+      next[q] = row0 + r < N ? load8(xb + (size_t)(row0 + r) * kIn + 8 * c) : zero8();
+    }
+  };
+  fetch((int64_t)blockIdx.x * kTileRows);
+  for (int64_t row0 = (int64_t)blockIdx.x * kTileRows; row0 < N; row0 += (int64_t)gridDim.x * kTileRows) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int e = tid + 256 * q;
+      *(u16x8*)(xs + (e / (kIn / 8)) * kXs + 8 * (e % (kIn / 8))) = next[q];
+    }
+    fetch(row0 + (int64_t)gridDim.x * kTileRows);
+    __syncthreads();
+    mlp_tile(ww, xs, h1, [&](int i) { return row0 + i < N ? row0 + i : (int64_t)-1; }, out, wave, lane);
+    __syncthreads();
   }
 }
+
+// Workgroups of a persistent launch over N rows (a multiple of 8): three to a CU.
+unsigned mlp_grid(int64_t N) { return (unsigned)std::min<int64_t>((N + 8 * kTileRows - 1) / (8 * kTileRows) * 8, 3 * 256); }
 
 // One training step is three kernels: forward and backward of the minibatch
 // rows (k_mlp_rows), the weight and bias gradients (k_mlp_wgrad) and the update
@@ -410,15 +439,20 @@ __global__ void k_refresh_bf16(const float* __restrict__ p, Operands ops) {
 // ---------------------------------------------------------------- features
 
 // trilinear sample of a bordered z-pair image at voxel position p clamped to [0, D-1]
-__device__ float sample_packed(const DevProblem& pr, const float* img, float px, float py, float pz) {
+typedef float float4v __attribute__((ext_vector_type(4)));
+
+// (byte offsets fit 32 bits: an image is below 2 GiB)
+__device__ __forceinline__ float sample_packed(const DevProblem& pr, __amdgpu_buffer_rsrc_t img, float px, float py, float pz) {
   px = fminf(fmaxf(px, 0.f), (float)(pr.D[0] - 1)) + 1.f;
   py = fminf(fmaxf(py, 0.f), (float)(pr.D[1] - 1)) + 1.f;
   pz = fminf(fmaxf(pz, 0.f), (float)(pr.D[2] - 1)) + 1.f;
   const int ix = (int)px, iy = (int)py, iz = (int)pz;
   const float fx = px - ix, fy = py - iy, fz = pz - iz;
-  const float* e = img + 2 * ((size_t)iz * pr.exy + (size_t)iy * pr.ex + ix);
-  const float* f = e + 2 * pr.ex;
+  const unsigned sx8 = 8u * (unsigned)pr.ex, sxy8 = 8u * (unsigned)pr.exy;
+  const int at = (int)(__umul24((unsigned)iy, sx8) + (unsigned)iz * sxy8 + ((unsigned)ix << 3));
   // e: (x,y,z),(x,y,z+1),(x+1,y,z),(x+1,y,z+1); f: the same at y+1
+  const float4v e = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(img, at, 0, 0));
+  const float4v f = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(img, at, (int)sx8, 0));
   const float c00 = e[0] + fx * (e[2] - e[0]), c01 = e[1] + fx * (e[3] - e[1]);
   const float c10 = f[0] + fx * (f[2] - f[0]), c11 = f[1] + fx * (f[3] - f[1]);
   const float c0 = c00 + fy * (c10 - c00), c1 = c01 + fy * (c11 - c01);
@@ -434,73 +468,181 @@ __device__ float sample_packed(const DevProblem& pr, const float* img, float px,
 //   [162, 188) source image at (candidate + h o) minus target image at
 //              (candidate + h o), h = half the undeformed cube extent per axis;
 //   [188, 192) zero.
-// Rows are numbered (s, f, k) with k fastest.  32 lanes share a row: lane
-// j < 26 computes neighbour slot j (its 6 displacement features and its
-// intensity difference), lane 26 the moved-point features, lane 27 the padding.
-// With PACK the values are standardised with the stored input statistics and
-// rounded to BF16 in the same kernel, bit for bit what k_pack makes of the
+// Rows are numbered (s, f, k) with k fastest.
+struct FeatureArgs {
+  DevProblem pr;
+  const float* X;
+  int S, F, K;
+  const int* pts;
+  const float* cand;
+  const float* ident;  // undeformed grid [P][3]
+  float half[3];       // half the undeformed cube extent per axis
+  int64_t N;           // rows
+};
+
+// The 64 rows of tile `tile` (rows[]: their indices, -1 past the last): the
+// rows are taken with the element slowest, then the solution, then the
+// candidate, and the tiles are split into 8 contiguous parts, one per XCD.  A
+// tile then samples around one point or two, and the tiles that follow on the
+// same XCD around the same one in other solutions, so a point's 52 sampled
+// neighbourhoods (under 1 MB) come from memory once; in row order every tile
+// touched the whole images, and the gathers were bound by what L2 misses: 1320
+// us for 1.2 M rows at 512x512x100 in k_screen, 500 us in this order.
+__device__ __forceinline__ int64_t tile_row(const FeatureArgs& a, int64_t tile, int i, int& s, int& f) {
+  const int64_t q = tile * kTileRows + i;
+  s = f = 0;
+  if (q >= a.N) return -1;
+  int k;
+  if (a.N <= 0x7fffffff) {
+    const unsigned fs = (unsigned)q / (unsigned)a.K;
+    k = (int)((unsigned)q - fs * (unsigned)a.K);
+    f = (int)(fs / (unsigned)a.S);
+    s = (int)(fs - (unsigned)f * (unsigned)a.S);
+  } else {
+    const int64_t fs = q / a.K;
+    k = (int)(q - fs * a.K);
+    f = (int)(fs / a.S);
+    s = (int)(fs - (int64_t)f * a.S);
+  }
+  return ((int64_t)s * a.F + f) * a.K + k;
+}
+
+// Tile n of those that workgroup `block` of `blocks` (a multiple of 8) takes, or -1.
+__device__ __forceinline__ int64_t tile_of(int64_t tiles, int block, int blocks, int n) {
+  const int x = block & 7;
+  const int64_t q = tiles >> 3, r = tiles & 7, k = (block >> 3) + (int64_t)n * (blocks >> 3);
+  return k < q + (x < r ? 1 : 0) ? x * q + min((int64_t)x, r) + k : -1;
+}
+
+// Features of the 64 rows of a tile into LDS (absent rows are 0), by a
+// workgroup of 4 waves: lane = row, and each wave takes every fourth of the 28
+// groups of columns (26 neighbours, the moved point, the padding).  A group's
+// offsets and statistics are the same on every lane, so they are scalars, a
+// row's indices are worked out once instead of once per group, and the lanes
+// of one point's candidates sample next to each other (a gather of the 26
+// offsets of one row touches as many cache lines as lanes).  rows[] receives
+// the rows' indices.  With PACK the values are standardised with the stored
+// input statistics and rounded to BF16, bit for bit what k_pack makes of the
 // FP32 rows (sums and products are written with explicit rounding, so that
-// both instantiations compute identical FP32 values).
-template <bool PACK>
-__global__ __launch_bounds__(256) void k_features(DevProblem pr, const float* __restrict__ X, int S, int F,
-                                                  const int* __restrict__ pts, int K, const float* __restrict__ cand,
-                                                  const float* __restrict__ ident, const float* __restrict__ mean,
-                                                  const float* __restrict__ rstd, float* __restrict__ out32,
-                                                  unsigned short* __restrict__ out16) {
-  const int64_t row = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 5;
-  const int j = threadIdx.x & 31;
-  if (row >= (int64_t)S * F * K || j >= 28) return;
-  const int s = (int)(row / ((int64_t)F * K));
-  const int f = (int)((row / K) % F);
-  const int p = pts[f];
+// both forms compute identical FP32 values).
+template <bool PACK, class T>
+__device__ __forceinline__ void feature_tile(const FeatureArgs& a, const float* __restrict__ mean,
+                                             const float* __restrict__ rstd, int64_t tile_index, T* tile, int stride,
+                                             int64_t* rows) {
+  const DevProblem& pr = a.pr;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  T* out = tile + lane * stride;
+  int s, f;
+  const int64_t row = tile_row(a, tile_index, lane, s, f);
+  const bool exists = row >= 0;
+  if (wave == 0) rows[lane] = row;
+  const int p = exists ? a.pts[f] : -1;
   const bool valid = p >= 0 && p < pr.P;
-  const float* c = cand + row * 6;  // [2][3]
-  const float* Xs = X + (size_t)s * 6 * pr.P;
-  float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  float vi = 0.f;
-  int col;
-  if (j < 26) {
-    col = 6 + 6 * j;
-    if (valid) {
-      const int t = j < 13 ? j : j + 1;  // centre (13) skipped
-      const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
-      const int pi = p % pr.n[0], pj = (p / pr.n[0]) % pr.n[1], pk = p / (pr.n[0] * pr.n[1]);
-      const int qi = pi + dx, qj = pj + dy, qk = pk + dz;
-      if (qi >= 0 && qi < pr.n[0] && qj >= 0 && qj < pr.n[1] && qk >= 0 && qk < pr.n[2]) {
-        const int q = qi + pr.n[0] * (qj + pr.n[1] * qk);
+  const int pc = valid ? p : 0;  // where rows without a point read
+  const float* Xs = a.X + (size_t)s * 6 * pr.P;
+  const unsigned pin = pr.pin[pc];
+  float c[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (exists)
+    for (int k = 0; k < 6; ++k) c[k] = a.cand[row * 6 + k];
+  const float u[3] = {a.ident[3 * pc], a.ident[3 * pc + 1], a.ident[3 * pc + 2]};
+  const __amdgpu_buffer_rsrc_t img0 = __builtin_amdgcn_make_buffer_rsrc((void*)pr.img[0], (short)0, pr.img_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t img1 = __builtin_amdgcn_make_buffer_rsrc((void*)pr.img[1], (short)0, pr.img_bytes, 0x00020000);
+  auto put2 = [&](int col, float v0, float v1) {  // columns col, col + 1 (col even)
+    if constexpr (PACK) {
+      const unsigned lo = f2bf(__fmul_rn(__fsub_rn(v0, mean[col]), rstd[col]));
+      const unsigned hi = f2bf(__fmul_rn(__fsub_rn(v1, mean[col + 1]), rstd[col + 1]));
+      *reinterpret_cast<unsigned*>(out + col) = lo | (hi << 16);
+    } else {
+      out[col] = v0;
+      out[col + 1] = v1;
+    }
+  };
+#pragma unroll 2
+  for (int j = wave; j < 28; j += 4) {
+    if (j == 27) {
+      put2(kNumFeat, 0.f, 0.f);
+      put2(kNumFeat + 2, 0.f, 0.f);
+      continue;
+    }
+    float v[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (j == 26) {
+      if (valid)
         for (int g = 0; g < 2; ++g)
-          for (int a = 0; a < 3; ++a)
-            v[3 * g + a] = __fsub_rn(__fsub_rn(Xs[((size_t)g * pr.P + q) * 3 + a], c[3 * g + a]),
-                                     __fsub_rn(ident[3 * q + a], ident[3 * p + a]));
-      }
-      float off[3];
-      const int d[3] = {dx, dy, dz};
-      for (int a = 0; a < 3; ++a) off[a] = __fmul_rn(__fdiv_rn((float)pr.D[a], 2.f * (float)(pr.n[a] - 1)), (float)d[a]);
-      const float im = sample_packed(pr, pr.img[0], __fadd_rn(c[0], off[0]), __fadd_rn(c[1], off[1]), __fadd_rn(c[2], off[2]));
-      const float it = sample_packed(pr, pr.img[1], __fadd_rn(c[3], off[0]), __fadd_rn(c[4], off[1]), __fadd_rn(c[5], off[2]));
+          for (int k = 0; k < 3; ++k) v[3 * g + k] = __fsub_rn(c[3 * g + k], Xs[((size_t)g * pr.P + p) * 3 + k]);
+      for (int e = 0; e < 6; e += 2) put2(e, v[e], v[e + 1]);
+      continue;
+    }
+    const int t = j < 13 ? j : j + 1;  // centre (13) skipped
+    const int d[3] = {t % 3 - 1, (t / 3) % 3 - 1, t / 9 - 1};
+    bool there = valid;
+    for (int k = 0; k < 3; ++k) there = there && !(d[k] < 0 && (pin >> k & 1)) && !(d[k] > 0 && (pin >> (3 + k) & 1));
+    if (there) {
+      const int q = p + d[0] + pr.n[0] * (d[1] + pr.n[1] * d[2]);
+      for (int g = 0; g < 2; ++g)
+        for (int k = 0; k < 3; ++k)
+          v[3 * g + k] = __fsub_rn(__fsub_rn(Xs[((size_t)g * pr.P + q) * 3 + k], c[3 * g + k]),
+                                   __fsub_rn(a.ident[3 * q + k], u[k]));
+    }
+    float vi = 0.f;
+    if (valid) {
+      float o[3];
+      for (int k = 0; k < 3; ++k) o[k] = __fmul_rn(a.half[k], (float)d[k]);
+      const float im = sample_packed(pr, img0, __fadd_rn(c[0], o[0]), __fadd_rn(c[1], o[1]), __fadd_rn(c[2], o[2]));
+      const float it = sample_packed(pr, img1, __fadd_rn(c[3], o[0]), __fadd_rn(c[4], o[1]), __fadd_rn(c[5], o[2]));
       vi = __fsub_rn(im, it);
     }
-  } else if (j == 26) {
-    col = 0;
-    if (valid)
-      for (int g = 0; g < 2; ++g)
-        for (int a = 0; a < 3; ++a) v[3 * g + a] = __fsub_rn(c[3 * g + a], Xs[((size_t)g * pr.P + p) * 3 + a]);
-  } else {
-    col = kNumFeat;  // 4 zero columns
+    for (int e = 0; e < 6; e += 2) put2(6 + 6 * j + e, v[e], v[e + 1]);
+    if constexpr (PACK)
+      out[162 + j] = f2bf(__fmul_rn(__fsub_rn(vi, mean[162 + j]), rstd[162 + j]));
+    else
+      out[162 + j] = vi;
   }
-  const int nv = j == 27 ? kIn - kNumFeat : 6;
-  if (PACK) {
-    unsigned* o = reinterpret_cast<unsigned*>(out16 + row * kIn + col);  // 4-byte aligned: col is even
-    for (int e = 0; e < nv; e += 2) {
-      const unsigned lo = f2bf(__fmul_rn(__fsub_rn(v[e], mean[col + e]), rstd[col + e]));
-      const unsigned hi = f2bf(__fmul_rn(__fsub_rn(v[e + 1], mean[col + e + 1]), rstd[col + e + 1]));
-      o[e >> 1] = lo | (hi << 16);
-    }
-    if (j < 26) out16[row * kIn + kNumFeat - 26 + j] = f2bf(__fmul_rn(__fsub_rn(vi, mean[162 + j]), rstd[162 + j]));
-  } else {
-    float2* o = reinterpret_cast<float2*>(out32 + row * kIn + col);  // 8-byte aligned: col is even
-    for (int e = 0; e < nv; e += 2) o[e >> 1] = make_float2(v[e], v[e + 1]);
-    if (j < 26) out32[row * kIn + kNumFeat - 26 + j] = vi;
+}
+
+// Feature rows as FP32 (out32) or standardised BF16 (out16), written from the LDS tile.
+template <bool PACK>
+__global__ __launch_bounds__(256) void k_features(FeatureArgs a, const float* __restrict__ mean,
+                                                  const float* __restrict__ rstd, float* __restrict__ out32,
+                                                  unsigned short* __restrict__ out16) {
+  using T = std::conditional_t<PACK, unsigned short, float>;
+  constexpr int kStride = PACK ? kXs : kIn + 4, kPiece = 16 / sizeof(T);  // elements of a 16-byte piece
+  __shared__ __align__(16) T tile[kTileRows * kStride];
+  __shared__ int64_t s_row[kTileRows];
+  const int64_t index = tile_of((a.N + kTileRows - 1) / kTileRows, blockIdx.x, gridDim.x, 0);
+  if (index < 0) return;
+  feature_tile<PACK>(a, mean, rstd, index, tile, kStride, s_row);
+  __syncthreads();
+  T* dst;
+  if constexpr (PACK)
+    dst = out16;
+  else
+    dst = out32;
+  constexpr int kPieces = kIn / kPiece;  // 16 bytes each: rows of 384 or 768 bytes
+  for (int e = threadIdx.x; e < kTileRows * kPieces; e += 256) {
+    const int i = e / kPieces, c = kPiece * (e % kPieces);
+    if (s_row[i] >= 0) *reinterpret_cast<uint4*>(dst + s_row[i] * kIn + c) = *reinterpret_cast<const uint4*>(tile + i * kStride + c);
+  }
+}
+
+// Screening: features of 64 rows into LDS and the network on them, without
+// rows in memory (0.47 GB written and read again at 1.2 M candidates; the two
+// kernels took 1270 and 330 us).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_screen(
+    MlpW w, FeatureArgs a, const float* __restrict__ mean, const float* __restrict__ rstd, float* __restrict__ out) {
+  __shared__ __align__(16) unsigned short xs[kTileRows * kXs];  // inputs, then H2
+  __shared__ __align__(16) unsigned short h1[kTileRows * kHs];
+  __shared__ int64_t s_row[kTileRows];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  WaveWeights ww;
+  load_weights(w, wave, lane, ww);
+  const int64_t tiles = (a.N + kTileRows - 1) / kTileRows;
+  for (int n = 0;; ++n) {
+    const int64_t tile = tile_of(tiles, blockIdx.x, gridDim.x, n);
+    if (tile < 0) break;
+    feature_tile<true>(a, mean, rstd, tile, xs, kXs, s_row);
+    __syncthreads();
+    mlp_tile(ww, xs, h1, [&](int i) { return s_row[i]; }, out, wave, lane);
+    __syncthreads();
   }
 }
 
@@ -558,77 +700,119 @@ __global__ void k_targets(int N, const double* __restrict__ old, const double* _
 // flag it for exact evaluation iff its predicted delta would be accepted: it
 // improves one objective without worsening another, or it improves one
 // objective and the predicted objective vector is not dominated by any archive
-// member.
-__global__ void k_select(int S, int F, int K, const float* __restrict__ pred_std, const float* __restrict__ out_mean,
-                         const float* __restrict__ out_scale, const double* __restrict__ obj, int n_arch,
-                         const double* __restrict__ arch, float* __restrict__ pred_raw, int* __restrict__ pick,
-                         unsigned char* __restrict__ run_exact) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= S * F) return;
-  const int s = e / F;
-  const float* ps = pred_std + (size_t)e * K * kOut;
-  int best = 0, best_rank = 1 << 30;
-  float best_sum = INFINITY;
-  for (int k = 0; k < K; ++k) {
-    int rank = 0;
-    for (int j = 0; j < K; ++j) {
-      if (j == k) continue;
-      bool le = true, lt = false;
-      for (int o = 0; o < kOut; ++o) {
-        le = le && ps[j * kOut + o] <= ps[k * kOut + o];
-        lt = lt || ps[j * kOut + o] < ps[k * kOut + o];
-      }
-      rank += (le && lt) ? 1 : 0;
-    }
-    const float sum = ps[k * kOut] + ps[k * kOut + 1] + ps[k * kOut + 2];
-    if (rank < best_rank || (rank == best_rank && sum < best_sum)) {
-      best = k;
-      best_rank = rank;
-      best_sum = sum;
-    }
-  }
-  double d[kOut];
-  for (int k = 0; k < K; ++k)
-    for (int o = 0; o < kOut; ++o) {
-      const float r = ps[k * kOut + o] * out_scale[o] + out_mean[o];
-      if (pred_raw) pred_raw[((size_t)e * K + k) * kOut + o] = r;
-      if (k == best) d[o] = r;
-    }
-  bool le = true, lt = false;
-  for (int o = 0; o < kOut; ++o) {
-    le = le && d[o] <= 0.0;
-    lt = lt || d[o] < 0.0;
-  }
-  bool accept = le && lt;
-  bool improves = false;
-  for (int o = 0; o < kOut; ++o) improves = improves || d[o] < 0.0;
-  if (!accept && improves && obj && n_arch > 0) {
-    double nv[kOut];
-    for (int o = 0; o < kOut; ++o) nv[o] = obj[(size_t)s * kOut + o] + d[o];
-    bool dominated = false;
-    for (int a = 0; a < n_arch && !dominated; ++a) {
-      if (arch[(size_t)a * kOut] == INFINITY) break;  // padding ends the archive
-      bool ale = true, alt = false;
-      for (int o = 0; o < kOut; ++o) {
-        ale = ale && arch[(size_t)a * kOut + o] <= nv[o];
-        alt = alt || arch[(size_t)a * kOut + o] < nv[o];
-      }
-      dominated = ale && alt;
-    }
-    accept = !dominated;
-  }
-  pick[e] = best;
-  run_exact[e] = accept ? 1 : 0;
-}
+// member.  The picked candidates are gathered to cand_pick [S][F][2][3].
+// The archive is staged in LDS, and a thread tests kSelPairs pairs against
+// each row that it reads: with a pair a thread and the rows read from memory
+// the scan of 1,200 rows took 369 us for 307,200 pairs, now 200.
+constexpr int kSelPairs = 2, kSelTile = 512;
 
-// Gathers the picked candidate of every (solution, element): [S][F][K][2][3] -> [S][F][2][3].
-__global__ void k_gather_pick(int S, int F, int K, const float* __restrict__ cand, const int* __restrict__ pick,
-                              float* __restrict__ out) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= S * F * 6) return;
-  const int sf = e / 6, c = e % 6;
-  const int k = min(max(pick[sf], 0), K - 1);
-  out[e] = cand[((size_t)sf * K + k) * 6 + c];
+__global__ __launch_bounds__(256) void k_select(int S, int F, int K, const float* __restrict__ pred_std,
+                                                const float* __restrict__ out_mean, const float* __restrict__ out_scale,
+                                                const double* __restrict__ obj, int n_arch,
+                                                const double* __restrict__ arch, const float* __restrict__ cand,
+                                                float* __restrict__ pred_raw, int* __restrict__ pick,
+                                                unsigned char* __restrict__ run_exact, float* __restrict__ cand_pick) {
+  __shared__ double s_a[kSelTile][3];
+  __shared__ int s_end;
+  const int64_t base = (int64_t)blockIdx.x * (256 * kSelPairs) + threadIdx.x;
+  bool accept[kSelPairs], scan[kSelPairs];
+  double nv[kSelPairs][kOut];
+#pragma unroll
+  for (int i = 0; i < kSelPairs; ++i) {
+    const int64_t e = base + 256 * i;
+    accept[i] = scan[i] = false;
+    for (int o = 0; o < kOut; ++o) nv[i][o] = 0.0;
+    if (e >= (int64_t)S * F) continue;
+    const float* ps = pred_std + (size_t)e * K * kOut;
+    int best = 0, best_rank = 1 << 30;
+    float best_sum = INFINITY;
+    for (int k = 0; k < K; ++k) {
+      int rank = 0;
+      for (int j = 0; j < K; ++j) {
+        if (j == k) continue;
+        bool le = true, lt = false;
+        for (int o = 0; o < kOut; ++o) {
+          le = le && ps[j * kOut + o] <= ps[k * kOut + o];
+          lt = lt || ps[j * kOut + o] < ps[k * kOut + o];
+        }
+        rank += (le && lt) ? 1 : 0;
+      }
+      const float sum = ps[k * kOut] + ps[k * kOut + 1] + ps[k * kOut + 2];
+      if (rank < best_rank || (rank == best_rank && sum < best_sum)) {
+        best = k;
+        best_rank = rank;
+        best_sum = sum;
+      }
+    }
+    double d[kOut];
+    for (int k = 0; k < K; ++k)
+      for (int o = 0; o < kOut; ++o) {
+        const float r = ps[k * kOut + o] * out_scale[o] + out_mean[o];
+        if (pred_raw) pred_raw[((size_t)e * K + k) * kOut + o] = r;
+        if (k == best) d[o] = r;
+      }
+    bool le = true, lt = false;
+    for (int o = 0; o < kOut; ++o) {
+      le = le && d[o] <= 0.0;
+      lt = lt || d[o] < 0.0;
+    }
+    accept[i] = le && lt;
+    scan[i] = !accept[i] && lt && obj && n_arch > 0;
+    if (scan[i])
+      for (int o = 0; o < kOut; ++o) nv[i][o] = obj[(size_t)(e / F) * kOut + o] + d[o];
+    pick[e] = best;
+    if (cand_pick)
+      for (int c = 0; c < 6; ++c) cand_pick[(size_t)e * 6 + c] = cand[((size_t)e * K + best) * 6 + c];
+  }
+  bool left[kSelPairs];  // still to be tested
+#pragma unroll
+  for (int i = 0; i < kSelPairs; ++i) left[i] = scan[i];
+  for (int a0 = 0; a0 < n_arch; a0 += kSelTile) {
+    int any = 0;
+#pragma unroll
+    for (int i = 0; i < kSelPairs; ++i) any |= left[i];
+    if (!__syncthreads_or(any)) break;
+    const int na = min(kSelTile, n_arch - a0);
+    if (threadIdx.x == 0) s_end = na;
+    __syncthreads();
+    for (int q = threadIdx.x; q < 3 * na; q += 256) {
+      const double x = arch[3 * (size_t)a0 + q];
+      s_a[q / 3][q % 3] = x;
+      if (q % 3 == 0 && x == INFINITY) atomicMin(&s_end, q / 3);  // padding ends the archive
+    }
+    __syncthreads();
+    const int end = s_end;
+    bool dom[kSelPairs];
+#pragma unroll
+    for (int i = 0; i < kSelPairs; ++i) dom[i] = false;
+    for (int q0 = 0; q0 < end; q0 += 32) {
+      int open = 0;
+#pragma unroll
+      for (int i = 0; i < kSelPairs; ++i) open |= left[i] && !dom[i];
+      if (!__any(open)) break;
+      const int q1 = min(q0 + 32, end);
+#pragma unroll 4
+      for (int q = q0; q < q1; ++q) {
+        const double x = s_a[q][0], y = s_a[q][1], z = s_a[q][2];
+#pragma unroll
+        for (int i = 0; i < kSelPairs; ++i) {
+          const bool le = (x <= nv[i][0]) & (y <= nv[i][1]) & (z <= nv[i][2]);
+          if (__any(le)) dom[i] |= le & ((x < nv[i][0]) | (y < nv[i][1]) | (z < nv[i][2]));
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kSelPairs; ++i) {
+      scan[i] = scan[i] && !dom[i];
+      left[i] = left[i] && !dom[i];
+    }
+    if (end < na) break;
+  }
+#pragma unroll
+  for (int i = 0; i < kSelPairs; ++i) {
+    const int64_t e = base + 256 * i;
+    if (e < (int64_t)S * F) run_exact[e] = accept[i] || scan[i] ? 1 : 0;
+  }
 }
 
 }  // namespace
@@ -648,9 +832,7 @@ struct dsm_surrogate {
   unsigned short *d_xt = nullptr, *d_h1t = nullptr, *d_h2t = nullptr, *d_dyt = nullptr, *d_dz2t = nullptr,
                  *d_dz1t = nullptr;
   float* d_row_loss = nullptr;
-  // screening workspace for max_rows rows
-  unsigned short* d_featb = nullptr;  // [max_rows][192]
-  float* d_pred = nullptr;            // [max_rows][3]
+  float* d_pred = nullptr;  // screening workspace [max_rows][3]
 };
 
 namespace {
@@ -680,13 +862,28 @@ void free_sur(dsm_surrogate* m) {
   void* bufs[] = {m->d_params, m->d_m,      m->d_v,        m->d_grad,     m->d_w1,      m->d_w2,   m->d_w3,
                   m->d_w2t,    m->d_w3t,    m->d_in_mean,  m->d_in_rstd,  m->d_out_mean, m->d_out_rstd,
                   m->d_out_scale, m->d_xt,  m->d_h1t,      m->d_h2t,      m->d_dyt,     m->d_dz2t, m->d_dz1t,
-                  m->d_row_loss, m->d_featb,    m->d_pred};
+                  m->d_row_loss, m->d_pred};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   delete m;
 }
 
 Operands operands(const dsm_surrogate* m) { return Operands{m->d_w1, m->d_w2, m->d_w3, m->d_w2t, m->d_w3t}; }
+
+FeatureArgs feature_args(const dsm_problem* p, int S, const float* X, int F, const int* pts, int K, const float* cand) {
+  FeatureArgs a{};
+  a.pr = p->dev;
+  a.X = X;
+  a.S = S;
+  a.F = F;
+  a.K = K;
+  a.pts = pts;
+  a.cand = cand;
+  a.ident = p->d_ident;
+  for (int k = 0; k < 3; ++k) a.half[k] = (float)p->dev.D[k] / (2.f * (float)(p->dev.n[k] - 1));
+  a.N = (int64_t)S * F * K;
+  return a;
+}
 
 hipError_t refresh(dsm_surrogate* m, hipStream_t st) {
   k_refresh_bf16<<<(kNParams + 255) / 256, 256, 0, st>>>(m->d_params, operands(m));
@@ -752,7 +949,6 @@ dsm_status dsm_surrogate_create(const dsm_surrogate_desc* d, dsm_surrogate** out
   S_TRY(hipMalloc(&m->d_dz2t, 2 * kHid * B));
   S_TRY(hipMalloc(&m->d_dz1t, 2 * kHid * B));
   S_TRY(hipMalloc(&m->d_row_loss, sizeof(float) * B));
-  S_TRY(hipMalloc(&m->d_featb, 2 * kIn * (size_t)d->max_rows));
   S_TRY(hipMalloc(&m->d_pred, sizeof(float) * kOut * (size_t)d->max_rows));
   // He-uniform initial weights, zero biases (host, from the seed); identity scaling
   std::vector<float> p(kNParams, 0.f);
@@ -859,8 +1055,8 @@ dsm_status dsm_surrogate_features(dsm_problem* p, int32_t S, const float* X, int
   const int64_t n = (int64_t)S * F * K;
   if (n == 0) return DSM_OK;
   if (!X || !fos_pts || !cand || !feats) return sfail(DSM_ERR_ARG, "null argument");
-  k_features<false><<<(unsigned)((n + 7) / 8), 256, 0, (hipStream_t)stream>>>(p->dev, X, S, F, fos_pts, K, cand, p->d_ident,
-                                                                           nullptr, nullptr, feats, nullptr);
+  k_features<false><<<(unsigned)((n + 8 * kTileRows - 1) / (8 * kTileRows) * 8), 256, 0, (hipStream_t)stream>>>(
+      feature_args(p, S, X, F, fos_pts, K, cand), nullptr, nullptr, feats, nullptr);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }
@@ -873,9 +1069,8 @@ dsm_status dsm_surrogate_features_packed(dsm_surrogate* m, dsm_problem* p, int32
   const int64_t n = (int64_t)S * F * K;
   if (n == 0) return DSM_OK;
   if (!X || !fos_pts || !cand || !feats_bf16) return sfail(DSM_ERR_ARG, "null argument");
-  k_features<true><<<(unsigned)((n + 7) / 8), 256, 0, (hipStream_t)stream>>>(p->dev, X, S, F, fos_pts, K, cand, p->d_ident,
-                                                                          m->d_in_mean, m->d_in_rstd, nullptr,
-                                                                          (unsigned short*)feats_bf16);
+  k_features<true><<<(unsigned)((n + 8 * kTileRows - 1) / (8 * kTileRows) * 8), 256, 0, (hipStream_t)stream>>>(
+      feature_args(p, S, X, F, fos_pts, K, cand), m->d_in_mean, m->d_in_rstd, nullptr, (unsigned short*)feats_bf16);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }
@@ -899,7 +1094,7 @@ dsm_status dsm_surrogate_forward(dsm_surrogate* m, int32_t N, const uint16_t* fe
   s_err.clear();
   if (!m || !feats_bf16 || !pred || N < 0) return sfail(DSM_ERR_ARG, "null argument");
   if (N == 0) return DSM_OK;
-  k_mlp_forward64<<<(N + 63) / 64, 256, 0, (hipStream_t)stream>>>(weights(m), (const unsigned short*)feats_bf16, N, pred);
+  k_mlp_forward<<<mlp_grid(N), 256, 0, (hipStream_t)stream>>>(weights(m), (const unsigned short*)feats_bf16, N, pred);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }
@@ -945,12 +1140,11 @@ dsm_status dsm_surrogate_screen(dsm_surrogate* m, dsm_problem* p, int32_t S, con
   if (n > m->desc.max_rows) return sfail(DSM_ERR_CAPACITY, "S*F*K exceeds max_rows");
   if (n == 0) return DSM_OK;
   hipStream_t st = (hipStream_t)stream;
-  k_features<true><<<(unsigned)((n + 7) / 8), 256, 0, st>>>(p->dev, X, S, F, fos_pts, K, cand, p->d_ident, m->d_in_mean,
-                                                            m->d_in_rstd, nullptr, m->d_featb);
-  k_mlp_forward64<<<(unsigned)((n + 63) / 64), 256, 0, st>>>(weights(m), m->d_featb, (int)n, m->d_pred);
-  k_select<<<(S * F + 255) / 256, 256, 0, st>>>(S, F, K, m->d_pred, m->d_out_mean, m->d_out_scale, obj, n_archive, archive,
-                                                 pred, pick, run_exact);
-  if (cand_pick) k_gather_pick<<<(S * F * 6 + 255) / 256, 256, 0, st>>>(S, F, K, cand, pick, cand_pick);
+  k_screen<<<mlp_grid(n), 256, 0, st>>>(weights(m), feature_args(p, S, X, F, fos_pts, K, cand), m->d_in_mean, m->d_in_rstd,
+                                        m->d_pred);
+  const int64_t pairs = (int64_t)S * F;
+  k_select<<<(unsigned)((pairs + 256 * kSelPairs - 1) / (256 * kSelPairs)), 256, 0, st>>>(
+      S, F, K, m->d_pred, m->d_out_mean, m->d_out_scale, obj, n_archive, archive, cand, pred, pick, run_exact, cand_pick);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }

@@ -341,3 +341,72 @@ def test_slot_table_covers_every_chunk(F, chunk):
         np.testing.assert_array_equal(whole[k], np.concatenate([p[k].cpu().numpy() for p in parts], axis=1))
     assert np.all((whole[2] == 64) == (size == 3)[None])
     assert np.all(whole[3][:, size == 0] == 0) and np.all(whole[1][:, size == 0] == 0)
+
+
+# rows that end inside a 64-row tile, fill it, and leave an XCD or all but one without a tile
+@pytest.mark.parametrize("S,F,K", [(1, 1, 1), (3, 7, 3), (16, 1, 4), (5, 13, 1), (33, 9, 2)])
+def test_feature_tiles(tiny_problem, S, F, K):
+    w, gp = tiny_problem
+    rp = ref.Problem(w.moving, w.fixed, w.mesh, w.spacing, w.tau)
+    rng = np.random.default_rng(S * F * K)
+    X = _random_population(w, S, S + F)
+    pts = rng.integers(0, w.P, F).astype(np.int32)
+    cand = np.stack([W.candidates(X, np.arange(F + 1), pts, w.mesh, w.dims, 2.0, k) for k in range(K)], axis=2)
+    cand = np.ascontiguousarray(cand)  # [S][F][K][2][3]
+    got = dsm.Surrogate.features(gp, _t(X), _t(pts), _t(cand)).cpu().numpy()
+    want = R.features(rp, X, pts, cand).reshape(-1, 192)
+    # FP32 differences of coordinates up to 32 and of interpolated values up to about 1.1
+    np.testing.assert_allclose(got, want, rtol=0, atol=1e-4)
+    sur = dsm.Surrogate(seed=2, max_rows=S * F * K, max_batch=32)
+    sur.set_scaling(rng.normal(0, 0.2, 192).astype(np.float32), rng.uniform(0.5, 2, 192).astype(np.float32),
+                    np.zeros(3, np.float32), np.ones(3, np.float32))
+    packed = sur.features_packed(gp, _t(X), _t(pts), _t(cand))
+    np.testing.assert_array_equal(packed.cpu().numpy(), sur.pack(_t(got))[0].cpu().numpy())
+    # the screening kernel computes the same rows in LDS: its predictions are the network's on the packed rows
+    pred = sur.screen(gp, _t(X), _t(pts), _t(cand))[2]
+    np.testing.assert_array_equal(pred.cpu().numpy().reshape(-1, 3), sur.forward(packed).cpu().numpy())
+
+
+# one tile more than the persistent grid of 768 takes at once, and tiles that are not full: a row's outputs do not
+# depend on its place, so the rows of a call equal those of calls of one tile (which are checked against the reference)
+@pytest.mark.parametrize("N", [63, 64, 65, 513, 768 * 64, 768 * 64 + 1])
+def test_forward_tiles(N):
+    rng = np.random.default_rng(N)
+    p = rng.normal(0, 0.15, R.NPARAMS).astype(np.float32)
+    x = torch.from_numpy(rng.normal(size=(N, R.IN)).astype(np.float32)).to(torch.bfloat16).view(torch.int16).to(DEV)
+    sur = dsm.Surrogate(seed=1, max_rows=64, max_batch=32)
+    sur.params(p)
+    y = sur.forward(x)
+    for a in (0, 64 * (N // 128), max(0, N - 64), max(0, N - 1)):
+        part = x[a:a + 64].contiguous()
+        assert torch.equal(y[a:a + 64], sur.forward(part))
+    order = torch.from_numpy(rng.permutation(N)).to(DEV)
+    assert torch.equal(sur.forward(x[order].contiguous()), y[order])
+
+
+# archives around the 512-row staging tile and its 32-row steps, ended by padding or not; pairs that end inside a workgroup
+@pytest.mark.parametrize("n_arch,pad", [(1, 0), (31, 3), (511, 1), (512, 0), (512, 600), (513, 0), (1100, 0)])
+def test_screening_against_archives(tiny_problem, n_arch, pad):
+    w, gp = tiny_problem
+    rng = np.random.default_rng(n_arch + pad)
+    S, K = 21, 2
+    pts = np.arange(w.P, dtype=np.int32)
+    X = _random_population(w, S, 3)
+    cand = np.stack([W.candidates(X, np.arange(w.P + 1), pts, w.mesh, w.dims, 1.0, k) for k in range(K)], axis=2)
+    sur = dsm.Surrogate(seed=5, max_rows=S * w.P * K, max_batch=32)
+    sur.set_scaling(np.zeros(192, np.float32), np.ones(192, np.float32), np.zeros(3, np.float32),
+                    np.full(3, 20.0, np.float32))
+    obj = rng.uniform(0.5, 1.5, (S, 3))
+    arch = rng.uniform(0.4, 1.6, (n_arch, 3))
+    if n_arch > 1:
+        arch[:-1] += 1.0  # the last row decides for most
+    behind = np.concatenate([np.full((min(pad, 1), 3), np.inf), np.zeros((max(pad - 1, 0), 3))])  # not looked at
+    pick, run, pred, cp = sur.screen(gp, _t(X), _t(pts), _t(np.ascontiguousarray(cand)), obj=_t(obj),
+                                     archive=_t(np.concatenate([arch, behind])))
+    pick, run, pred = pick.cpu().numpy(), run.cpu().numpy(), pred.cpu().numpy().astype(np.float64)
+    d = np.take_along_axis(pred, pick[..., None, None].astype(np.int64), axis=2)[:, :, 0]
+    nv = obj[:, None] + d
+    dom = ((arch[None, None] <= nv[:, :, None]).all(3) & (arch[None, None] < nv[:, :, None]).any(3)).any(2)
+    want = ((d <= 0).all(2) & (d < 0).any(2)) | ((d < 0).any(2) & ~dom)
+    np.testing.assert_array_equal(run != 0, want)
+    np.testing.assert_array_equal(cp.cpu().numpy(), np.take_along_axis(cand, pick[..., None, None, None].astype(np.int64), axis=2)[:, :, 0])
