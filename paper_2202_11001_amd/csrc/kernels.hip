@@ -480,7 +480,9 @@ __device__ __forceinline__ void row_span(const RasterTet& rt, bool used, int y, 
 
 // One compacted (non-empty) row: both fields are read from one LDS address.
 struct RowRec {
-  float4 rec;  // x: own-image linear index minus start (as int bits); yzw: mapped position of the span's first voxel
+  // x: own-image linear index minus start (as int bits); yzw: mapped position
+  // of the span's first voxel (sweep), or its x minus start, y, z (as int bits)
+  float4 rec;
   int start;   // exclusive prefix of span lengths
   int pad[3];
 };
@@ -505,7 +507,7 @@ constexpr int kWalkGroups = 3;
 // kOwnBytes the byte offset of its value in the bordered z-pair image minus 8
 // times the start (the second row of a pair reads the second value of the
 // element that holds the first row's voxel, so the two rows share the own
-// image's cache lines).  The mapped position of the first voxel is
+// image's cache lines) and the mapped position of the first voxel,
 // M (x0, y, z, 1) + shift.  *my_start receives the first voxel index of this
 // lane's row, or a large negative value if it is empty.  kPairs must equal
 // rt.pairs (a compile-time copy, so that the slice-by-slice order pays
@@ -569,10 +571,12 @@ __device__ __forceinline__ int build_rows(const RasterTet& rt, int b, int lane, 
       len = x1 - x0 + 1;
       lin = base + z * sz + y * sy + x0;
       if (kOwnBytes) lin = (lin - h * sz) * 8 + 4 * h;
-      const double v[3] = {(double)x0, (double)y, (double)z};
-      bx = (float)(rt.M[0][3] + rt.M[0][0] * v[0] + rt.M[0][1] * v[1] + rt.M[0][2] * v[2] + shift);
-      by = (float)(rt.M[1][3] + rt.M[1][0] * v[0] + rt.M[1][1] * v[1] + rt.M[1][2] * v[2] + shift);
-      bz = (float)(rt.M[2][3] + rt.M[2][0] * v[0] + rt.M[2][1] * v[1] + rt.M[2][2] * v[2] + shift);
+      if (kOwnBytes) {
+        const double v[3] = {(double)x0, (double)y, (double)z};
+        bx = (float)(rt.M[0][3] + rt.M[0][0] * v[0] + rt.M[0][1] * v[1] + rt.M[0][2] * v[2] + shift);
+        by = (float)(rt.M[1][3] + rt.M[1][0] * v[0] + rt.M[1][1] * v[1] + rt.M[1][2] * v[2] + shift);
+        bz = (float)(rt.M[2][3] + rt.M[2][0] * v[0] + rt.M[2][1] * v[1] + rt.M[2][2] * v[2] + shift);
+      }
     }
   }
   const int incl = wave_incl_scan(len);
@@ -582,6 +586,11 @@ __device__ __forceinline__ int build_rows(const RasterTet& rt, int b, int lane, 
   wave_sync();
   if (len > 0) {
     wr.row[slot].start = start;
+    if (!kOwnBytes) {
+      bx = __int_as_float(x0 - start);
+      by = __int_as_float(y);
+      bz = __int_as_float(z);
+    }
     wr.row[slot].rec = make_float4(__int_as_float(kOwnBytes ? lin - 8 * start : lin - start), bx, by, bz);
   }
   wave_sync();
@@ -1475,74 +1484,155 @@ __global__ __launch_bounds__(kWG) void k_owner(DevProblem pr, const float* __res
   }
 }
 
-// Value of voxel (x, y, z) of a bordered z-pair image: the second half of
-// element (x + 1, y + 1, z).
-__device__ __forceinline__ double raw_voxel(const float* img, int ex, int exy, int x, int y, int z) {
-  return (double)img[2 * ((size_t)(x + 1) + (size_t)ex * (y + 1) + (size_t)exy * z) + 1];
+// FP64 trilinear sample of a bordered image at voxel (i, j, k) plus d voxels,
+// clamped to [0, D-1] per axis (the resampling of the objectives, Sec. 2.3.1):
+// the element of cell (i, j, k) is (i + 1, j + 1, k + 1) and holds the values
+// at k and k + 1, its right neighbour those at i + 1.  cell64 turns d into the
+// fractions and returns the byte offset of the element.
+__device__ __forceinline__ int cell64(const DevProblem& pr, const int v[3], double d[3]) {
+  int i0[3];
+  for (int a = 0; a < 3; ++a) {
+    i0[a] = min(max(v[a] + (int)floor(d[a]), 0), pr.D[a] - 2);
+    d[a] = fmin(fmax(d[a] - (double)(i0[a] - v[a]), 0.0), 1.0);
+  }
+  return (int)(__umul24((unsigned)(i0[1] + 1), 8u * (unsigned)pr.ex) + (unsigned)(i0[2] + 1) * (8u * (unsigned)pr.exy) +
+               ((unsigned)(i0[0] + 1) << 3));
+}
+// p, q: the elements (x, z) (x, z+1) (x+1, z) (x+1, z+1) at y and y + 1.
+__device__ __forceinline__ double trilinear64(const double f[3], float4v p, float4v q) {
+  auto mix = [](double t, double u, double v) { return fma(t, v, (1.0 - t) * u); };
+  const double c0 = mix(f[1], mix(f[0], p[0], p[2]), mix(f[0], q[0], q[2]));
+  const double c1 = mix(f[1], mix(f[0], p[1], p[3]), mix(f[0], q[1], q[3]));
+  return mix(f[2], c0, c1);
 }
 
-// FP64 trilinear sample of a bordered image at voxel-unit position x, clamped
-// to [0, D-1] per axis (the resampling of the objectives, Sec. 2.3.1).
-__device__ double trilinear64(const DevProblem& pr, const float* img, const double x[3]) {
-  int i0[3];
-  double f[3];
-  for (int a = 0; a < 3; ++a) {
-    const double c = fmin(fmax(x[a], 0.0), (double)(pr.D[a] - 1));
-    int i = (int)floor(c);
-    if (i > pr.D[a] - 2) i = pr.D[a] - 2;
-    i0[a] = i;
-    f[a] = c - i;
-  }
-  double acc = 0.0;
-  for (int dz = 0; dz < 2; ++dz)
-    for (int dy = 0; dy < 2; ++dy)
-      for (int dx = 0; dx < 2; ++dx) {
-        const double w = (dx ? f[0] : 1.0 - f[0]) * (dy ? f[1] : 1.0 - f[1]) * (dz ? f[2] : 1.0 - f[2]);
-        acc += w * raw_voxel(img, pr.ex, pr.exy, i0[0] + dx, i0[1] + dy, i0[2] + dz);
+// Clears the outputs of dsm_transform to NaN, for the voxels that no usable
+// tetrahedron covers.  With `check` only where there may be some: if every
+// coordinate lies on the lattice, grid `own` keeps its border points on the
+// box and none of its tetrahedra is inverted, those tile the box and every
+// voxel is written.  Each workgroup looks at the whole grid by itself: no flag
+// to clear, no second launch, and no memory that two calls could share.
+__global__ __launch_bounds__(1024) void k_transform_clear(DevProblem pr, int own, const float* __restrict__ X2, int check,
+                                                          uint32_t* dvf, int64_t nd, uint32_t* warped, int64_t nw) {
+  if (check) {
+    bool bad = false;
+    for (int e = threadIdx.x; e < 2 * pr.P; e += blockDim.x) {
+      const int gr = e >= pr.P, v = e - gr * pr.P;
+      const unsigned pin = pr.pin[v];
+      for (int c = 0; c < 3; ++c) {
+        float x = X2[3 * (size_t)e + c];
+        bad |= lattice_bits(x, pr.D[c]) != 0u;
+        bad |= gr == own && ((pin >> c & 1 && x != -0.5f) || (pin >> (3 + c) & 1 && x != (float)pr.D[c] - 0.5f));
       }
-  return acc;
+    }
+    const float* Xo = X2 + (size_t)own * 3 * pr.P;
+    for (int t = threadIdx.x; t < pr.T; t += blockDim.x) {
+      const int4 tv = pr.tets[t];
+      const int vid[4] = {tv.x, tv.y, tv.z, tv.w};
+      double L[4][3];
+      for (int q = 0; q < 4; ++q)
+        for (int c = 0; c < 3; ++c) L[q][c] = ((double)Xo[3 * (size_t)vid[q] + c] + 0.5) * kLat;
+      bad |= !(orient(L[0], L[1], L[2], L[3]) > 0.0);
+    }
+    if (!__syncthreads_or(bad)) return;
+  }
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nd + nw; i += step)
+    (i < nd ? dvf + i : warped + (i - nd))[0] = 0x7fc00000u;
 }
 
 // The piecewise-affine map of one solution (Sec. 2.1) at every voxel of image
 // `own`: each tetrahedron of grid `own` rasterises its exact voxel set (the
-// same spans as the objectives) and maps every voxel centre with FP64
-// barycentric coordinates from exact orientations onto the same tetrahedron of
-// the other grid.  Writes the displacement (voxel units) and the other image
-// sampled there.  One workgroup per tetrahedron.
-__global__ __launch_bounds__(kWG) void k_transform(DevProblem pr, int own, const float* __restrict__ X2,
+// same spans as the objectives) and maps every voxel centre, in FP64, onto the
+// same tetrahedron of the other grid.  Writes the displacement (voxel units)
+// and the other image sampled there.  `parts` workgroups per tetrahedron share
+// its units of 64 rows.  The barycentric coordinates of a row's first voxel
+// come from the face functions that its span came from, exact integers over
+// the volume; along the row the displacement is linear, 3 multiply-adds per
+// voxel.  As four determinants of every voxel (about 250 FP64 instructions)
+// they made the kernel take 428 us at 512x512x100; 285 us now, for 206 MB read
+// and 419 MB written.  Memory bounds it there: with only the displacements
+// written it takes 75 us, with only the image 155 us, and with every load in
+// one 16 KB piece 180 us.  Longer batches of loads, stores held back to the
+// end of a unit, a pass for each output and an order by slices were all
+// slower or no faster, at 200^3 (64 us, all of it in the last-level cache) too.
+struct MapRow {
+  double d[3];  // displacement of the row's first voxel
+  int lin, x0;  // linear index and x of the row's first voxel, both minus start
+  int y, z;
+  int start;    // exclusive prefix of span lengths
+  int pad;
+};
+__global__ __launch_bounds__(kWG) void k_transform(DevProblem pr, int own, const float* __restrict__ X2, int parts,
                                                    float* dvf, float* warped) {
   __shared__ WaveRows rows[kWaves];
-  __shared__ RasterTet rts[kWaves];
+  __shared__ MapRow maps[kWaves][64];
+  __shared__ RasterTet rt;
+  __shared__ double s_vol;
   __shared__ float xs[2][12];
-  const int t = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int logical = xcd_logical(blockIdx.x & 7, blockIdx.x >> 3, pr.T * parts);
+  if (logical < 0) return;
+  const int t = logical / parts, part = logical - t * parts;
+  const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
   const int4 tv = pr.tets[t];
   const int vid[4] = {tv.x, tv.y, tv.z, tv.w};
-  const float* Xo = X2 + (size_t)own * 3 * pr.P;
-  const float* Xt = X2 + (size_t)(1 - own) * 3 * pr.P;
-  double L[4][3], Lt[4][3], Xv[4][3];
-  unsigned bad = 0u;
-  for (int q = 0; q < 4; ++q)
-    for (int c = 0; c < 3; ++c) {
-      bad |= lattice_of(Xo[(size_t)vid[q] * 3 + c], pr.D[c], L[q][c]);
-      const float xt = Xt[(size_t)vid[q] * 3 + c];
-      bad |= lattice_of(xt, pr.D[c], Lt[q][c]);
-      Xv[q][c] = (double)xt;
-    }
-  const double vol = orient(L[0], L[1], L[2], L[3]);
-  if (bad || !(vol > 0.0)) return;
+  bool bad = false;
   if (threadIdx.x < 24) {
-    const int g = threadIdx.x / 12, e = threadIdx.x % 12;
-    xs[g][e] = (g == 0 ? Xo : Xt)[(size_t)vid[e / 3] * 3 + e % 3];
+    const int g = threadIdx.x / 12, e = threadIdx.x % 12, c = e % 3;
+    float x = X2[((size_t)(g == 0 ? own : 1 - own) * pr.P + vid[e / 3]) * 3 + c];
+    bad = lattice_bits(x, c == 0 ? pr.D[0] : (c == 1 ? pr.D[1] : pr.D[2])) != 0u;
+    xs[g][e] = x;
+  }
+  if (__syncthreads_or(bad)) return;
+  if (wave == 0) {
+    double vol = 0.0;
+    if (lane == 0) s_vol = vol = -setup_face(xs[0], 0, rt);
+    if (lane_value(vol, 0) > 0.0) setup_raster(xs[0], xs[1], pr.D, lane, rt);
   }
   __syncthreads();
-  RasterTet& rt = rts[wave];
-  setup_raster(xs[0], xs[1], pr.D, lane, rt);
-  const float* other = pr.img[1 - own];
+  const double vol = lane_value(s_vol, 0);
+  if (!(vol > 0.0)) return;
+  // position = X3 + sum over f < 3 of o_f(voxel) (X_f - X3) / vol, o_f = C[f][0] + C[f][1] i + C[f][2] j + C[f][3] k
+  double C[3][4], E[3][3], X3[3], step[3] = {-1.0, 0.0, 0.0};
+  const double rvol = 1.0 / vol;
+  for (int a = 0; a < 3; ++a) X3[a] = lane_value((double)xs[1][9 + a], 0);
+  for (int f = 0; f < 3; ++f) {
+    C[f][0] = lane_value(rt.F[f][0] + rt.thr[f], 0);
+    C[f][1] = lane_value(rt.A[f], 0);
+    C[f][2] = lane_value(rt.F[f][1], 0);
+    C[f][3] = lane_value(rt.F[f][2], 0);
+    for (int a = 0; a < 3; ++a) {
+      E[f][a] = lane_value((double)(xs[1][3 * f + a] - xs[1][9 + a]) * rvol, 0);
+      step[a] = lane_value(step[a] + C[f][1] * E[f][a], 0);
+    }
+  }
+  const __amdgpu_buffer_rsrc_t other = image_rsrc(own ? pr.img[0] : pr.img[1], pr.img_bytes);
+  const int sy = 8 * pr.ex;
   const int nb = (rt.nrows + 63) >> 6;
-  for (int b = wave; b < nb; b += kWaves) {
-    WaveRows& wr = rows[wave];
+  WaveRows& wr = rows[wave];
+  MapRow* map = maps[wave];
+  for (int b = part * kWaves + wave; b < nb; b += kWaves * parts) {
     int my_start;
     const int nvox = build_rows<false, 0>(rt, b, lane, pr.D, pr.D[0], pr.DxDy, 0, 0.0f, wr, &my_start);
+    if (lane < __popcll(__ballot(my_start >= 0))) {
+      MapRow m;
+      const float4 rec = wr.row[lane].rec;
+      m.start = wr.row[lane].start;
+      m.lin = __float_as_int(rec.x);
+      m.x0 = __float_as_int(rec.y);
+      m.y = __float_as_int(rec.z);
+      m.z = __float_as_int(rec.w);
+      const double i = m.x0 + m.start, j = m.y, k = m.z;
+      double x[3] = {X3[0], X3[1], X3[2]};
+      for (int f = 0; f < 3; ++f) {
+        const double o = C[f][0] + C[f][1] * i + C[f][2] * j + C[f][3] * k;
+        for (int a = 0; a < 3; ++a) x[a] += o * E[f][a];
+      }
+      m.d[0] = x[0] - i;
+      m.d[1] = x[1] - j;
+      m.d[2] = x[2] - k;
+      map[lane] = m;
+    }
     int carry = 0;
     for (int q0 = 0; q0 < nvox; q0 += 64) {
       wr.marker[lane] = 0;
@@ -1551,30 +1641,23 @@ __global__ __launch_bounds__(kWG) void k_transform(DevProblem pr, int own, const
       if (pos < 64u) wr.marker[pos] = 1;
       wave_sync();
       const int mk = wr.marker[lane];
-      const unsigned long long M = __ballot(mk != 0);
-      const int r = carry + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(M >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)M, 0u)) +
+      const unsigned long long m = __ballot(mk != 0);
+      const int r = carry + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)) +
                     mk - 1;
-      carry += __popcll(M);
+      carry += __popcll(m);
       const int q = q0 + lane;
-      if (q < nvox) {
-        const int idx = __float_as_int(wr.row[r].rec.x) + q;
-        const int k = idx / pr.DxDy, rem = idx - k * pr.DxDy;
-        const int j = rem / pr.D[0], i = rem - j * pr.D[0];
-        const double U[3] = {kLat * i + 0.5 * kLat, kLat * j + 0.5 * kLat, kLat * k + 0.5 * kLat};
-        double x[3] = {0.0, 0.0, 0.0};
-        for (int v = 0; v < 4; ++v) {
-          double W[4][3];
-          for (int m = 0; m < 4; ++m)
-            for (int c = 0; c < 3; ++c) W[m][c] = m == v ? U[c] : L[m][c];
-          const double lam = orient(W[0], W[1], W[2], W[3]) / vol;
-          for (int c = 0; c < 3; ++c) x[c] += lam * Xv[v][c];
-        }
-        if (dvf) {
-          dvf[(size_t)idx * 3 + 0] = (float)(x[0] - i);
-          dvf[(size_t)idx * 3 + 1] = (float)(x[1] - j);
-          dvf[(size_t)idx * 3 + 2] = (float)(x[2] - k);
-        }
-        if (warped) warped[idx] = (float)trilinear64(pr, other, x);
+      if (q >= nvox) break;
+      const MapRow row = map[r];
+      const int idx = row.lin + q;
+      const double n = q - row.start;
+      double d[3];
+      for (int a = 0; a < 3; ++a) d[a] = row.d[a] + n * step[a];
+      if (dvf) reinterpret_cast<float3*>(dvf)[idx] = make_float3((float)d[0], (float)d[1], (float)d[2]);
+      if (warped) {
+        const int v[3] = {row.x0 + q, row.y, row.z};
+        const int at = cell64(pr, v, d);
+        const float4v p = load4(other, at, 0), u = load4(other, at, sy);
+        warped[idx] = (float)trilinear64(d, p, u);
       }
     }
   }
@@ -1768,23 +1851,28 @@ hipError_t launch_pack_bordered(const float* raw, float* out, int Dx, int Dy, in
   return hipGetLastError();
 }
 
+// Voxels of a tetrahedron (on average) per workgroup of k_transform: setting
+// one up takes about as long as 1000 voxels (2048 voxels each: 305 us at
+// 512x512x100, 8192: 297 us), and tetrahedra of more fill the device only if
+// they are split (27 tetrahedra of 42000 voxels a cube at 200^3).
+constexpr int kTransformVoxels = 8192;
+// k_transform_clear looks at the grid before it clears where that is the
+// shorter: clearing takes 2.5 us per million voxels, the look (every point and
+// tetrahedron, by each workgroup) 6 us for 2430 tetrahedra.
+constexpr int64_t kCheckVoxels = 1024;
+
 hipError_t launch_transform(const DevProblem& pr, int own, const float* X2, float* dvf, float* warped,
                             hipStream_t stream) {
-  const int64_t V = (int64_t)pr.DxDy * pr.D[2];
-  const uint32_t nan_bits = 0x7fc00000u;
-  hipError_t e = hipSuccess;
-  if (dvf) {
-    k_fill_u32<<<(unsigned)std::min<int64_t>((3 * V + 255) / 256, 4096), 256, 0, stream>>>((uint32_t*)dvf, 3 * V,
-                                                                                          nan_bits);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (warped) {
-    k_fill_u32<<<(unsigned)std::min<int64_t>((V + 255) / 256, 4096), 256, 0, stream>>>((uint32_t*)warped, V,
-                                                                                      nan_bits);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
   if (!dvf && !warped) return hipSuccess;
-  k_transform<<<pr.T, kWG, 0, stream>>>(pr, own, X2, dvf, warped);
+  const int64_t V = (int64_t)pr.DxDy * pr.D[2];
+  const int64_t nd = dvf ? 3 * V : 0, nw = warped ? V : 0;
+  const int check = V >= (1 << 20) + kCheckVoxels * (int64_t)pr.T;
+  k_transform_clear<<<(unsigned)std::min<int64_t>((nd + nw + 1023) / 1024, check ? 256 : 1024), 1024, 0, stream>>>(
+      pr, own, X2, check, (uint32_t*)dvf, nd, (uint32_t*)warped, nw);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(64, V / pr.T / kTransformVoxels));
+  k_transform<<<8u * (((unsigned)pr.T * parts + 7) / 8), kWG, 0, stream>>>(pr, own, X2, parts, dvf, warped);
   return hipGetLastError();
 }
 

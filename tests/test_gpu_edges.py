@@ -7,7 +7,7 @@ from oracle import gomea_ref as G
 from oracle import ref
 from oracle import surrogate_ref as R
 from paper_2202_11001_amd import workloads as W
-from tests._common import assert_delta_close, assert_objectives_close
+from tests._common import assert_delta_close, assert_objectives_close, oracle_problem
 
 pytestmark = pytest.mark.gpu
 
@@ -410,3 +410,37 @@ def test_screening_against_archives(tiny_problem, n_arch, pad):
     want = ((d <= 0).all(2) & (d < 0).any(2)) | ((d < 0).any(2) & ~dom)
     np.testing.assert_array_equal(run != 0, want)
     np.testing.assert_array_equal(cp.cpu().numpy(), np.take_along_axis(cand, pick[..., None, None, None].astype(np.int64), axis=2)[:, :, 0])
+
+
+# a volume whose outputs are cleared only if a voxel can stay uncovered, in tetrahedra split over workgroups and taller
+# than the slice table; each way in which a voxel can: a border point off the box, points off the lattice in either grid,
+# a grid that covers a part of the box, flat tetrahedra
+@pytest.mark.parametrize("what", ["covered", "border", "off-lattice", "other-off-lattice", "shrunk", "flat"])
+def test_transform_of_uncovered_voxels(what):
+    w = W.batched(shape=(200, 80, 112), mesh=(3, 3, 3))
+    rp = oracle_problem(w)
+    I = W.regular_grid(w.dims, w.mesh)
+    rng = np.random.default_rng(8)
+    X = np.stack([W.snap(np.clip(I + rng.normal(0, 2, I.shape) * W.free_mask(w.mesh), -0.5, np.array(w.dims) - 0.5))] * 2)
+    X[1] = W.snap(np.clip(I + rng.normal(0, 2, I.shape) * W.free_mask(w.mesh), -0.5, np.array(w.dims) - 0.5))
+    own = 1
+    if what == "border":
+        X[own, 12, 0] += 5.0  # the middle of the face x = -0.5
+    elif what == "off-lattice":
+        X[own, 12, 1] += 1.0 / 512
+    elif what == "other-off-lattice":
+        X[1 - own, 0, 2] = np.nan
+    elif what == "shrunk":
+        X[own] = W.snap(0.75 * X[own] + 0.125 * np.array(w.dims))
+    elif what == "flat":
+        X[own, 13, 0] = -0.5  # onto the face of the point next to it
+        X[own, 13, 1:] = X[own, 12, 1:]
+    rd, rm = rp.transform(own, X)
+    assert np.isnan(rm).any() == (what not in ("covered", "flat"))
+    gp = dsm.Problem.from_workload(w)
+    d, m = gp.transform(_t(X), own=own)
+    # displacements below 64 voxels rounded to FP32, and values up to 1
+    np.testing.assert_allclose(d.cpu().numpy(), rd, rtol=0, atol=4e-6)
+    np.testing.assert_allclose(m.cpu().numpy(), rm, rtol=0, atol=1e-6)
+    only = gp.transform(_t(X), own=own, dvf=False)[1]
+    np.testing.assert_array_equal(only.cpu().numpy(), m.cpu().numpy())
