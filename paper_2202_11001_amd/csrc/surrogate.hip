@@ -701,11 +701,16 @@ __global__ void k_targets(int N, const double* __restrict__ old, const double* _
 // improves one objective without worsening another, or it improves one
 // objective and the predicted objective vector is not dominated by any archive
 // member.  The picked candidates are gathered to cand_pick [S][F][2][3].
-// The archive is staged in LDS, and a thread tests kSelPairs pairs against
-// each row that it reads: with a pair a thread and the rows read from memory
-// the scan of 1,200 rows took 369 us for 307,200 pairs, now 200.
-constexpr int kSelPairs = 2, kSelTile = 512;
+// The archive is staged in LDS and G lanes share a pair and its rows.  A pair a
+// lane leaves the device idle while each walks the archive row by row (162 us
+// for 3,000 rows, however few the pairs); more lanes stage the archive more
+// often and repeat the choice among the K.  The whole screening call, in us,
+// with 64 / 16 / 4 lanes: 1,600 pairs and 600 rows 30 / - / 80, 32,400 pairs
+// and 2,000 rows 118 / 85 / 117, 307,200 pairs and 1,200 rows 1006 / 684 / 583
+// (678 with two pairs a lane).
+constexpr int kSelTile = 512;
 
+template <int G>
 __global__ __launch_bounds__(256) void k_select(int S, int F, int K, const float* __restrict__ pred_std,
                                                 const float* __restrict__ out_mean, const float* __restrict__ out_scale,
                                                 const double* __restrict__ obj, int n_arch,
@@ -714,15 +719,11 @@ __global__ __launch_bounds__(256) void k_select(int S, int F, int K, const float
                                                 unsigned char* __restrict__ run_exact, float* __restrict__ cand_pick) {
   __shared__ double s_a[kSelTile][3];
   __shared__ int s_end;
-  const int64_t base = (int64_t)blockIdx.x * (256 * kSelPairs) + threadIdx.x;
-  bool accept[kSelPairs], scan[kSelPairs];
-  double nv[kSelPairs][kOut];
-#pragma unroll
-  for (int i = 0; i < kSelPairs; ++i) {
-    const int64_t e = base + 256 * i;
-    accept[i] = scan[i] = false;
-    for (int o = 0; o < kOut; ++o) nv[i][o] = 0.0;
-    if (e >= (int64_t)S * F) continue;
+  const int64_t e = blockIdx.x * (int64_t)(256 / G) + threadIdx.x / G;
+  const int sub = threadIdx.x % G;
+  bool accept = false, scan = false;
+  double nv[kOut] = {0.0, 0.0, 0.0};
+  if (e < (int64_t)S * F) {
     const float* ps = pred_std + (size_t)e * K * kOut;
     int best = 0, best_rank = 1 << 30;
     float best_sum = INFINITY;
@@ -748,7 +749,7 @@ __global__ __launch_bounds__(256) void k_select(int S, int F, int K, const float
     for (int k = 0; k < K; ++k)
       for (int o = 0; o < kOut; ++o) {
         const float r = ps[k * kOut + o] * out_scale[o] + out_mean[o];
-        if (pred_raw) pred_raw[((size_t)e * K + k) * kOut + o] = r;
+        if (pred_raw && sub == 0) pred_raw[((size_t)e * K + k) * kOut + o] = r;
         if (k == best) d[o] = r;
       }
     bool le = true, lt = false;
@@ -756,22 +757,17 @@ __global__ __launch_bounds__(256) void k_select(int S, int F, int K, const float
       le = le && d[o] <= 0.0;
       lt = lt || d[o] < 0.0;
     }
-    accept[i] = le && lt;
-    scan[i] = !accept[i] && lt && obj && n_arch > 0;
-    if (scan[i])
-      for (int o = 0; o < kOut; ++o) nv[i][o] = obj[(size_t)(e / F) * kOut + o] + d[o];
-    pick[e] = best;
-    if (cand_pick)
+    accept = le && lt;
+    scan = !accept && lt && obj && n_arch > 0;
+    if (scan)
+      for (int o = 0; o < kOut; ++o) nv[o] = obj[(size_t)(e / F) * kOut + o] + d[o];
+    if (sub == 0) pick[e] = best;
+    if (cand_pick && sub == 0)
       for (int c = 0; c < 6; ++c) cand_pick[(size_t)e * 6 + c] = cand[((size_t)e * K + best) * 6 + c];
   }
-  bool left[kSelPairs];  // still to be tested
-#pragma unroll
-  for (int i = 0; i < kSelPairs; ++i) left[i] = scan[i];
+  bool left = scan;  // still to be tested
   for (int a0 = 0; a0 < n_arch; a0 += kSelTile) {
-    int any = 0;
-#pragma unroll
-    for (int i = 0; i < kSelPairs; ++i) any |= left[i];
-    if (!__syncthreads_or(any)) break;
+    if (!__syncthreads_or(left)) break;
     const int na = min(kSelTile, n_arch - a0);
     if (threadIdx.x == 0) s_end = na;
     __syncthreads();
@@ -782,37 +778,23 @@ __global__ __launch_bounds__(256) void k_select(int S, int F, int K, const float
     }
     __syncthreads();
     const int end = s_end;
-    bool dom[kSelPairs];
-#pragma unroll
-    for (int i = 0; i < kSelPairs; ++i) dom[i] = false;
-    for (int q0 = 0; q0 < end; q0 += 32) {
-      int open = 0;
-#pragma unroll
-      for (int i = 0; i < kSelPairs; ++i) open |= left[i] && !dom[i];
-      if (!__any(open)) break;
-      const int q1 = min(q0 + 32, end);
+    bool dom = false;
+    for (int q0 = sub; q0 < end; q0 += 32 * G) {
+      if (!__any(left && !dom)) break;
+      const int q1 = min(q0 + 32 * G, end);
 #pragma unroll 4
-      for (int q = q0; q < q1; ++q) {
+      for (int q = q0; q < q1; q += G) {
         const double x = s_a[q][0], y = s_a[q][1], z = s_a[q][2];
-#pragma unroll
-        for (int i = 0; i < kSelPairs; ++i) {
-          const bool le = (x <= nv[i][0]) & (y <= nv[i][1]) & (z <= nv[i][2]);
-          if (__any(le)) dom[i] |= le & ((x < nv[i][0]) | (y < nv[i][1]) | (z < nv[i][2]));
-        }
+        const bool le = (x <= nv[0]) & (y <= nv[1]) & (z <= nv[2]);
+        if (__any(le)) dom |= le & ((x < nv[0]) | (y < nv[1]) | (z < nv[2]));
       }
     }
-#pragma unroll
-    for (int i = 0; i < kSelPairs; ++i) {
-      scan[i] = scan[i] && !dom[i];
-      left[i] = left[i] && !dom[i];
-    }
+    dom = (__ballot(dom) >> (threadIdx.x & 63 & ~(G - 1)) & (~0ull >> (64 - G))) != 0;  // of any lane of the pair
+    scan = scan && !dom;
+    left = left && !dom;
     if (end < na) break;
   }
-#pragma unroll
-  for (int i = 0; i < kSelPairs; ++i) {
-    const int64_t e = base + 256 * i;
-    if (e < (int64_t)S * F) run_exact[e] = accept[i] || scan[i] ? 1 : 0;
-  }
+  if (sub == 0 && e < (int64_t)S * F) run_exact[e] = accept || scan ? 1 : 0;
 }
 
 }  // namespace
@@ -1143,8 +1125,17 @@ dsm_status dsm_surrogate_screen(dsm_surrogate* m, dsm_problem* p, int32_t S, con
   k_screen<<<mlp_grid(n), 256, 0, st>>>(weights(m), feature_args(p, S, X, F, fos_pts, K, cand), m->d_in_mean, m->d_in_rstd,
                                         m->d_pred);
   const int64_t pairs = (int64_t)S * F;
-  k_select<<<(unsigned)((pairs + 256 * kSelPairs - 1) / (256 * kSelPairs)), 256, 0, st>>>(
-      S, F, K, m->d_pred, m->d_out_mean, m->d_out_scale, obj, n_archive, archive, cand, pred, pick, run_exact, cand_pick);
+  auto select = [&](auto* kernel, int lanes) {
+    kernel<<<(unsigned)((pairs * lanes + 255) / 256), 256, 0, st>>>(S, F, K, m->d_pred, m->d_out_mean, m->d_out_scale,
+                                                                    obj, n_archive, archive, cand, pred, pick, run_exact,
+                                                                    cand_pick);
+  };
+  if (pairs <= 4096)
+    select(k_select<64>, 64);
+  else if (pairs <= 65536)
+    select(k_select<16>, 16);
+  else
+    select(k_select<4>, 4);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }

@@ -444,3 +444,26 @@ def test_transform_of_uncovered_voxels(what):
     np.testing.assert_allclose(m.cpu().numpy(), rm, rtol=0, atol=1e-6)
     only = gp.transform(_t(X), own=own, dvf=False)[1]
     np.testing.assert_array_equal(only.cpu().numpy(), m.cpu().numpy())
+
+
+# numbers of pairs on both sides of 4096 and 65536, where the lanes of a pair change: a pair's results do not depend on
+# the others, so they are those of calls of 2700 pairs
+@pytest.mark.parametrize("S", [151, 152, 2427, 2428])
+def test_screening_of_many_pairs(tiny_problem, S):
+    w, gp = tiny_problem
+    rng = np.random.default_rng(S)
+    K = 2
+    pts = _t(np.arange(w.P, dtype=np.int32))
+    base = _random_population(w, 100, 3)
+    X = np.ascontiguousarray(base[np.arange(S) % 100])
+    cand = np.ascontiguousarray(rng.normal(0, 1, (S, w.P, K, 2, 3)).astype(np.float32) +
+                                X.transpose(0, 2, 1, 3)[:, :, None])
+    obj, arch = rng.uniform(0.5, 1.5, (S, 3)), rng.uniform(0.8, 1.6, (700, 3))
+    sur = dsm.Surrogate(seed=5, max_rows=S * w.P * K, max_batch=32)
+    sur.set_scaling(np.zeros(192, np.float32), np.ones(192, np.float32), np.zeros(3, np.float32),
+                    np.full(3, 20.0, np.float32))
+    got = sur.screen(gp, _t(X), pts, _t(cand), obj=_t(obj), archive=_t(arch))
+    for a in range(0, S, 100):
+        part = sur.screen(gp, _t(X[a:a + 100]), pts, _t(cand[a:a + 100]), obj=_t(obj[a:a + 100]), archive=_t(arch))
+        for g, p in zip(got, part):
+            assert torch.equal(g[a:a + 100], p)
