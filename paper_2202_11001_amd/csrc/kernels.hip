@@ -1208,6 +1208,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(7, 8))) voi
 // the current terms: the chunks' second version, or the cached terms of the
 // affected tetrahedra (a fixed butterfly order over each kFinishLanes of them).
 // One group of kFinishLanes lanes per pair.
+constexpr int kFinishRounds = 4;
 __device__ __forceinline__ void finish_body(const EvalArgs& a, int logical, int lane) {
   const DevProblem& pr = a.pr;
   const int g = logical / a.S, s = logical - g * a.S;
@@ -1241,15 +1242,24 @@ __device__ __forceinline__ void finish_body(const EvalArgs& a, int logical, int 
     a.vcount[oi] = bits;
   }
   if (a.nver == 1) {
+    // kFinishRounds rounds' loads at a time: the loads that depend on one
+    // another, not their number, are the time
     double old[3] = {0.0, 0.0, 0.0};
-#pragma unroll 2
-    for (int base = 0; base < na; base += kFinishLanes) {
-      double t[3] = {0.0, 0.0, 0.0};
-      if (base + lane < na) {
-        const double* src = a.terms_in + ((size_t)s * pr.T + a.aff[(size_t)g * a.maxA + base + lane]) * 3;
-        for (int k = 0; k < 3; ++k) t[k] = src[k];
+    for (int base = 0; base < na; base += kFinishLanes * kFinishRounds) {
+      int id[kFinishRounds];
+      double t[kFinishRounds][3];
+#pragma unroll
+      for (int u = 0; u < kFinishRounds; ++u) {
+        const int i = base + u * kFinishLanes + lane;
+        id[u] = i < na ? a.aff[(size_t)g * a.maxA + i] : -1;
       }
-      for (int k = 0; k < 3; ++k) old[k] += group_sum(t[k]);
+#pragma unroll
+      for (int u = 0; u < kFinishRounds; ++u)
+        for (int k = 0; k < 3; ++k) t[u][k] = id[u] >= 0 ? a.terms_in[((size_t)s * pr.T + id[u]) * 3 + k] : 0.0;
+#pragma unroll
+      for (int u = 0; u < kFinishRounds; ++u)
+        if (base + u * kFinishLanes < na)
+          for (int k = 0; k < 3; ++k) old[k] += group_sum(t[u][k]);
     }
     if (lane >= 3 && lane < 6) acc = lane == 3 ? old[0] : (lane == 4 ? old[1] : old[2]);
   }
@@ -1350,13 +1360,17 @@ __device__ int affected_serial(const DevProblem& pr, int b, int e, const int* __
   return n;
 }
 
-constexpr int kAffCap = 1024;  // star entries of one element sorted in LDS
+constexpr int kAffCap = 1024;  // words of an element's bitmap, or its star entries sorted, in LDS
 
 // Affected sets of the FOS elements (Sec. 2.2: the tetrahedra to re-evaluate
-// when the element's points move): one wave per element gathers the stars of
-// its points into LDS, sorts them (bitonic) and keeps the first of every run
-// of equal ids, written in ascending order; aff_cnt[f] = their number, or -1
-// for a malformed element or one whose set would exceed maxA.
+// when the element's points move): the distinct ids of its points' stars in
+// ascending order; aff_cnt[f] = their number, or -1 for a malformed element or
+// one whose set would exceed maxA.  One wave per element.  On meshes of up to
+// 32 kAffCap tetrahedra the wave marks the ids in a bitmap in LDS and lists the
+// marked ones; on larger ones it sorts the star entries (bitonic) and keeps the
+// first of every run of equal ids.  The length of the chain bounds it: with the
+// points read one after the other and the sort, a call took 12.6 us for
+// 4-point elements, with a lane to a point and the bitmap 4.6.
 __global__ __launch_bounds__(64) void k_affected(DevProblem pr, int F, const int* __restrict__ fos_off,
                                                  const int* __restrict__ fos_pts, int max_pts, int maxA, int* aff,
                                                  int* aff_cnt) {
@@ -1364,28 +1378,50 @@ __global__ __launch_bounds__(64) void k_affected(DevProblem pr, int F, const int
   const int f = blockIdx.x, lane = threadIdx.x;
   const int b = fos_off[f], e = fos_off[f + 1];
   int* out = aff + (size_t)f * maxA;
+  const bool marks = pr.T <= 32 * kAffCap;
+  const int words = marks ? (pr.T + 2047) / 2048 : 0;  // of a lane
+  for (int w = 0; w < words; ++w) s_c[64 * w + lane] = 0;
   bool bad = b < 0 || e < b || e - b > max_pts;
   int total = 0;
-  for (int k = b; !bad && k < e; ++k) {
-    const int p = fos_pts[k];
-    if (p < 0 || p >= pr.P)
-      bad = true;
-    else
-      total += pr.star_off[p + 1] - pr.star_off[p];
+  for (int k0 = b; !bad && k0 < e; k0 += 64) {  // 64 points at a time, a lane each
+    const int p = k0 + lane < e ? fos_pts[k0 + lane] : 0;
+    bad = __any(p < 0 || p >= pr.P);
+    if (bad) break;
+    const int so = pr.star_off[p], n = k0 + lane < e ? pr.star_off[p + 1] - so : 0;
+    const int incl = wave_incl_scan(n), all = __builtin_amdgcn_readlane(incl, 63);
+    for (int i = lane; i < all; i += 64) {  // an entry's point is the last one whose entries start at or before it
+      int at = 0;
+      for (int k = 0; k < min(64, e - k0); ++k) {
+        const int first = __builtin_amdgcn_readlane(incl - n, k);
+        if (i >= first) at = __builtin_amdgcn_readlane(so, k) + i - first;
+      }
+      const int t = pr.star[at];
+      if (marks)
+        atomicOr((unsigned*)&s_c[t >> 5], 1u << (t & 31));
+      else if (total + i < kAffCap)
+        s_c[total + i] = t;
+    }
+    total += all;
   }
   if (bad) {
     if (lane == 0) aff_cnt[f] = -1;
     return;
   }
-  if (total > kAffCap) {
+  if (!marks && total > kAffCap) {
     if (lane == 0) aff_cnt[f] = affected_serial(pr, b, e, fos_pts, maxA, out);
     return;
   }
-  int base = 0;
-  for (int k = b; k < e; ++k) {
-    const int p = fos_pts[k], so = pr.star_off[p], n = pr.star_off[p + 1] - so;
-    for (int i = lane; i < n; i += 64) s_c[base + i] = pr.star[so + i];
-    base += n;
+  __syncthreads();
+  if (marks) {
+    int cnt = 0;
+    for (int w = 0; w < words; ++w) cnt += __popc((unsigned)s_c[words * lane + w]);
+    const int incl = wave_incl_scan(cnt), n_marked = __builtin_amdgcn_readlane(incl, 63);
+    if (lane == 0) aff_cnt[f] = n_marked > maxA ? -1 : n_marked;
+    if (n_marked > maxA) return;
+    int pos = incl - cnt;
+    for (int w = words * lane; w < words * (lane + 1); ++w)
+      for (unsigned m = (unsigned)s_c[w]; m; m &= m - 1) out[pos++] = 32 * w + __builtin_ctz(m);
+    return;
   }
   int n2 = 1;
   while (n2 < total) n2 <<= 1;
@@ -1732,39 +1768,56 @@ hipError_t launch_fold(const DevProblem& pr, int S, const float* X, uint32_t* fl
 // every XCD and the others exit on one scalar load.  Without it every second
 // or third workgroup looked up its element to find it had no such chunk: 520
 // of 3,600 us on a class of the phantom's tetrahedra, 770 of 6,000 us on the
-// uneven half-resolution batch.  Bitonic sort of (cost, index) keys in LDS,
-// one workgroup.
+// uneven half-resolution batch.  One workgroup orders (cost, index) keys in
+// LDS: by the number of smaller keys for up to kRankMax elements, where that is
+// shorter than the steps of a sort, by a bitonic sort beyond.
+constexpr int kRankMax = 256;
 __global__ __launch_bounds__(1024) void k_slots(int G, const int* __restrict__ aff_cnt, int pchunk,
                                                 int2* __restrict__ slots) {
   __shared__ unsigned long long key[kOrderMax];
   __shared__ int s_order[kOrderMax];
   __shared__ int s_wave[16];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  int n = 1;
-  while (n < G) n <<= 1;
-  for (int i = t; i < n; i += 1024)
-    key[i] = i < G ? ((unsigned long long)(0xffffffffu - (unsigned)max(aff_cnt[i], 0)) << 32) | (unsigned)i : ~0ull;
-  __syncthreads();
-  for (int k = 2; k <= n; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = t; i < n; i += 1024) {
-        const int l = i ^ j;
-        if (l > i) {
-          const unsigned long long u = key[i], v = key[l];
-          if ((u > v) == ((i & k) == 0)) {
-            key[i] = v;
-            key[l] = u;
-          }
-        }
-      }
-      __syncthreads();
-    }
+  auto key_of = [&](int i) {
+    return ((unsigned long long)(0xffffffffu - (unsigned)max(aff_cnt[i], 0)) << 32) | (unsigned)i;
+  };
   const int nb = G >> 4, rem = G & 15;
-  for (int i = t; i < G; i += 1024) {
+  auto deal = [&](int i, int g) {  // element g is i-th by cost
     const int r = i & 15, x = r < 8 ? r : 15 - r;
     int start = 0;  // elements dealt to the XCDs before x
     for (int y = 0; y < x; ++y) start += 2 * nb + (y < rem ? 1 : 0) + (15 - y < rem ? 1 : 0);
-    s_order[start + (i >> 4) * 2 + (r >= 8 ? 1 : 0)] = (int)(unsigned)(key[i] & 0xffffffffull);
+    s_order[start + (i >> 4) * 2 + (r >= 8 ? 1 : 0)] = g;
+  };
+  if (G <= kRankMax) {
+    if (t < kRankMax) key[t] = t < G ? key_of(t) : ~0ull;
+    __syncthreads();
+    if (t < G) {
+      const unsigned long long mine = key[t];
+      int rank = 0;
+#pragma unroll 4
+      for (int j = 0; j < G; ++j) rank += key[j] < mine;
+      deal(rank, t);
+    }
+  } else {
+    int n = 1;
+    while (n < G) n <<= 1;
+    for (int i = t; i < n; i += 1024) key[i] = i < G ? key_of(i) : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= n; k <<= 1)
+      for (int j = k >> 1; j > 0; j >>= 1) {
+        for (int i = t; i < n; i += 1024) {
+          const int l = i ^ j;
+          if (l > i) {
+            const unsigned long long u = key[i], v = key[l];
+            if ((u > v) == ((i & k) == 0)) {
+              key[i] = v;
+              key[l] = u;
+            }
+          }
+        }
+        __syncthreads();
+      }
+    for (int i = t; i < G; i += 1024) deal(i, (int)(unsigned)(key[i] & 0xffffffffull));
   }
   __syncthreads();
   int base = 1;

@@ -467,3 +467,53 @@ def test_screening_of_many_pairs(tiny_problem, S):
         part = sur.screen(gp, _t(X[a:a + 100]), pts, _t(cand[a:a + 100]), obj=_t(obj[a:a + 100]), archive=_t(arch))
         for g, p in zip(got, part):
             assert torch.equal(g[a:a + 100], p)
+
+
+# affected sets from a bitmap (one word a lane, two, the most that fit in LDS) and sorted on larger meshes; elements of
+# one point, a repeated one, more than a wave has lanes, and more star entries than the sort takes; an invalid point
+@pytest.mark.parametrize("mesh,dims", [((3, 3, 3), (16, 16, 16)), ((8, 8, 8), (24, 24, 24)), ((19, 19, 17), (40, 40, 36)),
+                                       ((21, 19, 17), (44, 40, 36))])
+def test_affected_sets(mesh, dims):
+    rng = np.random.default_rng(mesh[0])
+    img = [rng.uniform(0, 1, dims[::-1]).astype(np.float32) for _ in range(2)]
+    w = W.Workload("affected", img[0], img[1], mesh, (1.0, 1.0, 1.0), 0.2, 1, 1.0, 1.0, 7, 8)
+    rp = oracle_problem(w)
+    P = w.P
+    many = rng.permutation(P)[:min(70, P)]
+    groups = [[P // 2], [0, 1, mesh[0], mesh[0] * mesh[1]], [5, 5], list(range(min(P, 40))), list(many), [P], [P // 2, -1]]
+    off = np.cumsum([0] + [len(g) for g in groups]).astype(np.int32)
+    pts = np.concatenate(groups).astype(np.int32)
+    gp = dsm.Problem.from_workload(w, max_solutions=1, max_fos_points=70)
+    X = np.stack([W.regular_grid(dims, mesh)] * 2)[None]
+    Xd = _t(X)
+    cand = X[:, :, np.clip(pts, 0, P - 1)].transpose(0, 2, 1, 3).copy()
+    old, new, fl, vc = gp.eval_partial(Xd, _t(off), _t(pts), _t(cand), voxel_count=True)
+    n = off[5]  # the oracle takes valid points only
+    rold, rnew, rfl, rnv = rp.eval_partial(X, off[:6], pts[:n], np.ascontiguousarray(cand[:, :n]))
+    assert not rfl.any()
+    np.testing.assert_array_equal(fl.cpu().numpy(), [[0] * 5 + [dsm.FLAG_BAD_FOS] * 2])
+    np.testing.assert_array_equal(vc.cpu().numpy()[:, :5], rnv)
+    # the parts are sums over the affected tetrahedra: a missing or repeated one shows in each
+    assert_objectives_close(old.cpu().numpy()[:, :5], rold)
+    assert_objectives_close(new.cpu().numpy()[:, :5], rnew)
+
+
+# numbers of elements on both sides of 256, where the slot table's order is found in another way, and of its 1024 threads
+@pytest.mark.parametrize("F", [1, 16, 255, 256, 257, 1025])
+def test_slot_table_orders(tiny_problem, F):
+    w, gp0 = tiny_problem
+    rng = np.random.default_rng(F)
+    gp = dsm.Problem.from_workload(w, max_solutions=2, max_fos=F, max_fos_points=2)
+    sizes = rng.integers(1, 3, F)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    pts = rng.integers(0, w.P, off[-1]).astype(np.int32)
+    X = _random_population(w, 2, F)
+    cand = X[:, :, pts].transpose(0, 2, 1, 3).copy()
+    got = gp.eval_partial(_t(X), _t(off), _t(pts), _t(cand))
+    one = dsm.Problem.from_workload(w, max_solutions=2, max_fos=1, max_fos_points=2)
+    for f in rng.permutation(F)[:12]:  # an element's results do not depend on the others
+        o = np.array([0, sizes[f]], np.int32)
+        sl = slice(off[f], off[f + 1])
+        part = one.eval_partial(_t(X), _t(o), _t(pts[sl]), _t(cand[:, sl]))
+        for g, q in zip(got[:3], part[:3]):
+            assert torch.equal(g[:, f], q[:, 0])
