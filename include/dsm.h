@@ -522,6 +522,15 @@ dsm_status dsm_estimate_elements(dsm_problem* p, int32_t S, const float* X, int3
                                  const int32_t* fos_off, const int32_t* fos_pts, double* mean, double* chol,
                                  void* stream);
 
+/* The distributions of n_clusters (1 to 16) selections sel dev [n_clusters][n_sel]
+ * in one call: of elements as dsm_estimate_elements (mean dev [n_clusters][F][24],
+ * chol dev [n_clusters][F][300]), or with fos_off NULL of the single points
+ * fos_pts[F] as dsm_estimate_distributions ([n_clusters][F][6] and [..][21]).
+ * Errors: DSM_ERR_ARG. */
+dsm_status dsm_estimate_clusters(dsm_problem* p, int32_t S, const float* X, int32_t n_clusters, int32_t n_sel,
+                                 const int32_t* sel, int32_t F, const int32_t* fos_off, const int32_t* fos_pts,
+                                 double* mean, double* chol, void* stream);
+
 /* Candidates cand dev [S][fos_off[F]][2][3] (the layout of dsm_eval_partial)
  * drawn per solution and element from N(mean, mult[f] L L^T) on the element's
  * free variables (24 counter-based standard normal draws per solution and

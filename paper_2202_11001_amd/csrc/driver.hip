@@ -94,7 +94,8 @@ __device__ __forceinline__ double readlane64(double v, int l) {
 // rows and columns of pinned coordinates, and of variables beyond 6 x (number
 // of points), are 0, and a pivot that is not positive (a rank-deficient
 // selection) gives a zero column.  Elements with no point, more than NP
-// points, an invalid point or no valid solution get zeros.
+// points, an invalid point or no valid solution get zeros.  Cluster blockIdx.y
+// has a selection, means and factors of its own, one after the other.
 //
 // One workgroup per element, one thread per covariance entry.  There are few
 // elements in a call (5 to 75), so the kernel is bound by the length of its
@@ -118,8 +119,9 @@ __global__ __launch_bounds__(NP == 1 ? 64 : 320) void k_estimate(DevProblem pr, 
   __shared__ double s_C[NE];
   __shared__ bool s_ok[kEstTile], s_free[NV];
   const int f = blockIdx.x, t = threadIdx.x;
-  double* mu = mean + (size_t)f * NV;
-  double* L = chol + (size_t)f * NE;
+  sel += (size_t)blockIdx.y * n_sel;
+  double* mu = mean + ((size_t)blockIdx.y * F + f) * NV;
+  double* L = chol + ((size_t)blockIdx.y * F + f) * NE;
   const int b = off ? off[f] : f, np = off ? off[f + 1] - b : 1;
   bool ok = b >= 0 && np >= 1 && np <= NP && (!off || b + np <= off[F]);
   for (int k = 0; ok && k < np; ++k) ok = pts[b + k] >= 0 && pts[b + k] < pr.P;
@@ -728,6 +730,20 @@ dsm_status dsm_estimate_elements(dsm_problem* p, int32_t S, const float* X, int3
   if (!fos_off || !fos_pts || !mean || !chol || (n_sel > 0 && (!X || !sel))) return DSM_ERR_ARG;
   k_estimate<kEstPoints><<<(unsigned)F, 320, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, fos_off, fos_pts, mean,
                                                                       chol);
+  return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
+}
+
+dsm_status dsm_estimate_clusters(dsm_problem* p, int32_t S, const float* X, int32_t n_clusters, int32_t n_sel,
+                                 const int32_t* sel, int32_t F, const int32_t* fos_off, const int32_t* fos_pts,
+                                 double* mean, double* chol, void* stream) {
+  if (!p || S < 0 || F < 0 || n_sel < 0 || n_clusters < 1 || n_clusters > kClusterMax) return DSM_ERR_ARG;
+  if (F == 0) return DSM_OK;  // empty buffers may be null
+  if (!fos_pts || !mean || !chol || (n_sel > 0 && (!X || !sel))) return DSM_ERR_ARG;
+  const dim3 grid((unsigned)F, (unsigned)n_clusters);
+  if (fos_off)
+    k_estimate<kEstPoints><<<grid, 320, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, fos_off, fos_pts, mean, chol);
+  else
+    k_estimate<1><<<grid, 64, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, nullptr, fos_pts, mean, chol);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
 

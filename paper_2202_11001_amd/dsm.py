@@ -87,6 +87,7 @@ def lib():
             "dsm_sample_estimated": ([V, I, V, I, V, I, V, V, V, I, V, V, V, C.c_double, C.c_uint64, C.c_uint64, V,
                                       V, V], I),
             "dsm_estimate_elements": ([V, I, V, I, V, I, V, V, V, V, V], I),
+            "dsm_estimate_clusters": ([V, I, V, I, I, V, I, V, V, V, V, V], I),
             "dsm_sample_elements": ([V, I, V, I, V, V, V, V, V, I, V, V, V, C.c_double, C.c_uint64, C.c_uint64, V,
                                      V, V], I),
             "dsm_cluster_objectives": ([I, V, I, V, I, V, V, V, V], I),
@@ -589,6 +590,21 @@ class Problem:
         chol = torch.empty((F, 300), dtype=torch.float64, device=X.device)
         _check(lib().dsm_estimate_elements(self._h, X.shape[0], _dptr(X), sel.shape[0], _dptr(sel), F, _dptr(off),
                                            _dptr(pts), _dptr(mean), _dptr(chol), _stream(stream)))
+        return mean, chol
+
+    def estimate_clusters(self, X, members, pts, off=None, stream=None):
+        """The distributions of every cluster's selection members [C][n] int32:
+        estimate_elements (off given) or estimate_distributions of each, as
+        (mean [C][F][24 or 6], chol [C][F][300 or 21]) float64."""
+        torch = _torch()
+        if members.dtype != torch.int32 or X.dtype != torch.float32 or not members.is_contiguous():
+            raise ValueError("X float32 and contiguous members int32 expected")
+        C, n = members.shape
+        F, nv = (pts.shape[0], 6) if off is None else (off.shape[0] - 1, 24)
+        mean = torch.empty((C, F, nv), dtype=torch.float64, device=X.device)
+        chol = torch.empty((C, F, nv * (nv + 1) // 2), dtype=torch.float64, device=X.device)
+        _check(lib().dsm_estimate_clusters(self._h, X.shape[0], _dptr(X), C, n, _dptr(members), F, _dptr(off), _dptr(pts),
+                                           _dptr(mean), _dptr(chol), _stream(stream)))
         return mean, chol
 
     def sample_elements(self, X, off, pts, mean, chol, mult, seed, counter, out=None, stream=None, counter_dev=None,

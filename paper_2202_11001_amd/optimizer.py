@@ -300,9 +300,7 @@ class Optimiser:
                 cand = self.p.sample_candidates(self.X, pts, 1, self.sigma, self.seed, c + 1, counter_dev=self.counter_dev)
                 self._force(pts, cand)
             else:
-                est = [self.p.estimate_elements(self.X, m, off, pts) for m in members]
-                mean = torch.stack([e[0] for e in est]).contiguous()
-                chol = torch.stack([e[1] for e in est]).contiguous()
+                mean, chol = self.p.estimate_clusters(self.X, members, pts, off)
                 mult = self.mult_cube[:, cubes_d].contiguous()
                 cand = self.p.sample_elements(self.X, off, pts, mean, chol, mult, self.seed, c + 1,
                                               counter_dev=self.counter_dev, cluster=self._assign, shift=self._shift,
@@ -368,9 +366,9 @@ class Optimiser:
 
     def _cluster(self):
         """Selection, and with k > 1 clusters its balanced k-leader-means
-        clustering in objective space (MO-RV-GOMEA): the member lists whose
-        distributions are estimated, one per cluster; every solution samples
-        from its nearest cluster (self._assign)."""
+        clustering in objective space (MO-RV-GOMEA): the member lists [k][n]
+        whose distributions are estimated; every solution samples from its
+        nearest cluster (self._assign)."""
         sel = self.select()
         if self.use_ams:
             all_pts = self.torch.arange(self.p.P, dtype=self.torch.int32, device=self.X.device)
@@ -384,13 +382,13 @@ class Optimiser:
             half = np.random.default_rng([self.seed, self._gen, 7]).permutation(self.S) < self.S // 2
             self._ams = self.torch.from_numpy(half.astype(np.uint8)).to(self.X.device)
         if self.k == 1:
-            return [sel]
+            return sel.reshape(1, -1)
         members, self._assign, means = dsm.cluster_objectives(self.obj, sel, self.k)
         if self.use_so:
             # objective o takes the cluster with the lowest mean in o among those
             # not yet taken (in objective order), so each gets its own while k >= 3
             self._so = dsm.single_objective_clusters(means, self._assign)
-        return [members[j] for j in range(self.k)]
+        return members
 
     def _dominated_by(self):
         """Number of population members dominating each solution (device int32, dsm_select)."""
@@ -455,11 +453,7 @@ class Optimiser:
             self._draw_donors()
         if self.sampler == "estimated" and self.fos == "point":
             members = self._cluster()
-            self._dist = []
-            for pts in self.classes:
-                est = [self.p.estimate_distributions(self.X, m, pts) for m in members]
-                self._dist.append((torch.stack([e[0] for e in est]).contiguous(),
-                                   torch.stack([e[1] for e in est]).contiguous()))
+            self._dist = [self.p.estimate_clusters(self.X, members, pts) for pts in self.classes]
         if self.use_graph and self.collect is None:
             if self._graph is None or self._graph_sur is not surrogate:
                 # warm up once on a side stream, then capture

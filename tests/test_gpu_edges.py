@@ -517,3 +517,21 @@ def test_slot_table_orders(tiny_problem, F):
         part = one.eval_partial(_t(X), _t(o), _t(pts[sl]), _t(cand[:, sl]))
         for g, q in zip(got[:3], part[:3]):
             assert torch.equal(g[:, f], q[:, 0])
+
+
+@pytest.mark.parametrize("n_clusters,n_sel", [(1, 5), (3, 193), (16, 40)])
+def test_estimates_of_clusters(tiny_problem, n_clusters, n_sel):
+    w, gp = tiny_problem
+    rng = np.random.default_rng(n_sel)
+    X = _t(_random_population(w, 512, n_clusters))
+    members = _t(rng.integers(-1, 513, (n_clusters, n_sel)).astype(np.int32))
+    off, pts = _t(np.array([0, 4, 5, 7], np.int32)), _t(rng.integers(0, w.P, 7).astype(np.int32))
+    for o, single in ((off, lambda m: gp.estimate_elements(X, m, off, pts)),
+                      (None, lambda m: gp.estimate_distributions(X, m, pts))):
+        mean, chol = gp.estimate_clusters(X, members, pts, o)
+        for c in range(n_clusters):
+            m1, c1 = single(members[c])
+            assert torch.equal(mean[c], m1) and torch.equal(chol[c], c1)
+    for bad in (0, 17):
+        with pytest.raises(dsm.DsmError):
+            gp.estimate_clusters(X, members.new_zeros((bad, 4)), pts)
