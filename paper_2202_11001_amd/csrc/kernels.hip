@@ -161,21 +161,42 @@ __device__ __forceinline__ int row16_incl_scan(int v) {
 }
 
 // Parameters of one (tetrahedron, direction) for rasterising the own grid's
-// voxels and mapping them into the other grid.  Lives in LDS.
+// voxels and mapping them into the other grid.  Lives in LDS, where it decides
+// how many workgroups of the sweep a CU holds: 496 instead of 560 bytes here,
+// voxel markers of a byte and no partial sums beside the coordinates let 6
+// instead of 5 stay that sweep both versions of 8 tetrahedra (64^3, current
+// terms recomputed: 1375 -> 1280 us).
 constexpr int kMaxSlices = 64;  // slice-table capacity; taller tetrahedra enumerate bounding-box rows
 
 struct RasterTet {
   // o_i(x,y,z) - thr_i = A x + C0 + CY y + CZ z at voxel (x,y,z): F[i] = (C0, CY, CZ, -1 / A or 0)
-  double F[4][4], A[4];
+  double F[4][4];
   double M[3][4];  // own voxel coords -> other grid voxel coords: p' = M[.][3] + M[.][0..2] v
-  int thr[4];
-  int zlo, nz, ylo, ny;  // bounding box (slices, rows)
-  int nrows;             // candidate rows
-  int sliced;            // 1: candidate rows from the slice table, 0: every bounding-box row
-  int pairs;             // slice table: 0 one row group per slice, 1 one per pair of slices
+  int nrows;                       // candidate rows
+  unsigned short zlo, nz, ylo, ny; // bounding box (slices, rows)
+  unsigned char sliced;  // 1: candidate rows from the slice table, 0: every bounding-box row
+  unsigned char pairs;   // slice table: 0 one row group per slice, 1 one per pair of slices
   unsigned short y0[kMaxSlices];      // first candidate row (its y) of each row group
   unsigned short rs[kMaxSlices + 1];  // exclusive prefix of candidate rows per row group (<= 64 * 512)
 };
+static_assert(sizeof(RasterTet) == 496, "LDS budget of the sweep");
+
+// The x coefficient of a face, 128 times an integer below 2^34: exact from the
+// rounding of its reciprocal.  And thr_i (setup_face).
+__device__ __forceinline__ double face_A(const double F[4]) {
+  return F[3] != 0.0 ? kLat * rint(-1.0 / (F[3] * kLat)) : 0.0;
+}
+__device__ __forceinline__ double face_thr(const double F[4]) {
+  const bool pos = F[3] != 0.0 ? F[3] < 0.0 : (F[1] != 0.0 ? F[1] > 0.0 : F[2] > 0.0);
+  return pos ? 0.0 : 1.0;
+}
+
+// The row of the lane's voxel, with m the lanes of a chunk where a row starts
+// (mk: 1 on those) and `before` rows that start ahead of the chunk.
+__device__ __forceinline__ int row_at(unsigned long long m, int mk, int before) {
+  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((unsigned)m, (unsigned)(before - 1))) + mk;
+}
 
 // Conservative row range [ya, yb] of the cross-section of the tetrahedron
 // (own-grid lattice vertices L, integers below 2^17 and hence exact in FP32)
@@ -242,13 +263,11 @@ __device__ __forceinline__ double setup_face(const float* xo, int i, RasterTet& 
   if (s < 0.0)
     for (int c = 0; c < 3; ++c) g[c] = -g[c];
   const double K = -dot3(g, Lj);
-  rt.A[i] = kLat * g[0];
   rt.F[i][1] = kLat * g[1];
   rt.F[i][2] = kLat * g[2];
   const bool pos = g[0] != 0.0 ? g[0] > 0.0 : (g[1] != 0.0 ? g[1] > 0.0 : g[2] > 0.0);
   rt.F[i][0] = 64.0 * (g[0] + g[1] + g[2]) + K - (pos ? 0.0 : 1.0);
   rt.F[i][3] = g[0] != 0.0 ? -1.0 / (kLat * g[0]) : 0.0;
-  rt.thr[i] = pos ? 0 : 1;
   return s;
 }
 
@@ -281,10 +300,10 @@ __device__ __forceinline__ void setup_box(const float* xo, const int D[3], Raste
     lo[c] = max(0, (int)ceilf(a));
     hi[c] = min(D[c] - 1, (int)floorf(b));
   }
-  rt.zlo = lo[2];
-  rt.nz = max(0, hi[2] - lo[2] + 1);
-  rt.ylo = lo[1];
-  rt.ny = max(0, hi[1] - lo[1] + 1);
+  rt.zlo = (unsigned short)lo[2];
+  rt.nz = (unsigned short)max(0, hi[2] - lo[2] + 1);
+  rt.ylo = (unsigned short)lo[1];
+  rt.ny = (unsigned short)max(0, hi[1] - lo[1] + 1);
 }
 
 // Candidate rows of the row group that starts at slice k: slice k alone
@@ -415,7 +434,7 @@ __device__ __forceinline__ void row_span_exact(const RasterTet& rt, double y, do
   int lo = 0, hi = Dx - 1;
 #pragma unroll 1
   for (int i = 0; i < 4; ++i) {
-    const double A = rt.A[i];
+    const double A = face_A(rt.F[i]);
     const double h = rt.F[i][0] + rt.F[i][1] * y + rt.F[i][2] * z;  // need A x + h >= 0
     const double q = fmin(fmax(h * rt.F[i][3], -2.0), (double)Dx + 1.0);
     if (A > 0.0) {
@@ -489,7 +508,8 @@ struct RowRec {
 
 struct WaveRows {
   RowRec row[64];
-  int marker[128];  // per voxel slot of the current 128-voxel chunk pair: 1 where a row starts
+  // per voxel slot of the current 128-voxel chunk pair: 1 where a row starts (in build_rows the row's group)
+  unsigned char marker[128];
 };
 
 // A unit's rows find their row groups by a walk over the groups that start
@@ -555,9 +575,9 @@ __device__ __forceinline__ int build_rows(const RasterTet& rt, int b, int lane, 
       wr.marker[lane] = 0;
       wave_sync();
       const int at = rsk - r0;
-      if (lane < ng && at > 0 && at < 64 && rt.rs[lane + 1] > rsk) wr.marker[at] = lane;
+      if (lane < ng && at > 0 && at < 64 && rt.rs[lane + 1] > rsk) wr.marker[at] = (unsigned char)lane;
       wave_sync();
-      const int k = wave_incl_max(lane == 0 ? jb : wr.marker[lane]);
+      const int k = wave_incl_max(lane == 0 ? jb : (int)wr.marker[lane]);
       place(k, (int)rt.rs[k], (int)rt.y0[k]);
     }
   } else {
@@ -768,23 +788,23 @@ __device__ __forceinline__ double guidance_point(const DevProblem& pr, int g, in
                                                  const RasterTet& rt) {
   const double* U = pr.gpt[g] + 3 * i;
   const double p[3] = {U[0] * (1.0 / kLat) - 0.5, U[1] * (1.0 / kLat) - 0.5, U[2] * (1.0 / kLat) - 0.5};
-  double o[4], vol = 0.0;  // exact: the o_i at any point sum to 6 x the volume
+  // two passes over the faces, one at a time: few points come here, and the
+  // registers of this function decide how many waves of the sweep a SIMD holds
+  double vol = 0.0;  // exact: the o_i at any point sum to 6 x the volume
   bool in = true;
+#pragma unroll 1
   for (int q = 0; q < 4; ++q) {
-    const double over = rt.F[q][0] + rt.A[q] * p[0] + rt.F[q][1] * p[1] + rt.F[q][2] * p[2];
+    const double over = rt.F[q][0] + face_A(rt.F[q]) * p[0] + rt.F[q][1] * p[1] + rt.F[q][2] * p[2];
     in = in && over >= 0.0;
-    o[q] = over + (double)rt.thr[q];
-    vol += o[q];
+    vol += over + face_thr(rt.F[q]);
   }
   if (!in) return 0.0;
   double x[3] = {0, 0, 0};
 #pragma unroll 1
   for (int q = 0; q < 4; ++q) {
-    const double lam = o[0] / vol;
+    const double over = rt.F[q][0] + face_A(rt.F[q]) * p[0] + rt.F[q][1] * p[1] + rt.F[q][2] * p[2];
+    const double lam = (over + face_thr(rt.F[q])) / vol;
     for (int c = 0; c < 3; ++c) x[c] += lam * (double)Vt[3 * q + c];
-    o[0] = o[1];
-    o[1] = o[2];
-    o[2] = o[3];
   }
   double best = INFINITY;
   const int corr = pr.gcorr[g][i];
@@ -808,16 +828,16 @@ struct EvalLayout {
 __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~size_t(15); }
 
 __host__ __device__ inline EvalLayout eval_layout(int maxA, int nver) {
+  static_assert(sizeof(double) * kWaves * 2 <= sizeof(float) * 24, "part lies over xyz");
   EvalLayout L;
   size_t o = 0;
   L.tet = o;
   o = align16(o + sizeof(int) * maxA);
-  L.xyz = o;  // [nver][maxA][2][4][3] float
+  L.xyz = o;  // [nver][maxA][2][4][3] float; in the sweep [nver*2*maxA][kWaves] double (part)
+  L.part = o;
   o = align16(o + sizeof(float) * 24 * (size_t)nver * maxA);
   L.units = o;  // [nver*2*maxA + 1] int (unit counts, then exclusive prefix)
   o = align16(o + sizeof(int) * (2 * (size_t)nver * maxA + 1));
-  L.part = o;  // [nver*2*maxA][kWaves] double
-  o = align16(o + sizeof(double) * kWaves * 2 * (size_t)nver * maxA);
   L.waves = o;  // [kWaves] WaveRows
   o = align16(o + sizeof(WaveRows) * kWaves);
   L.rts = o;  // [nver*2*maxA] RasterTet, one per (version, direction, tetrahedron)
@@ -1051,8 +1071,8 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
     wave_sync();
     if (e < nent && sub == 0) s_units[e] = nunits;
   }
-  for (int e = tid; e < nent * kWaves; e += kWG) s_part[e] = 0.0;
   __syncthreads();
+  for (int e = tid; e < nent * kWaves; e += kWG) s_part[e] = 0.0;
   lds_exclusive_scan(s_units, nent, tid);
   if (wave == kWaves - 1 && lane < nvt) {
     double guid = 0.0;
@@ -1107,20 +1127,16 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
     for (int q0 = 0; q0 < nvox; q0 += 128) {
       // voxels q0 + lane and q0 + 64 + lane: rows starting in this pair of
       // chunks are marked, then counted below each slot with a ballot
-      wr.marker[lane] = 0;
-      wr.marker[64 + lane] = 0;
+      ((unsigned short*)wr.marker)[lane] = 0;
       wave_sync();
       const unsigned pos = (unsigned)(my_start - q0);
       if (pos < 128u) wr.marker[pos] = 1;
       wave_sync();
       const int mk0 = wr.marker[lane], mk1 = wr.marker[64 + lane];
       const unsigned long long M0 = __ballot(mk0 != 0), M1 = __ballot(mk1 != 0);
-      const int r0 = carry + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(M0 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)M0, 0u)) +
-                     mk0 - 1;
-      carry += __popcll(M0);
-      const int r1 = carry + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(M1 >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)M1, 0u)) +
-                     mk1 - 1;
-      carry += __popcll(M1);
+      const int before = carry + __popcll(M0);
+      const int r0 = row_at(M0, mk0, carry), r1 = row_at(M1, mk1, before);
+      carry = before + __popcll(M1);
       if (q0 + 128 <= nvox)
         sweep_pair<false>(wr, sc, q0, nvox, lane, r0, r1, jx, jy, jz, sum, comp);
       else if (q0 + 64 >= nvox)
@@ -1168,8 +1184,15 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   }
 }
 
-template <int PARTIAL, int ROWS>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_sweep(EvalArgs a) {
+// EU: the waves per SIMD that the instructions are ordered for.  Both orders
+// take 60 registers, which leaves room for 8; but where LDS holds fewer
+// workgroups (two versions) or the launch has fewer, the order for 8, which
+// brings a wave's loads and their uses closer together, is the slower one: 64^3
+// recomputed 1305 against 1280 us, 32^3 with 16 solutions 64.8 against 62.3, but
+// a class of the phantom 3,150 against 3,225 us and 512x512x100 164.6 against
+// 165.4 ms (7 waves, from 70 registers: 62.5, 3,420 and 168.5).
+template <int PARTIAL, int ROWS, int EU>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(EU, 8))) void k_sweep(EvalArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int n = PARTIAL && a.slots ? a.S * a.slots[0].x : a.S * a.G * (PARTIAL ? a.nchunk : 1);
   const int logical = xcd_logical(blockIdx.x & 7, blockIdx.x >> 3, n);
@@ -1184,11 +1207,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(6, 8))) voi
 // (jobs of very different tetrahedron sizes would otherwise load the XCDs
 // unevenly), and within a part the workgroups of one element's solutions stay
 // together.
-// Arguments read through the job table take more registers than kernel
-// arguments; the 7-wave target (at most 72 VGPRs) ran small problems 5 %
-// faster than 6 waves.  ROWS as for sweep_body.
+// Ordered for 8 waves per SIMD (7: 5,760 us for four uneven problems at half
+// resolution, 8: 5,650).  ROWS as for sweep_body.
 template <int ROWS>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(7, 8))) void k_sweep_batch(
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sweep_batch(
     const EvalArgs* __restrict__ jobs, const int* __restrict__ xcd_off, int n_jobs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
@@ -1507,8 +1529,7 @@ __global__ __launch_bounds__(kWG) void k_owner(DevProblem pr, const float* __res
       wave_sync();
       const int mk = wr.marker[lane];
       const unsigned long long M = __ballot(mk != 0);
-      const int r = carry + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(M >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)M, 0u)) +
-                    mk - 1;
+      const int r = row_at(M, mk, carry);
       carry += __popcll(M);
       const int q = q0 + lane;
       if (q < nvox) {
@@ -1633,8 +1654,8 @@ __global__ __launch_bounds__(kWG) void k_transform(DevProblem pr, int own, const
   const double rvol = 1.0 / vol;
   for (int a = 0; a < 3; ++a) X3[a] = lane_value((double)xs[1][9 + a], 0);
   for (int f = 0; f < 3; ++f) {
-    C[f][0] = lane_value(rt.F[f][0] + rt.thr[f], 0);
-    C[f][1] = lane_value(rt.A[f], 0);
+    C[f][0] = lane_value(rt.F[f][0] + face_thr(rt.F[f]), 0);
+    C[f][1] = lane_value(face_A(rt.F[f]), 0);
     C[f][2] = lane_value(rt.F[f][1], 0);
     C[f][3] = lane_value(rt.F[f][2], 0);
     for (int a = 0; a < 3; ++a) {
@@ -1678,8 +1699,7 @@ __global__ __launch_bounds__(kWG) void k_transform(DevProblem pr, int own, const
       wave_sync();
       const int mk = wr.marker[lane];
       const unsigned long long m = __ballot(mk != 0);
-      const int r = carry + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u)) +
-                    mk - 1;
+      const int r = row_at(m, mk, carry);
       carry += __popcll(m);
       const int q = q0 + lane;
       if (q >= nvox) break;
@@ -1852,6 +1872,11 @@ hipError_t launch_affected(const DevProblem& pr, int F, const int* fos_off, cons
   return hipGetLastError();
 }
 
+// Workgroups from which a sweep keeps every SIMD at 8 waves.  2,048 do, but the
+// launch has room for the largest element everywhere and two to four times the
+// workgroups that exist.
+constexpr unsigned kSweepMany = 4 * 8 * 256;
+
 hipError_t launch_eval(const EvalArgs& a, hipEvent_t ev_begin, hipEvent_t ev_end, hipStream_t stream) {
   const int64_t nwg = (int64_t)a.S * a.G;
   if (nwg <= 0) return hipSuccess;
@@ -1859,14 +1884,16 @@ hipError_t launch_eval(const EvalArgs& a, hipEvent_t ev_begin, hipEvent_t ev_end
   const unsigned grid = (unsigned)((nwg * (a.partial ? a.nchunk : 1) + 7) / 8 * 8);
   const size_t lds = eval_lds_bytes(kMaxChunk, a.nver);
   if (ev_begin) (void)hipEventRecord(ev_begin, stream);
+  const bool many = a.nver == 1 && grid > kSweepMany;
+  auto launch = [&](auto* dense, auto* sparse) { (many ? dense : sparse)<<<grid, kWG, lds, stream>>>(a); };
   if (a.partial && a.row_pairs)
-    k_sweep<1, 1><<<grid, kWG, lds, stream>>>(a);
+    launch(k_sweep<1, 1, 8>, k_sweep<1, 1, 6>);
   else if (a.partial)
-    k_sweep<1, 0><<<grid, kWG, lds, stream>>>(a);
+    launch(k_sweep<1, 0, 8>, k_sweep<1, 0, 6>);
   else if (a.row_pairs)
-    k_sweep<0, 1><<<grid, kWG, lds, stream>>>(a);
+    launch(k_sweep<0, 1, 8>, k_sweep<0, 1, 6>);
   else
-    k_sweep<0, 0><<<grid, kWG, lds, stream>>>(a);
+    launch(k_sweep<0, 0, 8>, k_sweep<0, 0, 6>);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ev_end) (void)hipEventRecord(ev_end, stream);

@@ -7,7 +7,7 @@ from oracle import gomea_ref as G
 from oracle import ref
 from oracle import surrogate_ref as R
 from paper_2202_11001_amd import workloads as W
-from tests._common import assert_delta_close, assert_objectives_close, oracle_problem
+from tests._common import assert_delta_close, assert_objectives_close, feasible_population, oracle_problem
 
 pytestmark = pytest.mark.gpu
 
@@ -535,3 +535,37 @@ def test_estimates_of_clusters(tiny_problem, n_clusters, n_sel):
     for bad in (0, 17):
         with pytest.raises(dsm.DsmError):
             gp.estimate_clusters(X, members.new_zeros((bad, 4)), pts)
+
+
+# launches on both sides of the 2048 workgroups from which the sweep's other instruction order is used, in both row
+# orders, with the current terms cached or recomputed: a solution's results do not depend on the others
+@pytest.mark.parametrize("rows", [0, 1])
+@pytest.mark.parametrize("cached", [True, False])
+def test_sweep_orders_agree(rows, cached):
+    w = W.batched(shape=(24, 24, 24), mesh=(4, 4, 4))
+    rp = oracle_problem(w)
+    S = 30
+    X = feasible_population(w, rp, S=S)
+    pts = np.arange(w.P, dtype=np.int32)
+    off = np.arange(w.P + 1, dtype=np.int32)
+    cand = W.candidates(X, off, pts, w.mesh, w.dims, 1.0, 3)
+    gp = dsm.Problem.from_workload(w, max_solutions=S)
+    gp.set_row_order(rows)
+
+    def run(s):
+        terms = torch.empty((len(s), gp.T, 3), dtype=torch.float64, device=DEV)
+        obj, _ = gp.eval_full(_t(X[s]), tet_terms=terms)
+        old, new, fl, vc = gp.eval_partial(_t(X[s]), _t(off), _t(pts), _t(cand[s]), tet_terms_in=terms if cached else None,
+                                           voxel_count=True)
+        return obj, terms, old, new, fl, vc
+
+    many = run(np.arange(S))  # 30 x 64 elements of up to 6 chunks
+    for s in (0, 7, S - 1):
+        for m, o in zip(many, run(np.array([s]))):
+            assert torch.equal(m[s:s + 1], o)
+    rold, rnew, rfl, rnv = rp.eval_partial(X, off, pts, cand)
+    np.testing.assert_array_equal(many[4].cpu().numpy().astype(np.uint32), rfl)
+    ok = rfl == 0
+    np.testing.assert_array_equal(many[5].cpu().numpy()[ok], rnv[ok])
+    assert_objectives_close(many[3].cpu().numpy()[ok], rnew[ok])
+    assert_objectives_close(many[2].cpu().numpy(), rold)
