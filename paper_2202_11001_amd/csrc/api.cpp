@@ -384,8 +384,8 @@ dsm_status dsm_eval_full(dsm_problem* p, int32_t S, const float* X, double* obj,
   if (!X || !obj || !flags) return fail(DSM_ERR_ARG, "null argument");
   if (S > p->max_S) return fail(DSM_ERR_CAPACITY, "S = %d exceeds max_solutions = %d", S, p->max_S);
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = launch_fold(p->dev, S, X, flags, nullptr, st);
-  if (e != hipSuccess) return hip_fail(e, "fold check launch");
+  hipError_t e = launch_fill_u32(flags, S, 0u, st);  // the sweep sets the bits
+  if (e != hipSuccess) return hip_fail(e, "flag clear launch");
   EvalArgs a{};
   a.pr = p->dev;
   a.S = S;
@@ -394,6 +394,7 @@ dsm_status dsm_eval_full(dsm_problem* p, int32_t S, const float* X, double* obj,
   a.X = X;
   a.maxA = kFullChunk;
   a.nver = 1;
+  a.flags = flags;
   a.terms_out = tet_terms ? tet_terms : p->d_terms;
   a.row_pairs = p->row_order;
   hipEvent_t eb, ee;

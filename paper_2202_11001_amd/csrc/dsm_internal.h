@@ -97,7 +97,7 @@ struct EvalArgs {
   const double* terms_in;  // [S][T][3] cache of current terms or null
   double* part_old;      // [S][G][3]
   double* part_new;
-  uint32_t* flags;       // [S][G]
+  uint32_t* flags;       // [S][G]; full: [S], cleared
   double* terms_out;     // [S][T][3] or null
   uint32_t* vcount;      // [S][G] or null
   const uint8_t* mask;   // [S][G] or null: evaluate only where non-zero (partial)

@@ -569,3 +569,24 @@ def test_sweep_orders_agree(rows, cached):
     np.testing.assert_array_equal(many[5].cpu().numpy()[ok], rnv[ok])
     assert_objectives_close(many[3].cpu().numpy()[ok], rnew[ok])
     assert_objectives_close(many[2].cpu().numpy(), rold)
+
+
+# the sweep sets the constraint bits of a full evaluation: one bad coordinate or fold at a time, in either grid, in the
+# first, a middle and the last group of 8 tetrahedra, against the fold check
+@pytest.mark.parametrize("grid", [0, 1])
+def test_full_evaluation_flags(grid):
+    w = W.batched(shape=(24, 24, 24), mesh=(4, 4, 4))
+    rp = oracle_problem(w)
+    gp = dsm.Problem.from_workload(w, max_solutions=40)
+    X = np.repeat(np.stack([W.regular_grid(w.dims, w.mesh)] * 2)[None], 40, axis=0)
+    P = w.P
+    for i, p in enumerate((0, 21, 42, P - 1)):
+        for j, (c, by) in enumerate(((0, 1 / 512), (1, np.nan), (2, 1.0), (0, 100.0), (1, -1.0), (2, np.inf), (0, 9.0), (1, -9.0))):
+            X[8 * i + j, grid, p, c] += by
+    X[36, grid, [21, 22]] = X[36, grid, [22, 21]]
+    X[37, :, 42] -= 8.0
+    rfl = rp.fold_check(X)[0]
+    fl = gp.eval_full(_t(X))[1].cpu().numpy().astype(np.uint32)
+    np.testing.assert_array_equal(fl, rfl)
+    np.testing.assert_array_equal(gp.fold_check(_t(X)).cpu().numpy().astype(np.uint32), rfl)
+    assert (rfl != 0).sum() > 25 and not rfl[38:].any()
