@@ -265,10 +265,15 @@ __global__ __launch_bounds__(256) void k_sample_dist(DevProblem pr, int S, const
   const double* L = chol + d * NE + v * (v + 1) / 2;
   double z = 0.0, w = 0.0;
   if (v < nv) z = normal(seed, counter * 0x100000000ull + (unsigned long long)(row * NV + v));
-#pragma unroll 6
-  for (int k = 0; k < nv; ++k) {
-    const double zk = __shfl(z, k, LG);
-    if (k <= v && v < nv) w += L[k] * zk;
+  for (int k0 = 0; k0 < nv; k0 += 6) {  // the factor's entries 6 at a time: one wait for memory each
+    double l[6];
+#pragma unroll
+    for (int u = 0; u < 6; ++u) l[u] = v < nv && k0 + u <= v ? L[k0 + u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 6; ++u) {
+      const double zk = __shfl(z, k0 + u, LG);
+      if (k0 + u <= v && v < nv) w += l[u] * zk;
+    }
   }
   if (v >= nv) return;
   const int p = pts[b + v / 6], c = v % 6, gr = c / 3, a = c % 3;

@@ -707,7 +707,8 @@ __global__ void k_targets(int N, const double* __restrict__ old, const double* _
 // often and repeat the choice among the K.  The whole screening call, in us,
 // with 64 / 16 / 4 lanes: 1,600 pairs and 600 rows 30 / - / 80, 32,400 pairs
 // and 2,000 rows 118 / 85 / 117, 307,200 pairs and 1,200 rows 1006 / 684 / 583
-// (678 with two pairs a lane).
+// (678 with two pairs a lane).  Rows taken 4 at a time, one vote for the 4,
+// took the last from 643 to 615 us on new inputs.
 constexpr int kSelTile = 512;
 
 template <int G>
@@ -782,11 +783,17 @@ __global__ __launch_bounds__(256) void k_select(int S, int F, int K, const float
     for (int q0 = sub; q0 < end; q0 += 32 * G) {
       if (!__any(left && !dom)) break;
       const int q1 = min(q0 + 32 * G, end);
-#pragma unroll 4
-      for (int q = q0; q < q1; q += G) {
-        const double x = s_a[q][0], y = s_a[q][1], z = s_a[q][2];
-        const bool le = (x <= nv[0]) & (y <= nv[1]) & (z <= nv[2]);
-        if (__any(le)) dom |= le & ((x < nv[0]) | (y < nv[1]) | (z < nv[2]));
+      for (int q = q0; q < q1; q += 4 * G) {  // 4 rows at a time; past the end the first of them again
+        double a[4][3];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          for (int o = 0; o < kOut; ++o) a[u][o] = s_a[q + u * G < end ? q + u * G : q][o];
+        bool le[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) le[u] = (a[u][0] <= nv[0]) & (a[u][1] <= nv[1]) & (a[u][2] <= nv[2]);
+        if (__any(le[0] | le[1] | le[2] | le[3]))
+#pragma unroll
+          for (int u = 0; u < 4; ++u) dom |= le[u] & ((a[u][0] < nv[0]) | (a[u][1] < nv[1]) | (a[u][2] < nv[2]));
       }
     }
     dom = (__ballot(dom) >> (threadIdx.x & 63 & ~(G - 1)) & (~0ull >> (64 - G))) != 0;  // of any lane of the pair
