@@ -169,14 +169,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // Workgroups of a persistent launch over N rows (a multiple of 8): three to a CU.
 unsigned mlp_grid(int64_t N) { return (unsigned)std::min<int64_t>((N + 8 * kTileRows - 1) / (8 * kTileRows) * 8, 3 * 256); }
 
-// One training step is three kernels: forward and backward of the minibatch
-// rows (k_mlp_rows), the weight and bias gradients (k_mlp_wgrad) and the update
-// (k_mlp_update).  At 4096 rows each is a few microseconds of a chain of
+// One training step is two kernels: forward and backward of the minibatch rows
+// (k_mlp_rows), then the weight and bias gradients with the update
+// (k_mlp_wgrad).  At 4096 rows each is a few microseconds of a chain of
 // dependent loads on a mostly idle chip, so the step is bound by the number of
 // kernels and by how short each chain is: a step took 150 us as nine kernels
 // (three weight-gradient products of 31 us each, one wave per 16x16 tile
 // waiting for each step's operands; rows 28; bias sums 16; Adam, operand
-// refresh and row draws 5 each).  The sums over the batch keep their order
+// refresh and row draws 5 each), 33.1 us as three (the update apart), 31.7 now.
+// The sums over the batch keep their order
 // (one accumulator per gradient entry over the whole batch): Adam's first
 // steps turn a changed rounding of a small gradient into a change of the
 // weights, so slices of the batch summed apart (the faster form by itself)
@@ -321,25 +322,70 @@ __global__ __launch_bounds__(256) void k_mlp_rows(MlpW w, const unsigned short* 
   store_transposed(dz1, kHs, kHid, ws.dz1t, ws.ld, b0, tid);
 }
 
+struct Operands {
+  unsigned short *w1, *w2, *w3, *w2t, *w3t;
+};
+
+__device__ __forceinline__ void refresh_operand(int t, float x, const Operands& o) {
+  const unsigned short b = f2bf(x);
+  if (t < kB1) {
+    o.w1[t] = b;
+  } else if (t >= kW2 && t < kB2) {
+    const int e = t - kW2;
+    o.w2[e] = b;
+    o.w2t[(e % kHid) * kHid + e / kHid] = b;
+  } else if (t >= kW3 && t < kB3) {
+    const int e = t - kW3;
+    o.w3[e] = b;
+    o.w3t[(e % kHid) * kOutPad + e / kHid] = b;
+  }
+}
+
+// Adam step on the FP32 master parameters, with the BF16 operand copies.
+struct Adam {
+  float *p, *m, *v;
+  float lr, b1, b2, eps, c1, c2;
+  Operands ops;
+};
+struct AdamState {  // of one parameter
+  float p, m, v;
+};
+__device__ __forceinline__ AdamState load_state(const Adam& ad, int t) { return {ad.p[t], ad.m[t], ad.v[t]}; }
+__device__ __forceinline__ void adam_step(const Adam& ad, int t, const AdamState& s, float gi) {
+  const float mi = ad.b1 * s.m + (1.f - ad.b1) * gi;
+  const float vi = ad.b2 * s.v + (1.f - ad.b2) * gi * gi;
+  ad.m[t] = mi;
+  ad.v[t] = vi;
+  const float x = s.p - ad.lr * (mi / ad.c1) / (sqrtf(vi / ad.c2) + ad.eps);
+  ad.p[t] = x;
+  refresh_operand(t, x, ad.ops);
+}
+
 // Weight gradients dW[o][c] = sum_b dZt[o][b] At[c][b], one wave per 16x16
 // tile of a layer's matrix, and, in further waves, the bias gradients and the
 // minibatch loss (lanes over the batch in a fixed order, then a fixed shuffle
 // tree).  A tile is one chain of matrix instructions over the batch; the wave
 // keeps the operands of kAhead steps of 32 rows in flight in registers, since
 // a step's operands take about 40 times as long to arrive from L2 as its
-// instruction takes to issue.
+// instruction takes to issue.  With TRAIN the wave that holds an entry's
+// gradient updates its parameter too, whose state it has read meanwhile
+// (nothing here reads the weights); without, the gradients go to grad.
 constexpr int kTiles1 = (kHid / 16) * (kIn / 16), kTiles2 = (kHid / 16) * (kHid / 16), kTiles3 = kHid / 16;
 constexpr int kTiles = kTiles1 + kTiles2 + kTiles3, kBiases = 2 * kHid + kOutPad;
 constexpr int kAhead = 16;
 
+template <bool TRAIN>
 __global__ __launch_bounds__(64) void k_mlp_wgrad(TrainWs ws, int B, float* __restrict__ grad,
-                                                  float* __restrict__ loss_out) {
+                                                  float* __restrict__ loss_out, Adam ad) {
   const int lane = threadIdx.x, i = lane & 15, kb = lane >> 4, ld = ws.ld;
   int tile = blockIdx.x;
   if (tile >= kTiles) {
     const int t = tile - kTiles;
+    const int at = t < kHid ? kB1 + t : (t < 2 * kHid ? kB2 + (t - kHid) : kB3 + (t - 2 * kHid));
+    AdamState state{};
     float acc = 0.f;
     if (t < kBiases) {
+      if (TRAIN) state = load_state(ad, at);
       const unsigned short* src = t < kHid ? ws.dz1t + (size_t)t * ld
                                            : (t < 2 * kHid ? ws.dz2t + (size_t)(t - kHid) * ld
                                                            : ws.dyt + (size_t)(t - 2 * kHid) * ld);
@@ -352,8 +398,10 @@ __global__ __launch_bounds__(64) void k_mlp_wgrad(TrainWs ws, int B, float* __re
     }
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if (lane != 0) return;
-    if (t < kBiases)
-      grad[t < kHid ? kB1 + t : (t < 2 * kHid ? kB2 + (t - kHid) : kB3 + (t - 2 * kHid))] = acc;
+    if (t < kBiases && TRAIN)
+      adam_step(ad, at, state, acc);
+    else if (t < kBiases)
+      grad[at] = acc;
     else
       *loss_out = acc / (3.f * (float)B);
     return;
@@ -373,6 +421,10 @@ __global__ __launch_bounds__(64) void k_mlp_wgrad(TrainWs ws, int B, float* __re
   const unsigned short* pa = dzt + (size_t)(16 * ot + i) * ld + 8 * kb;
   const unsigned short* pb = at + (size_t)(16 * ct + i) * ld + 8 * kb;
   const int nk = ld / 32, last = 32 * (nk - 1);
+  const int out = ow + (16 * ot + 4 * kb) * ncols + 16 * ct + i;  // the lane's entries: out, out + ncols, ...
+  AdamState state[4];
+  if (TRAIN)
+    for (int r = 0; r < 4; ++r) state[r] = load_state(ad, out + r * ncols);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   u16x8 a[kAhead], b[kAhead];
 #pragma unroll
@@ -393,42 +445,12 @@ __global__ __launch_bounds__(64) void k_mlp_wgrad(TrainWs ws, int B, float* __re
 #pragma unroll
   for (int j = 0; j < kAhead; ++j)
     if (k + j < nk) acc = mfma(a[j], b[j], acc);
-  for (int r = 0; r < 4; ++r) grad[ow + (size_t)(16 * ot + 4 * kb + r) * ncols + 16 * ct + i] = acc[r];
-}
-
-// Adam step on the FP32 master parameters, with the BF16 operand copies.
-struct Operands {
-  unsigned short *w1, *w2, *w3, *w2t, *w3t;
-};
-
-__device__ __forceinline__ void refresh_operand(int t, float x, const Operands& o) {
-  const unsigned short b = f2bf(x);
-  if (t < kB1) {
-    o.w1[t] = b;
-  } else if (t >= kW2 && t < kB2) {
-    const int e = t - kW2;
-    o.w2[e] = b;
-    o.w2t[(e % kHid) * kHid + e / kHid] = b;
-  } else if (t >= kW3 && t < kB3) {
-    const int e = t - kW3;
-    o.w3[e] = b;
-    o.w3t[(e % kHid) * kOutPad + e / kHid] = b;
+  for (int r = 0; r < 4; ++r) {
+    if (TRAIN)
+      adam_step(ad, out + r * ncols, state[r], acc[r]);
+    else
+      grad[out + r * ncols] = acc[r];
   }
-}
-
-__global__ __launch_bounds__(256) void k_mlp_update(const float* __restrict__ grad, float* __restrict__ p,
-                                                    float* __restrict__ m, float* __restrict__ v, float lr, float b1,
-                                                    float b2, float eps, float c1, float c2, Operands ops) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= kNParams) return;
-  const float gi = grad[t];
-  const float mi = b1 * m[t] + (1.f - b1) * gi;
-  const float vi = b2 * v[t] + (1.f - b2) * gi * gi;
-  m[t] = mi;
-  v[t] = vi;
-  const float x = p[t] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  p[t] = x;
-  refresh_operand(t, x, ops);
 }
 
 __global__ void k_refresh_bf16(const float* __restrict__ p, Operands ops) {
@@ -813,7 +835,7 @@ struct dsm_surrogate {
   dsm_surrogate_desc desc{};
   int device = 0;
   int64_t step = 0;  // Adam steps taken
-  float *d_params = nullptr, *d_m = nullptr, *d_v = nullptr, *d_grad = nullptr;
+  float *d_params = nullptr, *d_m = nullptr, *d_v = nullptr;
   unsigned short *d_w1 = nullptr, *d_w2 = nullptr, *d_w3 = nullptr, *d_w2t = nullptr, *d_w3t = nullptr;
   float *d_in_mean = nullptr, *d_in_rstd = nullptr, *d_out_mean = nullptr, *d_out_rstd = nullptr, *d_out_scale = nullptr;
   // training workspace for max_batch rows (padded to a multiple of 32)
@@ -848,10 +870,10 @@ MlpW weights(const dsm_surrogate* m) {
 
 void free_sur(dsm_surrogate* m) {
   if (!m) return;
-  void* bufs[] = {m->d_params, m->d_m,      m->d_v,        m->d_grad,     m->d_w1,      m->d_w2,   m->d_w3,
-                  m->d_w2t,    m->d_w3t,    m->d_in_mean,  m->d_in_rstd,  m->d_out_mean, m->d_out_rstd,
-                  m->d_out_scale, m->d_xt,  m->d_h1t,      m->d_h2t,      m->d_dyt,     m->d_dz2t, m->d_dz1t,
-                  m->d_row_loss, m->d_pred};
+  void* bufs[] = {m->d_params,   m->d_m,       m->d_v,        m->d_w1,        m->d_w2,  m->d_w3,  m->d_w2t,
+                  m->d_w3t,      m->d_in_mean, m->d_in_rstd,  m->d_out_mean,  m->d_out_rstd, m->d_out_scale,
+                  m->d_xt,       m->d_h1t,     m->d_h2t,      m->d_dyt,       m->d_dz2t, m->d_dz1t, m->d_row_loss,
+                  m->d_pred};
   for (void* b : bufs)
     if (b) (void)hipFree(b);
   delete m;
@@ -882,13 +904,16 @@ hipError_t refresh(dsm_surrogate* m, hipStream_t st) {
 // Forward and backward of B rows (those of minibatch `step` of the N rows, or
 // rows 0..B-1 for step < 0); writes the gradient to grad and the loss to loss (or null).
 hipError_t gradient_pass(dsm_surrogate* m, const unsigned short* feats, const float* targets, int step, int N, int B,
-                         float* loss, float* grad, hipStream_t st) {
+                         float* loss, float* grad, const Adam* ad, hipStream_t st) {
   const int ld = (B + 31) / 32 * 32;
   TrainWs ws{m->d_xt, m->d_h1t, m->d_h2t, m->d_dyt, m->d_dz2t, m->d_dz1t, m->d_row_loss, ld};
   k_mlp_rows<<<ld / 16, 256, 0, st>>>(weights(m), feats, targets, m->desc.seed, step, N, B, ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  k_mlp_wgrad<<<kTiles + kBiases + 1, 64, 0, st>>>(ws, B, grad, loss);
+  if (ad)
+    k_mlp_wgrad<true><<<kTiles + kBiases + 1, 64, 0, st>>>(ws, B, nullptr, loss, *ad);
+  else
+    k_mlp_wgrad<false><<<kTiles + kBiases + 1, 64, 0, st>>>(ws, B, grad, loss, Adam{});
   return hipGetLastError();
 }
 
@@ -919,7 +944,6 @@ dsm_status dsm_surrogate_create(const dsm_surrogate_desc* d, dsm_surrogate** out
   S_TRY(hipMalloc(&m->d_params, sizeof(float) * kNParams));
   S_TRY(hipMalloc(&m->d_m, sizeof(float) * kNParams));
   S_TRY(hipMalloc(&m->d_v, sizeof(float) * kNParams));
-  S_TRY(hipMalloc(&m->d_grad, sizeof(float) * kNParams));
   S_TRY(hipMalloc(&m->d_w1, 2 * kHid * kIn));
   S_TRY(hipMalloc(&m->d_w2, 2 * kHid * kHid));
   S_TRY(hipMalloc(&m->d_w3, 2 * kOutPad * kHid));
@@ -1094,7 +1118,7 @@ dsm_status dsm_surrogate_gradient(dsm_surrogate* m, int32_t N, const uint16_t* f
   if (!m || !feats_bf16 || !targets || !grad) return sfail(DSM_ERR_ARG, "null argument");
   if (N < 1 || N > m->bpad) return sfail(DSM_ERR_CAPACITY, "N outside [1, max_batch]");
   hipStream_t st = (hipStream_t)stream;
-  const hipError_t e = gradient_pass(m, (const unsigned short*)feats_bf16, targets, -1, N, N, loss, grad, st);
+  const hipError_t e = gradient_pass(m, (const unsigned short*)feats_bf16, targets, -1, N, N, loss, grad, nullptr, st);
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }
 
@@ -1107,14 +1131,12 @@ dsm_status dsm_surrogate_train(dsm_surrogate* m, int32_t N, const uint16_t* feat
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = hipSuccess;
   for (int k = 0; k < steps && e == hipSuccess; ++k) {
+    const double n = (double)(m->step + 1);
+    const Adam ad{m->d_params, m->d_m, m->d_v, m->desc.lr, m->desc.beta1, m->desc.beta2, m->desc.eps,
+                  1.f - powf(m->desc.beta1, (float)n), 1.f - powf(m->desc.beta2, (float)n), operands(m)};
     e = gradient_pass(m, (const unsigned short*)feats_bf16, targets, (int)m->step, N, batch, loss ? loss + k : nullptr,
-                      m->d_grad, st);
-    if (e != hipSuccess) break;
-    m->step++;
-    const float c1 = 1.f - powf(m->desc.beta1, (float)m->step), c2 = 1.f - powf(m->desc.beta2, (float)m->step);
-    k_mlp_update<<<(kNParams + 255) / 256, 256, 0, st>>>(m->d_grad, m->d_params, m->d_m, m->d_v, m->desc.lr,
-                                                         m->desc.beta1, m->desc.beta2, m->desc.eps, c1, c2, operands(m));
-    e = hipGetLastError();
+                      nullptr, &ad, st);
+    if (e == hipSuccess) m->step++;
   }
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }
