@@ -103,8 +103,9 @@ __device__ __forceinline__ double readlane64(double v, int l) {
 // entry is one pass over them in selection order, and the factorisation keeps
 // row r in the registers of lane r and subtracts column k's products as soon
 // as the column is known (the order of the products of an entry is that of
-// the row-by-row form).  On 64 elements of 4 points over 200 solutions: 208 us
-// a call with the factorisation on one thread and two staging passes.
+// the row-by-row form).  On 64 elements of 4 points over 70 solutions: 208 us
+// a call with the factorisation on one thread and two staging passes, 18.2 with
+// the library's root and division in it, 16.6 now.
 template <int NP>
 __global__ __launch_bounds__(NP == 1 ? 64 : 320) void k_estimate(DevProblem pr, int S, const float* __restrict__ X,
                                                                  int n_sel, const int* __restrict__ sel, int F,
@@ -200,8 +201,19 @@ __global__ __launch_bounds__(NP == 1 ? 64 : 320) void k_estimate(DevProblem pr, 
     for (int k = 0; k < NV; ++k)
       if (k < nv) {
         const double pivot = readlane64(v[k], k);
-        const double d = pivot > 0.0 ? sqrt(pivot) : 0.0;
-        const double l = row == k ? d : (d > 0.0 ? v[k] / d : 0.0);
+        double l = 0.0;
+        if (pivot > 0.0) {
+          // y = 1 / sqrt(pivot) by two Newton steps, then the root and the
+          // quotient each corrected by their residual (within an ulp): 11
+          // dependent steps, a square root and a division took 30
+          double y = __builtin_amdgcn_rsq(pivot);
+          y = fma(0.5 * y, fma(-(pivot * y), y, 1.0), y);
+          y = fma(0.5 * y, fma(-(pivot * y), y, 1.0), y);
+          double d = pivot * y;
+          d = fma(fma(-d, d, pivot), 0.5 * y, d);
+          l = v[k] * y;
+          l = row == k ? d : fma(fma(-l, d, v[k]), y, l);
+        }
         v[k] = l;
 #pragma unroll
         for (int j = k + 1; j < NV; ++j) v[j] -= l * readlane64(l, j);
