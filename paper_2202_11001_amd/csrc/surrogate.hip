@@ -351,9 +351,13 @@ struct AdamState {  // of one parameter
   float p, m, v;
 };
 __device__ __forceinline__ AdamState load_state(const Adam& ad, int t) { return {ad.p[t], ad.m[t], ad.v[t]}; }
+// The roundings of the averages are part of the definition: left to the
+// compiler, a sum of two products is contracted on either side, depending on
+// the code around it, and an ulp of one bias's average moved trained weights by
+// 5e-5 (relative norm) within 8 steps of 4,096 rows.
 __device__ __forceinline__ void adam_step(const Adam& ad, int t, const AdamState& s, float gi) {
-  const float mi = ad.b1 * s.m + (1.f - ad.b1) * gi;
-  const float vi = ad.b2 * s.v + (1.f - ad.b2) * gi * gi;
+  const float mi = __fmaf_rn(1.f - ad.b1, gi, __fmul_rn(ad.b1, s.m));
+  const float vi = __fmaf_rn(gi, __fmul_rn(1.f - ad.b2, gi), __fmul_rn(ad.b2, s.v));
   ad.m[t] = mi;
   ad.v[t] = vi;
   const float x = s.p - ad.lr * (mi / ad.c1) / (sqrtf(vi / ad.c2) + ad.eps);

@@ -375,3 +375,45 @@ def test_screen_run_exact_rule():
         assert kinds.get("pareto", 0) > 0 and kinds.get("archive", 0) > 0
         if name == "archive":
             assert kinds.get("dominated", 0) > 0
+
+
+def _fma32(a, b, c):
+    """float32 fma: the exact product and its FP64 sum rounded to odd, whose
+    rounding to float32 is then that of the exact sum."""
+    p, c = a.astype(np.float64) * b.astype(np.float64), c.astype(np.float64)
+    s = p + c
+    v = s - p
+    err = (p - (s - v)) + (c - v)
+    bits = s.view(np.int64)
+    to_odd = (err != 0.0) & ((bits & 1) == 0)
+    bits[to_odd] += np.where((err > 0) == (s > 0), 1, -1)[to_odd]
+    return s.astype(np.float32)
+
+
+# few and many steps of 32 rows in a weight tile's chain; every parameter (weights and biases) after every step
+@pytest.mark.parametrize("N,B,seed", [(200, 32, 1), (900, 96, 2), (9000, 4096, 3)])
+def test_training_steps_have_fixed_roundings(N, B, seed):
+    """Each step's averages and parameters equal, bit for bit, those computed in
+    float32 from the gradient of the same rows: the averages as
+    fma(1 - b1, g, b1 m) and fma(g, (1 - b2) g, b2 v), all else one rounding an
+    operation.  From the second step on this tells one contraction from another."""
+    import ctypes
+    f = np.float32
+    powf = ctypes.CDLL("libm.so.6").powf
+    powf.restype, powf.argtypes = ctypes.c_float, [ctypes.c_float, ctypes.c_float]
+    rng = np.random.default_rng(seed)
+    x = _t(_bf16_bits(rng.normal(size=(N, R.IN)).astype(np.float32)))
+    t = _t(rng.normal(size=(N, R.OUT)).astype(np.float32))
+    lr, b1, b2, eps = f(1e-3), f(0.9), f(0.999), f(1e-8)
+    sur = dsm.Surrogate(seed=seed, lr=1e-3, max_rows=1024, max_batch=4096)
+    sur.params(_rand_params(seed))
+    m, v, p = np.zeros(R.NPARAMS, f), np.zeros(R.NPARAMS, f), sur.params()
+    for step in range(4):
+        idx = torch.from_numpy(_splitmix_indices(seed, step, N, B)).to(DEV)
+        g = sur.gradient(x[idx].contiguous(), t[idx].contiguous())[0].cpu().numpy()
+        sur.train(x, t, steps=1, batch=B)
+        m = _fma32(np.full_like(g, f(1) - b1), g, b1 * m)
+        v = _fma32(g, (f(1) - b2) * g, b2 * v)
+        c1, c2 = f(1) - f(powf(b1, step + 1)), f(1) - f(powf(b2, step + 1))
+        p = p - lr * (m / c1) / (np.sqrt(v / c2) + eps)
+        np.testing.assert_array_equal(sur.params(), p, err_msg=f"step {step + 1}")
