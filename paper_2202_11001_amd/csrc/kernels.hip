@@ -940,7 +940,9 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   double* s_len = (double*)s_rows;                   // [nver*na][kLengths] length differences
   double* s_guid = s_len + 2 * kMaxChunk * kLengths;  // [kWG] partial guidance terms
   double* s_w = s_guid + kWG;                        // [na][6] edge weights
-  static_assert(sizeof(WaveRows) * kWaves >= sizeof(double) * (2 * kMaxChunk * kLengths + kWG + 6 * kMaxChunk), "set-up space");
+  int* s_in = (int*)(s_w + 6 * kMaxChunk);           // [2 nver na] 1 if the entry is set up
+  static_assert(sizeof(WaveRows) * kWaves >= sizeof(double) * (2 * kMaxChunk * kLengths + kWG + 6 * kMaxChunk) + sizeof(int) * 4 * kMaxChunk,
+                "set-up space");
 
   // this chunk's tetrahedra: slots [i0, i0 + na) of the group
   const int na_all = uniform(PARTIAL ? a.aff_cnt[g] : min(kFullChunk, pr.T - g * kFullChunk));
@@ -1010,7 +1012,7 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
             if (!pos && (t & 3) == 0 && e < 2 * na)  // evaluated version only
               atomicOr(&s_flags, own == 0 ? DSM_FLAG_INV_MOVING : DSM_FLAG_INV_FIXED);
           }
-          if ((t & 3) == 0) s_units[e] = ok;  // 1 if the entry is set up
+          if ((t & 3) == 0) s_in[e] = ok;
         }
       } else if (job < nj + nf + nl) {
         const int t = (job - nj - nf) * 64 + lane, vt = t / kLengths, k = t - vt * kLengths;
@@ -1029,13 +1031,15 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   // guidance points, kWG / (2 nver kMaxChunk) lanes per (version, tetrahedron,
   // grid) sharing its image's points: each is first tested against the
   // tetrahedron's bounding box (exactly, on the lattice), which holds few
+  // (no barrier parts this from the slice tables: what the waves read here, they
+  // do not write there)
   const int gper = kWG / (2 * kMaxChunk * nver);
   const bool guided = pr.ng[0] + pr.ng[1] > 0;
   if (guided) {
     const int tg = tid / gper, vt = tg >> 1, gr = tg & 1;
     const int e = vt < nvt ? (vt >= na ? na : 0) + vt + (1 - gr) * na : 0;  // the entry of grid gr's own voxels
     double acc = 0.0;
-    if (vt < nvt && s_units[e]) {
+    if (vt < nvt && s_in[e]) {
       const float *Vo = s_xyz + (size_t)vt * 24 + gr * 12, *Vt = s_xyz + (size_t)vt * 24 + (1 - gr) * 12;
       float lo[3], hi[3];
       for (int k = 0; k < 3; ++k) {
@@ -1061,7 +1065,7 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   for (int e0 = wave * 4; e0 < nent; e0 += kWaves * 4) {
     const int e = e0 + (lane >> 4), sub = lane & 15;
     int nunits = 0;
-    if (e < nent && s_units[e]) {
+    if (e < nent && s_in[e]) {
       int own;
       const float* xyz = entry_xyz(e, own);
       const float *xo = xyz + own * 12, *xt = xyz + (1 - own) * 12;
@@ -1070,7 +1074,6 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
                                   : setup_slices16<ROWS>(xo, xt, pr.D, lane, sub, s_rts[e]);
       nunits = (nrows + 63) >> 6;
     }
-    wave_sync();
     if (e < nent && sub == 0) s_units[e] = nunits;
   }
   __syncthreads();

@@ -590,3 +590,40 @@ def test_full_evaluation_flags(grid):
     np.testing.assert_array_equal(fl, rfl)
     np.testing.assert_array_equal(gp.fold_check(_t(X)).cpu().numpy().astype(np.uint32), rfl)
     assert (rfl != 0).sum() > 25 and not rfl[38:].any()
+
+
+# a layer of tetrahedra between two voxel slices: none of them has a candidate row, all of them hold guidance points
+@pytest.mark.parametrize("rows", [0, 1])
+def test_guidance_without_candidate_rows(rows):
+    dims, mesh, S = (16, 16, 16), (3, 3, 4), 24
+    rng = np.random.default_rng(rows)
+    img = [rng.uniform(0, 1, dims[::-1]).astype(np.float32) for _ in range(2)]
+    n = 40
+    guid = [np.concatenate([W.snap(rng.uniform(0.5, 14.5, (n, 2))), np.full((n, 1), z, np.float32)], 1) for z in (5.5, 5.53125)]
+    corr = np.arange(n, dtype=np.int32)
+    w = W.Workload("thin layer", img[0], img[1], mesh, (1.0, 1.0, 1.0), 0.2, S, 1.0, 1.0, 7, 8, guid_moving=guid[0],
+                   corr_moving=corr, guid_fixed=guid[1], corr_fixed=corr)
+    rp = oracle_problem(w)
+    X = np.repeat(np.stack([W.regular_grid(dims, mesh)] * 2)[None], S, axis=0)
+    X[:, :, 9:18, 2], X[:, :, 18:27, 2] = 5.25, 5.75  # the second and third layer of points
+    X[:, :, [13, 22], :2] += W.snap(rng.uniform(-2, 2, (S, 2, 2, 2)))  # their inner points, in x and y
+    rfl = rp.fold_check(X)[0]
+    assert not rfl.any()
+    robj, _, rterms, _ = rp.eval_full(X, want_terms=True)
+    layer = np.array([set(t) <= set(range(9, 27)) for t in rp.tets().tolist()])
+    assert (rterms[:, layer, 2] > 0).any(1).all() and (rterms[:, ~layer, 2] == 0).all()
+    gp = dsm.Problem.from_workload(w, max_solutions=S)
+    gp.set_row_order(rows)
+    terms = torch.empty((S, gp.T, 3), dtype=torch.float64, device=DEV)
+    obj, fl = gp.eval_full(_t(X), tet_terms=terms)
+    assert not fl.any()
+    np.testing.assert_allclose(terms.cpu().numpy()[:, :, 2], rterms[:, :, 2], rtol=1e-9, atol=1e-9)
+    assert_objectives_close(obj.cpu().numpy(), robj)
+    off, pts = w.fos()
+    cand = X[:, :, pts].transpose(0, 2, 1, 3).copy()
+    rold, _, _, _ = rp.eval_partial(X, off, pts, cand)
+    for cache in (None, terms):
+        old, new, fl, _ = gp.eval_partial(_t(X), _t(off), _t(pts), _t(cand), tet_terms_in=cache)
+        assert not fl.any()
+        for part in (old, new):
+            np.testing.assert_allclose(part.cpu().numpy()[..., 2], rold[..., 2], rtol=1e-9, atol=1e-9)
