@@ -275,7 +275,10 @@ dsm_status dsm_autotune_pitch(dsm_problem* p, int32_t S, const float* X, int32_t
  * count, only the speed (smaller chunks give more, shorter workgroups) and
  * the rounding of the dissimilarity: the waves' per-lane compensated FP32
  * sums follow the work split (relative differences of order 1e-9 for element
- * sums, up to about 1e-7 for single tetrahedra; at most 4 x 2^-24).
+ * sums, up to about 1e-7 for single tetrahedra; at most 4 x 2^-24).  Element
+ * sums are FP64 sums of their chunks' sums, so their last bits follow the chunk
+ * in every objective, those of part_old and part_new alike: terms that do not
+ * change leave a difference of exactly 0.
  * dsm_set_part_chunk sets it for later partial evaluations of p (default 8);
  * it neither allocates nor synchronises, but a stored batch configuration
  * keeps the chunk it was stored with.  Errors: DSM_ERR_ARG for a chunk

@@ -1234,8 +1234,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 // The normalised sums, flags and voxel count of a (group, solution) pair of a
 // partial evaluation from those of its chunks, in chunk order, and the sums of
 // the current terms: the chunks' second version, or the cached terms of the
-// affected tetrahedra (a fixed butterfly order over each kFinishLanes of them).
-// One group of kFinishLanes lanes per pair.
+// affected tetrahedra, added chunk by chunk in the sweep's order: equal terms
+// give equal sums, so a change that moves nothing has a delta of exactly 0 in
+// deformation and guidance.  One group of kFinishLanes lanes per pair.
 constexpr int kFinishRounds = 4;
 __device__ __forceinline__ void finish_body(const EvalArgs& a, int logical, int lane) {
   const DevProblem& pr = a.pr;
@@ -1270,23 +1271,23 @@ __device__ __forceinline__ void finish_body(const EvalArgs& a, int logical, int 
     a.vcount[oi] = bits;
   }
   if (a.nver == 1) {
-    // kFinishRounds rounds' loads at a time: the loads that depend on one
+    // kFinishRounds chunks' loads at a time: the loads that depend on one
     // another, not their number, are the time
     double old[3] = {0.0, 0.0, 0.0};
-    for (int base = 0; base < na; base += kFinishLanes * kFinishRounds) {
+    for (int c = 0; c < nc; c += kFinishRounds) {
       int id[kFinishRounds];
       double t[kFinishRounds][3];
 #pragma unroll
       for (int u = 0; u < kFinishRounds; ++u) {
-        const int i = base + u * kFinishLanes + lane;
-        id[u] = i < na ? a.aff[(size_t)g * a.maxA + i] : -1;
+        const int i = (c + u) * a.pchunk + lane;
+        id[u] = lane < a.pchunk && i < na ? a.aff[(size_t)g * a.maxA + i] : -1;
       }
 #pragma unroll
       for (int u = 0; u < kFinishRounds; ++u)
         for (int k = 0; k < 3; ++k) t[u][k] = id[u] >= 0 ? a.terms_in[((size_t)s * pr.T + id[u]) * 3 + k] : 0.0;
 #pragma unroll
       for (int u = 0; u < kFinishRounds; ++u)
-        if (base + u * kFinishLanes < na)
+        if (c + u < nc)
           for (int k = 0; k < 3; ++k) old[k] += group_sum(t[u][k]);
     }
     if (lane >= 3 && lane < 6) acc = lane == 3 ? old[0] : (lane == 4 ? old[1] : old[2]);

@@ -627,3 +627,32 @@ def test_guidance_without_candidate_rows(rows):
         assert not fl.any()
         for part in (old, new):
             np.testing.assert_allclose(part.cpu().numpy()[..., 2], rold[..., 2], rtol=1e-9, atol=1e-9)
+
+
+def _guided(shape, mesh, n, seed):
+    """A batched workload with n guidance pairs at random lattice positions."""
+    w = W.batched(shape=shape, mesh=mesh)
+    rng = np.random.default_rng(seed)
+    w.guid_moving, w.guid_fixed = (W.snap(rng.uniform(1, min(shape) - 2, (n, 3))) for _ in range(2))
+    w.corr_moving = w.corr_fixed = np.arange(n, dtype=np.int32)
+    return w
+
+
+# every chunk; elements of 1 point and of 4, whose last chunk is full or not; current terms cached or recomputed
+@pytest.mark.parametrize("chunk", [4, 5, 6, 7, 8])
+@pytest.mark.parametrize("cached", [True, False])
+def test_unchanged_candidates_have_no_delta(chunk, cached):
+    w = _guided((24, 24, 24), (4, 4, 4), 150, 5)
+    X = _t(feasible_population(w, oracle_problem(w), S=6))
+    gp = dsm.Problem.from_workload(w, max_solutions=6, max_fos=500, max_fos_points=4)
+    gp.set_part_chunk(chunk)
+    tets = gp.topology()["tets"]
+    off = np.concatenate([np.arange(w.P), w.P + 4 * np.arange(len(tets) + 1)]).astype(np.int32)
+    pts = np.concatenate([np.arange(w.P), tets.reshape(-1)]).astype(np.int32)
+    terms = torch.empty((6, gp.T, 3), dtype=torch.float64, device=DEV)
+    gp.eval_full(X, tet_terms=terms)
+    assert (terms[..., 2] > 0).sum() > 200
+    old, new, fl, _ = gp.eval_partial(X, _t(off), _t(pts), X[:, :, _t(pts).long()].transpose(1, 2).contiguous(),
+                                      tet_terms_in=terms if cached else None)
+    assert not fl.any()
+    assert torch.equal(old[..., 1:], new[..., 1:])
