@@ -938,10 +938,11 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   __shared__ double s_dg[2 * kMaxChunk][2];   // per (version, tetrahedron): deformation and guidance term
   // before the sweep, in the space of its rows
   double* s_len = (double*)s_rows;                   // [nver*na][kLengths] length differences
-  double* s_guid = s_len + 2 * kMaxChunk * kLengths;  // [kWG] partial guidance terms
-  double* s_w = s_guid + kWG;                        // [na][6] edge weights
+  constexpr int kGuidSums = kWG / (2 * kMaxChunk);   // partial sums of a guidance term and grid, whatever nver
+  double* s_guid = s_len + 2 * kMaxChunk * kLengths;  // [nver na][2][kGuidSums] partial guidance terms
+  double* s_w = s_guid + 2 * kWG;                    // [na][6] edge weights
   int* s_in = (int*)(s_w + 6 * kMaxChunk);           // [2 nver na] 1 if the entry is set up
-  static_assert(sizeof(WaveRows) * kWaves >= sizeof(double) * (2 * kMaxChunk * kLengths + kWG + 6 * kMaxChunk) + sizeof(int) * 4 * kMaxChunk,
+  static_assert(sizeof(WaveRows) * kWaves >= sizeof(double) * (2 * kMaxChunk * kLengths + 2 * kWG + 6 * kMaxChunk) + sizeof(int) * 4 * kMaxChunk,
                 "set-up space");
 
   // this chunk's tetrahedra: slots [i0, i0 + na) of the group
@@ -1030,15 +1031,18 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   __syncthreads();
   // guidance points, kWG / (2 nver kMaxChunk) lanes per (version, tetrahedron,
   // grid) sharing its image's points: each is first tested against the
-  // tetrahedron's bounding box (exactly, on the lattice), which holds few
+  // tetrahedron's bounding box (exactly, on the lattice), which holds few.
+  // Point i goes into partial sum i % kGuidSums, two to a lane where two
+  // versions are swept, so a tetrahedron's term has the same bits either way
   // (no barrier parts this from the slice tables: what the waves read here, they
   // do not write there)
   const int gper = kWG / (2 * kMaxChunk * nver);
   const bool guided = pr.ng[0] + pr.ng[1] > 0;
   if (guided) {
-    const int tg = tid / gper, vt = tg >> 1, gr = tg & 1;
+    const int tg = tid / gper, vt = tg >> 1, gr = tg & 1, first = tid - tg * gper;
     const int e = vt < nvt ? (vt >= na ? na : 0) + vt + (1 - gr) * na : 0;  // the entry of grid gr's own voxels
-    double acc = 0.0;
+    double* sums = s_guid + tg * kGuidSums;
+    for (int q = first; q < kGuidSums; q += gper) sums[q] = 0.0;
     if (vt < nvt && s_in[e]) {
       const float *Vo = s_xyz + (size_t)vt * 24 + gr * 12, *Vt = s_xyz + (size_t)vt * 24 + (1 - gr) * 12;
       float lo[3], hi[3];
@@ -1046,13 +1050,12 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
         lo[k] = fmaf(fminf(fminf(Vo[k], Vo[3 + k]), fminf(Vo[6 + k], Vo[9 + k])), 128.f, 64.f);
         hi[k] = fmaf(fmaxf(fmaxf(Vo[k], Vo[3 + k]), fmaxf(Vo[6 + k], Vo[9 + k])), 128.f, 64.f);
       }
-      for (int i = tid - tg * gper; i < pr.ng[gr]; i += gper) {
+      for (int i = first; i < pr.ng[gr]; i += gper) {
         const float4 u = pr.gbox[gr][i];
         if ((u.x >= lo[0]) & (u.x <= hi[0]) & (u.y >= lo[1]) & (u.y <= hi[1]) & (u.z >= lo[2]) & (u.z <= hi[2]))
-          acc += guidance_point(pr, gr, i, __float_as_int(u.w), Vt, s_rts[e]);
+          sums[i % kGuidSums] += guidance_point(pr, gr, i, __float_as_int(u.w), Vt, s_rts[e]);
       }
     }
-    s_guid[tid] = acc;
   }
   if (wave == kWaves - 1 && lane < nvt) {  // deformation: edges weighted 1/k_e, then spokes
     const double *len = s_len + kLengths * lane, *w = s_w + 6 * (lane >= na ? lane - na : lane);
@@ -1082,7 +1085,7 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
   if (wave == kWaves - 1 && lane < nvt) {
     double guid = 0.0;
     if (guided)
-      for (int k = 0; k < 2 * gper; ++k) guid += s_guid[2 * gper * lane + k];
+      for (int k = 0; k < 2 * kGuidSums; ++k) guid += s_guid[2 * kGuidSums * lane + k];
     s_dg[lane][1] = guid;
   }
   __syncthreads();

@@ -656,3 +656,25 @@ def test_unchanged_candidates_have_no_delta(chunk, cached):
                                       tet_terms_in=terms if cached else None)
     assert not fl.any()
     assert torch.equal(old[..., 1:], new[..., 1:])
+
+
+# several guidance points in most tetrahedra: one version swept (cached terms, full evaluation) or two (recomputed)
+@pytest.mark.parametrize("chunk", [4, 8])
+def test_guidance_terms_do_not_depend_on_the_cache(chunk):
+    w = _guided((24, 24, 24), (5, 5, 5), 1500, 6)
+    X = _t(feasible_population(w, oracle_problem(w), S=4))
+    gp = dsm.Problem.from_workload(w, max_solutions=4)
+    gp.set_part_chunk(chunk)
+    pts = np.array([i + 5 * j + 25 * k for k in (1, 3) for j in (1, 3) for i in (1, 3)], np.int32)  # disjoint stars
+    off = np.arange(len(pts) + 1, dtype=np.int32)
+    cand = _t(W.candidates(X.cpu().numpy(), off, pts, w.mesh, w.dims, 0.5, 3))
+    full, one, two = (torch.zeros((4, gp.T, 3), dtype=torch.float64, device=DEV) for _ in range(3))
+    gp.eval_full(X, tet_terms=full)
+    gp.eval_partial(X, _t(off), _t(pts), cand, tet_terms_in=full, tet_terms_new=one)
+    gp.eval_partial(X, _t(off), _t(pts), cand, tet_terms_new=two)
+    assert (one[..., 2] > 0).sum() > 300
+    assert torch.equal(one[..., 1:], two[..., 1:])
+    moved = X.clone()
+    moved[:, :, _t(pts).long()] = cand.transpose(1, 2)
+    gp.eval_full(moved, tet_terms=full)
+    assert torch.equal(full[..., 1:], one[..., 1:])  # every tetrahedron of this mesh is in the star of one of them
