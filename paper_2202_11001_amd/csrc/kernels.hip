@@ -44,10 +44,11 @@ __device__ __forceinline__ unsigned lattice_of(float x, int D, double& u) {
 
 // The constraint bits of lattice_of for coordinate x, in FP32: scaling by 128
 // is exact, and (x + 0.5) 128 is a lattice integer in [0, 128 D] iff 128 x is
-// one in [-64, 128 D - 64].  Coordinates that vanish next to 0.5 in FP64 count
-// as 0, as they do there; x is set to 0 then.
+// one in [-64, 128 D - 64].  Coordinates that vanish next to 0.5 in FP64, whose
+// spacing is 2^-53 above and 2^-54 below it (a tie at either end rounds to 0.5),
+// count as 0, as they do there; x is set to 0 then.
 __device__ __forceinline__ unsigned lattice_bits(float& x, int D) {
-  if (fabsf(x) <= 0x1p-54f) x = 0.f;
+  if (x <= 0x1p-54f && x >= -0x1p-55f) x = 0.f;
   const float t = x * 128.f;
   if (!isfinite(x)) return DSM_FLAG_NONFINITE;
   if (t != floorf(t)) return DSM_FLAG_LATTICE;

@@ -678,3 +678,33 @@ def test_guidance_terms_do_not_depend_on_the_cache(chunk):
     moved[:, :, _t(pts).long()] = cand.transpose(1, 2)
     gp.eval_full(moved, tet_terms=full)
     assert torch.equal(full[..., 1:], one[..., 1:])  # every tetrahedron of this mesh is in the star of one of them
+
+
+# coordinates about 0, on both sides of what vanishes next to 0.5 in FP64: 2^-54 above, 2^-55 below
+def test_flags_of_coordinates_about_zero():
+    w = W.batched(shape=(24, 24, 24), mesh=(4, 4, 4))
+    rp = oracle_problem(w)
+    f = np.float32
+    tiny = [f(2.0 ** -53), np.nextafter(f(2.0 ** -54), f(1)), f(2.0 ** -54), f(0.75 * 2.0 ** -54),
+            np.nextafter(f(2.0 ** -55), f(1)), f(2.0 ** -55), f(2.0 ** -60), f(1e-40), f(0)]
+    vals = np.array(tiny + [-v for v in tiny], f)
+    S, p = 3 * len(vals), 21  # the first inner point
+    X = np.repeat(np.stack([W.regular_grid(w.dims, w.mesh)] * 2)[None], S, axis=0)
+    cand = np.repeat(X[:, :, p][:, None], 1, axis=1).copy()
+    for c in range(3):
+        for i, v in enumerate(vals):
+            cand[3 * i + c, 0, c % 2, c] = v
+    moved = X.copy()
+    moved[:, :, p] = cand[:, 0]
+    rfl = rp.fold_check(moved)[0]
+    lat = (rfl & dsm.FLAG_LATTICE) != 0
+    assert lat.reshape(-1, 3).all(1).sum() == 2 + 5 and lat.reshape(-1, 3).any(1).sum() == 2 + 5
+    gp = dsm.Problem.from_workload(w, max_solutions=S)
+    np.testing.assert_array_equal(gp.eval_full(_t(moved))[1].cpu().numpy().astype(np.uint32), rfl)
+    np.testing.assert_array_equal(gp.fold_check(_t(moved)).cpu().numpy().astype(np.uint32), rfl)
+    off, pts = np.array([0, 1], np.int32), np.array([p], np.int32)
+    _, _, pfl, _ = rp.eval_partial(X, off, pts, cand)
+    fl = gp.eval_partial(_t(X), _t(off), _t(pts), _t(cand))[2]
+    np.testing.assert_array_equal(fl.cpu().numpy().astype(np.uint32), pfl)
+    for i in np.flatnonzero(lat)[:4]:  # a tetrahedron with such a vertex is not mapped
+        assert torch.isnan(gp.transform(_t(moved[i]), 1)[0]).any()
