@@ -663,7 +663,8 @@ size_t dsm_archive_work_bytes(int32_t capacity, int32_t m, int32_t row_floats);
  * order, later rows set to +inf, and *n_archive updated.  With row_floats > 0
  * every vector carries a payload row (e.g. its solution): archive_rows dev
  * [capacity][row_floats] moves with the archive, point_rows dev
- * [m][row_floats] are the points' rows.  If more than `capacity` vectors would
+ * [m][row_floats] are the points' rows; points and point_rows may lie in the
+ * archive's own buffers (its free rows, say).  If more than `capacity` vectors would
  * be kept, nothing changes and *overflow (dev int32, may be NULL) is set to 1,
  * else to 0.  work: dev, dsm_archive_work_bytes(capacity, m, row_floats)
  * bytes.  Errors: DSM_ERR_ARG (sizes, null pointers), DSM_ERR_DEVICE. */

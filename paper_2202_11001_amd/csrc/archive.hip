@@ -235,12 +235,16 @@ __device__ __forceinline__ void copy_row(float* __restrict__ dst, const float* _
 }
 
 // The merged vectors, and the payload of every archive row that moves, copied
-// to the workspace at their new positions.
+// to the workspace at their new positions; with `staged` the new rows too, for
+// points whose rows lie in the archive's own buffer (its free rows, say), which
+// k_merge_in writes.
 __global__ __launch_bounds__(kMergeWG) void k_merge_out(const double* __restrict__ arch,
                                                       const float* __restrict__ arch_rows, int cap,
-                                                      const double* __restrict__ pts, int row_floats, bool pairs,
-                                                      const int* __restrict__ src, const int* __restrict__ hdr,
-                                                      double* __restrict__ vec, float* __restrict__ rows) {
+                                                      const double* __restrict__ pts,
+                                                      const float* __restrict__ pt_rows, int row_floats, bool pairs,
+                                                      bool staged, const int* __restrict__ src,
+                                                      const int* __restrict__ hdr, double* __restrict__ vec,
+                                                      float* __restrict__ rows) {
   if (hdr[1]) return;  // overflow: the archive stays as it was
   const int k = hdr[0];
   for (int64_t e = blockIdx.x * (int64_t)kMergeWG + threadIdx.x; e < 3 * (int64_t)k; e += (int64_t)gridDim.x * kMergeWG) {
@@ -250,17 +254,21 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_out(const double* __restrict
   if (!row_floats) return;
   for (int r = blockIdx.x; r < k; r += gridDim.x) {
     const int from = src[r];
-    if (from >= 0 && from < cap && from != r)
-      copy_row(rows + (size_t)r * row_floats, arch_rows + (size_t)from * row_floats, row_floats, pairs);
+    if (from >= 0 && from != r && (from < cap || staged))
+      copy_row(rows + (size_t)r * row_floats,
+               from < cap ? arch_rows + (size_t)from * row_floats : pt_rows + (size_t)(from - cap) * row_floats, row_floats,
+               pairs);
   }
 }
 
 // Writes the archive: vectors and moved rows from the workspace, new rows from
-// the points, +inf after the count; the count and the overflow flag.
+// the points (the workspace with `staged`), +inf after the count; the count and
+// the overflow flag.
 __global__ __launch_bounds__(kMergeWG) void k_merge_in(double* __restrict__ arch, float* __restrict__ arch_rows, int cap,
                                                      const float* __restrict__ pt_rows, int row_floats, bool pairs,
-                                                     const int* __restrict__ src, const int* __restrict__ hdr,
-                                                     const double* __restrict__ vec, const float* __restrict__ rows,
+                                                     bool staged, const int* __restrict__ src,
+                                                     const int* __restrict__ hdr, const double* __restrict__ vec,
+                                                     const float* __restrict__ rows,
                                                      int* __restrict__ n_arch, int* __restrict__ overflow) {
   const int k = hdr[0];
   const bool over = hdr[1] != 0;
@@ -276,7 +284,7 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_in(double* __restrict__ arch
     const int from = src[r];
     if (from >= 0 && from != r)
       copy_row(arch_rows + (size_t)r * row_floats,
-               from < cap ? rows + (size_t)r * row_floats : pt_rows + (size_t)(from - cap) * row_floats, row_floats,
+               from < cap || staged ? rows + (size_t)r * row_floats : pt_rows + (size_t)(from - cap) * row_floats, row_floats,
                pairs);
   }
 }
@@ -540,9 +548,13 @@ dsm_status dsm_archive_merge(int32_t capacity, double* archive, int32_t* n_archi
   const bool pairs = row_floats % 2 == 0 && (((uintptr_t)archive_rows | (uintptr_t)point_rows | (uintptr_t)rows) & 7) == 0;
   // a workgroup per row with payload; the vectors alone (3 values a row) take few
   const unsigned wgs = row_floats ? std::min(capacity, 16384) : std::min((3 * (capacity / kMergeWG) + 3), 1024);
-  k_merge_out<<<wgs, kMergeWG, 0, st>>>(archive, archive_rows, capacity, points, row_floats, pairs, src, hdr, vec, rows);
-  k_merge_in<<<wgs, kMergeWG, 0, st>>>(archive, archive_rows, capacity, point_rows, row_floats, pairs, src, hdr, vec, rows,
-                                      n_archive, overflow);
+  const uintptr_t a0 = (uintptr_t)archive_rows, p0 = (uintptr_t)point_rows;
+  const bool staged = row_floats && p0 < a0 + sizeof(float) * (size_t)capacity * row_floats &&
+                      a0 < p0 + sizeof(float) * (size_t)m * row_floats;
+  k_merge_out<<<wgs, kMergeWG, 0, st>>>(archive, archive_rows, capacity, points, point_rows, row_floats, pairs, staged, src,
+                                       hdr, vec, rows);
+  k_merge_in<<<wgs, kMergeWG, 0, st>>>(archive, archive_rows, capacity, point_rows, row_floats, pairs, staged, src, hdr, vec,
+                                      rows, n_archive, overflow);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
 

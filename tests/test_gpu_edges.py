@@ -708,3 +708,26 @@ def test_flags_of_coordinates_about_zero():
     np.testing.assert_array_equal(fl.cpu().numpy().astype(np.uint32), pfl)
     for i in np.flatnonzero(lat)[:4]:  # a tetrahedron with such a vertex is not mapped
         assert torch.isnan(gp.transform(_t(moved[i]), 1)[0]).any()
+
+
+# the points' rows in the archive's own buffer: its free rows, its first rows, some of both; a result moves nearly every row
+@pytest.mark.parametrize("first", [40, 0, 30])
+def test_archive_rows_merged_in_place(first):
+    rng = np.random.default_rng(first)
+    m, row = 40, 33000
+    u = rng.uniform(0, 1, (2 * m, 2))
+    front = np.concatenate([u, 2.0 - u.sum(1, keepdims=True)], 1)  # a plane: no vector dominates another
+    rows = _t(rng.normal(size=(2 * m, row)).astype(np.float32))
+    both = []
+    for own in (False, True):
+        A = dsm.Archive(capacity=100, m_max=m, row_floats=row)
+        A.rows.zero_()
+        A.merge(_t(front[:m]), rows[:m].contiguous())
+        assert A.n == m
+        A.rows[m:2 * m] = rows[m:]
+        src = A.rows[first:first + m]
+        A.merge(_t(front[m:]), src if own else src.clone())
+        assert A.n == 2 * m
+        both.append((A.vec.clone(), A.rows[:2 * m].clone()))
+    for a, b in zip(*both):
+        assert torch.equal(a, b)
