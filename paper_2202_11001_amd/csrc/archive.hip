@@ -220,19 +220,28 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_positions(const double* __re
   }
 }
 
-// One workgroup's copy of a payload row, in pairs of floats where every row
-// starts at a multiple of 8 bytes (pairs).
+// The copy of a payload row by the gridDim.y workgroups of its column of the
+// grid, in pairs of floats where every row starts at a multiple of 8 bytes
+// (pairs).
 __device__ __forceinline__ void copy_row(float* __restrict__ dst, const float* __restrict__ src, int n, bool pairs) {
+  const int first = blockIdx.y * kMergeWG + threadIdx.x, step = gridDim.y * kMergeWG;
   if (pairs) {
     float2* d = reinterpret_cast<float2*>(dst);
     const float2* s = reinterpret_cast<const float2*>(src);
 #pragma unroll 4
-    for (int i = threadIdx.x; i < n / 2; i += kMergeWG) d[i] = s[i];
+    for (int i = first; i < n / 2; i += step) d[i] = s[i];
   } else {
 #pragma unroll 4
-    for (int i = threadIdx.x; i < n; i += kMergeWG) dst[i] = src[i];
+    for (int i = first; i < n; i += step) dst[i] = src[i];
   }
 }
+
+// Floats of a row per workgroup: longer rows are split.  One workgroup copies
+// some 25 GB/s, so with one to a row an archive of few, long rows (solutions on a
+// fine mesh) left the device idle: 4 points merged into 8 rows of 6.4 MB took 542
+// us, 16 into 32 of them 720, in parts 39 and 115 (4,096 or 16,384 floats a part:
+// the same within 3 %).
+constexpr int kMergePart = 8192;
 
 // The merged vectors, and the payload of every archive row that moves, copied
 // to the workspace at their new positions; with `staged` the new rows too, for
@@ -247,7 +256,8 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_out(const double* __restrict
                                                       float* __restrict__ rows) {
   if (hdr[1]) return;  // overflow: the archive stays as it was
   const int k = hdr[0];
-  for (int64_t e = blockIdx.x * (int64_t)kMergeWG + threadIdx.x; e < 3 * (int64_t)k; e += (int64_t)gridDim.x * kMergeWG) {
+  const int64_t wg = blockIdx.x + (int64_t)gridDim.x * blockIdx.y, step = (int64_t)gridDim.x * gridDim.y * kMergeWG;
+  for (int64_t e = wg * kMergeWG + threadIdx.x; e < 3 * (int64_t)k; e += step) {
     const int r = (int)(e / 3), c = (int)(e - 3 * (int64_t)r), from = src[r];
     vec[e] = from < 0 ? INFINITY : (from < cap ? arch[3 * (size_t)from + c] : pts[3 * (size_t)(from - cap) + c]);
   }
@@ -272,12 +282,13 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_in(double* __restrict__ arch
                                                      int* __restrict__ n_arch, int* __restrict__ overflow) {
   const int k = hdr[0];
   const bool over = hdr[1] != 0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  const int64_t wg = blockIdx.x + (int64_t)gridDim.x * blockIdx.y, step = (int64_t)gridDim.x * gridDim.y * kMergeWG;
+  if (wg == 0 && threadIdx.x == 0) {
     if (overflow) *overflow = over ? 1 : 0;
     if (!over) *n_arch = k;
   }
   if (over) return;
-  for (int64_t e = blockIdx.x * (int64_t)kMergeWG + threadIdx.x; e < 3 * (int64_t)cap; e += (int64_t)gridDim.x * kMergeWG)
+  for (int64_t e = wg * kMergeWG + threadIdx.x; e < 3 * (int64_t)cap; e += step)
     arch[e] = e < 3 * (int64_t)k ? vec[e] : INFINITY;
   if (!row_floats) return;
   for (int r = blockIdx.x; r < k; r += gridDim.x) {
@@ -546,8 +557,9 @@ dsm_status dsm_archive_merge(int32_t capacity, double* archive, int32_t* n_archi
   k_merge_positions<<<words + m / kMergeWaves + 1, kMergeWG, 0, st>>>(archive, n_archive, capacity, m, points, alive,
                                                                      keep_n, src, hdr);
   const bool pairs = row_floats % 2 == 0 && (((uintptr_t)archive_rows | (uintptr_t)point_rows | (uintptr_t)rows) & 7) == 0;
-  // a workgroup per row with payload; the vectors alone (3 values a row) take few
-  const unsigned wgs = row_floats ? std::min(capacity, 16384) : std::min((3 * (capacity / kMergeWG) + 3), 1024);
+  // a workgroup per row (or part of one) with payload; the vectors alone (3 values a row) take few
+  const unsigned most = row_floats ? std::min(capacity, 16384) : std::min((3 * (capacity / kMergeWG) + 3), 1024);
+  const dim3 wgs(most, std::max(1u, std::min(((unsigned)row_floats + kMergePart - 1) / kMergePart, 16384u / most)));
   const uintptr_t a0 = (uintptr_t)archive_rows, p0 = (uintptr_t)point_rows;
   const bool staged = row_floats && p0 < a0 + sizeof(float) * (size_t)capacity * row_floats &&
                       a0 < p0 + sizeof(float) * (size_t)m * row_floats;

@@ -731,3 +731,21 @@ def test_archive_rows_merged_in_place(first):
         both.append((A.vec.clone(), A.rows[:2 * m].clone()))
     for a, b in zip(*both):
         assert torch.equal(a, b)
+
+
+# rows of one part (8192 floats), one part and a bit, several, in pairs of floats and alone, against the merge on the host
+@pytest.mark.parametrize("capacity,row", [(7, 8192), (7, 8193), (5, 40000), (64, 16386)])
+def test_archive_rows_in_parts(capacity, row):
+    rng = np.random.default_rng(row)
+    A = dsm.Archive(capacity=capacity, m_max=3, row_floats=row)
+    vec, rows = np.zeros((0, 3)), np.zeros((0, row), np.float32)
+    for _ in range(4):
+        pts = rng.integers(0, 12, (3, 3)) / 4.0
+        new = rng.normal(size=(3, row)).astype(np.float32)
+        A.merge(_t(pts), _t(new))
+        want, want_rows = G.archive_merge(vec, pts, rows, new)
+        if len(want) <= capacity:
+            vec, rows = want, want_rows
+        assert A.n == len(vec) and int(A.overflow.item()) == (len(want) > capacity)
+        np.testing.assert_array_equal(A.vec[:len(vec)].cpu().numpy(), vec)
+        np.testing.assert_array_equal(A.rows[:len(vec)].cpu().numpy(), rows)
