@@ -300,12 +300,50 @@ __global__ __launch_bounds__(256) void k_sample_dist(DevProblem pr, int S, const
   out[v] = (float)(rint((x + 0.5) * kLat) / kLat - 0.5);
 }
 
-// Accept / apply one colour class of elements, one wave per (solution,
-// element) pair: the lanes share the scan of the archive (64 rows a round, up
-// to the first row of padding) and the copy of the element's coordinates and
-// of its points' candidate terms.  With a thread per pair, a pair's dependent
-// loads (up to the whole archive, then up to 4 x 48 tetrahedra x 3 terms) ran
-// one after another: 75 us a class of the phantom's 6^3 grid (2,000 pairs).
+// Whether a row of the archive, up to the first row of padding (first value
+// +inf), dominates v: the G lanes of a group take a row each.
+template <int G>
+__device__ __forceinline__ bool archive_dominates(const double* __restrict__ arch, int n_arch, const double v[3], int lane) {
+  bool dominated = false;
+  for (int q0 = 0; q0 < n_arch && !dominated; q0 += G) {
+    const int q = q0 + lane;
+    const double* a = arch + (size_t)q * 3;
+    bool le = true, lt = false;
+    if constexpr (G == 1) {
+      if (a[0] == INFINITY) break;
+      for (int o = 0; o < 3; ++o) {
+        le = le && a[o] <= v[o];
+        lt = lt || a[o] < v[o];
+      }
+      dominated = le && lt;
+    } else {
+      bool end = q >= n_arch, dom = false;
+      if (!end) {
+        end = a[0] == INFINITY;
+        for (int o = 0; o < 3; ++o) {
+          le = le && a[o] <= v[o];
+          lt = lt || a[o] < v[o];
+        }
+        dom = le && lt;
+      }
+      // the group's lanes of the wave's votes
+      const int shift = threadIdx.x & 63 & ~(G - 1);
+      const unsigned long long ends = __ballot(end) >> shift & (~0ull >> (64 - G));
+      const unsigned long long doms = __ballot(dom) >> shift & (~0ull >> (64 - G));
+      dominated = (doms & (ends ? (ends & -ends) - 1 : ~0ull)) != 0;  // of the rows ahead of the end
+      if (ends) break;
+    }
+  }
+  return dominated;
+}
+
+// Accept / apply one colour class of elements, G lanes per (solution, element)
+// pair: they share the scan of the archive and the copy of the element's
+// coordinates and of its points' candidate terms.  With a thread per pair, a
+// pair's dependent loads (up to the whole archive, then up to 4 x 48 tetrahedra
+// x 3 terms) run one after another: 75 us a class of the phantom's 6^3 grid
+// (2,000 pairs).
+template <int G>
 __global__ __launch_bounds__(256) void k_accept(DevProblem pr, int S, float* __restrict__ X, int F,
                                                 const int* __restrict__ off, const int* __restrict__ pts,
                                                 const float* __restrict__ cand, const double* __restrict__ part_old,
@@ -315,8 +353,8 @@ __global__ __launch_bounds__(256) void k_accept(DevProblem pr, int S, float* __r
                                                 const double* __restrict__ arch,
                                                 const int* __restrict__ single_objective,
                                                 unsigned char* __restrict__ accepted) {
-  const int64_t e = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;  // the same on every lane of a wave
-  const int lane = threadIdx.x & 63;
+  const int64_t e = blockIdx.x * (int64_t)(256 / G) + threadIdx.x / G;  // the same on every lane of a group
+  const int lane = threadIdx.x % G;
   if (e >= (int64_t)S * F) return;
   const int s = (int)(e / F), f = (int)(e - (int64_t)s * F);
   bool acc = flags[e] == 0u;
@@ -336,26 +374,7 @@ __global__ __launch_bounds__(256) void k_accept(DevProblem pr, int S, float* __r
     } else if (!acc && n_arch > 0) {
       bool improves = false;
       for (int o = 0; o < 3; ++o) improves = improves || d[o] < 0.0;
-      bool dominated = false;
-      for (int q0 = 0; improves && q0 < n_arch && !dominated; q0 += 64) {
-        const int q = q0 + lane;
-        bool end = q >= n_arch, dom = false;
-        if (!end) {
-          const double* a = arch + (size_t)q * 3;
-          end = a[0] == INFINITY;  // padding ends the archive
-          bool ale = true, alt = false;
-          for (int o = 0; o < 3; ++o) {
-            ale = ale && a[o] <= nv[o];
-            alt = alt || a[o] < nv[o];
-          }
-          dom = ale && alt;
-        }
-        const unsigned long long ends = __ballot(end), doms = __ballot(dom);
-        const unsigned long long before = ends ? (ends & -ends) - 1 : ~0ull;  // rows ahead of the end
-        dominated = (doms & before) != 0;
-        if (ends) break;
-      }
-      acc = improves && !dominated;
+      acc = improves && !archive_dominates<G>(arch, n_arch, nv, lane);
     }
   }
   if (accepted && lane == 0) accepted[e] = acc ? 1 : 0;
@@ -366,12 +385,19 @@ __global__ __launch_bounds__(256) void k_accept(DevProblem pr, int S, float* __r
   for (int j = j0; j < j1; ++j) {
     const int p = pts[j];
     if (p < 0 || p >= pr.P) continue;  // such elements are flagged by the evaluator
-    if (lane < 6)
-      X[(((size_t)s * 2 + lane / 3) * pr.P + p) * 3 + lane % 3] = cand[((size_t)s * n + j) * 6 + lane];
-    const int k0 = pr.star_off[p], m = 3 * (pr.star_off[p + 1] - k0);
-    for (int i = lane; i < m; i += 64) {
-      const size_t t = ((size_t)s * pr.T + pr.star[k0 + i / 3]) * 3 + i % 3;
-      cache[t] = terms_cand[t];
+    for (int c = lane; c < 6; c += G)
+      X[(((size_t)s * 2 + c / 3) * pr.P + p) * 3 + c % 3] = cand[((size_t)s * n + j) * 6 + c];
+    const int k0 = pr.star_off[p], k1 = pr.star_off[p + 1];
+    if constexpr (G == 1) {
+      for (int k = k0; k < k1; ++k) {
+        const size_t t = ((size_t)s * pr.T + pr.star[k]) * 3;
+        for (int o = 0; o < 3; ++o) cache[t + o] = terms_cand[t + o];
+      }
+    } else {
+      for (int i = lane; i < 3 * (k1 - k0); i += G) {
+        const size_t t = ((size_t)s * pr.T + pr.star[k0 + i / 3]) * 3 + i % 3;
+        cache[t] = terms_cand[t];
+      }
     }
   }
 }
@@ -695,6 +721,31 @@ __global__ __launch_bounds__(kClusterWG) void k_cluster(int S, const double* __r
   if (means_out && tid < 3 * k) means_out[tid] = s_mu[tid / 3][tid % 3];
 }
 
+// Lanes of a pair by the number of pairs: once there are enough to fill the
+// device, more lanes only repeat the pair's own loads.  In us, with 64 / 16 / 1
+// lanes, for 30 % of the pairs accepted without an archive and for all of them
+// tested against 3,000 rows: 13,500 pairs 23 / 23 / 29 and 89 / 129 / 890,
+// 51,200 pairs 29 / 28 / 37 and 238 / 278 / 901, 125,000 pairs 43 / 38 / 45 and 538
+// / 593 / 918, 729,000 pairs 121 / 78 / 71 and 3,001 / 3,106 / 2,706 (51,200 pairs
+// all rejected: 24 / 21 / 20).
+void launch_accept(const DevProblem& pr, int S, float* X, int F, const int* off, const int* pts, const float* cand,
+                   const double* part_old, const double* part_new, const uint32_t* flags, const double* terms_cand,
+                   double* cache, const double* obj, int n_arch, const double* arch, const int* single_objective,
+                   unsigned char* accepted, hipStream_t st) {
+  const int64_t pairs = (int64_t)S * F;
+  auto launch = [&](auto* kernel, int lanes) {
+    kernel<<<(unsigned)((pairs * lanes + 255) / 256), 256, 0, st>>>(pr, S, X, F, off, pts, cand, part_old, part_new, flags,
+                                                                   terms_cand, cache, obj, n_arch, arch,
+                                                                   single_objective, accepted);
+  };
+  if (pairs <= 49152)
+    launch(k_accept<64>, 64);
+  else if (pairs <= 196608)
+    launch(k_accept<16>, 16);
+  else
+    launch(k_accept<1>, 1);
+}
+
 }  // namespace
 }  // namespace dsm
 
@@ -811,9 +862,8 @@ dsm_status dsm_accept(dsm_problem* p, int32_t S, float* X, int32_t F, const int3
     return DSM_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
   if (F > 0)
-    k_accept<<<(unsigned)(((int64_t)S * F + 3) / 4), 256, 0, st>>>(p->dev, S, X, F, nullptr, fos_pts, cand, part_old, part_new, flags,
-                                                   terms_cand, terms_cache, obj, n_archive, archive, single_objective,
-                                                   accepted);
+    launch_accept(p->dev, S, X, F, nullptr, fos_pts, cand, part_old, part_new, flags, terms_cand, terms_cache, obj, n_archive,
+                  archive, single_objective, accepted, st);
   if (hipGetLastError() != hipSuccess) return DSM_ERR_DEVICE;
   return launch_full_reduce(p->dev, S, terms_cache, obj, st) == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
@@ -852,9 +902,8 @@ dsm_status dsm_accept_elements(dsm_problem* p, int32_t S, float* X, int32_t F, c
     return DSM_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
   if (F > 0)
-    k_accept<<<(unsigned)(((int64_t)S * F + 3) / 4), 256, 0, st>>>(p->dev, S, X, F, fos_off, fos_pts, cand, part_old, part_new, flags,
-                                                   terms_cand, terms_cache, obj, n_archive, archive, single_objective,
-                                                   accepted);
+    launch_accept(p->dev, S, X, F, fos_off, fos_pts, cand, part_old, part_new, flags, terms_cand, terms_cache, obj, n_archive,
+                  archive, single_objective, accepted, st);
   if (hipGetLastError() != hipSuccess) return DSM_ERR_DEVICE;
   return launch_full_reduce(p->dev, S, terms_cache, obj, st) == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }

@@ -749,3 +749,52 @@ def test_archive_rows_in_parts(capacity, row):
         assert A.n == len(vec) and int(A.overflow.item()) == (len(want) > capacity)
         np.testing.assert_array_equal(A.vec[:len(vec)].cpu().numpy(), vec)
         np.testing.assert_array_equal(A.rows[:len(vec)].cpu().numpy(), rows)
+
+
+# the last and first sizes of the acceptance rule's three ranges (49,152 and 196,608 pairs), points and elements of 4
+# points, an archive of more rows than a group's lanes that ends inside a round, some solutions with one objective only
+@pytest.mark.parametrize("S", [1820, 1821, 7281, 7282])
+@pytest.mark.parametrize("elements", [False, True])
+def test_acceptance_of_many_pairs(tiny_problem, S, elements):
+    w, _ = tiny_problem
+    gp = dsm.Problem.from_workload(w, max_solutions=S)
+    topo = gp.topology()
+    F = 27
+    groups = [t.tolist() for t in topo["tets"][:F]] if elements else [[p] for p in range(F)]
+    rng = np.random.default_rng(S)
+    X, moved = (rng.uniform(0, 31, (S, 2, w.P, 3)).astype(np.float32) for _ in range(2))
+    pts = np.concatenate(groups).astype(np.int32)
+    off = np.cumsum([0] + [len(g) for g in groups]).astype(np.int32)
+    cand = moved[:, :, pts].transpose(0, 2, 1, 3).copy()  # a point moves to the same place in every element
+    obj, old = rng.uniform(1, 2, (S, 3)), rng.uniform(0, 1, (S, F, 3))
+    new = old + rng.choice([-0.2, 0.0, 0.2], (S, F, 3))
+    flags = rng.choice([0, 0, 0, 1], (S, F)).astype(np.int32)
+    arch = rng.uniform(0.9, 2.2, (70, 3))
+    single = rng.integers(-1, 9, S).astype(np.int32)
+    tc, cache = (torch.rand((S, gp.T, 3), dtype=torch.float64, device=DEV) for _ in range(2))
+    dX, dcache, dobj = _t(X), cache.clone(), _t(obj)
+    acc = torch.empty((S, F), dtype=torch.uint8, device=DEV)
+    args = (_t(cand), _t(old), _t(new), _t(flags), tc, dcache, dobj)
+    kw = dict(archive=_t(np.concatenate([arch, np.full((9, 3), np.inf), np.zeros((5, 3))])), accepted=acc,
+              single_objective=_t(single))
+    if elements:
+        gp.accept_elements(dX, _t(off), _t(pts), *args, **kw)
+    else:
+        gp.accept(dX, _t(pts), *args, **kw)
+    d = new - old
+    nv = obj[:, None] + d
+    dom = np.zeros((S, F), bool)
+    for a in arch:
+        dom |= (a <= nv).all(2) & (a < nv).any(2)
+    want = (d <= 0).all(2) & (d < 0).any(2) | (d < 0).any(2) & ~dom
+    one = (single >= 0) & (single < 3)
+    want[one] = np.take_along_axis(d[one], single[one][:, None, None].repeat(F, 1), 2)[..., 0] < 0
+    want &= flags == 0
+    np.testing.assert_array_equal(acc.cpu().numpy() != 0, want)
+    hit_p, hit_t = np.zeros((S, w.P), bool), np.zeros((S, gp.T), bool)
+    for f, g in enumerate(groups):
+        hit_p[:, g] |= want[:, f][:, None]
+        for p in g:
+            hit_t[:, topo["star"][topo["star_off"][p]:topo["star_off"][p + 1]]] |= want[:, f][:, None]
+    assert torch.equal(dX, torch.where(_t(hit_p)[:, None, :, None], _t(moved), _t(X)))
+    assert torch.equal(dcache, torch.where(_t(hit_t)[..., None], tc, cache))
