@@ -237,11 +237,13 @@ __global__ __launch_bounds__(NP == 1 ? 64 : 320) void k_estimate(DevProblem pr, 
 // gives NaN (flagged as non-finite by the evaluator); elements with malformed
 // offsets are not written.
 //
-// A group of LG lanes per candidate, lane v drawing and combining variable v
-// (z passed between the lanes), so that the FP64 logarithm and cosine of the
-// draws, which bound the kernel, run once per lane instead of NV times in a
-// row, and nothing is kept in scratch memory.  Candidates are numbered with
-// the element slowest, so the groups of a wave read the same factor.
+// A group of LG lanes per candidate, lane t drawing and combining variables t,
+// t + LG, ... (z passed between the lanes), so that the FP64 logarithm and
+// cosine of the draws, which bound the kernel, run side by side instead of NV
+// times in a row, and nothing is kept in scratch memory.  Candidates are
+// numbered as they are stored, so a wave reads and writes in one piece (with
+// the element slowest, for one factor a wave: 5 % slower at 729,000 points, the
+// same at 13,500 elements).
 template <int NP, int LG>
 __global__ __launch_bounds__(256) void k_sample_dist(DevProblem pr, int S, const float* __restrict__ X, int F,
                                                      const int* __restrict__ off, const int* __restrict__ pts, int K,
@@ -252,52 +254,63 @@ __global__ __launch_bounds__(256) void k_sample_dist(DevProblem pr, int S, const
                                                      unsigned long long seed, unsigned long long counter,
                                                      const unsigned long long* __restrict__ counter_dev,
                                                      float* __restrict__ cand) {
-  constexpr int NV = 6 * NP, NE = NV * (NV + 1) / 2;
-  static_assert(NV <= LG && 64 % LG == 0, "one lane per variable");
-  const int64_t g = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / LG;
-  const int v = threadIdx.x % LG;
+  constexpr int NV = 6 * NP, NE = NV * (NV + 1) / 2, NU = (NV + LG - 1) / LG;  // variables of a lane
+  static_assert(64 % LG == 0 && (NU == 1 || NP == 1), "several variables a lane for single points only");
+  const int64_t g = blockIdx.x * (int64_t)(256 / LG) + threadIdx.x / LG;
+  const int t = threadIdx.x % LG;
   if (counter_dev) counter += *counter_dev;
   if (g >= (int64_t)S * F * K) return;
-  const int f = (int)(g / ((int64_t)S * K));
-  const int64_t sk = g - (int64_t)f * S * K;
-  const int s = (int)(sk / K);
-  const int64_t row = ((int64_t)s * F + f) * K + (sk - (int64_t)s * K);
+  const int64_t sf = g / K;
+  const int s = (int)(sf / F), f = (int)(sf - (int64_t)s * F);
   const int b = off ? off[f] : f, np = off ? off[f + 1] - b : 1;
   if (off && (b < 0 || np < 0 || b + np > off[F])) return;  // malformed offsets: nothing of this element to write
-  float* out = off ? cand + ((size_t)s * off[F] + b) * 6 : cand + row * 6;
+  float* out = off ? cand + ((size_t)s * off[F] + b) * 6 : cand + g * 6;
   const int cl = cluster ? cluster[s] : 0;
   bool ok = np >= 1 && np <= NP && cl >= 0 && cl < n_clusters;
   for (int k = 0; ok && k < np; ++k) ok = pts[b + k] >= 0 && pts[b + k] < pr.P;
   if (!ok) {
-    for (int e = v; e < 6 * np; e += LG) out[e] = NAN;
+    for (int e = t; e < 6 * np; e += LG) out[e] = NAN;
     return;
   }
   const int nv = 6 * np;
   const size_t d = (size_t)cl * F + f;  // distribution of the solution's cluster
-  const double* L = chol + d * NE + v * (v + 1) / 2;
-  double z = 0.0, w = 0.0;
-  if (v < nv) z = normal(seed, counter * 0x100000000ull + (unsigned long long)(row * NV + v));
+  double z[NU], w[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int v = t + LG * u;
+    z[u] = v < nv ? normal(seed, counter * 0x100000000ull + (unsigned long long)(g * NV + v)) : 0.0;
+    w[u] = 0.0;
+  }
   for (int k0 = 0; k0 < nv; k0 += 6) {  // the factor's entries 6 at a time: one wait for memory each
-    double l[6];
 #pragma unroll
-    for (int u = 0; u < 6; ++u) l[u] = v < nv && k0 + u <= v ? L[k0 + u] : 0.0;
+    for (int u = 0; u < NU; ++u) {
+      const int v = t + LG * u;
+      const double* L = chol + d * NE + v * (v + 1) / 2;
+      double l[6];
 #pragma unroll
-    for (int u = 0; u < 6; ++u) {
-      const double zk = __shfl(z, k0 + u, LG);
-      if (k0 + u <= v && v < nv) w += l[u] * zk;
+      for (int q = 0; q < 6; ++q) l[q] = v < nv && k0 + q <= v ? L[k0 + q] : 0.0;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        const double zk = LG == 1 ? z[q % NU] : __shfl(z[q / LG % NU], NU == 1 ? k0 + q : q % LG, LG);  // k0 = 0 if NU > 1
+        if (k0 + q <= v && v < nv) w[u] += l[q] * zk;
+      }
     }
   }
-  if (v >= nv) return;
-  const int p = pts[b + v / 6], c = v % 6, gr = c / 3, a = c % 3;
-  const int idx = a == 0 ? p % pr.n[0] : (a == 1 ? (p / pr.n[0]) % pr.n[1] : p / (pr.n[0] * pr.n[1]));
-  double x = X[(((size_t)s * 2 + gr) * pr.P + p) * 3 + a];
-  if (idx > 0 && idx < pr.n[a] - 1) {
-    const double sc = sqrt((double)mult[d]);
-    double m = mean[d * NV + v];
-    if (shift && ams[s]) m += delta * (double)mult[d] * shift[(size_t)p * 6 + c];  // anticipated mean shift
-    x = fmin(fmax(m + sc * w, -0.5), pr.D[a] - 0.5);
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int v = t + LG * u;
+    if (v >= nv) continue;
+    const int p = pts[b + v / 6], c = v % 6, gr = c / 3, a = c % 3;
+    const int idx = a == 0 ? p % pr.n[0] : (a == 1 ? (p / pr.n[0]) % pr.n[1] : p / (pr.n[0] * pr.n[1]));
+    double x = X[(((size_t)s * 2 + gr) * pr.P + p) * 3 + a];
+    if (idx > 0 && idx < pr.n[a] - 1) {
+      const double sc = sqrt((double)mult[d]);
+      double m = mean[d * NV + v];
+      if (shift && ams[s]) m += delta * (double)mult[d] * shift[(size_t)p * 6 + c];  // anticipated mean shift
+      x = fmin(fmax(m + sc * w[u], -0.5), pr.D[a] - 0.5);
+    }
+    out[v] = (float)(rint((x + 0.5) * kLat) / kLat - 0.5);
   }
-  out[v] = (float)(rint((x + 0.5) * kLat) / kLat - 0.5);
 }
 
 // Whether a row of the archive, up to the first row of padding (first value
@@ -784,9 +797,18 @@ dsm_status dsm_sample_estimated(dsm_problem* p, int32_t S, const float* X, int32
   const int64_t n = (int64_t)S * F * K;
   if (n == 0) return DSM_OK;  // empty buffers may be null
   if (!X || !fos_pts || !mean || !chol || !mult || !cand || n_clusters < 1 || (shift && !ams)) return DSM_ERR_ARG;
-  k_sample_dist<1, 8><<<(unsigned)((n + 31) / 32), 256, 0, (hipStream_t)stream>>>(
-      p->dev, S, X, F, nullptr, fos_pts, K, mean, chol, mult, n_clusters, cluster, shift, ams, delta, seed, counter,
-      (const unsigned long long*)counter_dev, cand);
+  auto launch = [&](auto* kernel, int lanes) {
+    kernel<<<(unsigned)((n * lanes + 255) / 256), 256, 0, (hipStream_t)stream>>>(
+        p->dev, S, X, F, nullptr, fos_pts, K, mean, chol, mult, n_clusters, cluster, shift, ams, delta, seed, counter,
+        (const unsigned long long*)counter_dev, cand);
+  };
+  // a lane per variable while the lanes are too few to fill the device (13,500
+  // candidates: 18.8 us, a thread each 20.2); beyond, a quarter of those lanes is
+  // idle and every load is repeated (54,000: 23.5 against 20.8, 729,000: 106 against 57)
+  if (n <= 40960)
+    launch(k_sample_dist<1, 8>, 8);
+  else
+    launch(k_sample_dist<1, 1>, 1);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
 

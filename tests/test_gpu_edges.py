@@ -798,3 +798,30 @@ def test_acceptance_of_many_pairs(tiny_problem, S, elements):
             hit_t[:, topo["star"][topo["star_off"][p]:topo["star_off"][p + 1]]] |= want[:, f][:, None]
     assert torch.equal(dX, torch.where(_t(hit_p)[:, None, :, None], _t(moved), _t(X)))
     assert torch.equal(dcache, torch.where(_t(hit_t)[..., None], tc, cache))
+
+
+# the last number of candidates with a lane per variable (40,960) and the first with a thread each; clusters, shifts,
+# points that do not exist: a candidate does not depend on the others of its call
+@pytest.mark.parametrize("S", [512, 513])
+def test_candidates_of_many_points(tiny_problem, S):
+    w, gp = tiny_problem
+    F, K, C = 20, 4, 3
+    rng = np.random.default_rng(S)
+    X = _random_population(w, S, 8)
+    pts = np.array([13, 4, -1, 22, 27, 0] + rng.integers(0, w.P, 14).tolist(), np.int32)
+    mean = _t(rng.uniform(8, 20, (C, F, 6)))
+    chol = _t(np.array([[G.packed_lower(np.tril(rng.uniform(0.2, 1.0, (6, 6)))) for _ in range(F)] for _ in range(C)]))
+    mult = _t(rng.uniform(0.5, 2, (C, F)).astype(np.float32))
+    cluster = rng.integers(0, C, S).astype(np.int32)
+    cluster[7] = C  # no such cluster
+    shift, ams = _t(rng.uniform(-1, 1, (w.P, 6))), rng.integers(0, 2, S).astype(np.uint8)
+
+    def sample(n):
+        return gp.sample_estimated(_t(X[:n]), _t(pts), K, mean, chol, mult, 5, 9, cluster=_t(cluster[:n]), shift=shift,
+                                   ams=_t(ams[:n])).cpu().numpy()
+
+    got, few = sample(S), sample(200)  # counters follow (s, f, k), so the first solutions draw the same
+    np.testing.assert_array_equal(got[:200], few)
+    assert np.isnan(got[7]).all() and np.isnan(got[:, [2, 4]]).all()
+    rest = np.delete(np.delete(got, 7, 0), [2, 4], 1)
+    assert not np.isnan(rest).any() and np.all(np.rint((rest + 0.5) * 128) == (rest + 0.5) * 128)
