@@ -85,6 +85,8 @@ __device__ __forceinline__ double readlane64(double v, int l) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+__device__ __forceinline__ int64_t wide_block() { return blockIdx.x + (int64_t)gridDim.x * blockIdx.y; }
+
 // Mean and Cholesky factor of the elements' distributions, for elements of up
 // to NP points (NP = 1: the single points pts[f], off null; else CSR).  Per
 // element f: mean [F][NV] of the variables over the solutions sel[0..n_sel)
@@ -94,7 +96,7 @@ __device__ __forceinline__ double readlane64(double v, int l) {
 // rows and columns of pinned coordinates, and of variables beyond 6 x (number
 // of points), are 0, and a pivot that is not positive (a rank-deficient
 // selection) gives a zero column.  Elements with no point, more than NP
-// points, an invalid point or no valid solution get zeros.  Cluster blockIdx.y
+// points, an invalid point or no valid solution get zeros.  Cluster blockIdx.z
 // has a selection, means and factors of its own, one after the other.
 //
 // One workgroup per element, one thread per covariance entry.  There are few
@@ -119,10 +121,11 @@ __global__ __launch_bounds__(NP == 1 ? 64 : 320) void k_estimate(DevProblem pr, 
   __shared__ double s_mu[NV];
   __shared__ double s_C[NE];
   __shared__ bool s_ok[kEstTile], s_free[NV];
-  const int f = blockIdx.x, t = threadIdx.x;
-  sel += (size_t)blockIdx.y * n_sel;
-  double* mu = mean + ((size_t)blockIdx.y * F + f) * NV;
-  double* L = chol + ((size_t)blockIdx.y * F + f) * NE;
+  if (wide_block() >= F) return;
+  const int f = (int)wide_block(), t = threadIdx.x;
+  sel += (size_t)blockIdx.z * n_sel;
+  double* mu = mean + ((size_t)blockIdx.z * F + f) * NV;
+  double* L = chol + ((size_t)blockIdx.z * F + f) * NE;
   const int b = off ? off[f] : f, np = off ? off[f + 1] - b : 1;
   bool ok = b >= 0 && np >= 1 && np <= NP && (!off || b + np <= off[F]);
   for (int k = 0; ok && k < np; ++k) ok = pts[b + k] >= 0 && pts[b + k] < pr.P;
@@ -256,7 +259,7 @@ __global__ __launch_bounds__(256) void k_sample_dist(DevProblem pr, int S, const
                                                      float* __restrict__ cand) {
   constexpr int NV = 6 * NP, NE = NV * (NV + 1) / 2, NU = (NV + LG - 1) / LG;  // variables of a lane
   static_assert(64 % LG == 0 && (NU == 1 || NP == 1), "several variables a lane for single points only");
-  const int64_t g = blockIdx.x * (int64_t)(256 / LG) + threadIdx.x / LG;
+  const int64_t g = wide_block() * (256 / LG) + threadIdx.x / LG;
   const int t = threadIdx.x % LG;
   if (counter_dev) counter += *counter_dev;
   if (g >= (int64_t)S * F * K) return;
@@ -476,8 +479,10 @@ __global__ __launch_bounds__(kSdrTile) void k_sdr(int S, int F, const int* __res
   __shared__ int s_row[kSdrTile];
   __shared__ int s_cnt[kSdrTile / 64];
   __shared__ double s_L[kEstTri];
-  const int e = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int j = e / F, f = e % F;
+  const int64_t e = wide_block();  // (cluster, element)
+  if (e >= (int64_t)n_clusters * F) return;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int j = (int)(e / F), f = (int)(e - (int64_t)j * F);
   const int b = off[f], np = off[f + 1] - b, total = off[F];
   const int nv = 6 * np;
   if (b < 0 || np < 1 || nv > nvar || b + np > total) {
@@ -784,7 +789,7 @@ dsm_status dsm_estimate_distributions(dsm_problem* p, int32_t S, const float* X,
   if (!p || S < 0 || F < 0 || n_sel < 0) return DSM_ERR_ARG;
   if (F == 0) return DSM_OK;  // empty buffers may be null
   if (!fos_pts || !mean || !chol || (n_sel > 0 && (!X || !sel))) return DSM_ERR_ARG;
-  k_estimate<1><<<(unsigned)F, 64, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, nullptr, fos_pts, mean, chol);
+  k_estimate<1><<<wide_grid(F), 64, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, nullptr, fos_pts, mean, chol);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
 
@@ -798,7 +803,7 @@ dsm_status dsm_sample_estimated(dsm_problem* p, int32_t S, const float* X, int32
   if (n == 0) return DSM_OK;  // empty buffers may be null
   if (!X || !fos_pts || !mean || !chol || !mult || !cand || n_clusters < 1 || (shift && !ams)) return DSM_ERR_ARG;
   auto launch = [&](auto* kernel, int lanes) {
-    kernel<<<(unsigned)((n * lanes + 255) / 256), 256, 0, (hipStream_t)stream>>>(
+    kernel<<<wide_grid((n * lanes + 255) / 256), 256, 0, (hipStream_t)stream>>>(
         p->dev, S, X, F, nullptr, fos_pts, K, mean, chol, mult, n_clusters, cluster, shift, ams, delta, seed, counter,
         (const unsigned long long*)counter_dev, cand);
   };
@@ -818,7 +823,7 @@ dsm_status dsm_estimate_elements(dsm_problem* p, int32_t S, const float* X, int3
   if (!p || S < 0 || F < 0 || n_sel < 0) return DSM_ERR_ARG;
   if (F == 0) return DSM_OK;  // empty buffers may be null
   if (!fos_off || !fos_pts || !mean || !chol || (n_sel > 0 && (!X || !sel))) return DSM_ERR_ARG;
-  k_estimate<kEstPoints><<<(unsigned)F, 320, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, fos_off, fos_pts, mean,
+  k_estimate<kEstPoints><<<wide_grid(F), 320, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, fos_off, fos_pts, mean,
                                                                       chol);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }
@@ -829,7 +834,8 @@ dsm_status dsm_estimate_clusters(dsm_problem* p, int32_t S, const float* X, int3
   if (!p || S < 0 || F < 0 || n_sel < 0 || n_clusters < 1 || n_clusters > kClusterMax) return DSM_ERR_ARG;
   if (F == 0) return DSM_OK;  // empty buffers may be null
   if (!fos_pts || !mean || !chol || (n_sel > 0 && (!X || !sel))) return DSM_ERR_ARG;
-  const dim3 grid((unsigned)F, (unsigned)n_clusters);
+  dim3 grid = wide_grid(F);
+  grid.z = (unsigned)n_clusters;
   if (fos_off)
     k_estimate<kEstPoints><<<grid, 320, 0, (hipStream_t)stream>>>(p->dev, S, X, n_sel, sel, F, fos_off, fos_pts, mean, chol);
   else
@@ -847,7 +853,7 @@ dsm_status dsm_sample_elements(dsm_problem* p, int32_t S, const float* X, int32_
   if (n == 0) return DSM_OK;  // empty buffers may be null
   if (!X || !fos_off || !fos_pts || !mean || !chol || !mult || !cand || n_clusters < 1 || (shift && !ams))
     return DSM_ERR_ARG;
-  k_sample_dist<kEstPoints, 32><<<(unsigned)((n + 7) / 8), 256, 0, (hipStream_t)stream>>>(
+  k_sample_dist<kEstPoints, 32><<<wide_grid((n + 7) / 8), 256, 0, (hipStream_t)stream>>>(
       p->dev, S, X, F, fos_off, fos_pts, 1, mean, chol, mult, n_clusters, cluster, shift, ams, delta, seed, counter,
       (const unsigned long long*)counter_dev, cand);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
@@ -897,7 +903,7 @@ dsm_status dsm_improvement_ratio(int32_t S, int32_t F, const int32_t* fos_off, c
   const int64_t n = (int64_t)n_clusters * F;
   if (n == 0) return DSM_OK;
   if (!fos_off || !mean || !chol || !sdr || (S > 0 && (!cand || !accepted))) return DSM_ERR_ARG;
-  k_sdr<<<(unsigned)n, kSdrTile, 0, (hipStream_t)stream>>>(S, F, fos_off, cand, accepted, n_clusters, cluster, mean, chol,
+  k_sdr<<<wide_grid(n), kSdrTile, 0, (hipStream_t)stream>>>(S, F, fos_off, cand, accepted, n_clusters, cluster, mean, chol,
                                                     n_vars, sdr);
   return hipGetLastError() == hipSuccess ? DSM_OK : DSM_ERR_DEVICE;
 }

@@ -825,3 +825,38 @@ def test_candidates_of_many_points(tiny_problem, S):
     assert np.isnan(got[7]).all() and np.isnan(got[:, [2, 4]]).all()
     rest = np.delete(np.delete(got, 7, 0), [2, 4], 1)
     assert not np.isnan(rest).any() and np.all(np.rint((rest + 0.5) * 128) == (rest + 0.5) * 128)
+
+
+# more threads than a dimension of a grid holds (2^32): 32 to a candidate of an element, 320 to an element's factor, 256 to
+# a standard-deviation ratio
+def test_more_elements_than_a_grid_dimension():
+    img = [np.random.default_rng(3).uniform(0, 1, (4, 4, 4)).astype(np.float32) for _ in range(2)]
+    w = W.Workload("cube", img[0], img[1], (2, 2, 2), (1.0, 1.0, 1.0), 0.2, 1, 1.0, 1.0, 7, 8)
+    gp = dsm.Problem.from_workload(w, max_solutions=1, max_fos=1, max_fos_points=1)
+    F, S = 4, (1 << 25) + 3
+    X = torch.randint(0, 512, (S, 2, 8, 3), dtype=torch.int32, device=DEV).float().div_(128).sub_(0.5)
+    pts, off = _t(np.array([0, 5, 2, 7], np.int32)), _t(np.arange(F + 1, dtype=np.int32))
+    mean, chol = (torch.ones((1, F, n), dtype=torch.float64, device=DEV) for n in (24, 300))
+    out = torch.full((S, F, 2, 3), -7.0, device=DEV)
+    gp.sample_elements(X, off, pts, mean, chol, torch.ones((1, F), device=DEV), 1, 1, out=out)
+    for i, p in enumerate((0, 5, 2, 7)):  # corners: every coordinate is pinned and stays the solution's
+        assert torch.equal(out[:, i], X[:, :, p])
+    F = (1 << 32) // 320 + 5
+    X = X[:3].contiguous()
+    del out
+    torch.cuda.empty_cache()
+    off, pts = torch.arange(F + 1, dtype=torch.int32, device=DEV), torch.arange(F, dtype=torch.int32, device=DEV) % 8
+    mean, chol = gp.estimate_elements(X, _t(np.arange(3, dtype=np.int32)), off, pts)
+    want = X.double().mean(0).transpose(0, 1).reshape(8, 6)
+    for a in (0, F // 16 * 8, F // 8 * 8 - 8):
+        torch.testing.assert_close(mean[a:a + 8, :6], want, rtol=1e-14, atol=0)
+    assert (mean[:, 0] != 0).all() and not chol[F - 1].any()
+    del mean, chol
+    torch.cuda.empty_cache()
+    C, F = 16, (1 << 20) + 1
+    off, acc = torch.arange(F + 1, dtype=torch.int32, device=DEV), torch.ones((1, F), dtype=torch.uint8, device=DEV)
+    mean, chol = torch.zeros((C, F, 6), dtype=torch.float64, device=DEV), torch.zeros((C, F, 21), dtype=torch.float64, device=DEV)
+    chol[..., 0] = 2.0  # the first variable alone varies
+    sdr = dsm.improvement_ratio(off, torch.full((1, F, 2, 3), 3.0, device=DEV), acc, mean, chol,
+                                cluster=torch.full((1,), C - 1, dtype=torch.int32, device=DEV))
+    assert (sdr[:C - 1] == -1).all() and (sdr[C - 1] == 1.5).all()
