@@ -65,6 +65,8 @@ __host__ __device__ inline MergeWork merge_work(int cap, int m, int row_floats) 
 // element of the whole capacity divided into row and column: 110 and 76 us;
 // a prefix sum over the capacity by one workgroup: 25 us).
 
+__device__ __forceinline__ int64_t wide_block() { return blockIdx.x + (int64_t)gridDim.x * blockIdx.y; }
+
 constexpr int kMergeTile = 512;  // new points staged in LDS at a time
 
 // Workgroups [0, ceil(cap / 64)): the 64 archive rows of a word, each wave
@@ -83,11 +85,13 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_mark(const double* __restric
   __shared__ int drop;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, words = (cap + 63) / 64;
   const int n = min(*n_arch, cap);
-  if ((int)blockIdx.x < words) {
-    const int i = blockIdx.x * 64 + lane;
+  const int64_t wg = wide_block();
+  if (wg < words) {
+    const int word = (int)wg;
+    const int64_t i = (int64_t)word * 64 + lane;
     if (t < 64 && i < cap) src[i] = -1;  // NaN vectors have no place in the order and may leave positions free
-    if ((int)blockIdx.x * 64 >= n) {
-      if (t == 0) alive[blockIdx.x] = 0;
+    if ((int64_t)word * 64 >= n) {
+      if (t == 0) alive[word] = 0;
       return;
     }
     double a[3] = {0.0, 0.0, 0.0};
@@ -108,11 +112,12 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_mark(const double* __restric
     if (t == 0) {
       unsigned long long all = 0;
       for (int w = 0; w < kMergeWaves; ++w) all |= s_dead[w];
-      alive[blockIdx.x] = ~all;
+      alive[word] = ~all;
     }
     return;
   }
-  const int j = blockIdx.x - words;
+  if (wg - words >= m) return;
+  const int j = (int)(wg - words);
   if (t == 0) drop = 0;
   __syncthreads();
   const double* p = pts + 3 * (size_t)j;
@@ -161,13 +166,15 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_positions(const double* __re
   __shared__ int s_pre;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, words = (cap + 63) / 64;
   const int n = min(*n_arch, cap);
-  if ((int)blockIdx.x < words) {
-    const unsigned long long mine = alive[blockIdx.x];
+  const int64_t wg = wide_block();
+  if (wg < words) {
+    const int word = (int)wg;
+    const unsigned long long mine = alive[word];
     if (!mine) return;
-    const int i = blockIdx.x * 64 + lane;
+    const int i = word * 64 + lane;
     const bool kept = (mine >> lane) & 1;
     if (wave == 0) {
-      const int pre = kept_before(alive, blockIdx.x, lane);
+      const int pre = kept_before(alive, word, lane);
       if (lane == 0) s_pre = pre;
     }
     double a[3] = {0.0, 0.0, 0.0};
@@ -192,7 +199,7 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_positions(const double* __re
     }
     return;
   }
-  const int j = (blockIdx.x - words) * kMergeWaves + wave;  // the same on every lane of a wave
+  const int64_t j = (wg - words) * kMergeWaves + wave;  // the same on every lane of a wave
   if (j < m) {
     if (!keep_n[j]) return;
     const double p[3] = {pts[3 * (size_t)j], pts[3 * (size_t)j + 1], pts[3 * (size_t)j + 2]};
@@ -208,8 +215,8 @@ __global__ __launch_bounds__(kMergeWG) void k_merge_positions(const double* __re
     int below = 0;
     for (int k = lane; k < m; k += 64) below += keep_n[k] & (int)lex_less(pts + 3 * (size_t)k, p);
     pos += wave_add(below);
-    if (lane == 0 && pos < cap) src[pos] = cap + j;
-  } else if (blockIdx.x == gridDim.x - 1 && wave == kMergeWaves - 1) {
+    if (lane == 0 && pos < cap) src[pos] = cap + (int)j;
+  } else if (wg == words + m / kMergeWaves && wave == kMergeWaves - 1) {
     int k = kept_before(alive, words, lane), kn = 0;
     for (int q = lane; q < m; q += 64) kn += keep_n[q];
     k += wave_add(kn);
@@ -552,9 +559,9 @@ dsm_status dsm_archive_merge(int32_t capacity, double* archive, int32_t* n_archi
   float* rows = (float*)(base + w.rows);
   int* hdr = (int*)(base + w.hdr);
   const int words = (capacity + 63) / 64;
-  k_merge_mark<<<words + m, kMergeWG, 0, st>>>(archive, n_archive, capacity, m, points, alive, keep_n, src);
+  k_merge_mark<<<wide_grid((int64_t)words + m), kMergeWG, 0, st>>>(archive, n_archive, capacity, m, points, alive, keep_n, src);
   // m / waves + 1 workgroups after the words: the last one's last wave has no point and writes the header
-  k_merge_positions<<<words + m / kMergeWaves + 1, kMergeWG, 0, st>>>(archive, n_archive, capacity, m, points, alive,
+  k_merge_positions<<<wide_grid((int64_t)words + m / kMergeWaves + 1), kMergeWG, 0, st>>>(archive, n_archive, capacity, m, points, alive,
                                                                      keep_n, src, hdr);
   const bool pairs = row_floats % 2 == 0 && (((uintptr_t)archive_rows | (uintptr_t)point_rows | (uintptr_t)rows) & 7) == 0;
   // a workgroup per row (or part of one) with payload; the vectors alone (3 values a row) take few

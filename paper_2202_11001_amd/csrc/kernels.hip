@@ -66,6 +66,9 @@ __device__ __forceinline__ double orient(const double a[3], const double b[3], c
   return u[0] * cx + u[1] * cy + u[2] * cz;
 }
 
+// Number of a workgroup in a grid of wide_grid.
+__device__ __forceinline__ int64_t wide_block() { return blockIdx.x + (int64_t)gridDim.x * blockIdx.y; }
+
 // Blockid -> logical index so that each of the 8 XCDs (which receive
 // workgroups round robin) processes one contiguous range of logical indices;
 // consecutive logical indices share a FOS element and hence an image region.
@@ -1205,7 +1208,7 @@ template <int PARTIAL, int ROWS, int EU>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(EU, 8))) void k_sweep(EvalArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int n = PARTIAL && a.slots ? a.S * a.slots[0].x : a.S * a.G * (PARTIAL ? a.nchunk : 1);
-  const int logical = xcd_logical(blockIdx.x & 7, blockIdx.x >> 3, n);
+  const int logical = xcd_logical(blockIdx.x & 7, (int)(wide_block() >> 3), n);
   if (logical >= 0) sweep_body<PARTIAL, ROWS>(a, logical, smem);
 }
 
@@ -1223,7 +1226,7 @@ template <int ROWS>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sweep_batch(
     const EvalArgs* __restrict__ jobs, const int* __restrict__ xcd_off, int n_jobs) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
+  const int x = blockIdx.x & 7, k = (int)(wide_block() >> 3);
   int j = 0;
   while (j + 1 < n_jobs && xcd_off[j + 1] <= k) ++j;
   j = uniform(j);
@@ -1886,16 +1889,17 @@ hipError_t launch_affected(const DevProblem& pr, int F, const int* fos_off, cons
 // Workgroups from which a sweep keeps every SIMD at 8 waves.  2,048 do, but the
 // launch has room for the largest element everywhere and two to four times the
 // workgroups that exist.
-constexpr unsigned kSweepMany = 4 * 8 * 256;
+constexpr int64_t kSweepMany = 4 * 8 * 256;
 
 hipError_t launch_eval(const EvalArgs& a, hipEvent_t ev_begin, hipEvent_t ev_end, hipStream_t stream) {
   const int64_t nwg = (int64_t)a.S * a.G;
   if (nwg <= 0) return hipSuccess;
-  // a multiple of 8: every XCD gets an eighth of the workgroups that exist, rounded up
-  const unsigned grid = (unsigned)((nwg * (a.partial ? a.nchunk : 1) + 7) / 8 * 8);
+  // XCD x gets the workgroups x, x + 8, ...: as many as xcd_logical gives it, whatever the slot table leaves of them
+  const int64_t most = nwg * (a.partial ? a.nchunk : 1);
+  const dim3 grid = wide_grid(most);
   const size_t lds = eval_lds_bytes(kMaxChunk, a.nver);
   if (ev_begin) (void)hipEventRecord(ev_begin, stream);
-  const bool many = a.nver == 1 && grid > kSweepMany;
+  const bool many = a.nver == 1 && most > kSweepMany;
   auto launch = [&](auto* dense, auto* sparse) { (many ? dense : sparse)<<<grid, kWG, lds, stream>>>(a); };
   if (a.partial && a.row_pairs)
     launch(k_sweep<1, 1, 8>, k_sweep<1, 1, 6>);
@@ -1916,7 +1920,7 @@ hipError_t launch_eval(const EvalArgs& a, hipEvent_t ev_begin, hipEvent_t ev_end
 hipError_t launch_eval_batch(const EvalArgs* jobs_dev, const int* wg_off_dev, int n_jobs, int per_xcd, int total_finish,
                              size_t lds, int rows, hipStream_t stream) {
   if (per_xcd <= 0) return hipSuccess;
-  const unsigned nwg = (unsigned)(8 * per_xcd);
+  const dim3 nwg = wide_grid(8 * (int64_t)per_xcd);
   if (rows == 0)
     k_sweep_batch<0><<<nwg, kWG, lds, stream>>>(jobs_dev, wg_off_dev, n_jobs);
   else if (rows == 1)

@@ -746,7 +746,7 @@ __global__ __launch_bounds__(256) void k_select(int S, int F, int K, const float
                                                 unsigned char* __restrict__ run_exact, float* __restrict__ cand_pick) {
   __shared__ double s_a[kSelTile][3];
   __shared__ int s_end;
-  const int64_t e = blockIdx.x * (int64_t)(256 / G) + threadIdx.x / G;
+  const int64_t e = (blockIdx.x + (int64_t)gridDim.x * blockIdx.y) * (256 / G) + threadIdx.x / G;
   const int sub = threadIdx.x % G;
   bool accept = false, scan = false;
   double nv[kOut] = {0.0, 0.0, 0.0};
@@ -1159,7 +1159,7 @@ dsm_status dsm_surrogate_screen(dsm_surrogate* m, dsm_problem* p, int32_t S, con
                                         m->d_pred);
   const int64_t pairs = (int64_t)S * F;
   auto select = [&](auto* kernel, int lanes) {
-    kernel<<<(unsigned)((pairs * lanes + 255) / 256), 256, 0, st>>>(S, F, K, m->d_pred, m->d_out_mean, m->d_out_scale,
+    kernel<<<wide_grid((pairs * lanes + 255) / 256), 256, 0, st>>>(S, F, K, m->d_pred, m->d_out_mean, m->d_out_scale,
                                                                     obj, n_archive, archive, cand, pred, pick, run_exact,
                                                                     cand_pick);
   };

@@ -860,3 +860,28 @@ def test_more_elements_than_a_grid_dimension():
     sdr = dsm.improvement_ratio(off, torch.full((1, F, 2, 3), 3.0, device=DEV), acc, mean, chol,
                                 cluster=torch.full((1,), C - 1, dtype=torch.int32, device=DEV))
     assert (sdr[:C - 1] == -1).all() and (sdr[C - 1] == 1.5).all()
+
+
+# two workgroups of 256 threads an element: nearly as many as a dimension of a grid holds (2^24), and more
+@pytest.mark.parametrize("F", [(1 << 23) - 3, (1 << 23) + 6])
+def test_more_chunks_than_a_grid_dimension(F):
+    rng = np.random.default_rng(F)
+    img = [rng.uniform(0, 1, (4, 4, 4)).astype(np.float32) for _ in range(2)]
+    w = W.Workload("cube", img[0], img[1], (3, 2, 2), (1.0, 1.0, 1.0), 0.2, 1, 1.0, 1.0, 7, 8)
+    gp = dsm.Problem.from_workload(w, max_solutions=1, max_fos=F, max_fos_points=1)
+    assert gp.max_affected == 12  # two chunks of 8 an element
+    gp.set_part_chunk(8)
+    X = np.stack([W.regular_grid(w.dims, w.mesh)] * 2)[None]
+    one = X[:, :, np.arange(F, F + 12) % 12].transpose(0, 2, 1, 3).copy()
+    one[..., 0] += rng.integers(-20, 21, one.shape[:3]) / 128
+    pts = torch.arange(F, F + F, dtype=torch.int32, device=DEV) % 12
+    cand = _t(one).repeat(1, F // 12 + 1, 1, 1)[:, :F].contiguous()
+    off = torch.arange(F + 1, dtype=torch.int32, device=DEV)
+    out = tuple(torch.full((1, F, 3), -7.0, dtype=torch.float64, device=DEV) for _ in range(2)) + (
+        torch.full((1, F), -7, dtype=torch.int32, device=DEV), None)
+    old, new, fl = gp.eval_partial(_t(X), off, pts, cand, out=out)[:3]
+    small = dsm.Problem.from_workload(w, max_solutions=1, max_fos=12, max_fos_points=1)
+    small.set_part_chunk(8)
+    want = small.eval_partial(_t(X), off[:13].contiguous(), pts[:12].contiguous(), cand[:, :12].contiguous())
+    for got, ref_ in zip((old, new, fl), want):
+        assert torch.equal(got[:, :F // 12 * 12].reshape(F // 12, 12, -1), ref_.reshape(1, 12, -1).expand(F // 12, -1, -1))
