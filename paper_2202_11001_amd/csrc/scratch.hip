@@ -47,7 +47,8 @@ ScratchLayout scratch_layout(int S, int F, int maxA, int nver, int nchunk) {
   size_t o = 0;
   L.aff = o;
   o = align256(o + sizeof(int) * (size_t)F * maxA);
-  L.aff_cnt = o;
+  L.aff_cnt = o;  // two words an element, as the interface states the workspace: the second is not used
+  o = align256(o + sizeof(int) * (size_t)F);
   o = align256(o + sizeof(int) * (size_t)F);
   L.sums = o;  // 3 sums per chunk of at least kMinPartChunk tetrahedra and version: at most one double per tetrahedron
   o = align256(o + sizeof(double) * (size_t)S * F * nver * maxA);

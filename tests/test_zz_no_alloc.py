@@ -101,3 +101,39 @@ def test_noalloc_without_partial_capacity_and_capacity_error():
         small.eval_partial_noalloc(Xb, offd, ptsd, cb)
     assert ei.value.status == dsm.ERR_CAPACITY
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("cached", [True, False])
+def test_noalloc_limit_is_the_stated_one(cached):
+    """The largest S whose workspace, as dsm.h states it, fits the fixed array
+    is evaluated and the next one refused."""
+    w = W.tiny()
+    off, pts = w.fos()
+    F = len(off) - 1
+    gp = dsm.Problem.from_workload(w, max_solutions=1, max_fos=0, max_fos_points=1)
+    maxA, nver = gp.max_affected, 1 if cached else 2
+
+    def need(S, f):
+        return sum(-(-b // 256) * 256 for b in (4 * f * maxA, 4 * f, 4 * f, 8 * S * f * nver * maxA,
+                                                4 * S * f * -(-maxA // 8), 4 * S * f * -(-maxA // 8)))
+
+    # elements repeated so that one solution's share of the workspace is smaller than a word an element
+    reps = 400
+    f = F * reps
+    S = max(s for s in range(1, 100) if need(s, f) <= 64 << 20)
+    extra = next(r for r in range(1, 10 ** 6) if need(S, f + r) > 64 << 20)
+    base = W.regular_grid(w.dims, w.mesh)
+    for n, fits in ((f + extra - 1, True), (f + extra, False)):
+        p = torch.arange(n, dtype=torch.int32, device=DEV) % w.P
+        o = torch.arange(n + 1, dtype=torch.int32, device=DEV)
+        X = _t(np.repeat(np.stack([base] * 2)[None], S, axis=0))
+        cand = X[:, :, p.long()].transpose(1, 2).contiguous()
+        terms = torch.zeros((S, gp.T, 3), dtype=torch.float64, device=DEV) if cached else None
+        _say(f"S={S} F={n} workspace {need(S, n)}")
+        if fits:
+            assert not gp.eval_partial_noalloc(X, o, p, cand, tet_terms_in=terms)[2].any()
+        else:
+            with pytest.raises(dsm.DsmError) as ei:
+                gp.eval_partial_noalloc(X, o, p, cand, tet_terms_in=terms)
+            assert ei.value.status == dsm.ERR_CAPACITY
+    torch.cuda.synchronize()
