@@ -885,3 +885,30 @@ def test_more_chunks_than_a_grid_dimension(F):
     want = small.eval_partial(_t(X), off[:13].contiguous(), pts[:12].contiguous(), cand[:, :12].contiguous())
     for got, ref_ in zip((old, new, fl), want):
         assert torch.equal(got[:, :F // 12 * 12].reshape(F // 12, 12, -1), ref_.reshape(1, 12, -1).expand(F // 12, -1, -1))
+
+
+# full evaluations on both sides of the 8,192 workgroups (21 a solution here) from which the sweep's other instruction
+# order is used, in both row orders: a solution's results do not depend on the others
+@pytest.mark.parametrize("rows", [0, 1])
+def test_full_evaluation_orders_agree(rows):
+    w = W.batched(shape=(24, 24, 24), mesh=(4, 4, 4))
+    rp = oracle_problem(w)
+    S = 391
+    X = feasible_population(w, rp, S=S)
+    gp = dsm.Problem.from_workload(w, max_solutions=S)
+    gp.set_row_order(rows)
+    assert S * 21 > 8192 >= (S - 1) * 21 and -(-gp.T // 8) == 21
+
+    def run(x):
+        terms = torch.empty((len(x), gp.T, 3), dtype=torch.float64, device=DEV)
+        return gp.eval_full(_t(x), tet_terms=terms) + (terms,)
+
+    many, fewer = run(X), run(X[1:])
+    for m, o in zip(many, fewer):
+        assert torch.equal(m[1:], o)
+    for s in (0, 195, S - 1):
+        for m, o in zip(many, run(X[s:s + 1])):
+            assert torch.equal(m[s:s + 1], o)
+    robj, rfl, _, _ = rp.eval_full(X[::30], want_terms=True)
+    np.testing.assert_array_equal(many[1].cpu().numpy()[::30].astype(np.uint32), rfl)
+    assert_objectives_close(many[0].cpu().numpy()[::30], robj)
