@@ -70,16 +70,23 @@ struct WaveWeights {
   float b1[2], b2[2], b3;
 };
 
-__device__ __forceinline__ void load_weights(const MlpW& w, int wave, int lane, WaveWeights& r) {
+__device__ __forceinline__ void load_layer1(const MlpW& w, int wave, int lane, WaveWeights& r) {
   const int i = lane & 15, kb = lane >> 4;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     const int col = 32 * wave + 16 * t + i;
 #pragma unroll
     for (int kk = 0; kk < kIn / 32; ++kk) r.w1[t][kk] = load8(w.w1 + (size_t)col * kIn + 32 * kk + 8 * kb);
+    r.b1[t] = w.b1[col];
+  }
+}
+__device__ __forceinline__ void load_layers23(const MlpW& w, int wave, int lane, WaveWeights& r) {
+  const int i = lane & 15, kb = lane >> 4;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int col = 32 * wave + 16 * t + i;
 #pragma unroll
     for (int kk = 0; kk < kHid / 32; ++kk) r.w2[t][kk] = load8(w.w2 + (size_t)col * kHid + 32 * kk + 8 * kb);
-    r.b1[t] = w.b1[col];
     r.b2[t] = w.b2[col];
   }
 #pragma unroll
@@ -116,12 +123,14 @@ __device__ __forceinline__ void layer64(const unsigned short* in, int in_stride,
 
 // Outputs of a tile's rows from the inputs in xs, all threads of the workgroup,
 // after a barrier; xs is overwritten with the second hidden layer.  where(i) is
-// the output row of the tile's row i, negative if there is none.
-template <class Where>
+// the output row of the tile's row i, negative if there is none; rest() loads
+// the weights of the later layers where they are not there yet.
+template <class Where, class Rest>
 __device__ __forceinline__ void mlp_tile(const WaveWeights& w, unsigned short* xs, unsigned short* h1, Where where,
-                                         float* __restrict__ out, int wave, int lane) {
+                                         float* __restrict__ out, int wave, int lane, Rest rest) {
   const int i = lane & 15, kb = lane >> 4;
   layer64<kIn>(xs, kXs, w.w1, w.b1, h1, wave, lane);
+  rest();
   __syncthreads();  // H1 complete, and every read of the inputs done
   layer64<kHid>(h1, kHs, w.w2, w.b2, xs, wave, lane);
   __syncthreads();
@@ -142,7 +151,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __shared__ __align__(16) unsigned short h1[kTileRows * kHs];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   WaveWeights ww;
-  load_weights(w, wave, lane, ww);
+  load_layer1(w, wave, lane, ww);
+  load_layers23(w, wave, lane, ww);
   constexpr int kPer = kTileRows * kIn / 8 / 256;  // 16-byte pieces of a tile per thread
   u16x8 next[kPer];
   auto fetch = [&](int64_t row0) {  // the tile after the current one, in flight while that is computed
@@ -161,13 +171,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     fetch(row0 + (int64_t)gridDim.x * kTileRows);
     __syncthreads();
-    mlp_tile(ww, xs, h1, [&](int i) { return row0 + i < N ? row0 + i : (int64_t)-1; }, out, wave, lane);
+    mlp_tile(ww, xs, h1, [&](int i) { return row0 + i < N ? row0 + i : (int64_t)-1; }, out, wave, lane, [] {});
     __syncthreads();
   }
 }
 
+// The same for one tile a workgroup: the weights arrive layer by layer, so the
+// first one waits for its own alone, and take 105 instead of 216 registers, so
+// more workgroups share a CU.  Up to the 768 tiles of a persistent launch, whose
+// workgroups take one tile each as well: 20,000 rows 11.1 us persistent, 9.4 so,
+// 40,000 16.2 and 12.0.
+__global__ __launch_bounds__(256) void k_mlp_forward_once(MlpW w, const unsigned short* __restrict__ xb, int N,
+                                                          float* __restrict__ out) {
+  __shared__ __align__(16) unsigned short xs[kTileRows * kXs];  // inputs, then H2
+  __shared__ __align__(16) unsigned short h1[kTileRows * kHs];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row0 = blockIdx.x * kTileRows;
+  for (int e = tid; e < kTileRows * kIn / 8; e += 256) {
+    const int r = e / (kIn / 8), c = e % (kIn / 8);
+    *(u16x8*)(xs + r * kXs + 8 * c) = row0 + r < N ? load8(xb + (size_t)(row0 + r) * kIn + 8 * c) : zero8();
+  }
+  WaveWeights ww;
+  load_layer1(w, wave, lane, ww);
+  __syncthreads();
+  mlp_tile(ww, xs, h1, [&](int i) { return row0 + i < N ? (int64_t)(row0 + i) : (int64_t)-1; }, out, wave, lane,
+           [&] { load_layers23(w, wave, lane, ww); });
+}
+
 // Workgroups of a persistent launch over N rows (a multiple of 8): three to a CU.
-unsigned mlp_grid(int64_t N) { return (unsigned)std::min<int64_t>((N + 8 * kTileRows - 1) / (8 * kTileRows) * 8, 3 * 256); }
+constexpr int kPersistent = 3 * 256;
+unsigned mlp_grid(int64_t N) { return (unsigned)std::min<int64_t>((N + 8 * kTileRows - 1) / (8 * kTileRows) * 8, kPersistent); }
 
 // One training step is two kernels: forward and backward of the minibatch rows
 // (k_mlp_rows), then the weight and bias gradients with the update
@@ -540,28 +572,28 @@ __device__ __forceinline__ int64_t tile_of(int64_t tiles, int block, int blocks,
   return k < q + (x < r ? 1 : 0) ? x * q + min((int64_t)x, r) + k : -1;
 }
 
-// Features of the 64 rows of a tile into LDS (absent rows are 0), by a
-// workgroup of 4 waves: lane = row, and each wave takes every fourth of the 28
-// groups of columns (26 neighbours, the moved point, the padding).  A group's
+// Features of the 64 rows of a tile (absent rows are 0), lane = row: the wave
+// takes groups `first`, first + step, ... of the 28 groups of columns (26
+// neighbours, the moved point, the padding) and writes lane's row to out(row).  A group's
 // offsets and statistics are the same on every lane, so they are scalars, a
 // row's indices are worked out once instead of once per group, and the lanes
 // of one point's candidates sample next to each other (a gather of the 26
-// offsets of one row touches as many cache lines as lanes).  rows[] receives
-// the rows' indices.  With PACK the values are standardised with the stored
+// offsets of one row touches as many cache lines as lanes).  Returns the row's
+// index, -1 past the last.  With PACK the values are standardised with the stored
 // input statistics and rounded to BF16, bit for bit what k_pack makes of the
 // FP32 rows (sums and products are written with explicit rounding, so that
 // both forms compute identical FP32 values).
-template <bool PACK, class T>
-__device__ __forceinline__ void feature_tile(const FeatureArgs& a, const float* __restrict__ mean,
-                                             const float* __restrict__ rstd, int64_t tile_index, T* tile, int stride,
-                                             int64_t* rows) {
+template <bool PACK, class Out>
+__device__ __forceinline__ int64_t feature_tile(const FeatureArgs& a, const float* __restrict__ mean,
+                                                const float* __restrict__ rstd, int64_t tile_index, int first, int step,
+                                                Out where) {
   const DevProblem& pr = a.pr;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  T* out = tile + lane * stride;
+  const int lane = threadIdx.x & 63;
   int s, f;
   const int64_t row = tile_row(a, tile_index, lane, s, f);
   const bool exists = row >= 0;
-  if (wave == 0) rows[lane] = row;
+  auto* const out = where(row);
+  if (!out) return row;
   const int p = exists ? a.pts[f] : -1;
   const bool valid = p >= 0 && p < pr.P;
   const int pc = valid ? p : 0;  // where rows without a point read
@@ -584,7 +616,7 @@ __device__ __forceinline__ void feature_tile(const FeatureArgs& a, const float* 
     }
   };
 #pragma unroll 2
-  for (int j = wave; j < 28; j += 4) {
+  for (int j = first; j < 28; j += step) {
     if (j == 27) {
       put2(kNumFeat, 0.f, 0.f);
       put2(kNumFeat + 2, 0.f, 0.f);
@@ -623,9 +655,13 @@ __device__ __forceinline__ void feature_tile(const FeatureArgs& a, const float* 
     else
       out[162 + j] = vi;
   }
+  return row;
 }
 
-// Feature rows as FP32 (out32) or standardised BF16 (out16), written from the LDS tile.
+// Feature rows as FP32 (out32) or standardised BF16 (out16), written from an LDS
+// tile by one workgroup, or, where the grid has kFeatureParts in its second
+// dimension, straight to memory with a group to a wave.
+constexpr int kFeatureParts = 7;
 template <bool PACK>
 __global__ __launch_bounds__(256) void k_features(FeatureArgs a, const float* __restrict__ mean,
                                                   const float* __restrict__ rstd, float* __restrict__ out32,
@@ -636,13 +672,20 @@ __global__ __launch_bounds__(256) void k_features(FeatureArgs a, const float* __
   __shared__ int64_t s_row[kTileRows];
   const int64_t index = tile_of((a.N + kTileRows - 1) / kTileRows, blockIdx.x, gridDim.x, 0);
   if (index < 0) return;
-  feature_tile<PACK>(a, mean, rstd, index, tile, kStride, s_row);
-  __syncthreads();
   T* dst;
   if constexpr (PACK)
     dst = out16;
   else
     dst = out32;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (gridDim.y > 1) {
+    feature_tile<PACK>(a, mean, rstd, index, 4 * blockIdx.y + wave, 4 * kFeatureParts,
+                       [&](int64_t row) { return row >= 0 ? dst + row * kIn : nullptr; });
+    return;
+  }
+  const int64_t row = feature_tile<PACK>(a, mean, rstd, index, wave, 4, [&](int64_t) { return tile + lane * kStride; });
+  if (wave == 0) s_row[lane] = row;
+  __syncthreads();
   constexpr int kPieces = kIn / kPiece;  // 16 bytes each: rows of 384 or 768 bytes
   for (int e = threadIdx.x; e < kTileRows * kPieces; e += 256) {
     const int i = e / kPieces, c = kPiece * (e % kPieces);
@@ -660,14 +703,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   __shared__ int64_t s_row[kTileRows];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   WaveWeights ww;
-  load_weights(w, wave, lane, ww);
+  load_layer1(w, wave, lane, ww);
+  load_layers23(w, wave, lane, ww);
   const int64_t tiles = (a.N + kTileRows - 1) / kTileRows;
   for (int n = 0;; ++n) {
     const int64_t tile = tile_of(tiles, blockIdx.x, gridDim.x, n);
     if (tile < 0) break;
-    feature_tile<true>(a, mean, rstd, tile, xs, kXs, s_row);
+    const int64_t row = feature_tile<true>(a, mean, rstd, tile, __builtin_amdgcn_readfirstlane(wave), 4,
+                                           [&](int64_t) { return xs + lane * kXs; });
+    if (wave == 0) s_row[lane] = row;
     __syncthreads();
-    mlp_tile(ww, xs, h1, [&](int i) { return s_row[i]; }, out, wave, lane);
+    mlp_tile(ww, xs, h1, [&](int i) { return s_row[i]; }, out, wave, lane, [] {});
     __syncthreads();
   }
 }
@@ -900,6 +946,15 @@ FeatureArgs feature_args(const dsm_problem* p, int S, const float* X, int F, con
   return a;
 }
 
+// Grid of k_features for n rows: a workgroup per tile of 64 rows (a multiple of
+// 8), or kFeatureParts while the tiles are too few to hide the 7 groups that a
+// wave of a tile takes one after the other.  A call by itself in us, one
+// workgroup / parts: 2,048 rows 18.2 / 14.9, BF16 8,192 19.0 / 15.8 and 16,038
+// 20.3 / 19.8, FP32 8,192 18.7 / 17.5 and 11,664 20.0 / 20.7.
+dim3 features_grid(int64_t n, bool packed) {
+  return dim3((unsigned)((n + 8 * kTileRows - 1) / (8 * kTileRows) * 8), n <= (packed ? 16384 : 8192) ? kFeatureParts : 1);
+}
+
 hipError_t refresh(dsm_surrogate* m, hipStream_t st) {
   k_refresh_bf16<<<(kNParams + 255) / 256, 256, 0, st>>>(m->d_params, operands(m));
   return hipGetLastError();
@@ -1072,7 +1127,7 @@ dsm_status dsm_surrogate_features(dsm_problem* p, int32_t S, const float* X, int
   const int64_t n = (int64_t)S * F * K;
   if (n == 0) return DSM_OK;
   if (!X || !fos_pts || !cand || !feats) return sfail(DSM_ERR_ARG, "null argument");
-  k_features<false><<<(unsigned)((n + 8 * kTileRows - 1) / (8 * kTileRows) * 8), 256, 0, (hipStream_t)stream>>>(
+  k_features<false><<<features_grid(n, false), 256, 0, (hipStream_t)stream>>>(
       feature_args(p, S, X, F, fos_pts, K, cand), nullptr, nullptr, feats, nullptr);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
@@ -1086,7 +1141,7 @@ dsm_status dsm_surrogate_features_packed(dsm_surrogate* m, dsm_problem* p, int32
   const int64_t n = (int64_t)S * F * K;
   if (n == 0) return DSM_OK;
   if (!X || !fos_pts || !cand || !feats_bf16) return sfail(DSM_ERR_ARG, "null argument");
-  k_features<true><<<(unsigned)((n + 8 * kTileRows - 1) / (8 * kTileRows) * 8), 256, 0, (hipStream_t)stream>>>(
+  k_features<true><<<features_grid(n, true), 256, 0, (hipStream_t)stream>>>(
       feature_args(p, S, X, F, fos_pts, K, cand), m->d_in_mean, m->d_in_rstd, nullptr, (unsigned short*)feats_bf16);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
@@ -1111,7 +1166,11 @@ dsm_status dsm_surrogate_forward(dsm_surrogate* m, int32_t N, const uint16_t* fe
   s_err.clear();
   if (!m || !feats_bf16 || !pred || N < 0) return sfail(DSM_ERR_ARG, "null argument");
   if (N == 0) return DSM_OK;
-  k_mlp_forward<<<mlp_grid(N), 256, 0, (hipStream_t)stream>>>(weights(m), (const unsigned short*)feats_bf16, N, pred);
+  if (N <= kPersistent * kTileRows)
+    k_mlp_forward_once<<<(N + kTileRows - 1) / kTileRows, 256, 0, (hipStream_t)stream>>>(weights(m), (const unsigned short*)feats_bf16,
+                                                                                        N, pred);
+  else
+    k_mlp_forward<<<mlp_grid(N), 256, 0, (hipStream_t)stream>>>(weights(m), (const unsigned short*)feats_bf16, N, pred);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? DSM_OK : sfail(DSM_ERR_DEVICE, hipGetErrorString(e));
 }

@@ -912,3 +912,40 @@ def test_full_evaluation_orders_agree(rows):
     robj, rfl, _, _ = rp.eval_full(X[::30], want_terms=True)
     np.testing.assert_array_equal(many[1].cpu().numpy()[::30].astype(np.uint32), rfl)
     assert_objectives_close(many[0].cpu().numpy()[::30], robj)
+
+
+# the last and first sizes on either side of the rules for few rows: network outputs (768 tiles of 64 rows), features in
+# FP32 (8,192 rows) and BF16 (16,384): a row's values do not depend on the others of its call
+@pytest.mark.parametrize("N", [49152, 49153])
+def test_forward_of_few_tiles(N):
+    rng = np.random.default_rng(5)
+    x = _t(rng.integers(-(1 << 14), 1 << 14, (49153, R.IN)).astype(np.int16) & np.int16(~0x4000))  # |x| < 2
+    sur = dsm.Surrogate(seed=3, max_rows=64, max_batch=32)
+    got, first, last = sur.forward(x[:N]), sur.forward(x[:640].contiguous()), sur.forward(x[N - 641:N].contiguous())
+    assert not torch.isnan(got).any()
+    assert torch.equal(got[:640], first) and torch.equal(got[N - 641:], last)
+
+
+@pytest.mark.parametrize("packed,rows", [(False, 8192), (True, 16384)])
+@pytest.mark.parametrize("K", [1, 3])
+def test_features_of_few_rows(tiny_problem, packed, rows, K):
+    w, gp = tiny_problem
+    pts = np.array([13, 0, 5, 22, -1, 26, 4, 14], np.int32)
+    F = len(pts)
+    S = rows // (F * K) + 1
+    rng = np.random.default_rng(K)
+    X = _t(rng.uniform(0, 31, (S, 2, w.P, 3)).astype(np.float32))
+    cand = _t(rng.uniform(0, 31, (S, F, K, 2, 3)).astype(np.float32))
+    sur = dsm.Surrogate(seed=3, max_rows=64, max_batch=32)
+    sur.set_scaling(rng.normal(size=R.IN), rng.uniform(0.5, 2, R.IN), np.zeros(3), np.ones(3))
+
+    def run(a, b):
+        args = (X[a:b].contiguous(), _t(pts), cand[a:b].contiguous())
+        return sur.features_packed(gp, *args) if packed else dsm.Surrogate.features(gp, *args)
+
+    many = run(0, S)  # more rows than the rule's line
+    n = rows // (F * K)
+    assert (S * F * K > rows) and n * F * K <= rows
+    assert torch.equal(many[:n * F * K], run(0, n))
+    assert torch.equal(many[F * K:], run(1, S))
+    assert torch.equal(many[-F * K:], run(S - 1, S))
