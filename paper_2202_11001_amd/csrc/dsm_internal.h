@@ -120,13 +120,15 @@ struct HostTopology {
 bool build_topology(const int mesh[3], HostTopology& out);
 void identity_grid(const int mesh[3], const int dims[3], float* X);
 
-// Grid of n workgroups of at most 512 threads for kernels that number their
-// workgroups blockIdx.x + gridDim.x * blockIdx.y: a grid's dimension holds less
-// than 2^32 threads, and a launch with more runs with what is left modulo 2^32,
-// without an error.  The second dimension may end with workgroups past n.
+// Workgroups of up to 320 threads in one dimension of a grid, which holds less
+// than 2^32 threads (a launch with more runs with what is left modulo 2^32,
+// without an error).
+constexpr int64_t kGridMax = 1 << 23;
+// Grid of n workgroups for kernels that number them
+// blockIdx.x + gridDim.x * blockIdx.y: even rows, so few workgroups lie past n.
 inline dim3 wide_grid(int64_t n) {
-  const int64_t x = std::min<int64_t>(n, 1 << 22);
-  return dim3((unsigned)x, (unsigned)((n + x - 1) / x));
+  const int64_t rows = (n + kGridMax - 1) / kGridMax;
+  return dim3((unsigned)((n + rows - 1) / rows), (unsigned)rows);
 }
 
 // Kernel launchers (kernels.hip).  All enqueue on `stream` and return the

@@ -66,9 +66,6 @@ __device__ __forceinline__ double orient(const double a[3], const double b[3], c
   return u[0] * cx + u[1] * cy + u[2] * cz;
 }
 
-// Number of a workgroup in a grid of wide_grid.
-__device__ __forceinline__ int64_t wide_block() { return blockIdx.x + (int64_t)gridDim.x * blockIdx.y; }
-
 // Blockid -> logical index so that each of the 8 XCDs (which receive
 // workgroups round robin) processes one contiguous range of logical indices;
 // consecutive logical indices share a FOS element and hence an image region.
@@ -1205,10 +1202,10 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
 // a class of the phantom 3,150 against 3,225 us and 512x512x100 164.6 against
 // 165.4 ms (7 waves, from 70 registers: 62.5, 3,420 and 168.5).
 template <int PARTIAL, int ROWS, int EU>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(EU, 8))) void k_sweep(EvalArgs a) {
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(EU, 8))) void k_sweep(EvalArgs a, int first) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int n = PARTIAL && a.slots ? a.S * a.slots[0].x : a.S * a.G * (PARTIAL ? a.nchunk : 1);
-  const int logical = xcd_logical(blockIdx.x & 7, (int)(wide_block() >> 3), n);
+  const int logical = xcd_logical(blockIdx.x & 7, (first + (int)blockIdx.x) >> 3, n);
   if (logical >= 0) sweep_body<PARTIAL, ROWS>(a, logical, smem);
 }
 
@@ -1224,9 +1221,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(EU, 8))) vo
 // resolution, 8: 5,650).  ROWS as for sweep_body.
 template <int ROWS>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_sweep_batch(
-    const EvalArgs* __restrict__ jobs, const int* __restrict__ xcd_off, int n_jobs) {
+    const EvalArgs* __restrict__ jobs, const int* __restrict__ xcd_off, int n_jobs, int first) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int x = blockIdx.x & 7, k = (int)(wide_block() >> 3);
+  const int x = blockIdx.x & 7, k = (first + (int)blockIdx.x) >> 3;
   int j = 0;
   while (j + 1 < n_jobs && xcd_off[j + 1] <= k) ++j;
   j = uniform(j);
@@ -1891,16 +1888,26 @@ hipError_t launch_affected(const DevProblem& pr, int F, const int* fos_off, cons
 // workgroups that exist.
 constexpr int64_t kSweepMany = 4 * 8 * 256;
 
+// Launches a sweep of n workgroups in slices of kGridMax (a multiple of 8, so a
+// slice goes on where the last one left the XCDs).  Slices and not a second
+// dimension, whose numbers every workgroup would read: 5,832 elements for 8
+// solutions, all masked, without a slot table 998 us so and 1,026 with it.
+template <class Launch>
+void sweep_slices(int64_t n, Launch launch) {
+  for (int64_t first = 0; first < n; first += kGridMax) launch((unsigned)std::min(kGridMax, n - first), (int)first);
+}
+
 hipError_t launch_eval(const EvalArgs& a, hipEvent_t ev_begin, hipEvent_t ev_end, hipStream_t stream) {
   const int64_t nwg = (int64_t)a.S * a.G;
   if (nwg <= 0) return hipSuccess;
   // XCD x gets the workgroups x, x + 8, ...: as many as xcd_logical gives it, whatever the slot table leaves of them
   const int64_t most = nwg * (a.partial ? a.nchunk : 1);
-  const dim3 grid = wide_grid(most);
   const size_t lds = eval_lds_bytes(kMaxChunk, a.nver);
   if (ev_begin) (void)hipEventRecord(ev_begin, stream);
   const bool many = a.nver == 1 && most > kSweepMany;
-  auto launch = [&](auto* dense, auto* sparse) { (many ? dense : sparse)<<<grid, kWG, lds, stream>>>(a); };
+  auto launch = [&](auto* dense, auto* sparse) {
+    sweep_slices(most, [&](unsigned wgs, int first) { (many ? dense : sparse)<<<wgs, kWG, lds, stream>>>(a, first); });
+  };
   if (a.partial && a.row_pairs)
     launch(k_sweep<1, 1, 8>, k_sweep<1, 1, 6>);
   else if (a.partial)
@@ -1920,13 +1927,9 @@ hipError_t launch_eval(const EvalArgs& a, hipEvent_t ev_begin, hipEvent_t ev_end
 hipError_t launch_eval_batch(const EvalArgs* jobs_dev, const int* wg_off_dev, int n_jobs, int per_xcd, int total_finish,
                              size_t lds, int rows, hipStream_t stream) {
   if (per_xcd <= 0) return hipSuccess;
-  const dim3 nwg = wide_grid(8 * (int64_t)per_xcd);
-  if (rows == 0)
-    k_sweep_batch<0><<<nwg, kWG, lds, stream>>>(jobs_dev, wg_off_dev, n_jobs);
-  else if (rows == 1)
-    k_sweep_batch<1><<<nwg, kWG, lds, stream>>>(jobs_dev, wg_off_dev, n_jobs);
-  else
-    k_sweep_batch<2><<<nwg, kWG, lds, stream>>>(jobs_dev, wg_off_dev, n_jobs);
+  auto* kernel = rows == 0 ? k_sweep_batch<0> : (rows == 1 ? k_sweep_batch<1> : k_sweep_batch<2>);
+  sweep_slices(8 * (int64_t)per_xcd,
+               [&](unsigned wgs, int first) { kernel<<<wgs, kWG, lds, stream>>>(jobs_dev, wg_off_dev, n_jobs, first); });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_finish_batch<<<(unsigned)total_finish, 64, 0, stream>>>(jobs_dev, wg_off_dev + (n_jobs + 1), n_jobs);
