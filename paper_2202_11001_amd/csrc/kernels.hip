@@ -1195,7 +1195,7 @@ __device__ __forceinline__ void sweep_body(const EvalArgs& a, int logical, unsig
 }
 
 // EU: the waves per SIMD that the instructions are ordered for.  Both orders
-// take 60 registers, which leaves room for 8; but where LDS holds fewer
+// take 58 to 60 registers, which leaves room for 8; but where LDS holds fewer
 // workgroups (two versions) or the launch has fewer, the order for 8, which
 // brings a wave's loads and their uses closer together, is the slower one: 64^3
 // recomputed 1305 against 1280 us, 32^3 with 16 solutions 64.8 against 62.3, but
@@ -1885,7 +1885,9 @@ hipError_t launch_affected(const DevProblem& pr, int F, const int* fos_off, cons
 
 // Workgroups from which a sweep keeps every SIMD at 8 waves.  2,048 do, but the
 // launch has room for the largest element everywhere and two to four times the
-// workgroups that exist.
+// workgroups that exist.  The number of workgroups does not tell everything:
+// with few, large tetrahedra (150^3, a 4^3 mesh, chunk 6) 8 waves take 5.93 ms
+// and 7 took 5.68.
 constexpr int64_t kSweepMany = 4 * 8 * 256;
 
 // Launches a sweep of n workgroups in slices of kGridMax (a multiple of 8, so a

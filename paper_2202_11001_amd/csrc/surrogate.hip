@@ -695,7 +695,8 @@ __global__ __launch_bounds__(256) void k_features(FeatureArgs a, const float* __
 
 // Screening: features of 64 rows into LDS and the network on them, without
 // rows in memory (0.47 GB written and read again at 1.2 M candidates; the two
-// kernels took 1270 and 330 us).
+// kernels took 1270 and 330 us).  Three waves per SIMD leave 168 registers, of
+// which the weights take 101: two values are spilled.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_screen(
     MlpW w, FeatureArgs a, const float* __restrict__ mean, const float* __restrict__ rstd, float* __restrict__ out) {
   __shared__ __align__(16) unsigned short xs[kTileRows * kXs];  // inputs, then H2

@@ -537,6 +537,8 @@ def test_estimates_of_clusters(tiny_problem, n_clusters, n_sel):
             gp.estimate_clusters(X, members.new_zeros((bad, 4)), pts)
 
 
+# (2048 workgroups that exist keep every SIMD at 8 waves; the switch is at 8192 launched ones, which have room for the
+# largest element everywhere, and only where one version is swept: 30 solutions lie above it with cached terms)
 # launches on both sides of the 2048 workgroups from which the sweep's other instruction order is used, in both row
 # orders, with the current terms cached or recomputed: a solution's results do not depend on the others
 @pytest.mark.parametrize("rows", [0, 1])
